@@ -19,11 +19,7 @@
 struct tl_forest {
     int device;
     tl::ForestDev dev;
-    void* nodes_mem;
-    void* leaves_mem;
-    void* box_mem;
-    void* records_mem;
-    void* cuts_mem;   // [kMaxCuts] KV cuts, then [kMaxCuts] batch cuts
+    void* mem;        // every array of `dev`
     // Work-order scratch of the grid and column kernels, on the forest's
     // device: kept from call to call and only replaced by a larger one when a
     // larger grid comes.  ws_done is recorded on the stream of the last call that used
@@ -67,6 +63,120 @@ tl_status from_hip(hipError_t e, const char* what) {
     return fail(e == hipErrorOutOfMemory ? TL_ENOMEM : TL_EDEVICE, "%s: %s", what, hipGetErrorString(e));
 }
 
+tl_status forest_create(int32_t n_trees, int32_t depth, int32_t n_features, float base_score, const uint8_t* feature,
+                        const float* threshold, const float* leaf, tl_forest** out) {
+    if (n_trees < 0) return fail(TL_EINVAL, "tl_forest_create: n_trees %d < 0", n_trees);
+    if (depth < 0 || depth > TL_MAX_DEPTH)
+        return fail(TL_EINVAL, "tl_forest_create: depth %d outside [0, %d]", depth, TL_MAX_DEPTH);
+    if (n_features < 1 || n_features > TL_MAX_FEATURES)
+        return fail(TL_EINVAL, "tl_forest_create: n_features %d outside [1, %d]", n_features, TL_MAX_FEATURES);
+    const int64_t n_int = (1ll << depth) - 1;
+    const int64_t n_leaf = 1ll << depth;
+    if (n_trees > 0 && (!leaf || (n_int > 0 && (!feature || !threshold))))
+        return fail(TL_EINVAL, "tl_forest_create: NULL tree array");
+    for (int64_t i = 0; i < n_trees * n_int; ++i)
+        if (feature[i] >= n_features)
+            return fail(TL_EINVAL, "tl_forest_create: node %lld uses feature %d >= n_features %d", (long long)i,
+                        (int)feature[i], n_features);
+    const size_t cells = (size_t)n_trees * n_leaf;
+    std::vector<tl::host::Box> leaf_box;
+    std::vector<float4> boxes;
+    tl::host::RankForest ranks;
+    if (n_features >= 3) {
+        if (depth <= tl::kMaxRecordDepth) {
+            tl::host::build_rank_records(n_trees, depth, feature, threshold, leaf, ranks);
+        } else {
+            tl::host::leaf_boxes(n_trees, depth, feature, threshold, leaf_box);
+            boxes.assign(cells + 4, make_float4(0, 0, 0, 0));
+            for (size_t i = 0; i < leaf_box.size(); ++i)
+                boxes[i] = make_float4(leaf_box[i].kv_lo, leaf_box[i].kv_hi, leaf_box[i].batch_lo, leaf_box[i].batch_hi);
+        }
+    }
+    std::vector<float> cuts_kv, cuts_bs;
+    if (n_features >= 3 && n_int > 0) {
+        cuts_kv = tl::host::threshold_cuts(n_trees * n_int, feature, threshold, 1);
+        cuts_bs = tl::host::threshold_cuts(n_trees * n_int, feature, threshold, 2);
+    }
+
+    const bool cuts = !cuts_kv.empty() && !cuts_bs.empty();
+    // one device allocation and one copy: each array on a 256-byte boundary,
+    // nodes and leaves with a per-tree stride of 2^d entries and 64 bytes of
+    // tail padding
+    enum { kNodes, kLeaves, kBoxes, kRecords, kDict, kStarts, kGroups, kCutsKv, kCutsBs, kParts };
+    const size_t part_bytes[kParts] = {cells * sizeof(uint2) + 64,
+                                       cells * sizeof(float) + 64,
+                                       boxes.size() * sizeof(float4),
+                                       ranks.records.size(),
+                                       ranks.dict.size() * sizeof(float),
+                                       ranks.starts.size() * sizeof(uint16_t),
+                                       ranks.groups.size() * sizeof(tl::RankGroup),
+                                       cuts ? cuts_kv.size() * sizeof(float) : 0,
+                                       cuts ? cuts_bs.size() * sizeof(float) : 0};
+    size_t at[kParts + 1] = {0};
+    for (int q = 0; q < kParts; ++q) at[q + 1] = (at[q] + part_bytes[q] + 255) & ~(size_t)255;
+    std::vector<unsigned char> image(at[kParts], 0);
+    {
+        uint2* nodes = (uint2*)(image.data() + at[kNodes]);
+        for (int64_t t = 0; t < n_trees; ++t)
+            for (int64_t k = 0; k < n_int; ++k) {
+                const int64_t i = t * n_int + k;
+                uint32_t bits;
+                std::memcpy(&bits, &threshold[i], 4);
+                nodes[t * n_leaf + k] = make_uint2(bits, feature[i]);
+            }
+        const void* const part[kParts] = {nullptr,           leaf,
+                                          boxes.data(),      ranks.records.data(),
+                                          ranks.dict.data(), ranks.starts.data(),
+                                          ranks.groups.data(), cuts_kv.data(),
+                                          cuts_bs.data()};
+        for (int q = 1; q < kParts; ++q) {
+            const size_t n = q == kLeaves ? cells * sizeof(float) : part_bytes[q];
+            if (n > 0) std::memcpy(image.data() + at[q], part[q], n);
+        }
+    }
+
+    tl_forest* f = new (std::nothrow) tl_forest();
+    if (!f) return fail(TL_ENOMEM, "tl_forest_create: host allocation failed");
+    hipError_t e = hipGetDevice(&f->device);
+    if (e != hipSuccess) { delete f; return from_hip(e, "tl_forest_create: hipGetDevice"); }
+    e = hipEventCreateWithFlags(&f->ws_done, hipEventDisableTiming);
+    if (e != hipSuccess) { delete f; return from_hip(e, "tl_forest_create: hipEventCreate"); }
+    e = hipMalloc(&f->mem, image.size());
+    if (e != hipSuccess) {
+        (void)hipEventDestroy(f->ws_done);
+        delete f;
+        return from_hip(e, "tl_forest_create: hipMalloc");
+    }
+    e = hipMemcpy(f->mem, image.data(), image.size(), hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        (void)hipFree(f->mem);
+        (void)hipEventDestroy(f->ws_done);
+        delete f;
+        return from_hip(e, "tl_forest_create: hipMemcpy");
+    }
+    const unsigned char* const mem = (const unsigned char*)f->mem;
+    auto array = [&](int q) { return part_bytes[q] > 0 ? mem + at[q] : nullptr; };
+    f->dev.n_trees = n_trees;
+    f->dev.depth = depth;
+    f->dev.n_features = n_features;
+    f->dev.base_score = base_score;
+    f->dev.nodes = (const uint2*)array(kNodes);
+    f->dev.leaves = (const float*)array(kLeaves);
+    f->dev.kvb_box = (const float4*)array(kBoxes);
+    f->dev.records = (const uint4*)array(kRecords);
+    f->dev.dict = (const float*)array(kDict);
+    f->dev.starts = (const uint16_t*)array(kStarts);
+    f->dev.groups = (const tl::RankGroup*)array(kGroups);
+    f->dev.group_trees = ranks.group_trees;
+    f->dev.n_groups = (int32_t)ranks.groups.size();
+    f->dev.cuts_kv = (const float*)array(kCutsKv);
+    f->dev.cuts_bs = (const float*)array(kCutsBs);
+    f->dev.n_cuts_kv = cuts ? (int32_t)cuts_kv.size() : 0;
+    f->dev.n_cuts_bs = cuts ? (int32_t)cuts_bs.size() : 0;
+    *out = f;
+    return ok();
+}
+
 }  // namespace
 
 extern "C" {
@@ -80,111 +190,11 @@ tl_status tl_forest_create(int32_t n_trees, int32_t depth, int32_t n_features, f
                            tl_forest** out) {
     if (!out) return fail(TL_EINVAL, "tl_forest_create: out is NULL");
     *out = nullptr;
-    if (n_trees < 0) return fail(TL_EINVAL, "tl_forest_create: n_trees %d < 0", n_trees);
-    if (depth < 0 || depth > TL_MAX_DEPTH)
-        return fail(TL_EINVAL, "tl_forest_create: depth %d outside [0, %d]", depth, TL_MAX_DEPTH);
-    if (n_features < 1 || n_features > TL_MAX_FEATURES)
-        return fail(TL_EINVAL, "tl_forest_create: n_features %d outside [1, %d]", n_features, TL_MAX_FEATURES);
-    const int64_t n_int = (1ll << depth) - 1;
-    const int64_t n_leaf = 1ll << depth;
-    if (n_trees > 0 && (!leaf || (n_int > 0 && (!feature || !threshold))))
-        return fail(TL_EINVAL, "tl_forest_create: NULL tree array");
-    // device arrays use a per-tree stride of 2^d entries and 64 bytes of tail
-    // padding, so staged blocks are whole, aligned 16-byte words
-    const size_t cells = (size_t)n_trees * n_leaf;
-    std::vector<uint2> nodes(cells + 8, make_uint2(0, 0));
-    std::vector<float> leaves(cells + 16, 0.0f);
-    for (int64_t t = 0; t < n_trees; ++t)
-        for (int64_t k = 0; k < n_int; ++k) {
-            const int64_t i = t * n_int + k;
-            if (feature[i] >= n_features)
-                return fail(TL_EINVAL, "tl_forest_create: node %lld uses feature %d >= n_features %d",
-                            (long long)i, (int)feature[i], n_features);
-            uint32_t bits;
-            std::memcpy(&bits, &threshold[i], 4);
-            nodes[(size_t)(t * n_leaf + k)] = make_uint2(bits, feature[i]);
-        }
-    for (size_t i = 0; i < cells; ++i) leaves[i] = leaf[i];
-    std::vector<tl::host::Box> leaf_box;
-    std::vector<float4> boxes;
-    std::vector<unsigned char> records;
-    if (n_features >= 3) {
-        tl::host::leaf_boxes(n_trees, depth, feature, threshold, leaf_box);
-        if (depth <= tl::kMaxRecordDepth) tl::host::build_records(n_trees, depth, feature, threshold, leaf, leaf_box, records);
-        boxes.assign(cells + 4, make_float4(0, 0, 0, 0));
-        for (size_t i = 0; i < leaf_box.size(); ++i)
-            boxes[i] = make_float4(leaf_box[i].kv_lo, leaf_box[i].kv_hi, leaf_box[i].batch_lo, leaf_box[i].batch_hi);
+    try {
+        return forest_create(n_trees, depth, n_features, base_score, feature, threshold, leaf, out);
+    } catch (const std::bad_alloc&) {
+        return fail(TL_ENOMEM, "tl_forest_create: host allocation failed");
     }
-    std::vector<float> cuts_kv, cuts_bs;
-    if (n_features >= 3 && n_int > 0) {
-        cuts_kv = tl::host::threshold_cuts(n_trees * n_int, feature, threshold, 1);
-        cuts_bs = tl::host::threshold_cuts(n_trees * n_int, feature, threshold, 2);
-    }
-
-    tl_forest* f = new (std::nothrow) tl_forest();
-    if (!f) return fail(TL_ENOMEM, "tl_forest_create: host allocation failed");
-    hipError_t e = hipGetDevice(&f->device);
-    if (e != hipSuccess) { delete f; return from_hip(e, "tl_forest_create: hipGetDevice"); }
-    e = hipEventCreateWithFlags(&f->ws_done, hipEventDisableTiming);
-    if (e != hipSuccess) { delete f; return from_hip(e, "tl_forest_create: hipEventCreate"); }
-    e = hipMalloc(&f->nodes_mem, nodes.size() * sizeof(uint2));
-    if (e != hipSuccess) { (void)hipEventDestroy(f->ws_done); delete f; return from_hip(e, "tl_forest_create: hipMalloc(nodes)"); }
-    e = hipMalloc(&f->leaves_mem, leaves.size() * sizeof(float));
-    if (e != hipSuccess) { (void)hipFree(f->nodes_mem); (void)hipEventDestroy(f->ws_done); delete f; return from_hip(e, "tl_forest_create: hipMalloc(leaves)"); }
-    f->box_mem = nullptr;
-    f->records_mem = nullptr;
-    f->cuts_mem = nullptr;
-    const size_t cut_bytes = 2 * (size_t)tl::kMaxCuts * sizeof(float);
-    if (!boxes.empty()) e = hipMalloc(&f->box_mem, boxes.size() * sizeof(float4));
-    if (e == hipSuccess && !records.empty()) e = hipMalloc(&f->records_mem, records.size());
-    if (e == hipSuccess && !cuts_kv.empty() && !cuts_bs.empty()) e = hipMalloc(&f->cuts_mem, cut_bytes);
-    if (e != hipSuccess) {
-        (void)hipFree(f->nodes_mem);
-        (void)hipFree(f->leaves_mem);
-        if (f->box_mem) (void)hipFree(f->box_mem);
-        if (f->records_mem) (void)hipFree(f->records_mem);
-        if (f->cuts_mem) (void)hipFree(f->cuts_mem);
-        (void)hipEventDestroy(f->ws_done);
-        delete f;
-        return from_hip(e, "tl_forest_create: hipMalloc");
-    }
-    e = hipMemcpy(f->nodes_mem, nodes.data(), nodes.size() * sizeof(uint2), hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-        e = hipMemcpy(f->leaves_mem, leaves.data(), leaves.size() * sizeof(float), hipMemcpyHostToDevice);
-    if (e == hipSuccess && f->box_mem)
-        e = hipMemcpy(f->box_mem, boxes.data(), boxes.size() * sizeof(float4), hipMemcpyHostToDevice);
-    if (e == hipSuccess && f->records_mem)
-        e = hipMemcpy(f->records_mem, records.data(), records.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess && f->cuts_mem) {
-        std::vector<float> cuts(2 * (size_t)tl::kMaxCuts, 0.0f);
-        std::copy(cuts_kv.begin(), cuts_kv.end(), cuts.begin());
-        std::copy(cuts_bs.begin(), cuts_bs.end(), cuts.begin() + tl::kMaxCuts);
-        e = hipMemcpy(f->cuts_mem, cuts.data(), cut_bytes, hipMemcpyHostToDevice);
-    }
-    if (e != hipSuccess) {
-        (void)hipFree(f->nodes_mem);
-        (void)hipFree(f->leaves_mem);
-        if (f->box_mem) (void)hipFree(f->box_mem);
-        if (f->records_mem) (void)hipFree(f->records_mem);
-        if (f->cuts_mem) (void)hipFree(f->cuts_mem);
-        (void)hipEventDestroy(f->ws_done);
-        delete f;
-        return from_hip(e, "tl_forest_create: hipMemcpy");
-    }
-    f->dev.n_trees = n_trees;
-    f->dev.depth = depth;
-    f->dev.n_features = n_features;
-    f->dev.base_score = base_score;
-    f->dev.nodes = (const uint2*)f->nodes_mem;
-    f->dev.leaves = (const float*)f->leaves_mem;
-    f->dev.kvb_box = (const float4*)f->box_mem;
-    f->dev.records = (const uint4*)f->records_mem;
-    f->dev.cuts_kv = f->cuts_mem ? (const float*)f->cuts_mem : nullptr;
-    f->dev.cuts_bs = f->cuts_mem ? (const float*)f->cuts_mem + tl::kMaxCuts : nullptr;
-    f->dev.n_cuts_kv = f->cuts_mem ? (int32_t)cuts_kv.size() : 0;
-    f->dev.n_cuts_bs = f->cuts_mem ? (int32_t)cuts_bs.size() : 0;
-    *out = f;
-    return ok();
 }
 
 void tl_forest_destroy(tl_forest* f) {
@@ -193,11 +203,7 @@ void tl_forest_destroy(tl_forest* f) {
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(f->device);
     (void)hipDeviceSynchronize();
-    (void)hipFree(f->nodes_mem);
-    (void)hipFree(f->leaves_mem);
-    if (f->box_mem) (void)hipFree(f->box_mem);
-    if (f->records_mem) (void)hipFree(f->records_mem);
-    if (f->cuts_mem) (void)hipFree(f->cuts_mem);
+    (void)hipFree(f->mem);
     if (f->ws) (void)hipFree(f->ws);
     (void)hipEventDestroy(f->ws_done);
     (void)hipSetDevice(cur);
@@ -462,7 +468,7 @@ tl_status tl_admit(const tl_admit_args* a, void* stream) {
     c.kv = a->proj.kv;
     c.batch = a->proj.batch;
     c.freq = a->max_freq_mhz;
-    c.engine = a->engine_size;
+    c.engine = f->dev.n_features == 4 ? a->engine_size : nullptr;
     c.out = a->ips;
     int32_t lat_f = -1;
     if (a->lattice) {
@@ -814,7 +820,7 @@ tl_status tl_select_freq_binary(const tl_forest* f, int64_t n_scenarios, int32_t
     c.batch = batch;
     c.freqs = freqs_mhz;
     c.fidx = search_work + 2 * n_scenarios;
-    c.engine = engine_size;
+    c.engine = f->dev.n_features == 4 ? engine_size : nullptr;
     c.out = ips_work;
     tl::GatherParams gp{};
     gp.S = n_scenarios;

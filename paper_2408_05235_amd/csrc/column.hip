@@ -72,53 +72,13 @@ __device__ __forceinline__ float column_freq(const ColumnParams& P, int64_t s) {
     return P.fidx ? P.freqs[max(P.fidx[s], 0)] : P.freq;
 }
 
-// The leaves lf[r][t] that NR rows (each with its own features) reach in NT
-// consecutive staged trees (records R.bytes apart, the first at LDS byte
-// address `tree`), all NR x NT chains of dependent LDS reads interleaved:
-// every chain's node reads issue back to back, then the compares.
-template <int NF, int NT, int NR>
-__device__ __forceinline__ void walk_rows(uint32_t tree, const RecordLayout& R, int32_t depth, const float (&xf)[NR],
-                                          const float (&kv)[NR], const float (&bs)[NR], const float (&xe)[NR],
-                                          LeafAt (&lf)[NR][NT]) {
-    const uint32_t rec_bytes = R.bytes;
-    uint32_t a[NR][NT], cl[NT], cr[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const uint32_t root = tree + t * rec_bytes;
-        cl[t] = 16u - root;
-        cr[t] = 32u - root;
-        asm volatile("" : "+v"(cl[t]), "+v"(cr[t]));
-#pragma unroll
-        for (int r = 0; r < NR; ++r) a[r][t] = root;
-    }
-    for (int32_t level = 0; level < depth; ++level) {
-        uint4 w[NR][NT];
-#pragma unroll
-        for (int r = 0; r < NR; ++r)
-#pragma unroll
-            for (int t = 0; t < NT; ++t) w[r][t] = read_node(a[r][t]);
-#pragma unroll
-        for (int r = 0; r < NR; ++r)
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const bool left = node_feature<NF>(w[r][t], xf[r], kv[r], bs[r], xe[r]) < __uint_as_float(w[r][t].x);
-                a[r][t] = 2u * a[r][t] + (left ? cl[t] : cr[t]);
-            }
-    }
-#pragma unroll
-    for (int r = 0; r < NR; ++r)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) lf[r][t] = leaf_at(a[r][t], tree + t * rec_bytes, R, depth);
-}
-
 // Walks NT consecutive staged trees for the RPL rows of a lane and adds the
 // leaves to each row's sum in tree order.
-template <int NF, int NT, int RPL>
-__device__ __forceinline__ void add_leaves(uint32_t tree, const RecordLayout& R, int32_t depth,
-                                           const float (&xf)[RPL], const float (&kv)[RPL], const float (&bs)[RPL],
-                                           const float (&xe)[RPL], float (&acc)[RPL]) {
-    LeafAt k[RPL][NT];
-    walk_rows<NF, NT, RPL>(tree, R, depth, xf, kv, bs, xe, k);
+template <int NT, int RPL>
+__device__ __forceinline__ void add_leaves(uint32_t tree, uint32_t rec_bytes, int32_t depth,
+                                           const uint32_t (&row)[RPL], const uint32_t (&fe)[RPL], float (&acc)[RPL]) {
+    uint32_t k[RPL][NT];
+    walk_rows<NT, RPL>(tree, rec_bytes, depth, row, fe, k);
 #pragma unroll
     for (int r = 0; r < RPL; ++r)
 #pragma unroll
@@ -126,19 +86,20 @@ __device__ __forceinline__ void add_leaves(uint32_t tree, const RecordLayout& R,
 }
 
 template <int NF, int RPL, bool ROWS>
-__global__ __launch_bounds__(kColThreads) void forest_column_lds_kernel(const uint4* __restrict__ records,
-                                                                       int32_t n_trees, int32_t depth, int32_t tb,
-                                                                       float base, ColumnParams P) {
+__global__ __launch_bounds__(kColThreads) void forest_column_lds_kernel(RankDev D, TreeBlocks B, ColumnParams P) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const RecordLayout R = record_layout(depth);
-    const uint32_t rec_words = R.bytes / 16u;
-    const uint32_t buf_bytes = stage_buffer_bytes(tb, R);
+    const uint32_t rec_bytes = rank_record_bytes(D.depth);
+    const uint32_t buf_bytes = stage_buffer_bytes(B.tb, rec_bytes);
     const int wave = threadIdx.x / kWave;
     const int64_t item = __builtin_amdgcn_readfirstlane((int64_t)blockIdx.x * kColWaves + wave);
-    float xf[RPL], kv[RPL], bs[RPL], xe[RPL];
+    StageSync* sync = (StageSync*)(smem + 2 * buf_bytes);
+    if (threadIdx.x == 0) stage_sync_init(sync);
+    if (B.n_blocks > 0) stage_block(D, B, 0, lds_addr(smem), wave, kColWaves);
     float acc[RPL];
     int64_t o[RPL];     // output index of each row, < 0: none
+    int64_t in[RPL];    // input index of each row
     bool valid;         // the wavefront has rows (uniform)
+    int64_t s = 0;
     if (ROWS) {
         const int64_t first = item * (kWave * RPL);
         valid = first < P.n_rows;
@@ -146,57 +107,57 @@ __global__ __launch_bounds__(kColThreads) void forest_column_lds_kernel(const ui
         for (int r = 0; r < RPL; ++r) {
             const int64_t i = first + lane_id() + r * kWave;
             o[r] = i < P.n_rows ? i : -1;
-            const float* x = P.rows + (valid ? min(i, P.n_rows - 1) : 0) * NF;
-            xf[r] = x[0];
-            kv[r] = x[1];
-            bs[r] = x[2];
-            xe[r] = NF == 4 ? x[3] : 0.0f;
+            in[r] = valid ? min(i, P.n_rows - 1) : 0;
         }
     } else {
         const ColumnItem<RPL> c = column_item<RPL>(P, item);
         valid = c.valid;
-        const float f_s = column_freq(P, c.s);
-        const float e_s = NF == 4 ? P.engine[c.s] : 0.0f;
+        s = c.s;
 #pragma unroll
         for (int r = 0; r < RPL; ++r) {
-            xf[r] = f_s;
-            xe[r] = e_s;
-            kv[r] = (float)P.kv[c.s * P.H + c.j[r]];
-            bs[r] = (float)P.batch[c.s * P.H + c.j[r]];
-            o[r] = c.row[r] ? c.s * P.H + c.j[r] : -1;
+            in[r] = c.s * P.H + c.j[r];
+            o[r] = c.row[r] ? in[r] : -1;
         }
     }
 #pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-        acc[r] = base;
-        // the rows are complete before any staging load is in flight
-        asm volatile("" ::"v"(xf[r]), "v"(kv[r]), "v"(bs[r]), "v"(xe[r]));
-    }
-
-    const int32_t n_blocks = (n_trees + tb - 1) / tb;
-    StageSync* sync = (StageSync*)(smem + 2 * buf_bytes);
-    if (threadIdx.x == 0) stage_sync_init(sync);
-    if (n_blocks > 0) stage_block(records, n_trees, tb, rec_words, 0, lds_addr(smem), wave, kColWaves);
+    for (int r = 0; r < RPL; ++r) acc[r] = D.base;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     bool sync_ok = true;
-    for (int32_t b = 0; b < n_blocks; ++b) {
-        const int cur = b & 1;
-        if (b > 0)
-            sync_ok &= stage_acquire(sync, b, kColWaves, records, n_trees, tb, rec_words,
-                                     lds_addr(smem) + cur * buf_bytes);
+    for (int32_t grp = 0; grp < D.n_groups; ++grp) {
+        // this group's ranks of the rows
+        uint32_t row[RPL], fe[RPL];
         if (valid) {
-            const int32_t cnt = min(tb, n_trees - b * tb);
-            const uint32_t first = lds_addr(smem) + cur * buf_bytes;
-            int32_t t = 0;
-            if (RPL == 1)
-                for (; t + 4 <= cnt; t += 4)
-                    add_leaves<NF, 4, RPL>(first + t * R.bytes, R, depth, xf, kv, bs, xe, acc);
-            for (; t + 2 <= cnt; t += 2)
-                add_leaves<NF, 2, RPL>(first + t * R.bytes, R, depth, xf, kv, bs, xe, acc);
-            if (t < cnt) add_leaves<NF, 1, RPL>(first + t * R.bytes, R, depth, xf, kv, bs, xe, acc);
+            const uint32_t fe_s = ROWS ? 0u : rank_lane(D, grp, column_freq(P, s), NF == 4 ? P.engine[s] : 0.0f);
+#pragma unroll
+            for (int r = 0; r < RPL; ++r) {
+                if (ROWS) {
+                    const float* x = P.rows + in[r] * NF;
+                    row[r] = rank_row(D, grp, x[1], x[2]);
+                    fe[r] = rank_lane(D, grp, x[0], NF == 4 ? x[3] : 0.0f);
+                } else {
+                    row[r] = rank_row(D, grp, (float)P.kv[in[r]], (float)P.batch[in[r]]);
+                    fe[r] = fe_s;
+                }
+                // the ranks are complete before this wavefront stages again
+                asm volatile("" ::"v"(row[r]), "v"(fe[r]));
+            }
         }
-        stage_release(sync, b, kColWaves);
+        const int32_t b_end = min((grp + 1) * B.group_blocks, B.n_blocks);
+        for (int32_t b = grp * B.group_blocks; b < b_end; ++b) {
+            const uint32_t buf = lds_addr(smem) + (uint32_t)(b & 1) * buf_bytes;
+            if (b > 0) sync_ok &= stage_acquire(sync, b, kColWaves, D, B, buf);
+            if (valid) {
+                const int32_t cnt = block_count(D, B, b, block_first(D, B, b));
+                int32_t t = 0;
+                for (; t + 4 <= cnt; t += 4)
+                    add_leaves<4, RPL>(buf + t * rec_bytes, rec_bytes, D.depth, row, fe, acc);
+                for (; t + 2 <= cnt; t += 2)
+                    add_leaves<2, RPL>(buf + t * rec_bytes, rec_bytes, D.depth, row, fe, acc);
+                if (t < cnt) add_leaves<1, RPL>(buf + t * rec_bytes, rec_bytes, D.depth, row, fe, acc);
+            }
+            stage_release(sync, b, kColWaves);
+        }
     }
 #pragma unroll
     for (int r = 0; r < RPL; ++r)
@@ -211,31 +172,29 @@ __global__ __launch_bounds__(kColThreads) void forest_column_lds_kernel(const ui
 // row inside a leaf's box reaches that leaf), or of the leaf of the lane's
 // last walk in between.  Only rows in none of these boxes walk, the trees
 // they need, both in one pass when the wavefront needs both.
-template <int NF, int NT, int RPL>
-__device__ __forceinline__ void add_leaves_anchored(uint32_t tree, const RecordLayout& R, int32_t depth, float xf,
-                                                    const float (&kv)[RPL], const float (&bs)[RPL], float xe,
-                                                    float (&acc)[RPL]) {
+template <int NT, int RPL>
+__device__ __forceinline__ void add_leaves_anchored(uint32_t tree, uint32_t rec_bytes, int32_t depth, uint32_t fe,
+                                                    const uint32_t (&row)[RPL], float (&acc)[RPL]) {
     float va[2][NT];
-    float4 ba[2][NT];
+    Box ba[2][NT];
     {
-        const float xfa[2] = {xf, xf}, kva[2] = {kv[0], kv[RPL - 1]}, bsa[2] = {bs[0], bs[RPL - 1]},
-                    xea[2] = {xe, xe};
-        LeafAt ka[2][NT];
-        walk_rows<NF, NT, 2>(tree, R, depth, xfa, kva, bsa, xea, ka);
+        const uint32_t rows[2] = {row[0], row[RPL - 1]}, fes[2] = {fe, fe};
+        uint32_t ka[2][NT];
+        walk_rows<NT, 2>(tree, rec_bytes, depth, rows, fes, ka);
 #pragma unroll
         for (int e = 0; e < 2; ++e)
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 va[e][t] = leaf_value(ka[e][t]);
-                ba[e][t] = leaf_box(ka[e][t]);
+                ba[e][t] = leaf_box(ka[e][t], tree + t * rec_bytes);
             }
     }
     float vl[NT];
-    float4 bl[NT];   // the last walk's leaf (none yet: empty box)
+    Box bl[NT];   // the last walk's leaf (none yet: empty box)
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         vl[t] = 0.0f;
-        bl[t] = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
+        bl[t] = empty_box();
     }
 #pragma unroll
     for (int r = 0; r < RPL; ++r) {
@@ -247,29 +206,29 @@ __device__ __forceinline__ void add_leaves_anchored(uint32_t tree, const RecordL
             bool need[NT];
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-                const bool in0 = in_box(ba[0][t], kv[r], bs[r]);
-                const bool in1 = in_box(ba[1][t], kv[r], bs[r]);
-                need[t] = !in0 && !in1 && !in_box(bl[t], kv[r], bs[r]);
+                const bool in0 = in_box(ba[0][t], row[r]);
+                const bool in1 = in_box(ba[1][t], row[r]);
+                need[t] = !in0 && !in1 && !in_box(bl[t], row[r]);
                 v[t] = in0 ? va[0][t] : (in1 ? va[1][t] : vl[t]);
             }
             if (NT == 2 && __builtin_amdgcn_ballot_w64(need[0]) != 0 &&
                 __builtin_amdgcn_ballot_w64(need[NT - 1]) != 0) {
-                LeafAt k[NT];
-                walk<NF, NT>(tree, R, depth, xf, kv[r], bs[r], xe, k);
+                uint32_t k[NT];
+                walk<NT>(tree, rec_bytes, depth, row[r], fe, k);
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
                     if (need[t]) {
                         v[t] = vl[t] = leaf_value(k[t]);
-                        bl[t] = leaf_box(k[t]);
+                        bl[t] = leaf_box(k[t], tree + t * rec_bytes);
                     }
             } else {
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
                     if (need[t]) {
-                        LeafAt k[1];
-                        walk<NF, 1>(tree + t * R.bytes, R, depth, xf, kv[r], bs[r], xe, k);
+                        uint32_t k[1];
+                        walk<1>(tree + t * rec_bytes, rec_bytes, depth, row[r], fe, k);
                         v[t] = vl[t] = leaf_value(k[0]);
-                        bl[t] = leaf_box(k[0]);
+                        bl[t] = leaf_box(k[0], tree + t * rec_bytes);
                     }
             }
         }
@@ -283,14 +242,11 @@ __device__ __forceinline__ void add_leaves_anchored(uint32_t tree, const RecordL
 // consecutive iterations (a wavefront takes 64 x RPL consecutive
 // iterations of one scenario); staging as in forest_column_lds_kernel.
 // LIVE: the items are the first *P.n_live entries of P.order.
-template <int NF, int RPL, bool LIVE>
-__global__ __launch_bounds__(kColThreads) void forest_column_reuse_kernel(const uint4* __restrict__ records,
-                                                                         int32_t n_trees, int32_t depth,
-                                                                         int32_t tb, float base, ColumnParams P) {
+template <int RPL, bool LIVE>
+__global__ __launch_bounds__(kColThreads) void forest_column_reuse_kernel(RankDev D, TreeBlocks B, ColumnParams P) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const RecordLayout R = record_layout(depth);
-    const uint32_t rec_words = R.bytes / 16u;
-    const uint32_t buf_bytes = stage_buffer_bytes(tb, R);
+    const uint32_t rec_bytes = rank_record_bytes(D.depth);
+    const uint32_t buf_bytes = stage_buffer_bytes(B.tb, rec_bytes);
     const int wave = threadIdx.x / kWave;
     const int64_t item = __builtin_amdgcn_readfirstlane((int64_t)blockIdx.x * kColWaves + wave);
     const int32_t span = kWave * RPL;
@@ -304,40 +260,41 @@ __global__ __launch_bounds__(kColThreads) void forest_column_reuse_kernel(const 
     const int64_t s = code / n_cols;
     if (P.fidx && P.fidx[s] < 0) valid = false;
     const int32_t j0 = (int32_t)(code % n_cols) * span + lane_id() * RPL;
-    const float xf = column_freq(P, s);
-    const float xe = NF == 4 ? P.engine[s] : 0.0f;
-    float kv[RPL], bs[RPL];
     float acc[RPL];
 #pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-        const int32_t j = min(j0 + r, P.H - 1);
-        kv[r] = (float)P.kv[s * P.H + j];
-        bs[r] = (float)P.batch[s * P.H + j];
-        acc[r] = base;
-        asm volatile("" ::"v"(kv[r]), "v"(bs[r]));
-    }
-    asm volatile("" ::"v"(xf), "v"(xe));
-    const int32_t n_blocks = (n_trees + tb - 1) / tb;
+    for (int r = 0; r < RPL; ++r) acc[r] = D.base;
     StageSync* sync = (StageSync*)(smem + 2 * buf_bytes);
     if (threadIdx.x == 0) stage_sync_init(sync);
-    if (n_blocks > 0) stage_block(records, n_trees, tb, rec_words, 0, lds_addr(smem), wave, kColWaves);
+    if (B.n_blocks > 0) stage_block(D, B, 0, lds_addr(smem), wave, kColWaves);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     bool sync_ok = true;
-    for (int32_t b = 0; b < n_blocks; ++b) {
-        const int cur = b & 1;
-        if (b > 0)
-            sync_ok &= stage_acquire(sync, b, kColWaves, records, n_trees, tb, rec_words,
-                                     lds_addr(smem) + cur * buf_bytes);
+    for (int32_t grp = 0; grp < D.n_groups; ++grp) {
+        uint32_t row[RPL], fe = 0;
         if (valid) {
-            const int32_t cnt = min(tb, n_trees - b * tb);
-            const uint32_t first = lds_addr(smem) + cur * buf_bytes;
-            int32_t t = 0;
-            for (; t + 2 <= cnt; t += 2)
-                add_leaves_anchored<NF, 2, RPL>(first + t * R.bytes, R, depth, xf, kv, bs, xe, acc);
-            if (t < cnt) add_leaves_anchored<NF, 1, RPL>(first + t * R.bytes, R, depth, xf, kv, bs, xe, acc);
+            fe = rank_lane(D, grp, column_freq(P, s), P.engine ? P.engine[s] : 0.0f);
+#pragma unroll
+            for (int r = 0; r < RPL; ++r) {
+                const int64_t i = s * P.H + min(j0 + r, P.H - 1);
+                row[r] = rank_row(D, grp, (float)P.kv[i], (float)P.batch[i]);
+                // the ranks are complete before this wavefront stages again
+                asm volatile("" ::"v"(row[r]));
+            }
+            asm volatile("" ::"v"(fe));
         }
-        stage_release(sync, b, kColWaves);
+        const int32_t b_end = min((grp + 1) * B.group_blocks, B.n_blocks);
+        for (int32_t b = grp * B.group_blocks; b < b_end; ++b) {
+            const uint32_t buf = lds_addr(smem) + (uint32_t)(b & 1) * buf_bytes;
+            if (b > 0) sync_ok &= stage_acquire(sync, b, kColWaves, D, B, buf);
+            if (valid) {
+                const int32_t cnt = block_count(D, B, b, block_first(D, B, b));
+                int32_t t = 0;
+                for (; t + 2 <= cnt; t += 2)
+                    add_leaves_anchored<2, RPL>(buf + t * rec_bytes, rec_bytes, D.depth, fe, row, acc);
+                if (t < cnt) add_leaves_anchored<1, RPL>(buf + t * rec_bytes, rec_bytes, D.depth, fe, row, acc);
+            }
+            stage_release(sync, b, kColWaves);
+        }
     }
     if (valid) {
 #pragma unroll
@@ -379,9 +336,9 @@ __global__ __launch_bounds__(256) void forest_column_global_kernel(const uint2* 
 // Trees per staged block: double buffers within the LDS budget.
 int32_t column_trees_per_block(const ForestDev& f, size_t* lds) {
     if (!f.records || f.n_trees == 0) return 0;
-    const RecordLayout R = record_layout(f.depth);
+    const uint32_t rec_bytes = rank_record_bytes(f.depth);
     // two tree buffers and their hand-over counters
-    auto bytes = [&](int32_t n) { return 2 * (size_t)stage_buffer_bytes(n, R) + sizeof(StageSync); };
+    auto bytes = [&](int32_t n) { return 2 * (size_t)stage_buffer_bytes(n, rec_bytes) + sizeof(StageSync); };
     int32_t tb = std::min<int32_t>(f.n_trees, 64);
     while (tb > 1 && bytes(tb) > kColLdsBudget) --tb;
     if (bytes(tb) > kColLdsBudget) return 0;
@@ -398,7 +355,7 @@ hipError_t launch_column_lds(const ForestDev& f, const ColumnParams& c, int32_t 
     const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)((items + kColWaves - 1) / kColWaves)), dim3(kColThreads), lds, stream,
-                       f.records, f.n_trees, f.depth, tb, f.base_score, c);
+                       rank_dev(f), tree_blocks(f.n_trees, f.group_trees, tb), c);
     return hipGetLastError();
 }
 
@@ -482,17 +439,17 @@ hipError_t reuse_rows_per_lane(const ForestDev& f, const ColumnParams& c, int* r
     return hipSuccess;
 }
 
-template <int NF, int RPL>
+template <int RPL>
 hipError_t launch_column_reuse(const ForestDev& f, const ColumnParams& c, int32_t tb, size_t lds,
                                hipStream_t stream) {
     const int64_t items = c.S * ((c.H + kWave * RPL - 1) / (kWave * RPL));
     if (!grid_fits((items + kColWaves - 1) / kColWaves)) return hipErrorInvalidConfiguration;
     const auto kern =
-        c.n_live ? forest_column_reuse_kernel<NF, RPL, true> : forest_column_reuse_kernel<NF, RPL, false>;
+        c.n_live ? forest_column_reuse_kernel<RPL, true> : forest_column_reuse_kernel<RPL, false>;
     const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)((items + kColWaves - 1) / kColWaves)), dim3(kColThreads), lds, stream,
-                       f.records, f.n_trees, f.depth, tb, f.base_score, c);
+                       rank_dev(f), tree_blocks(f.n_trees, f.group_trees, tb), c);
     return hipGetLastError();
 }
 
@@ -504,8 +461,8 @@ hipError_t launch_column(const ForestDev& f, const ColumnParams& c, hipStream_t 
         int rpl = 0, cus = 0;
         const hipError_t e = reuse_rows_per_lane(f, c, &rpl, &cus);
         if (e != hipSuccess) return e;
-        if (rpl == 16) return launch_column_reuse<NF, 16>(f, c, tb, lds, stream);
-        if (rpl == 8) return launch_column_reuse<NF, 8>(f, c, tb, lds, stream);
+        if (rpl == 16) return launch_column_reuse<16>(f, c, tb, lds, stream);
+        if (rpl == 8) return launch_column_reuse<8>(f, c, tb, lds, stream);
     }
     if (tb > 0) {
         // rows per lane: enough chains to overlap, without idle stripes on

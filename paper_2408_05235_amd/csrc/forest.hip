@@ -18,15 +18,16 @@
 //
 //   forest_grid_lds_kernel     (depth <= 11) A 1024-thread workgroup (16
 //       wavefronts, 16 x 64 x 64 rows) walks the ensemble in blocks of trees
-//       staged in three LDS buffers.  A tree is one record (nodes, leaf values,
-//       leaf boxes), so a block is one contiguous copy, made straight from
-//       global memory into LDS and handed from wavefront to wavefront without
-//       block barriers (stage_acquire / stage_release).  Tree walks read LDS
-//       only.  A node step picks the tested feature with byte permutes and
-//       compares once, all in vector registers (no lane-mask round trip).
+//       staged in LDS buffers.  A tree is one rank record (nodes, leaf values,
+//       leaf boxes; record_format.h), so a block is one contiguous copy, made
+//       straight from global memory into LDS and handed from wavefront to
+//       wavefront without block barriers (stage_acquire / stage_release).
+//       Tree walks read LDS only, four vector instructions a level.
 //       Trees are taken in pairs that share one box test (a row that leaves
 //       it walks only the tree whose own box it left), and rows in groups of
-//       eight whose (KV, batch) hull is tested before any single row.  The
+//       eight whose (KV, batch) hull is tested before any single row.  Rows,
+//       hulls and boxes are pairs of 16-bit ranks in one register: a row's
+//       box test is a packed min, a packed max and a compare.  The
 //       (scenario, chunk) items are ordered by an estimate of their walks,
 //       so a workgroup's wavefronts do similar work.
 //   forest_grid_global_kernel  (deeper trees) The same per-lane scheme with
@@ -35,7 +36,7 @@
 // Device layout (built by tl_forest_create): nodes [T][2^d] (8 bytes:
 // threshold bits, feature; the last entry of each tree is padding), leaves
 // [T][2^d] fp32, and for 3-4 features the leaf boxes [T][2^d] (kv_lo, kv_hi,
-// batch_lo, batch_hi) and, up to depth 11, the tree records of the LDS
+// batch_lo, batch_hi) or, up to depth 11, the rank records of the LDS
 // kernel.
 //
 // forest_rows_kernel evaluates arbitrary rows: each thread walks RPT
@@ -113,22 +114,22 @@ __global__ __launch_bounds__(256) void forest_rows_kernel(const uint2* __restric
         if (r < nr) out[r0 + r] = acc[r];
 }
 
-#ifndef TL_LDS_J
-#define TL_LDS_J 64
-#endif
-#ifndef TL_LDS_WAVES
-#define TL_LDS_WAVES 16
-#endif
-#ifndef TL_LDS_BUDGET_KIB
-#define TL_LDS_BUDGET_KIB 160
-#endif
-// Tree buffers: three blocks of 2 trees at depth 10 (against two of 3) let a
-// wavefront run two blocks ahead of the slowest and pair every tree.
-constexpr int kLdsBuffers = 3;
-#ifndef TL_LDS_WAVES_PER_SIMD
-#define TL_LDS_WAVES_PER_SIMD 4
-#endif
-constexpr int kLdsJ = TL_LDS_J;          // future iterations per wavefront (LDS kernel)
+constexpr int kLdsJ = 32;                // future iterations per wavefront (LDS kernel)
+constexpr int kLdsWaves = 16;            // wavefronts per workgroup
+constexpr int kLdsThreads = kLdsWaves * kWave;
+// Two workgroups share a CU: half its LDS each, and 64 registers a lane.
+// Measured (ms a step; 1024 boards x 2048 iterations x 64 frequencies with
+// 500 trees of depth 8 / 4096 x 1024 x 64 with 2000 of depth 10 / 256 x 4096 x
+// 32 with 300 of depth 8): J = 32 at 8 wavefronts per SIMD 6.9 / 86.5 / 2.10;
+// J = 40 at 6 7.5 / 86.8 / 2.26; J = 64 at 4 (one workgroup, the whole LDS)
+// 8.7 / 84.4 / 2.42.  A longer chunk saves walks of first rows, more
+// wavefronts hide the walks' chains of LDS reads; at 8 the VALU issues nearly
+// all the time.
+constexpr int kLdsWavesPerSimd = 8;
+constexpr size_t kLdsBudget = 80 * 1024;
+constexpr int kLdsBuffers = 2;           // tree buffers
+constexpr int kOrderJ = 64;              // future iterations per entry of the work order
+constexpr int kOrderItems = kOrderJ / kLdsJ;
 constexpr int kGlobalJ = 32;             // future iterations per wavefront (global kernel)
 
 // Which (scenario, frequency group, iteration chunk) a wavefront evaluates.
@@ -138,20 +139,24 @@ struct GridItem {
     int32_t f, j0, nj;
 };
 
-// Items are numbered scenario-fastest: the wavefronts of one workgroup take
-// the same iteration chunk (and frequency group) of consecutive scenarios.
+// Items are numbered scenario-fastest within an iteration chunk of J * PER
+// rows, the PER items of one chunk next to each other: the wavefronts of one
+// workgroup take the same chunk (and frequency group) of consecutive
+// scenarios.
 // How many walks a chunk needs follows how fast KV and batch change there;
 // workgroups whose wavefronts do similar work lose less time waiting for
 // their slowest wavefront to release a tree buffer.  With a work order
-// (P.order), item i of a frequency group takes
+// (P.order), entry i of a frequency group takes
 // the (scenario, chunk) pair order[i] instead: pairs sorted by estimated
 // cost, most expensive first.
-__device__ __forceinline__ GridItem grid_item(const GridParams& P, int64_t item, int J) {
-    const int32_t n_chunks = (P.H + J - 1) / J;
+template <int J, int PER>
+__device__ __forceinline__ GridItem grid_item(const GridParams& P, int64_t item) {
+    const int32_t n_chunks = (P.H + J * PER - 1) / (J * PER);
     const int32_t n_fg = (P.F + kWave - 1) / kWave;
     GridItem g;
-    g.valid = item < P.S * n_fg * n_chunks;
-    const int64_t it = g.valid ? item : 0;
+    g.valid = item < P.S * n_fg * n_chunks * PER;
+    const int64_t it = g.valid ? item / PER : 0;
+    const int32_t part = g.valid ? (int32_t)(item % PER) : 0;
     const int64_t n_pairs = P.S * n_chunks;
     int32_t chunk;
     if (P.order) {
@@ -165,7 +170,11 @@ __device__ __forceinline__ GridItem grid_item(const GridParams& P, int64_t item,
         g.f = (int32_t)(rest % n_fg) * kWave + lane_id();
         chunk = (int32_t)(rest / n_fg);
     }
-    g.j0 = chunk * J;
+    g.j0 = (chunk * PER + part) * J;
+    if (g.j0 >= P.H) {   // the last chunk may hold fewer items
+        g.valid = false;
+        g.j0 = 0;
+    }
     g.nj = min(J, P.H - g.j0);
     return g;
 }
@@ -215,117 +224,102 @@ __global__ __launch_bounds__(kCostThreads) void grid_cost_kernel(const float* __
 
 // ---------------------------------------------------------------- LDS-staged
 
-constexpr int kLdsWaves = TL_LDS_WAVES;  // wavefronts per workgroup
-constexpr int kLdsThreads = kLdsWaves * kWave;
 // A wavefront-uniform value read into a scalar register: the compiler's lane
 // read, with the empty asm statements hiding how x was computed and pinning
 // the result to the scalar register file (the compiler would otherwise
 // rematerialize it in vector registers).
-__device__ __forceinline__ float to_sgpr(float x) {
+__device__ __forceinline__ uint32_t to_sgpr(uint32_t x) {
     asm volatile("" : "+v"(x));
-    int32_t r = __builtin_amdgcn_readfirstlane(__float_as_int(x));
+    uint32_t r = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)x);
     asm volatile("" : "+s"(r));
-    return __int_as_float(r);
+    return r;
 }
 
-#ifndef TL_ROW_GROUP
-#define TL_ROW_GROUP 8
-#endif
-constexpr int kRowGroup = TL_ROW_GROUP;   // rows whose (KV, batch) hull is tested as one
+constexpr int kRowGroup = 8;   // rows whose (KV, batch) hull is tested as one
 
-// Adds the leaves of NT (1 or 2) consecutive staged trees (records R.bytes
-// apart, the first at `tree`) to the J row sums of a wavefront, in tree
-// order.  hull[g] = (min KV, max KV, min batch, max batch) over the rows of
-// group g; kv4 holds the rows' (KV, batch) pairs, two per 16 bytes.  A lane
-// keeps the values of the leaves its walks reached, their boxes and the
-// intersection of the boxes.  A group whose hull lies inside that
-// intersection on every lane needs only its adds; other groups test row by
-// row.  A lane whose row leaves the intersection walks only the trees whose
-// own box it left (both in one pass when the wavefront needs both) and reads
-// the new leaves' values and boxes.
-template <int NF, int J, int NT>
-__device__ __forceinline__ void eval_trees(const unsigned char* lds, uint32_t tree_off, const RecordLayout& R,
-                                           int32_t depth,
-                                           const float4* kv4, const float (&hull)[J / kRowGroup][4], float xf,
-                                           float xe, float (&acc)[J]) {
-    static_assert(J % kRowGroup == 0, "whole row groups");
+// Adds the leaves of NT (1 or 2) consecutive staged trees (rec_bytes apart,
+// the first at LDS byte address `tree`) to the J row sums of a wavefront, in
+// tree order.  hull[g] is the box of the rows of group g; rows4 holds the
+// rows' rank pairs, four per 16 bytes.  A lane keeps the values of the leaves
+// its walks reached, their boxes and the intersection of the boxes.  A group
+// whose hull lies inside that intersection on every lane needs only its adds;
+// other groups test row by row.  A lane whose row leaves the intersection
+// walks only the trees whose own box it left (both in one pass when the
+// wavefront needs both) and reads the new leaves' values and boxes.
+template <int J, int NT>
+__device__ __forceinline__ void eval_trees(uint32_t tree, uint32_t rec_bytes, int32_t depth, const uint4* rows4,
+                                           const Box (&hull)[J / kRowGroup], uint32_t fe, float (&acc)[J]) {
+    static_assert(J % kRowGroup == 0 && kRowGroup % 4 == 0, "whole row groups");
     static_assert(NT == 1 || NT == 2, "one tree or a pair");
-    // the pairs are re-read from LDS for each group that needs them rather
+    // the rows are re-read from LDS for each group that needs them rather
     // than held in registers across the tree loop
     asm volatile("" ::: "memory");
-    const unsigned char* tree = lds + tree_off;
-    const uint32_t tree_addr = lds_addr(tree);
-    const uint32_t tree1 = tree_addr + R.bytes;
-    // a pair's own leaf boxes, decoded, beside their intersection: after a
-    // walk only the walked tree's box is read again
-    float4 box, b0, b1 = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
+    const uint32_t tree1 = tree + rec_bytes;
+    // a pair's own leaf boxes beside their intersection: after a walk only
+    // the walked tree's box is read again
+    Box box, b0, b1 = empty_box();
     float v[NT];
     {
         // the chunk's first row walks every tree on every lane, outside the
         // group loop so that the loop's walks carry no first-row case
-        const float4 q0 = kv4[0];
-        LeafAt k[NT];
-        walk<NF, NT>(tree_addr, R, depth, xf, q0.x, q0.y, xe, k);
+        uint32_t k[NT];
+        walk<NT>(tree, rec_bytes, depth, rows4[0].x, fe, k);
         v[0] = leaf_value(k[0]);
-        b0 = leaf_box(k[0]);
+        b0 = leaf_box(k[0], tree);
         box = b0;
         if (NT == 2) {
             v[NT - 1] = leaf_value(k[NT - 1]);
-            b1 = leaf_box(k[NT - 1]);
+            b1 = leaf_box(k[NT - 1], tree1);
             box = box_meet(b0, b1);
         }
     }
 #pragma unroll
     for (int gi = 0; gi < J / kRowGroup; ++gi) {
-        const uint64_t inside = __builtin_amdgcn_fcmpf(hull[gi][0], box.x, 3) &   // min KV >= kv_lo
-                                __builtin_amdgcn_fcmpf(hull[gi][1], box.y, 4) &   // max KV < kv_hi
-                                __builtin_amdgcn_fcmpf(hull[gi][2], box.z, 3) &
-                                __builtin_amdgcn_fcmpf(hull[gi][3], box.w, 4);
-        const bool test_rows = inside != __builtin_amdgcn_read_exec();   // wavefront-uniform
-        float4 q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        const uint32_t outside = pair_above(hull[gi].lo, box.lo) | pair_above(box.hi, hull[gi].hi);
+        const bool test_rows = __builtin_amdgcn_ballot_w64(outside != 0) != 0;   // wavefront-uniform
+        uint4 q = make_uint4(0, 0, 0, 0);
 #pragma unroll
         for (int i = 0; i < kRowGroup; ++i) {
             if (test_rows) {
-                if ((i & 1) == 0) {
-                    // two rows per read; the barrier keeps the compiler from
+                if ((i & 3) == 0) {
+                    // four rows per read; the barrier keeps the compiler from
                     // hoisting all reads of the group (registers)
                     asm volatile("" ::: "memory");
-                    q = kv4[gi * (kRowGroup / 2) + i / 2];
+                    q = rows4[gi * (kRowGroup / 4) + i / 4];
                 }
-                const float kv = (i & 1) ? q.z : q.x;
-                const float bs = (i & 1) ? q.w : q.y;
-                if (!in_box(box, kv, bs)) {
+                const uint32_t row = (i & 3) == 0 ? q.x : (i & 3) == 1 ? q.y : (i & 3) == 2 ? q.z : q.w;
+                if (!in_box(box, row)) {
                     if (NT == 1) {
-                        LeafAt k[1];
-                        walk<NF, 1>(tree_addr, R, depth, xf, kv, bs, xe, k);
+                        uint32_t k[1];
+                        walk<1>(tree, rec_bytes, depth, row, fe, k);
                         v[0] = leaf_value(k[0]);
-                        box = leaf_box(k[0]);
+                        box = leaf_box(k[0], tree);
                     } else {
-                        const bool n0 = !in_box(b0, kv, bs);
-                        const bool n1 = !in_box(b1, kv, bs);
+                        const bool n0 = !in_box(b0, row);
+                        const bool n1 = !in_box(b1, row);
                         if (__builtin_amdgcn_ballot_w64(n0) != 0 && __builtin_amdgcn_ballot_w64(n1) != 0) {
-                            LeafAt k[2];
-                            walk<NF, 2>(tree_addr, R, depth, xf, kv, bs, xe, k);
+                            uint32_t k[2];
+                            walk<2>(tree, rec_bytes, depth, row, fe, k);
                             if (n0) {
                                 v[0] = leaf_value(k[0]);
-                                b0 = leaf_box(k[0]);
+                                b0 = leaf_box(k[0], tree);
                             }
                             if (n1) {
                                 v[NT - 1] = leaf_value(k[1]);
-                                b1 = leaf_box(k[1]);
+                                b1 = leaf_box(k[1], tree1);
                             }
                         } else {
                             if (n0) {
-                                LeafAt k[1];
-                                walk<NF, 1>(tree_addr, R, depth, xf, kv, bs, xe, k);
+                                uint32_t k[1];
+                                walk<1>(tree, rec_bytes, depth, row, fe, k);
                                 v[0] = leaf_value(k[0]);
-                                b0 = leaf_box(k[0]);
+                                b0 = leaf_box(k[0], tree);
                             }
                             if (n1) {
-                                LeafAt k[1];
-                                walk<NF, 1>(tree1, R, depth, xf, kv, bs, xe, k);
+                                uint32_t k[1];
+                                walk<1>(tree1, rec_bytes, depth, row, fe, k);
                                 v[NT - 1] = leaf_value(k[0]);
-                                b1 = leaf_box(k[0]);
+                                b1 = leaf_box(k[0], tree1);
                             }
                         }
                         box = box_meet(b0, b1);
@@ -342,88 +336,80 @@ __device__ __forceinline__ void eval_trees(const unsigned char* lds, uint32_t tr
     }
 }
 
-template <int NF, int J>
-__global__ __launch_bounds__(kLdsThreads, TL_LDS_WAVES_PER_SIMD) void forest_grid_lds_kernel(const uint4* __restrict__ records,
-                                                                      int32_t n_trees, int32_t depth,
-                                                                      int32_t tb, float base, GridParams P) {
+template <int J>
+__global__ __launch_bounds__(kLdsThreads, kLdsWavesPerSimd) void forest_grid_lds_kernel(RankDev D, TreeBlocks B,
+                                                                                             GridParams P) {
+    static_assert(J <= kWave, "one lane ranks each row");
     extern __shared__ __align__(16) unsigned char smem[];
-    const int32_t n_leaf = 1 << depth;
-    const RecordLayout R = record_layout(depth);
-    const uint32_t rec_words = R.bytes / 16u;
-    const uint32_t buf_bytes = stage_buffer_bytes(tb, R);
+    const uint32_t rec_bytes = rank_record_bytes(D.depth);
+    const uint32_t buf_bytes = stage_buffer_bytes(B.tb, rec_bytes);
 
     const int wave = threadIdx.x / kWave;
     const int lane = lane_id();
     const int64_t item = __builtin_amdgcn_readfirstlane((int64_t)blockIdx.x * kLdsWaves + wave);
-    const GridItem g = grid_item(P, item, J);
+    const GridItem g = grid_item<J, kOrderItems>(P, item);
     const int32_t F = P.F, H = P.H;
     const bool active = g.valid && g.f < F;
-    // (a NaN frequency or engine size fails every "x < threshold" test and
-    // takes every right turn, as in a plain walk)
-    const float xf = P.freqs[g.f < F ? g.f : F - 1];
-    const float xe = (NF == 4) ? P.engine[g.s] : 0.0f;
-    // the J (KV, batch) pairs of this wavefront are the same for every lane;
-    // they sit in LDS after the two tree buffers and are read as broadcasts
-    float2* kvb = (float2*)(smem + kLdsBuffers * buf_bytes) + wave * J;
-    StageSync* sync = (StageSync*)(smem + kLdsBuffers * buf_bytes + (size_t)kLdsWaves * J * sizeof(float2));
+    // the J rank pairs of this wavefront are the same for every lane; they
+    // sit in LDS after the tree buffers and are read as broadcasts
+    uint32_t* rows = (uint32_t*)(smem + kLdsBuffers * buf_bytes) + wave * J;
+    StageSync* sync = (StageSync*)(smem + kLdsBuffers * buf_bytes + (size_t)kLdsWaves * J * sizeof(uint32_t));
     if (threadIdx.x == 0) stage_sync_init<kLdsBuffers>(sync);
-    for (int r = lane; r < J; r += kWave) {
-        const int32_t j = g.j0 + min(r, g.nj - 1);
-        kvb[r] = make_float2((float)P.kv[g.s * H + j], (float)P.batch[g.s * H + j]);
-    }
 
     // staging: block 0 by every wavefront before the barrier, the others
     // handed over without barriers (stage_acquire / stage_release)
-    const int32_t n_blocks = (n_trees + tb - 1) / tb;
     float acc[J];
 #pragma unroll
-    for (int jj = 0; jj < J; ++jj) acc[jj] = base;
-
-    // Make the lane's frequency / engine size complete here, before any
-    // staging copy is in flight: otherwise the walks inside the loop would
-    // each wait for all outstanding copies.
-    asm volatile("" ::"v"(xf), "v"(xe));
-    if (n_blocks > 0) stage_block(records, n_trees, tb, rec_words, 0, lds_addr(smem), wave, kLdsWaves);
+    for (int jj = 0; jj < J; ++jj) acc[jj] = D.base;
+    if (B.n_blocks > 0) stage_block(D, B, 0, lds_addr(smem), wave, kLdsWaves);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    // per row group, the (KV, batch) hull of its rows (wavefront-uniform)
-    const float4* kvb4 = (const float4*)kvb;
-    float hull[J / kRowGroup][4];
-#pragma unroll
-    for (int gi = 0; gi < J / kRowGroup; ++gi) {
-        float klo = INFINITY, khi = -INFINITY, blo = INFINITY, bhi = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < kRowGroup; ++i) {
-            const float2 p = kvb[gi * kRowGroup + i];
-            klo = fminf(klo, p.x);
-            khi = fmaxf(khi, p.x);
-            blo = fminf(blo, p.y);
-            bhi = fmaxf(bhi, p.y);
-        }
-        hull[gi][0] = to_sgpr(klo);
-        hull[gi][1] = to_sgpr(khi);
-        hull[gi][2] = to_sgpr(blo);
-        hull[gi][3] = to_sgpr(bhi);
-    }
     bool sync_ok = true;
-    for (int32_t b = 0; b < n_blocks; ++b) {
-        const int cur = b % kLdsBuffers;
-        if (b > 0)
-            sync_ok &= stage_acquire<kLdsBuffers>(sync, b, kLdsWaves, records, n_trees, tb, rec_words,
-                                                  lds_addr(smem + cur * buf_bytes));
-        if (g.valid) {
-            const int32_t cnt = min(tb, n_trees - b * tb);
-            const uint32_t bp = cur * buf_bytes;
-            // Trees are taken two at a time and a lane keeps the intersection
-            // of the two leaf boxes: a row inside it reaches both leaves
-            // again.  When a row leaves it, both trees are walked in one pass,
-            // so the two chains of dependent LDS reads overlap.
-            int32_t tt = 0;
-            for (; tt + 1 < cnt; tt += 2)
-                eval_trees<NF, J, 2>(smem, bp + tt * R.bytes, R, depth, kvb4, hull, xf, xe, acc);
-            if (tt < cnt) eval_trees<NF, J, 1>(smem, bp + tt * R.bytes, R, depth, kvb4, hull, xf, xe, acc);
+    for (int32_t grp = 0; grp < D.n_groups; ++grp) {
+        // this group's ranks of the lane's frequency and engine size (a NaN
+        // ranks above every threshold: every right turn, as in a plain walk)
+        // and of row `lane` (rows past the chunk repeat its last)
+        const int32_t j = g.j0 + min(min(lane, J - 1), g.nj - 1);
+        const uint32_t fe = rank_lane(D, grp, P.freqs[g.f < F ? g.f : F - 1], P.engine ? P.engine[g.s] : 0.0f);
+        const uint32_t own = rank_row(D, grp, (float)P.kv[g.s * H + j], (float)P.batch[g.s * H + j]);
+        if (lane < J) rows[lane] = own;
+        asm volatile("" ::: "memory");
+        // per row group, the box of its rows (wavefront-uniform)
+        const uint4* rows4 = (const uint4*)rows;
+        Box hull[J / kRowGroup];
+#pragma unroll
+        for (int gi = 0; gi < J / kRowGroup; ++gi) {
+            uint32_t lo = 0xffffffffu, hi = 0;
+#pragma unroll
+            for (int i = 0; i < kRowGroup / 4; ++i) {
+                const uint4 q = rows4[gi * (kRowGroup / 4) + i];
+                lo = pair_min(lo, pair_min(pair_min(q.x, q.y), pair_min(q.z, q.w)));
+                hi = pair_max(hi, pair_max(pair_max(q.x, q.y), pair_max(q.z, q.w)));
+            }
+            hull[gi].lo = to_sgpr(lo);
+            hull[gi].hi = to_sgpr(hi);
         }
-        stage_release<kLdsBuffers>(sync, b, kLdsWaves);
+        // the ranks are complete before this wavefront stages again: the
+        // walks then never wait for a copy in flight
+        asm volatile("" ::"v"(fe));
+        const int32_t b_end = min((grp + 1) * B.group_blocks, B.n_blocks);
+        for (int32_t b = grp * B.group_blocks; b < b_end; ++b) {
+            const uint32_t buf = lds_addr(smem) + (uint32_t)(b % kLdsBuffers) * buf_bytes;
+            if (b > 0) sync_ok &= stage_acquire<kLdsBuffers>(sync, b, kLdsWaves, D, B, buf);
+            if (g.valid) {
+                const int32_t cnt = block_count(D, B, b, block_first(D, B, b));
+                // Trees are taken two at a time and a lane keeps the
+                // intersection of the two leaf boxes: a row inside it reaches
+                // both leaves again.  When a row leaves it, both trees are
+                // walked in one pass, so the two chains of dependent LDS
+                // reads overlap.
+                int32_t tt = 0;
+                for (; tt + 1 < cnt; tt += 2)
+                    eval_trees<J, 2>(buf + tt * rec_bytes, rec_bytes, D.depth, rows4, hull, fe, acc);
+                if (tt < cnt) eval_trees<J, 1>(buf + tt * rec_bytes, rec_bytes, D.depth, rows4, hull, fe, acc);
+            }
+            stage_release<kLdsBuffers>(sync, b, kLdsWaves);
+        }
     }
     if (active) {
         float* o = P.out + ((int64_t)g.s * F + g.f) * H + g.j0;
@@ -447,7 +433,7 @@ __global__ __launch_bounds__(256) void forest_grid_global_kernel(const uint2* __
     const int wave = threadIdx.x / kWave;
     const int lane = lane_id();
     const int64_t item = __builtin_amdgcn_readfirstlane((int64_t)blockIdx.x * kGlobalWaves + wave);
-    const GridItem g = grid_item(P, item, J);
+    const GridItem g = grid_item<J, 1>(P, item);
     const int32_t F = P.F, H = P.H;
     const bool active = g.valid && g.f < F;
     const float xf = P.freqs[g.f < F ? g.f : F - 1];
@@ -512,34 +498,32 @@ hipError_t launch_nf(const ForestDev& f, const float* rows, int64_t n_rows, floa
     return hipGetLastError();
 }
 
-// Trees per staged block for the LDS kernel: two blocks and the wavefronts'
-// (KV, batch) pairs must fit the LDS budget, and one block the staging
-// registers.  0 = the LDS kernel cannot run.
+// Trees per staged block for the LDS kernel: the buffers and the wavefronts'
+// rows must fit the LDS budget.  0 = the LDS kernel cannot run.
 int32_t lds_trees_per_block(const ForestDev& f, size_t* lds_bytes) {
     if (!f.records || f.depth > kMaxRecordDepth) return 0;
-    const RecordLayout R = record_layout(f.depth);
-    const size_t head = (size_t)kLdsWaves * kLdsJ * sizeof(float2) + sizeof(StageSync);
-    const size_t budget = (size_t)TL_LDS_BUDGET_KIB * 1024;
-    auto fits = [&](int32_t tb) { return kLdsBuffers * (size_t)stage_buffer_bytes(tb, R) + head <= budget; };
+    const uint32_t rec_bytes = rank_record_bytes(f.depth);
+    const size_t head = (size_t)kLdsWaves * kLdsJ * sizeof(uint32_t) + sizeof(StageSync);
+    auto fits = [&](int32_t tb) { return kLdsBuffers * (size_t)stage_buffer_bytes(tb, rec_bytes) + head <= kLdsBudget; };
+    // whole pairs of trees where two fit
     int32_t tb = 64;
-    while (tb > 1 && !fits(tb)) --tb;
+    while (tb > 1 && !fits(tb)) tb -= tb > 2 ? 2 : 1;
     if (!fits(tb)) return 0;
-    *lds_bytes = kLdsBuffers * (size_t)stage_buffer_bytes(tb, R) + head;
+    *lds_bytes = kLdsBuffers * (size_t)stage_buffer_bytes(tb, rec_bytes) + head;
     return tb;
 }
 
-template <int NF>
 hipError_t launch_grid_lds(const ForestDev& f, const GridParams& g, int32_t tb, size_t lds, hipStream_t stream) {
-    const auto kern = forest_grid_lds_kernel<NF, kLdsJ>;
+    const auto kern = forest_grid_lds_kernel<kLdsJ>;
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    const int64_t n_chunks = (g.H + kLdsJ - 1) / kLdsJ;
+    const int64_t n_chunks = (g.H + kOrderJ - 1) / kOrderJ;
     const int64_t n_fg = (g.F + kWave - 1) / kWave;
-    const int64_t items = g.S * n_fg * n_chunks;
+    const int64_t items = g.S * n_fg * n_chunks * kOrderItems;
     const int64_t blocks = (items + kLdsWaves - 1) / kLdsWaves;
     if (!grid_fits(blocks)) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kLdsThreads), lds, stream, f.records, f.n_trees,
-                       f.depth, tb, f.base_score, g);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kLdsThreads), lds, stream, rank_dev(f),
+                       tree_blocks(f.n_trees, f.group_trees, tb), g);
     return hipGetLastError();
 }
 
@@ -595,7 +579,7 @@ hipError_t plan_order(const ForestDev& f, const GridParams& g, PairOrderPlan* p)
     *p = PairOrderPlan{0, 0, 0, 0};
     size_t lds = 0;
     if (lds_trees_per_block(f, &lds) <= 0) return hipSuccess;   // the global kernel takes no order
-    return pair_order_plan(f, g.S * ((g.H + kLdsJ - 1) / kLdsJ), 2 * kLdsWaves, p);
+    return pair_order_plan(f, g.S * ((g.H + kOrderJ - 1) / kOrderJ), 2 * 16, p);
 }
 
 }  // namespace
@@ -622,12 +606,12 @@ hipError_t launch_forest_grid(const ForestDev& f, const GridParams& g_in, void* 
     if (p.n > 0 && ws && ws_bytes >= p.bytes) {
         hipLaunchKernelGGL(grid_cost_kernel, dim3((unsigned)((p.n + kCostThreads - 1) / kCostThreads)),
                            dim3(kCostThreads), 0, stream, f.cuts_kv, f.n_cuts_kv, f.cuts_bs, f.n_cuts_bs, g.kv,
-                           g.batch, g.S, g.H, kLdsJ, pair_order_cost(p, ws), pair_order_code(p, ws));
+                           g.batch, g.S, g.H, kOrderJ, pair_order_cost(p, ws), pair_order_code(p, ws));
         e = hipGetLastError();
         if (e == hipSuccess) e = pair_order_sort(p, ws, &g.order, stream);
         if (e != hipSuccess) return e;
     }
-    return f.n_features == 4 ? launch_grid_lds<4>(f, g, tb, lds, stream) : launch_grid_lds<3>(f, g, tb, lds, stream);
+    return launch_grid_lds(f, g, tb, lds, stream);
 }
 
 // Workspace of the grid kernel's work order for callers that cannot

@@ -1,8 +1,12 @@
 // Node walks over tree records staged in LDS and leaf-box tests, shared by
-// the forest kernels.
-// A record node is (threshold, sel1, sel2, sel3): the byte-permute selectors
-// that pick the tested feature out of the row (see node_feature); internal
-// nodes sit in heap order 16 bytes apart from the record's start.
+// the forest kernels.  Records, rows and boxes are in rank space (layout and
+// definitions: record_format.h).
+//
+// A node step is one 4-byte LDS read, a byte permute that picks the tested
+// feature's 16-bit rank out of the row's two words, a 16-bit compare, a
+// select and a shift-add to the child's address.  Nodes holding the fp32
+// threshold and two permute selectors took a 16-byte read and six vector
+// instructions; per tree the record was 24 instead of 16 bytes per leaf.
 #pragma once
 
 #include "device_util.h"
@@ -11,42 +15,12 @@
 namespace tl {
 namespace {
 
-// The value of the feature a record node tests, picked with byte permutes:
-// node = (threshold, sel_lo, sel_hi, leaf value); sel_lo picks frequency or
-// KV and, with the same selector, batch or engine size; sel_hi picks between
-// the two (v_perm_b32: selector 0x03020100 keeps the second operand,
-// 0x07060504 takes the first).
-template <int NF>
-__device__ __forceinline__ float node_feature(const uint4& nd, float xf, float kv, float bs, float xe) {
-    const uint32_t x01 = __builtin_amdgcn_perm(__float_as_uint(kv), __float_as_uint(xf), nd.y);
-    const uint32_t x23 = NF == 4 ? __builtin_amdgcn_perm(__float_as_uint(xe), __float_as_uint(bs), nd.y)
-                                 : __float_as_uint(bs);
-    return __uint_as_float(__builtin_amdgcn_perm(x23, x01, nd.z));
-}
-
-// Whether (kv, batch) lies in a leaf box (kv_lo, kv_hi, batch_lo, batch_hi).
-__device__ __forceinline__ bool in_box(const float4& b, float kv, float bs) {
-    return (kv >= b.x) & (kv < b.y) & (bs >= b.z) & (bs < b.w);
-}
-
-// The intersection of two decoded leaf boxes.  Their bounds are
-// non-negative integers as floats, whose bit patterns order like the values,
-// so an integer max / min (one instruction each; fmaxf / fminf would first
-// canonicalize both operands) gives the float max / min exactly.
-__device__ __forceinline__ float bound_max(float a, float b) {
-    return __int_as_float(max(__float_as_int(a), __float_as_int(b)));
-}
-__device__ __forceinline__ float bound_min(float a, float b) {
-    return __int_as_float(min(__float_as_int(a), __float_as_int(b)));
-}
-__device__ __forceinline__ float4 box_meet(const float4& a, const float4& b) {
-    return make_float4(bound_max(a.x, b.x), bound_min(a.y, b.y), bound_max(a.z, b.z), bound_min(a.w, b.w));
-}
-
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
 typedef __attribute__((address_space(3))) const u32x2 lds_u32x2;
+typedef __attribute__((address_space(3))) const uint32_t lds_u32;
 typedef __attribute__((address_space(3))) const float lds_f32;
 
 // LDS byte address of a location in the kernel's dynamic LDS.
@@ -54,44 +28,73 @@ __device__ __forceinline__ uint32_t lds_addr(const unsigned char* p) {
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)p;
 }
 
-// The node slot at LDS byte address `a`, (threshold, sel_lo, sel_hi, leaf
-// value), read whole (a 12-byte read of the node alone measured slower).
-__device__ __forceinline__ uint4 read_node(uint32_t a) {
-    const u32x4 w = *(lds_u32x4*)(uintptr_t)a;
-    return make_uint4(w.x, w.y, w.z, w.w);
+// Pairs of 16-bit ranks, KV in the low half and batch in the high half.
+__device__ __forceinline__ uint32_t pair_min(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+__device__ __forceinline__ uint32_t pair_max(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+// How far b lies above a in each half, 0 where it does not.
+__device__ __forceinline__ uint32_t pair_above(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t,
+                              __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, b), __builtin_bit_cast(u16x2, a)));
 }
 
-// A leaf reached by a walk, as the LDS byte addresses of its value and of
-// its box.
-struct LeafAt {
-    uint32_t value, box;
+// A leaf box: the lowest and highest rank pair inside it.
+struct Box {
+    uint32_t lo, hi;
+};
+__device__ __forceinline__ Box empty_box() { return Box{kEmptyBoxLo, kEmptyBoxHi}; }
+
+// Whether a rank pair lies in a box: clamping it into the box leaves it as it
+// is.  (With hi applied first, an empty box clamps everything to (65535,
+// 65535), which no row is.)
+__device__ __forceinline__ bool in_box(const Box& b, uint32_t row) {
+    return pair_max(pair_min(row, b.hi), b.lo) == row;
+}
+
+// The intersection of two boxes that hold a common row.
+__device__ __forceinline__ Box box_meet(const Box& a, const Box& b) {
+    return Box{pair_max(a.lo, b.lo), pair_min(a.hi, b.hi)};
+}
+
+// The forest as the record kernels read it.
+struct RankDev {
+    const uint4* records;
+    const RankGroup* groups;
+    const float* dict;
+    const uint16_t* starts;
+    int32_t n_trees, depth, group_trees, n_groups;
+    float base;
 };
 
-// The leaf at which a walk of the staged tree whose record starts at LDS
-// byte address `tree` ended, from the walk's final address a = tree +
-// 16 (n_int + L) (heap slot n_int + L, leaf L): its value is word 3 of node
-// slot L, i.e. at a - 16 n_int + 12, and its box at tree + boxes + 8 L =
-// a / 2 + (tree / 2 + boxes - 8 n_int) (tree and a are multiples of 16).
-__device__ __forceinline__ LeafAt leaf_at(uint32_t a, uint32_t tree, const RecordLayout& R, int32_t depth) {
-    const uint32_t n_int16 = 16u * ((1u << depth) - 1u);
-    return LeafAt{a - (n_int16 - 12u), (a >> 1) + ((tree >> 1) + R.boxes - n_int16 / 2u)};
+__host__ inline RankDev rank_dev(const ForestDev& f) {
+    return RankDev{f.records, f.groups, f.dict, f.starts, f.n_trees, f.depth, f.group_trees, f.n_groups, f.base_score};
 }
 
-// The value of a leaf.
-__device__ __forceinline__ float leaf_value(const LeafAt& l) {
-    return *(lds_f32*)(uintptr_t)l.value;
+// A row's two words in group g: the rank pair of (KV, batch), and of
+// (frequency, engine size).
+__device__ __forceinline__ uint32_t rank_pair(const RankDev& D, int32_t g, int lo, int hi, float x, float y) {
+    const RankFeature a = D.groups[g].f[lo], b = D.groups[g].f[hi];
+    return rank_of(a, D.dict, D.starts, x) | rank_of(b, D.dict, D.starts, y) << 16;
+}
+__device__ __forceinline__ uint32_t rank_row(const RankDev& D, int32_t g, float kv, float bs) {
+    return rank_pair(D, g, 1, 2, kv, bs);
+}
+__device__ __forceinline__ uint32_t rank_lane(const RankDev& D, int32_t g, float xf, float xe) {
+    return rank_pair(D, g, 0, 3, xf, xe);
 }
 
-// The KV / batch box of a leaf, decoded from its packed integer bounds into
-// (kv_lo, kv_hi, batch_lo, batch_hi) as floats (exact: all bounds are below
-// 2^24).
-__device__ __forceinline__ float4 leaf_box(const LeafAt& l) {
-    const u32x2 w = *(lds_u32x2*)(uintptr_t)l.box;
-    return make_float4((float)(w.x & kBoxKvMax), (float)(w.y & kBoxKvMax), (float)(w.x >> 20),
-                       (float)(w.y >> 20));
+// A leaf reached by a walk, as the LDS byte address of its value: the walk's
+// final address tree + 4 (2^d + L).  Its box is at tree + 8 (2^d + L).
+__device__ __forceinline__ float leaf_value(uint32_t a) { return *(lds_f32*)(uintptr_t)a; }
+__device__ __forceinline__ Box leaf_box(uint32_t a, uint32_t tree) {
+    const u32x2 w = *(lds_u32x2*)(uintptr_t)(2u * a - tree);
+    return Box{w.x, w.y};
 }
 
-// Staging of tree blocks: block b is trees [b*tb, b*tb + cnt), one
+// Staging of tree blocks: a block is consecutive trees of one group, one
 // contiguous range of 16-byte words in global memory and in LDS.  It is
 // copied in pieces of 64 lanes x 16 bytes straight from global memory into
 // LDS (global_load_lds_dwordx4, no registers), wavefront w of n taking
@@ -100,8 +103,27 @@ __device__ __forceinline__ float4 leaf_box(const LeafAt& l) {
 // are whole pieces), so no lane writes outside its buffer.
 constexpr uint32_t kStagePiece = kWave * 16;
 
-__host__ __device__ inline uint32_t stage_buffer_bytes(int32_t tb, const RecordLayout& R) {
-    return ((uint32_t)tb * R.bytes + kStagePiece - 1) / kStagePiece * kStagePiece;
+__host__ __device__ inline uint32_t stage_buffer_bytes(int32_t tb, uint32_t rec_bytes) {
+    return ((uint32_t)tb * rec_bytes + kStagePiece - 1) / kStagePiece * kStagePiece;
+}
+
+// The blocks of a forest, tb trees each: group_blocks per group, a group's
+// last block and the last group possibly short.
+struct TreeBlocks {
+    int32_t tb, group_blocks, n_blocks;
+};
+__host__ __device__ inline TreeBlocks tree_blocks(int32_t n_trees, int32_t group_trees, int32_t tb) {
+    const int32_t gb = group_trees > 0 ? (group_trees + tb - 1) / tb : 1;
+    const int32_t n_groups = group_trees > 0 ? (n_trees + group_trees - 1) / group_trees : 0;
+    const int32_t last = n_groups > 0 ? n_trees - (n_groups - 1) * group_trees : 0;
+    return TreeBlocks{tb, gb, n_groups > 0 ? (n_groups - 1) * gb + (last + tb - 1) / tb : 0};
+}
+// First tree and number of trees of block b.
+__device__ __forceinline__ int32_t block_first(const RankDev& D, const TreeBlocks& B, int32_t b) {
+    return b / B.group_blocks * D.group_trees + b % B.group_blocks * B.tb;
+}
+__device__ __forceinline__ int32_t block_count(const RankDev& D, const TreeBlocks& B, int32_t b, int32_t first) {
+    return min(B.tb, min((b / B.group_blocks + 1) * D.group_trees, D.n_trees) - first);
 }
 
 // One piece: lane l copies the 16 bytes at its `src` to LDS byte address
@@ -116,12 +138,14 @@ __device__ __forceinline__ void stage_piece(const uint4* src, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(base), "v"(src) : "memory", "m0");
 }
 
-// Enqueues this wavefront's pieces of block b (rec_words 16-byte words per
-// tree) into the LDS buffer at byte address dst.
-__device__ __forceinline__ void stage_block(const uint4* records, int32_t n_trees, int32_t tb, uint32_t rec_words,
-                                            int32_t b, uint32_t dst, int wave, int n_waves) {
-    const uint32_t words = (uint32_t)min(tb, n_trees - b * tb) * rec_words;
-    const uint4* src = records + (int64_t)b * tb * rec_words;
+// Enqueues this wavefront's pieces of block b into the LDS buffer at byte
+// address dst.
+__device__ __forceinline__ void stage_block(const RankDev& D, const TreeBlocks& B, int32_t b, uint32_t dst, int wave,
+                                            int n_waves) {
+    const uint32_t rec_words = rank_record_bytes(D.depth) / 16u;
+    const int32_t first = block_first(D, B, b);
+    const uint32_t words = (uint32_t)block_count(D, B, b, first) * rec_words;
+    const uint4* src = D.records + (int64_t)first * rec_words;
     const uint32_t n_pieces = (words + kWave - 1) / kWave;
     for (uint32_t pc = (uint32_t)wave; pc < n_pieces; pc += (uint32_t)n_waves) {
         const uint32_t i = pc * kWave + lane_id();
@@ -147,7 +171,7 @@ __device__ __forceinline__ void stage_block(const uint4* records, int32_t n_tree
 // otherwise keep winning issue and the youngest set the pace.  Every wait is
 // bounded (kSyncSpins sleeps); one that runs out makes stage_acquire return
 // false, and the caller marks its results invalid, so every wavefront ends.
-constexpr int kMaxStageBuffers = 3;
+constexpr int kMaxStageBuffers = 4;
 struct StageSync {
     int32_t claimed[kMaxStageBuffers];
     int32_t ready[kMaxStageBuffers];
@@ -171,12 +195,11 @@ __device__ __forceinline__ int32_t sync_load(const int32_t* p) {
     return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Makes block b >= 1 (trees [b*tb, ...), rec_words 16-byte words per tree)
-// available in its buffer at LDS byte address buf; n_waves wavefronts share
-// the buffers.
+// Makes block b >= 1 available in its buffer at LDS byte address buf;
+// n_waves wavefronts share the buffers.
 template <int NB = 2>
-__device__ __forceinline__ bool stage_acquire(StageSync* sync, int32_t b, int n_waves, const uint4* records,
-                                              int32_t n_trees, int32_t tb, uint32_t rec_words, uint32_t buf) {
+__device__ __forceinline__ bool stage_acquire(StageSync* sync, int32_t b, int n_waves, const RankDev& D,
+                                              const TreeBlocks& B, uint32_t buf) {
     const int cur = b % NB;
     const int32_t need_done = n_waves * (b / NB);
     int32_t spins = 0;
@@ -196,7 +219,7 @@ __device__ __forceinline__ bool stage_acquire(StageSync* sync, int32_t b, int n_
                 __builtin_amdgcn_s_sleep(1);
                 ++spins;
             }
-            stage_block(records, n_trees, tb, rec_words, b, buf, 0, 1);
+            stage_block(D, B, b, buf, 0, 1);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             if (lane_id() == 0) __hip_atomic_store(&sync->ready[cur], b, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
             break;
@@ -223,36 +246,52 @@ __device__ __forceinline__ void stage_release(StageSync* sync, int32_t b, int n_
     else __builtin_amdgcn_s_setprio(0);
 }
 
-// Walks NT consecutive staged trees (records R.bytes apart, the first at
-// LDS byte address `tree`) from the root for one row; lf[t] = the leaf
-// reached in tree t.  The walks of two trees interleave, so their chains of
-// dependent LDS reads overlap.
-template <int NF, int NT>
-__device__ __forceinline__ void walk(uint32_t tree, const RecordLayout& R, int32_t depth, float xf, float kv, float bs,
-                                     float xe, LeafAt (&lf)[NT]) {
-    const uint32_t rec_bytes = R.bytes;
-    // the loop carries node byte addresses: child 2k+1 of the node at
-    // a = root + 16 k sits at 2 a + (16 - root), child 2k+2 16 bytes later
-    uint32_t a[NT], cl[NT], cr[NT];
+// The leaves (lf[r][t], see leaf_value) that NR rows reach in NT consecutive
+// staged trees (rec_bytes apart, the first at LDS byte address `tree`), all
+// NR x NT chains of dependent LDS reads interleaved: every chain's node reads
+// issue back to back, then the compares.
+template <int NT, int NR>
+__device__ __forceinline__ void walk_rows(uint32_t tree, uint32_t rec_bytes, int32_t depth, const uint32_t (&row)[NR],
+                                          const uint32_t (&fe)[NR], uint32_t (&lf)[NR][NT]) {
+    // a = tree + 4 k for node k; its children sit at 2 a - tree and 4 bytes on
+    uint32_t cl[NT], cr[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-        a[t] = tree + t * rec_bytes;
-        cl[t] = 16u - a[t];
-        cr[t] = 32u - a[t];
+        const uint32_t root = tree + t * rec_bytes;
+        cl[t] = 0u - root;
+        cr[t] = 4u - root;
         // opaque to the optimizer, which would otherwise rewrite the select
         // of the two offsets as an add after the compare
         asm volatile("" : "+v"(cl[t]), "+v"(cr[t]));
+#pragma unroll
+        for (int r = 0; r < NR; ++r) lf[r][t] = root + 4u;
     }
     for (int32_t level = 0; level < depth; ++level) {
+        uint32_t w[NR][NT];
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const uint4 nd = read_node(a[t]);
-            const bool left = node_feature<NF>(nd, xf, kv, bs, xe) < __uint_as_float(nd.x);
-            a[t] = 2u * a[t] + (left ? cl[t] : cr[t]);
-        }
+        for (int r = 0; r < NR; ++r)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) w[r][t] = *(lds_u32*)(uintptr_t)lf[r][t];
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const uint32_t x = __builtin_amdgcn_perm(row[r], fe[r], w[r][t]);
+                const bool left = (uint16_t)x < (uint16_t)(w[r][t] >> 16);
+                lf[r][t] = 2u * lf[r][t] + (left ? cl[t] : cr[t]);
+            }
     }
+}
+
+// The same for one row.
+template <int NT>
+__device__ __forceinline__ void walk(uint32_t tree, uint32_t rec_bytes, int32_t depth, uint32_t row, uint32_t fe,
+                                     uint32_t (&lf)[NT]) {
+    const uint32_t rows[1] = {row}, fes[1] = {fe};
+    uint32_t l[1][NT];
+    walk_rows<NT, 1>(tree, rec_bytes, depth, rows, fes, l);
 #pragma unroll
-    for (int t = 0; t < NT; ++t) lf[t] = leaf_at(a[t], tree + t * rec_bytes, R, depth);
+    for (int t = 0; t < NT; ++t) lf[t] = l[0][t];
 }
 
 }  // namespace

@@ -38,6 +38,20 @@ uint32_t box_bound(float x, uint32_t maxv);
 void build_records(int32_t n_trees, int32_t depth, const uint8_t* feature, const float* threshold, const float* leaf,
                    const std::vector<Box>& boxes, std::vector<unsigned char>& out);
 
+// The rank records of all trees (rank_record_bytes(depth) each, back to back,
+// plus 64 bytes of padding), and the groups, dictionaries and bucket tables
+// that rank rows for them (record_format.h).  depth <= kMaxRecordDepth,
+// n_features 3 or 4.
+struct RankForest {
+    int32_t group_trees = 0;                // every group but the last has this many trees
+    std::vector<RankGroup> groups;
+    std::vector<float> dict;
+    std::vector<uint16_t> starts;
+    std::vector<unsigned char> records;
+};
+void build_rank_records(int32_t n_trees, int32_t depth, const uint8_t* feature, const float* threshold,
+                        const float* leaf, RankForest& out);
+
 // Up to kMaxCuts quantiles of the finite thresholds of feature fi over
 // n_nodes nodes, ascending.
 std::vector<float> threshold_cuts(int64_t n_nodes, const uint8_t* feature, const float* threshold, int fi);

@@ -138,12 +138,17 @@ struct ForestDev {
     // batch_hi): a row with lo <= x < hi in both features, and with the
     // frequency and engine size of a row known to reach the leaf, reaches the
     // same leaf.  Empty (lo = +inf) for leaves no row can reach.  Present when
-    // n_features >= 3, else NULL.
+    // n_features >= 3 and the trees are too deep for records, else NULL.
     const float4* kvb_box;  // [T][2^d]
-    // Tree records of the LDS-staged grid kernel, one per tree, back to back
-    // (layout: record_layout).  Present when n_features >= 3 and the depth
-    // is at most kMaxRecordDepth, else NULL.
+    // Rank records of the LDS-staged kernels, one per tree, back to back, and
+    // the groups, dictionaries and bucket tables that rank rows for them
+    // (record_format.h).  Present when n_features >= 3 and the depth is at
+    // most kMaxRecordDepth, else NULL.
     const uint4* records;
+    const RankGroup* groups;
+    const float* dict;
+    const uint16_t* starts;
+    int32_t group_trees, n_groups;
     // Quantiles of the forest's KV (feature 1) and batch (feature 2)
     // thresholds, ascending, at most kMaxCuts each (NULL / 0 when
     // n_features < 3).  Between two rows, the number of cuts crossed by KV
