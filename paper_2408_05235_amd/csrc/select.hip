@@ -117,29 +117,67 @@ __global__ __launch_bounds__(256) void select_kernel(SelectParams P) {
     }
 }
 
-// Eq. 3-4 at one frequency for one scenario, by one wavefront: with
-// per-iteration times of `ips` over the n projected iterations, returns
-// T_R[n] and whether some deadline of `dl` (T_R[j+1] < dl[j]) is missed;
-// *miss_own tells whether T_R[own_at + 1] < d_own fails (own_at < 0: none).
-// Every lane returns the same values.
-__device__ __forceinline__ uint64_t wave_times(const float* ips, const uint64_t* dl, int32_t n, int32_t own_at,
-                                               uint64_t d_own, bool* miss, bool* miss_own) {
-    const int lane = lane_id();
-    uint64_t carry = 0;
-    bool m = false, mo = false;
-    for (int32_t j0 = 0; j0 < n; j0 += kWave) {
-        const int32_t j = j0 + lane;
-        const bool in = j < n;
-        const uint64_t lat = in ? latency_ns(ips[j]) : 0ull;
-        const uint64_t tr = wave_incl_scan_u64(lat) + carry;
-        const uint64_t d = in ? dl[j] : kNoDeadline;
-        m |= in && d != kNoDeadline && !(tr < d);
-        mo |= in && j == own_at && !(tr < d_own);
-        carry = lane63_u64(tr);
+// Eq. 3-4 at one frequency for one scenario, by a workgroup of kTimeWaves
+// wavefronts: with per-iteration times of `ips` over the n projected
+// iterations, returns T_R[n] and whether some deadline of `dl` (T_R[j+1] <
+// dl[j]) is missed; *miss_own tells whether T_R[own_at + 1] < d_own fails
+// (own_at < 0: none).  Each wavefront takes a run of consecutive iterations,
+// four a lane and 256 at a time: its run's total first, then, from the totals
+// of the wavefronts before it, the times of its iterations.  Every thread
+// returns the same values; all of them call it.  (One wavefront stepping
+// through the iterations 64 at a time was a chain of loads and scans: 13 us for
+// 2048 iterations, however few the scenarios.)
+constexpr int kTimeWaves = 4;
+constexpr int kTimeThreads = kTimeWaves * kWave;
+
+__device__ __forceinline__ uint64_t block_times(const float* ips, const uint64_t* dl, int32_t n, int32_t own_at,
+                                                uint64_t d_own, bool* miss, bool* miss_own) {
+    __shared__ uint64_t totals[kTimeWaves];
+    __shared__ uint32_t missed[2];
+    const int wave = threadIdx.x / kWave;
+    const int32_t run = (n + kTimeWaves * kStep - 1) / (kTimeWaves * kStep) * kStep;
+    const int32_t r0 = min(wave * run, n), r1 = min(r0 + run, n);
+    if (threadIdx.x == 0) missed[0] = missed[1] = 0;
+    uint64_t sum = 0;
+    for (int32_t j0 = r0; j0 < r1; j0 += kStep) {
+        const int32_t jb = j0 + kPerLane * lane_id();
+#pragma unroll
+        for (int k = 0; k < kPerLane; ++k) sum += jb + k < r1 ? latency_ns(ips[jb + k]) : 0ull;
     }
-    *miss = __ballot(m) != 0;
-    *miss_own = __ballot(mo) != 0;
-    return carry;
+    sum = wave_sum_u64(sum);
+    if (lane_id() == 0) totals[wave] = sum;
+    __syncthreads();
+    uint64_t carry = 0, all = 0;   // T_R[r0] and T_R[n]
+#pragma unroll
+    for (int w = 0; w < kTimeWaves; ++w) {
+        if (w < wave) carry += totals[w];
+        all += totals[w];
+    }
+    bool m = false, mo = false;
+    for (int32_t j0 = r0; j0 < r1; j0 += kStep) {
+        const int32_t jb = j0 + kPerLane * lane_id();
+        uint64_t t[kPerLane], step = 0;
+#pragma unroll
+        for (int k = 0; k < kPerLane; ++k) {
+            step += jb + k < r1 ? latency_ns(ips[jb + k]) : 0ull;
+            t[k] = step;
+        }
+        const uint64_t before = wave_incl_scan_u64(step) - step + carry;   // T_R[jb]
+#pragma unroll
+        for (int k = 0; k < kPerLane; ++k)
+            if (jb + k < r1) {
+                const uint64_t d = dl[jb + k];
+                m |= d != kNoDeadline && !(before + t[k] < d);
+                mo |= jb + k == own_at && !(before + t[k] < d_own);
+            }
+        carry = lane63_u64(before + step);
+    }
+    if (m) missed[0] = 1;
+    if (mo) missed[1] = 1;
+    __syncthreads();
+    *miss = missed[0] != 0;
+    *miss_own = missed[1] != 0;
+    return all;
 }
 
 __device__ __forceinline__ bool within_tbt(uint64_t t_r_n, uint64_t slo, int32_t n) {
@@ -148,15 +186,12 @@ __device__ __forceinline__ bool within_tbt(uint64_t t_r_n, uint64_t slo, int32_t
 }
 
 // Admission decision (Sec. 4.3.2 checks 1-3) of one new query per scenario
-// from the projection with it and M at the maximum frequency: one wavefront
+// from the projection with it and M at the maximum frequency: one workgroup
 // per scenario; the deadline of the query itself (ending at cand_len, when
 // inside the horizon) is checked apart from the scheduled requests'
 // deadlines in deadline_at.
-constexpr int kAdmitWaves = 4;
-
-__global__ __launch_bounds__(kAdmitWaves * kWave) void admit_kernel(AdmitParams P) {
-    const int64_t s = (int64_t)blockIdx.x * kAdmitWaves + threadIdx.x / kWave;
-    if (s >= P.S) return;
+__global__ __launch_bounds__(kTimeThreads) void admit_kernel(AdmitParams P) {
+    const int64_t s = blockIdx.x;
     const int32_t H = P.H;
     const uint32_t fl = P.proj_flags[s];
     uint32_t dec;
@@ -174,13 +209,13 @@ __global__ __launch_bounds__(kAdmitWaves * kWave) void admit_kernel(AdmitParams 
         const uint64_t d_own = P.cand_deadline ? P.cand_deadline[s] : kNoDeadline;
         const int32_t own_at = (d_own != kNoDeadline && L <= H) ? L - 1 : -1;   // T_R[L] = T_R[own_at + 1]
         bool miss, miss_own;
-        const uint64_t t_r = wave_times(P.ips + s * H, P.deadline_at + s * H, n, own_at, d_own, &miss, &miss_own);
+        const uint64_t t_r = block_times(P.ips + s * H, P.deadline_at + s * H, n, own_at, d_own, &miss, &miss_own);
         if (!within_tbt(t_r, P.tbt_slo_ns[s], n)) dec = TL_ADMIT_QUEUE_TBT;
         else if (miss) dec = TL_ADMIT_QUEUE_E2E;
         else if (miss_own) dec = TL_ADMIT_LOST;
         else dec = TL_ADMIT_OK;
     }
-    if (lane_id() == 0) P.decision[s] = dec;
+    if (threadIdx.x == 0) P.decision[s] = dec;
 }
 
 // Binary search over the candidate frequencies (Sec. 4.5), one step per
@@ -190,37 +225,35 @@ __global__ __launch_bounds__(kAdmitWaves * kWave) void admit_kernel(AdmitParams 
 // next probe is the midpoint while lo < hi.  The last step (final = true)
 // checks lo itself and writes the result.  Scenarios flagged overflow / lost
 // are settled by the first step (mode init) without probes.
-constexpr int kSearchWaves = 4;
-
-__global__ __launch_bounds__(kSearchWaves * kWave) void search_kernel(SearchParams P, int mode) {
-    const int64_t s = (int64_t)blockIdx.x * kSearchWaves + threadIdx.x / kWave;
+// One workgroup per scenario; the init, without times to add up, one thread.
+__global__ __launch_bounds__(kTimeThreads) void search_init_kernel(SearchParams P) {
+    const int64_t s = (int64_t)blockIdx.x * kTimeThreads + threadIdx.x;
     if (s >= P.S) return;
-    const int lane = lane_id();
+    const int32_t F = P.F;
+    const uint32_t fl = P.proj_flags ? P.proj_flags[s] : 0u;
+    const bool settled = (fl & (TL_FLAG_OVERFLOW | TL_FLAG_LOST)) != 0;
+    P.work[s] = settled ? -1 : 0;
+    P.work[P.S + s] = settled ? -1 : F - 1;
+    P.work[2 * P.S + s] = (settled || F == 1) ? -1 : (F - 1) / 2;
+    if (settled) {
+        P.freq_idx[s] = F - 1;
+        P.status[s] = (fl & TL_FLAG_OVERFLOW) ? TL_STATUS_INVALID : TL_STATUS_LOST;
+    }
+}
+
+__global__ __launch_bounds__(kTimeThreads) void search_kernel(SearchParams P, int mode) {
+    const int64_t s = blockIdx.x;
     int32_t* lo = P.work;
     int32_t* hi = P.work + P.S;
     int32_t* probe = P.work + 2 * P.S;
     const int32_t F = P.F, H = P.H;
-    if (mode == 0) {   // init
-        const uint32_t fl = P.proj_flags ? P.proj_flags[s] : 0u;
-        const bool settled = (fl & (TL_FLAG_OVERFLOW | TL_FLAG_LOST)) != 0;
-        if (lane == 0) {
-            lo[s] = settled ? -1 : 0;
-            hi[s] = settled ? -1 : F - 1;
-            probe[s] = (settled || F == 1) ? -1 : (F - 1) / 2;
-            if (settled) {
-                P.freq_idx[s] = F - 1;
-                P.status[s] = (fl & TL_FLAG_OVERFLOW) ? TL_STATUS_INVALID : TL_STATUS_LOST;
-            }
-        }
-        return;
-    }
     const int32_t p = probe[s];
     if (p < 0) return;
     const int32_t n = min(max(P.n_iters[s], 0), H);
     bool miss, miss_own;
-    const uint64_t t_r = wave_times(P.ips + s * H, P.deadline_at + s * H, n, -1, kNoDeadline, &miss, &miss_own);
+    const uint64_t t_r = block_times(P.ips + s * H, P.deadline_at + s * H, n, -1, kNoDeadline, &miss, &miss_own);
     const bool ok = !miss && within_tbt(t_r, P.tbt_slo_ns[s], n);
-    if (lane != 0) return;
+    if (threadIdx.x != 0) return;
     if (mode == 2) {   // final check of lo
         P.freq_idx[s] = ok ? p : F - 1;
         P.status[s] = ok ? TL_STATUS_OK : TL_STATUS_INFEASIBLE;
@@ -256,8 +289,7 @@ __global__ __launch_bounds__(256) void search_final_probe_kernel(SearchParams P)
 
 hipError_t launch_admit(const AdmitParams& p, hipStream_t stream) {
     if (p.S == 0) return hipSuccess;
-    hipLaunchKernelGGL(admit_kernel, dim3((unsigned)((p.S + kAdmitWaves - 1) / kAdmitWaves)),
-                       dim3(kAdmitWaves * kWave), 0, stream, p);
+    hipLaunchKernelGGL(admit_kernel, dim3((unsigned)p.S), dim3(kTimeThreads), 0, stream, p);
     return hipGetLastError();
 }
 
@@ -265,9 +297,11 @@ hipError_t launch_search_step(const SearchParams& p, int mode, hipStream_t strea
     if (p.S == 0) return hipSuccess;
     if (mode == 3) {
         hipLaunchKernelGGL(search_final_probe_kernel, dim3((unsigned)((p.S + 255) / 256)), dim3(256), 0, stream, p);
+    } else if (mode == 0) {
+        hipLaunchKernelGGL(search_init_kernel, dim3((unsigned)((p.S + kTimeThreads - 1) / kTimeThreads)),
+                           dim3(kTimeThreads), 0, stream, p);
     } else {
-        hipLaunchKernelGGL(search_kernel, dim3((unsigned)((p.S + kSearchWaves - 1) / kSearchWaves)),
-                           dim3(kSearchWaves * kWave), 0, stream, p, mode);
+        hipLaunchKernelGGL(search_kernel, dim3((unsigned)p.S), dim3(kTimeThreads), 0, stream, p, mode);
     }
     return hipGetLastError();
 }
