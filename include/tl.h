@@ -228,6 +228,11 @@ tl_status tl_project(const tl_project_args* args, void* stream);
 /* ------------------------------------------------------------------------
  * Stage 2 -- the model M on arbitrary feature rows (Sec. 4.3.1).
  * rows [n_rows][n_features of the forest] fp32 row-major; out [n_rows] fp32.
+ * Calls with few rows (here, on the grid and at one frequency per scenario)
+ * are cut along the trees as well and take up to 64 MiB of the forest
+ * handle's device scratch (tl_forest_predict_grid says how it is kept);
+ * without it, or under stream capture, they give the same results in more
+ * time.
  * ---------------------------------------------------------------------- */
 tl_status tl_forest_predict(const tl_forest* forest, const float* rows, int64_t n_rows,
                             float* out, void* stream);
@@ -243,16 +248,16 @@ tl_status tl_forest_predict(const tl_forest* forest, const float* rows, int64_t 
  * ignored otherwise; out [S][F][H] fp32.  The forest must have 3 or 4
  * features in the order (frequency, KV, batch[, engine size]).
  * 1 <= F <= TL_MAX_FREQS, 1 <= H <= TL_MAX_HORIZON.
- * Work is ordered by an estimate of its cost (results do not depend on the
- * order).  The ordering needs 16 bytes per (scenario, 64-iteration chunk)
- * plus a radix sort's temporary storage of device scratch, which the forest
- * handle owns: it is allocated
- * on the first call, kept, and replaced only when a larger grid comes, so
- * repeated calls of one size allocate nothing.  If that allocation fails, or
- * the stream is being captured into a graph, the call runs without the
- * ordering (same results; tl_forest_predict_grid_noalloc keeps it under
- * capture).  Calls with one forest
- * share its scratch: a call on another stream than the previous one first
+ * Work on grids of more than two workgroups per CU is ordered by an estimate
+ * of its cost (results do not depend on the order).  The ordering needs 16
+ * bytes per (scenario, 64-iteration chunk) plus a radix sort's temporary
+ * storage of device scratch, which the forest handle owns: up to four arrays,
+ * allocated when a call first needs one, kept, and replaced only when a larger
+ * call comes, so repeated calls of one size allocate nothing.  If that
+ * allocation fails, or the stream is being captured into a graph, the call
+ * runs without the ordering (same results; tl_forest_predict_grid_noalloc
+ * keeps it under capture).  A call takes the array its stream used last, or an
+ * idle one; when four other streams' calls still use all of them it first
  * waits (on the device) for the previous call's work.  The forest's device
  * must be the current device.
  * ---------------------------------------------------------------------- */

@@ -20,16 +20,23 @@ struct tl_forest {
     int device;
     tl::ForestDev dev;
     void* mem;        // every array of `dev`
-    // Work-order scratch of the grid and column kernels, on the forest's
-    // device: kept from call to call and only replaced by a larger one when a
-    // larger grid comes.  ws_done is recorded on the stream of the last call that used
-    // it; a call on another stream waits for it first.
+    // Scratch of the grid and column kernels' work orders and of calls with
+    // few rows, on the forest's device: kept from call to call, each array
+    // only replaced by a larger one when a larger call comes.  `done` is
+    // recorded on the stream of the last call that used it.  A call takes the
+    // array its stream used last, else an idle one, else it waits for another
+    // stream's; kWorkspaces streams can use the forest without waiting.
+    struct Workspace {
+        void* ptr = nullptr;
+        size_t bytes = 0;
+        hipEvent_t done = nullptr;
+        hipStream_t stream = nullptr;
+        bool used = false;
+    };
+    static constexpr int kWorkspaces = 4;
     mutable std::mutex ws_mutex;
-    mutable void* ws = nullptr;
-    mutable size_t ws_bytes = 0;
-    mutable hipEvent_t ws_done = nullptr;
-    mutable hipStream_t ws_stream = nullptr;
-    mutable bool ws_used = false;
+    mutable Workspace ws[kWorkspaces];
+    mutable int ws_next = 0;
 };
 
 struct tl_lattice {
@@ -92,26 +99,22 @@ tl_status forest_create(int32_t n_trees, int32_t depth, int32_t n_features, floa
                 boxes[i] = make_float4(leaf_box[i].kv_lo, leaf_box[i].kv_hi, leaf_box[i].batch_lo, leaf_box[i].batch_hi);
         }
     }
-    std::vector<float> cuts_kv, cuts_bs;
-    if (n_features >= 3 && n_int > 0) {
-        cuts_kv = tl::host::threshold_cuts(n_trees * n_int, feature, threshold, 1);
-        cuts_bs = tl::host::threshold_cuts(n_trees * n_int, feature, threshold, 2);
-    }
+    bool finite[4] = {false, false, false, false};
+    for (const tl::RankGroup& g : ranks.groups)
+        for (int q = 0; q < 4; ++q)
+            for (int32_t i = 0; i < g.f[q].n && !finite[q]; ++i) finite[q] = std::isfinite(ranks.dict[g.f[q].dict + i]);
 
-    const bool cuts = !cuts_kv.empty() && !cuts_bs.empty();
     // one device allocation and one copy: each array on a 256-byte boundary,
     // nodes and leaves with a per-tree stride of 2^d entries and 64 bytes of
     // tail padding
-    enum { kNodes, kLeaves, kBoxes, kRecords, kDict, kStarts, kGroups, kCutsKv, kCutsBs, kParts };
+    enum { kNodes, kLeaves, kBoxes, kRecords, kDict, kStarts, kGroups, kParts };
     const size_t part_bytes[kParts] = {cells * sizeof(uint2) + 64,
                                        cells * sizeof(float) + 64,
                                        boxes.size() * sizeof(float4),
                                        ranks.records.size(),
                                        ranks.dict.size() * sizeof(float),
                                        ranks.starts.size() * sizeof(uint16_t),
-                                       ranks.groups.size() * sizeof(tl::RankGroup),
-                                       cuts ? cuts_kv.size() * sizeof(float) : 0,
-                                       cuts ? cuts_bs.size() * sizeof(float) : 0};
+                                       ranks.groups.size() * sizeof(tl::RankGroup)};
     size_t at[kParts + 1] = {0};
     for (int q = 0; q < kParts; ++q) at[q + 1] = (at[q] + part_bytes[q] + 255) & ~(size_t)255;
     std::vector<unsigned char> image(at[kParts], 0);
@@ -127,8 +130,7 @@ tl_status forest_create(int32_t n_trees, int32_t depth, int32_t n_features, floa
         const void* const part[kParts] = {nullptr,           leaf,
                                           boxes.data(),      ranks.records.data(),
                                           ranks.dict.data(), ranks.starts.data(),
-                                          ranks.groups.data(), cuts_kv.data(),
-                                          cuts_bs.data()};
+                                          ranks.groups.data()};
         for (int q = 1; q < kParts; ++q) {
             const size_t n = q == kLeaves ? cells * sizeof(float) : part_bytes[q];
             if (n > 0) std::memcpy(image.data() + at[q], part[q], n);
@@ -139,18 +141,14 @@ tl_status forest_create(int32_t n_trees, int32_t depth, int32_t n_features, floa
     if (!f) return fail(TL_ENOMEM, "tl_forest_create: host allocation failed");
     hipError_t e = hipGetDevice(&f->device);
     if (e != hipSuccess) { delete f; return from_hip(e, "tl_forest_create: hipGetDevice"); }
-    e = hipEventCreateWithFlags(&f->ws_done, hipEventDisableTiming);
-    if (e != hipSuccess) { delete f; return from_hip(e, "tl_forest_create: hipEventCreate"); }
     e = hipMalloc(&f->mem, image.size());
     if (e != hipSuccess) {
-        (void)hipEventDestroy(f->ws_done);
         delete f;
         return from_hip(e, "tl_forest_create: hipMalloc");
     }
     e = hipMemcpy(f->mem, image.data(), image.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         (void)hipFree(f->mem);
-        (void)hipEventDestroy(f->ws_done);
         delete f;
         return from_hip(e, "tl_forest_create: hipMemcpy");
     }
@@ -169,10 +167,7 @@ tl_status forest_create(int32_t n_trees, int32_t depth, int32_t n_features, floa
     f->dev.groups = (const tl::RankGroup*)array(kGroups);
     f->dev.group_trees = ranks.group_trees;
     f->dev.n_groups = (int32_t)ranks.groups.size();
-    f->dev.cuts_kv = (const float*)array(kCutsKv);
-    f->dev.cuts_bs = (const float*)array(kCutsBs);
-    f->dev.n_cuts_kv = cuts ? (int32_t)cuts_kv.size() : 0;
-    f->dev.n_cuts_bs = cuts ? (int32_t)cuts_bs.size() : 0;
+    f->dev.orderable = finite[1] && finite[2];
     *out = f;
     return ok();
 }
@@ -204,8 +199,10 @@ void tl_forest_destroy(tl_forest* f) {
     (void)hipSetDevice(f->device);
     (void)hipDeviceSynchronize();
     (void)hipFree(f->mem);
-    if (f->ws) (void)hipFree(f->ws);
-    (void)hipEventDestroy(f->ws_done);
+    for (tl_forest::Workspace& w : f->ws) {
+        if (w.ptr) (void)hipFree(w.ptr);
+        if (w.done) (void)hipEventDestroy(w.done);
+    }
     (void)hipSetDevice(cur);
     delete f;
 }
@@ -227,54 +224,113 @@ bool capturing(hipStream_t st) {
     return cs != hipStreamCaptureStatusNone;
 }
 
-// Runs launch(ws, ws_bytes) with the forest's cached work-order workspace
-// of at least `need` bytes, all of its launches on st.  In the steady state
+// Runs launch(ws, ws_bytes) with one of the forest's cached workspaces of at
+// least `need` bytes, all of its launches on st.  In the steady state
 // nothing is allocated; a larger need than any before replaces the
 // workspace (after the last call that used it is done).  Without a
 // workspace (need 0, allocation failed, or the stream is being captured)
-// launch gets (nullptr, 0) and runs without the order, which changes only
-// its speed.
+// launch gets (nullptr, 0) and runs without, which changes only its speed.
 template <class Launch>
 hipError_t with_workspace(const tl_forest* f, size_t need, hipStream_t st, Launch&& launch) {
     if (need == 0 || capturing(st)) return launch(nullptr, (size_t)0);
     std::lock_guard<std::mutex> lock(f->ws_mutex);
     hipError_t e;
-    if (need > f->ws_bytes) {
-        if (f->ws) {
-            if (f->ws_used) {
-                e = hipEventSynchronize(f->ws_done);
+    tl_forest::Workspace* w = nullptr;
+    for (tl_forest::Workspace& c : f->ws)
+        if (c.used && c.stream == st) { w = &c; break; }
+    for (int i = 0; i < tl_forest::kWorkspaces && !w; ++i) {
+        tl_forest::Workspace& c = f->ws[i];
+        if (!c.used) {
+            w = &c;
+        } else {
+            e = hipEventQuery(c.done);
+            if (e == hipSuccess) w = &c;
+            else if (e != hipErrorNotReady) return e;
+            else (void)hipGetLastError();   // not ready: no error of the launches below
+        }
+    }
+    if (!w) {
+        w = &f->ws[f->ws_next];
+        f->ws_next = (f->ws_next + 1) % tl_forest::kWorkspaces;
+    }
+    if (!w->done) {
+        e = hipEventCreateWithFlags(&w->done, hipEventDisableTiming);
+        if (e != hipSuccess) {
+            w->done = nullptr;
+            (void)hipGetLastError();
+            return launch(nullptr, (size_t)0);
+        }
+    }
+    if (need > w->bytes) {
+        if (w->ptr) {
+            if (w->used) {
+                e = hipEventSynchronize(w->done);
                 if (e != hipSuccess) return e;
             }
-            (void)hipFree(f->ws);
-            f->ws = nullptr;
-            f->ws_bytes = 0;
-            f->ws_used = false;
+            (void)hipFree(w->ptr);
+            w->ptr = nullptr;
+            w->bytes = 0;
+            w->used = false;
         }
-        if (hipMalloc(&f->ws, need) == hipSuccess) {
-            f->ws_bytes = need;
+        if (hipMalloc(&w->ptr, need) == hipSuccess) {
+            w->bytes = need;
         } else {
-            f->ws = nullptr;
+            w->ptr = nullptr;
             (void)hipGetLastError();   // clear the allocation error before the launches check theirs
         }
     }
-    if (!f->ws) return launch(nullptr, (size_t)0);
-    if (f->ws_used && f->ws_stream != st) {
-        e = hipStreamWaitEvent(st, f->ws_done, 0);
+    if (!w->ptr) return launch(nullptr, (size_t)0);
+    if (w->used && w->stream != st) {
+        e = hipStreamWaitEvent(st, w->done, 0);
         if (e != hipSuccess) return e;
     }
-    const hipError_t el = launch(f->ws, f->ws_bytes);
+    const hipError_t el = launch(w->ptr, w->bytes);
     // recorded also after a failed launch, whose earlier kernels may have
     // been enqueued on st and use the workspace
-    e = hipEventRecord(f->ws_done, st);
+    e = hipEventRecord(w->done, st);
     if (e == hipSuccess) {
-        f->ws_stream = st;
-        f->ws_used = true;
+        w->stream = st;
+        w->used = true;
     }
     return el != hipSuccess ? el : e;
 }
 
+tl::SmallParams small_params(const tl::GridParams& g) {
+    tl::SmallParams p{};
+    p.grid = true;
+    p.S = g.S;
+    p.F = g.F;
+    p.H = g.H;
+    p.freqs = g.freqs;
+    p.kv = g.kv;
+    p.batch = g.batch;
+    p.engine = g.engine;
+    p.out = g.out;
+    return p;
+}
+
+tl::SmallParams small_params(const tl::ColumnParams& c) {
+    tl::SmallParams p{};
+    p.S = c.S;
+    p.H = c.H;
+    p.freqs = c.freqs;
+    p.freq = c.freq;
+    p.fidx = c.fidx;
+    p.kv = c.kv;
+    p.batch = c.batch;
+    p.engine = c.engine;
+    p.out = c.out;
+    return p;
+}
+
 hipError_t grid_with_workspace(const tl_forest* f, const tl::GridParams& g, hipStream_t st) {
     size_t need = 0;
+    const tl::SmallParams sp = small_params(g);
+    need = tl::small_bytes(f->dev, sp);
+    if (need > 0)
+        return with_workspace(f, need, st, [&](void* ws, size_t) {
+            return ws ? tl::launch_forest_small(f->dev, sp, ws, st) : tl::launch_forest_grid(f->dev, g, nullptr, 0, st);
+        });
     const hipError_t e = tl::grid_order_bytes(f->dev, g, &need);
     if (e != hipSuccess) return e;
     return with_workspace(f, need, st,
@@ -286,7 +342,12 @@ hipError_t grid_with_workspace(const tl_forest* f, const tl::GridParams& g, hipS
 // one: the order is computed once, before run, and serves every launch.
 template <class Run>
 hipError_t column_with_order(const tl_forest* f, tl::ColumnParams& c, hipStream_t st, Run&& run) {
-    size_t need = 0;
+    const tl::SmallParams sp = small_params(c);
+    size_t need = tl::small_bytes(f->dev, sp);
+    if (need > 0)
+        return with_workspace(f, need, st, [&](void* ws, size_t) {
+            return ws ? tl::launch_forest_small(f->dev, sp, ws, st) : run();
+        });
     const hipError_t e = tl::column_order_bytes(f->dev, c, &need);
     if (e != hipSuccess) return e;
     return with_workspace(f, need, st, [&](void* ws, size_t) {
@@ -511,7 +572,18 @@ tl_status tl_forest_predict(const tl_forest* f, const float* rows, int64_t n_row
     if (n_rows > (int64_t)0x7fffffff * 256 * 4)
         return fail(TL_EUNSUPPORTED, "tl_forest_predict: n_rows %lld too large", (long long)n_rows);
     if (n_rows == 0) return ok();
-    return from_hip(tl::launch_forest_rows(f->dev, rows, n_rows, out, (hipStream_t)stream),
+    const hipStream_t st = (hipStream_t)stream;
+    tl::SmallParams sp{};
+    sp.rows = rows;
+    sp.n_rows = n_rows;
+    sp.nf = f->dev.n_features;
+    sp.out = out;
+    const size_t need = tl::small_bytes(f->dev, sp);
+    return from_hip(with_workspace(f, need, st,
+                                   [&](void* ws, size_t) {
+                                       return ws ? tl::launch_forest_small(f->dev, sp, ws, st)
+                                                 : tl::launch_forest_rows(f->dev, rows, n_rows, out, st);
+                                   }),
                     "tl_forest_predict: launch");
 }
 
@@ -830,9 +902,12 @@ tl_status tl_select_freq_binary(const tl_forest* f, int64_t n_scenarios, int32_t
     gp.engine = f->dev.n_features == 4 ? engine_size : nullptr;
     gp.out = ips_work;
     // M at every scenario's probe: a table read per row with a lattice, walks otherwise
+    const tl::SmallParams few = small_params(c);
+    void* few_ws = nullptr;   // set while the call runs as one with few rows
     auto model = [&]() {
-        return lattice ? tl::launch_lattice_column(f->dev, lattice->dev, gp, c.fidx, 0, st)
-                       : tl::launch_forest_column(f->dev, c, st);
+        return lattice  ? tl::launch_lattice_column(f->dev, lattice->dev, gp, c.fidx, 0, st)
+               : few_ws ? tl::launch_forest_small(f->dev, few, few_ws, st)
+                        : tl::launch_forest_column(f->dev, c, st);
     };
     int32_t rounds = 0;
     while ((int64_t)1 << rounds < n_freqs) ++rounds;
@@ -850,6 +925,14 @@ tl_status tl_select_freq_binary(const tl_forest* f, int64_t n_scenarios, int32_t
         return e;
     };
     if (lattice) return from_hip(search(nullptr), "tl_select_freq_binary: launch");
+    const size_t need_few = tl::small_bytes(f->dev, few);
+    if (need_few > 0)
+        return from_hip(with_workspace(f, need_few, st,
+                                       [&](void* ws, size_t) {
+                                           few_ws = ws;
+                                           return search(nullptr);
+                                       }),
+                        "tl_select_freq_binary: launch");
     // The probes walk the same rows every round: one work order serves them
     // all.  Scratch: the order, then the final probe's live items.
     size_t need_order = 0, need_live = 0;

@@ -5,8 +5,8 @@
 // for every projected iteration) and of one probe of a search over
 // frequencies (Sec. 4.5).
 //
-// A wavefront takes RPL stripes of 64 consecutive iterations of one scenario,
-// RPL rows per lane; the rows differ, so every lane walks every tree (the grid
+// A wavefront takes RPL (1 or 2) stripes of 64 consecutive iterations of one
+// scenario, RPL rows per lane; the rows differ, so every lane walks every tree (the grid
 // kernel's leaf reuse needs many frequencies on the same row sequence).
 // Sixteen wavefronts of a workgroup share two LDS buffers of tree-record
 // blocks, copied straight from global memory and handed over without block
@@ -40,6 +40,7 @@ namespace {
 constexpr int kColWaves = 16;
 constexpr int kColThreads = kColWaves * kWave;
 constexpr size_t kColLdsBudget = 152 * 1024;
+constexpr size_t kColLdsHalf = 76 * 1024;
 
 template <int RPL>
 struct ColumnItem {
@@ -88,13 +89,13 @@ __device__ __forceinline__ void add_leaves(uint32_t tree, uint32_t rec_bytes, in
 template <int NF, int RPL, bool ROWS>
 __global__ __launch_bounds__(kColThreads) void forest_column_lds_kernel(RankDev D, TreeBlocks B, ColumnParams P) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const uint32_t rec_bytes = rank_record_bytes(D.depth);
+    const uint32_t rec_bytes = staged_bytes<true>(D.depth);
     const uint32_t buf_bytes = stage_buffer_bytes(B.tb, rec_bytes);
     const int wave = threadIdx.x / kWave;
     const int64_t item = __builtin_amdgcn_readfirstlane((int64_t)blockIdx.x * kColWaves + wave);
     StageSync* sync = (StageSync*)(smem + 2 * buf_bytes);
     if (threadIdx.x == 0) stage_sync_init(sync);
-    if (B.n_blocks > 0) stage_block(D, B, 0, lds_addr(smem), wave, kColWaves);
+    if (B.n_blocks > 0) stage_block<true>(D, B, 0, lds_addr(smem), wave, kColWaves);
     float acc[RPL];
     int64_t o[RPL];     // output index of each row, < 0: none
     int64_t in[RPL];    // input index of each row
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(kColThreads) void forest_column_lds_kernel(RankDev 
         const int32_t b_end = min((grp + 1) * B.group_blocks, B.n_blocks);
         for (int32_t b = grp * B.group_blocks; b < b_end; ++b) {
             const uint32_t buf = lds_addr(smem) + (uint32_t)(b & 1) * buf_bytes;
-            if (b > 0) sync_ok &= stage_acquire(sync, b, kColWaves, D, B, buf);
+            if (b > 0) sync_ok &= stage_acquire<2, true>(sync, b, kColWaves, D, B, buf);
             if (valid) {
                 const int32_t cnt = block_count(D, B, b, block_first(D, B, b));
                 int32_t t = 0;
@@ -333,88 +334,48 @@ __global__ __launch_bounds__(256) void forest_column_global_kernel(const uint2* 
     P.out[c.s * P.H + c.j[0]] = acc;
 }
 
-// Trees per staged block: double buffers within the LDS budget.
-int32_t column_trees_per_block(const ForestDev& f, size_t* lds) {
+hipError_t device_cus(int* cus) {
+    int dev = 0;
+    const hipError_t e = hipGetDevice(&dev);
+    return e != hipSuccess ? e : hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev);
+}
+
+// Trees per staged block: double buffers within the LDS budget.  HALF: of
+// trees without their boxes.
+template <bool HALF>
+int32_t column_trees_per_block(const ForestDev& f, size_t budget, size_t* lds) {
     if (!f.records || f.n_trees == 0) return 0;
-    const uint32_t rec_bytes = rank_record_bytes(f.depth);
+    const uint32_t rec_bytes = staged_bytes<HALF>(f.depth);
     // two tree buffers and their hand-over counters
     auto bytes = [&](int32_t n) { return 2 * (size_t)stage_buffer_bytes(n, rec_bytes) + sizeof(StageSync); };
-    int32_t tb = std::min<int32_t>(f.n_trees, 64);
-    while (tb > 1 && bytes(tb) > kColLdsBudget) --tb;
-    if (bytes(tb) > kColLdsBudget) return 0;
+    // whole quads of trees where four fit
+    int32_t tb = 64;
+    while (tb > 1 && bytes(tb) > budget) tb -= tb > 4 ? 4 : 1;
+    if (bytes(tb) > budget) return 0;
     *lds = bytes(tb);
     return tb;
 }
 
 template <int NF, int RPL, bool ROWS = false>
-hipError_t launch_column_lds(const ForestDev& f, const ColumnParams& c, int32_t tb, size_t lds, hipStream_t stream) {
+hipError_t launch_column_lds(const ForestDev& f, const ColumnParams& c, hipStream_t stream) {
     const int64_t span = kWave * RPL;
     const int64_t items = ROWS ? (c.n_rows + span - 1) / span : c.S * ((c.H + span - 1) / span);
+    int cus = 0;
+    hipError_t e = device_cus(&cus);
+    if (e != hipSuccess) return e;
+    // Half a CU's LDS where there are workgroups for both halves, all of it
+    // where there are not: fewer, larger copies (500 trees of depth 8: 200 000
+    // rows 182 us with all of it, 197 with half; a million 577 and 544).
+    size_t lds = 0;
+    const int32_t tb =
+        column_trees_per_block<true>(f, items > (int64_t)kColWaves * cus ? kColLdsHalf : kColLdsBudget, &lds);
     if (!grid_fits((items + kColWaves - 1) / kColWaves)) return hipErrorInvalidConfiguration;
     const auto kern = forest_column_lds_kernel<NF, RPL, ROWS>;
-    const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)((items + kColWaves - 1) / kColWaves)), dim3(kColThreads), lds, stream,
                        rank_dev(f), tree_blocks(f.n_trees, f.group_trees, tb), c);
     return hipGetLastError();
-}
-
-// Estimated cost of each (scenario, column) pair of the leaf-reuse kernel,
-// for its work order.  A row is taken to need a walk when its cell of the
-// KV / batch cut grid (the forest's threshold cuts) differs from the cells of
-// its lane's two anchors and of the lane's last walked row; the kernel pays
-// one walk time per row position at which any lane of the wavefront walks.
-// cost = (those positions << 10) | (walks over all lanes, at most 64 x 14);
-// with many trees nearly every position has a walk, and the second term,
-// how fast the column's rows change, decides the order.
-// One wavefront per pair; the cuts sit in LDS.  Writes cost[i] and the pair
-// code i = s * n_cols + col.
-constexpr int kColCostWaves = 4;
-
-__global__ __launch_bounds__(kColCostWaves* kWave) void column_cost_kernel(
-    const float* __restrict__ cuts_kv, int32_t n_kv, const float* __restrict__ cuts_bs, int32_t n_bs,
-    const int32_t* __restrict__ kv, const int32_t* __restrict__ batch, int64_t S, int32_t H, int32_t rpl,
-    uint32_t* __restrict__ cost, uint32_t* __restrict__ code) {
-    __shared__ float ck[kMaxCuts], cb[kMaxCuts];
-    for (int32_t i = threadIdx.x; i < n_kv; i += kColCostWaves * kWave) ck[i] = cuts_kv[i];
-    for (int32_t i = threadIdx.x; i < n_bs; i += kColCostWaves * kWave) cb[i] = cuts_bs[i];
-    __syncthreads();
-    const int32_t span = kWave * rpl;
-    const int32_t n_cols = (H + span - 1) / span;
-    const int64_t pair = (int64_t)blockIdx.x * kColCostWaves + threadIdx.x / kWave;
-    if (pair >= S * n_cols) return;
-    const int64_t s = pair / n_cols;
-    const int32_t j0 = (int32_t)(pair % n_cols) * span + lane_id() * rpl;
-    // number of cuts <= x
-    auto rank = [](const float* c, int32_t n, float x) {
-        int32_t lo = 0, hi = n;
-        while (lo < hi) {
-            const int32_t mid = (lo + hi) >> 1;
-            if (c[mid] <= x) lo = mid + 1;
-            else hi = mid;
-        }
-        return (uint32_t)lo;
-    };
-    // the cell of the lane's row r (rows past the horizon repeat the last, as
-    // in the kernel)
-    auto cell = [&](int32_t r) {
-        const int64_t i = s * H + min(j0 + r, H - 1);
-        return rank(ck, n_kv, (float)kv[i]) << 16 | rank(cb, n_bs, (float)batch[i]);
-    };
-    const uint32_t a0 = cell(0), a1 = cell(rpl - 1);
-    uint32_t last = a0, positions = 0, walks = 0;
-    for (int32_t r = 1; r < rpl - 1; ++r) {
-        const uint32_t c = cell(r);
-        const bool need = c != a0 && c != a1 && c != last;
-        if (need) last = c;
-        const uint64_t lanes = __builtin_amdgcn_ballot_w64(need);
-        positions += lanes != 0;
-        walks += (uint32_t)__builtin_popcountll(lanes);
-    }
-    if (lane_id() == 0) {
-        cost[pair] = positions << 10 | walks;
-        code[pair] = (uint32_t)pair;
-    }
 }
 
 // Rows per lane of the leaf-reuse kernel for these rows: 16 (else 8) where
@@ -424,10 +385,8 @@ __global__ __launch_bounds__(kColCostWaves* kWave) void column_cost_kernel(
 hipError_t reuse_rows_per_lane(const ForestDev& f, const ColumnParams& c, int* rpl, int* cus) {
     *rpl = 0;
     size_t lds = 0;
-    if (c.rows || column_trees_per_block(f, &lds) <= 0) return hipSuccess;
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (c.rows || column_trees_per_block<false>(f, kColLdsBudget, &lds) <= 0) return hipSuccess;
+    const hipError_t e = device_cus(cus);
     if (e != hipSuccess) return e;
     for (int r : {16, 8}) {
         const int64_t items = c.S * ((c.H + kWave * r - 1) / (kWave * r));
@@ -456,7 +415,7 @@ hipError_t launch_column_reuse(const ForestDev& f, const ColumnParams& c, int32_
 template <int NF>
 hipError_t launch_column(const ForestDev& f, const ColumnParams& c, hipStream_t stream) {
     size_t lds = 0;
-    const int32_t tb = column_trees_per_block(f, &lds);
+    const int32_t tb = column_trees_per_block<false>(f, kColLdsBudget, &lds);
     if (tb > 0) {
         int rpl = 0, cus = 0;
         const hipError_t e = reuse_rows_per_lane(f, c, &rpl, &cus);
@@ -465,11 +424,14 @@ hipError_t launch_column(const ForestDev& f, const ColumnParams& c, hipStream_t 
         if (rpl == 8) return launch_column_reuse<8>(f, c, tb, lds, stream);
     }
     if (tb > 0) {
-        // rows per lane: enough chains to overlap, without idle stripes on
-        // short horizons
-        if (c.H > 2 * kWave) return launch_column_lds<NF, 4>(f, c, tb, lds, stream);
-        if (c.H > kWave) return launch_column_lds<NF, 2>(f, c, tb, lds, stream);
-        return launch_column_lds<NF, 1>(f, c, tb, lds, stream);
+        int cus = 0;
+        const hipError_t e = device_cus(&cus);
+        if (e != hipSuccess) return e;
+        // rows per lane: 2, with twice the chains to overlap, where that
+        // leaves every CU a workgroup and no idle stripes on short horizons
+        if (c.H > kWave && c.S * ((c.H + kWave * 2 - 1) / (kWave * 2)) >= (int64_t)kColWaves * cus)
+            return launch_column_lds<NF, 2>(f, c, stream);
+        return launch_column_lds<NF, 1>(f, c, stream);
     }
     const int64_t items = c.S * ((c.H + kWave - 1) / kWave);
     if (!grid_fits((items + 3) / 4)) return hipErrorInvalidConfiguration;
@@ -541,12 +503,7 @@ hipError_t order_forest_column(const ForestDev& f, ColumnParams& c, void* ws, hi
     PairOrderPlan p;
     hipError_t e = plan_column_order(f, c, &rpl, &p);
     if (e != hipSuccess || p.n == 0) return e;
-    hipLaunchKernelGGL(column_cost_kernel, dim3((unsigned)((p.n + kColCostWaves - 1) / kColCostWaves)),
-                       dim3(kColCostWaves * kWave), 0, stream, f.cuts_kv, f.n_cuts_kv, f.cuts_bs, f.n_cuts_bs, c.kv,
-                       c.batch, c.S, c.H, rpl, pair_order_cost(p, ws), pair_order_code(p, ws));
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return pair_order_sort(p, ws, &c.order, stream);
+    return pair_order(f, p, c.kv, c.batch, c.H, kWave * rpl, ws, &c.order, stream);
 }
 
 hipError_t column_live_bytes(const ForestDev& f, const ColumnParams& c, size_t* bytes) {
@@ -592,15 +549,23 @@ hipError_t launch_forest_column_live(const ForestDev& f, const ColumnParams& c, 
 hipError_t launch_forest_rows_lds(const ForestDev& f, const float* rows, int64_t n_rows, float* out,
                                   hipStream_t stream) {
     size_t lds = 0;
-    const int32_t tb = (f.n_features == 3 || f.n_features == 4) ? column_trees_per_block(f, &lds) : 0;
+    const int32_t tb = (f.n_features == 3 || f.n_features == 4) ? column_trees_per_block<false>(f, kColLdsBudget, &lds) : 0;
     if (tb <= 0) return hipErrorNotSupported;
     if (n_rows == 0) return hipSuccess;
     ColumnParams c{};
     c.rows = rows;
     c.n_rows = n_rows;
     c.out = out;
-    return f.n_features == 4 ? launch_column_lds<4, 4, true>(f, c, tb, lds, stream)
-                             : launch_column_lds<3, 4, true>(f, c, tb, lds, stream);
+    int cus = 0;
+    const hipError_t e = device_cus(&cus);
+    if (e != hipSuccess) return e;
+    const bool four = f.n_features == 4;
+    // two rows a lane where that leaves every CU a workgroup (four, at half
+    // the wavefronts a CU: 500 trees of depth 8 on 3 M rows 1559 against 1443 us,
+    // 2000 of depth 10 on 1.5 M 6037 against 4793)
+    if (n_rows >= (int64_t)2 * kColThreads * cus)
+        return four ? launch_column_lds<4, 2, true>(f, c, stream) : launch_column_lds<3, 2, true>(f, c, stream);
+    return four ? launch_column_lds<4, 1, true>(f, c, stream) : launch_column_lds<3, 1, true>(f, c, stream);
 }
 
 }  // namespace tl

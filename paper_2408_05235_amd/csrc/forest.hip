@@ -44,6 +44,7 @@
 // others take the column kernel's staged walks).
 #include <hipcub/hipcub.hpp>
 
+#include <algorithm>
 #include <mutex>
 
 #include "device_util.h"
@@ -129,7 +130,6 @@ constexpr int kLdsWavesPerSimd = 8;
 constexpr size_t kLdsBudget = 80 * 1024;
 constexpr int kLdsBuffers = 2;           // tree buffers
 constexpr int kOrderJ = 64;              // future iterations per entry of the work order
-constexpr int kOrderItems = kOrderJ / kLdsJ;
 constexpr int kGlobalJ = 32;             // future iterations per wavefront (global kernel)
 
 // Which (scenario, frequency group, iteration chunk) a wavefront evaluates.
@@ -177,49 +177,6 @@ __device__ __forceinline__ GridItem grid_item(const GridParams& P, int64_t item)
     }
     g.nj = min(J, P.H - g.j0);
     return g;
-}
-
-// Estimated cost of each (scenario, chunk) pair of the grid: how many KV and
-// batch threshold cuts its rows cross from one row to the next (each crossing
-// may change a leaf, i.e. cost a walk).  One thread per pair; the cuts sit in
-// LDS.  Writes cost[i] and the pair code i = s * n_chunks + chunk.
-constexpr int kCostThreads = 256;
-
-__global__ __launch_bounds__(kCostThreads) void grid_cost_kernel(const float* __restrict__ cuts_kv, int32_t n_kv,
-                                                                 const float* __restrict__ cuts_bs, int32_t n_bs,
-                                                                 const int32_t* __restrict__ kv,
-                                                                 const int32_t* __restrict__ batch, int64_t S,
-                                                                 int32_t H, int32_t J, uint32_t* __restrict__ cost,
-                                                                 uint32_t* __restrict__ code) {
-    __shared__ float ck[kMaxCuts], cb[kMaxCuts];
-    for (int32_t i = threadIdx.x; i < n_kv; i += kCostThreads) ck[i] = cuts_kv[i];
-    for (int32_t i = threadIdx.x; i < n_bs; i += kCostThreads) cb[i] = cuts_bs[i];
-    __syncthreads();
-    const int32_t n_chunks = (H + J - 1) / J;
-    const int64_t i = (int64_t)blockIdx.x * kCostThreads + threadIdx.x;
-    if (i >= S * n_chunks) return;
-    const int64_t s = i / n_chunks;
-    const int32_t j0 = (int32_t)(i % n_chunks) * J, j1 = min(j0 + J, H);
-    // number of cuts <= x
-    auto rank = [](const float* c, int32_t n, float x) {
-        int32_t lo = 0, hi = n;
-        while (lo < hi) {
-            const int32_t mid = (lo + hi) >> 1;
-            if (c[mid] <= x) lo = mid + 1;
-            else hi = mid;
-        }
-        return lo;
-    };
-    int32_t rk = rank(ck, n_kv, (float)kv[s * H + j0]), rb = rank(cb, n_bs, (float)batch[s * H + j0]);
-    uint32_t c = 0;
-    for (int32_t j = j0 + 1; j < j1; ++j) {
-        const int32_t nk = rank(ck, n_kv, (float)kv[s * H + j]), nb = rank(cb, n_bs, (float)batch[s * H + j]);
-        c += (uint32_t)(abs(nk - rk) + abs(nb - rb));
-        rk = nk;
-        rb = nb;
-    }
-    cost[i] = c;
-    code[i] = (uint32_t)i;
 }
 
 // ---------------------------------------------------------------- LDS-staged
@@ -347,7 +304,7 @@ __global__ __launch_bounds__(kLdsThreads, kLdsWavesPerSimd) void forest_grid_lds
     const int wave = threadIdx.x / kWave;
     const int lane = lane_id();
     const int64_t item = __builtin_amdgcn_readfirstlane((int64_t)blockIdx.x * kLdsWaves + wave);
-    const GridItem g = grid_item<J, kOrderItems>(P, item);
+    const GridItem g = grid_item<J, kOrderJ / J>(P, item);
     const int32_t F = P.F, H = P.H;
     const bool active = g.valid && g.f < F;
     // the J rank pairs of this wavefront are the same for every lane; they
@@ -513,18 +470,42 @@ int32_t lds_trees_per_block(const ForestDev& f, size_t* lds_bytes) {
     return tb;
 }
 
-hipError_t launch_grid_lds(const ForestDev& f, const GridParams& g, int32_t tb, size_t lds, hipStream_t stream) {
-    const auto kern = forest_grid_lds_kernel<kLdsJ>;
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
+int64_t grid_workgroups(const GridParams& g, int J) {
     const int64_t n_chunks = (g.H + kOrderJ - 1) / kOrderJ;
     const int64_t n_fg = (g.F + kWave - 1) / kWave;
-    const int64_t items = g.S * n_fg * n_chunks * kOrderItems;
-    const int64_t blocks = (items + kLdsWaves - 1) / kLdsWaves;
+    const int64_t items = g.S * n_fg * n_chunks * (kOrderJ / J);
+    return (items + kLdsWaves - 1) / kLdsWaves;
+}
+
+template <int J>
+hipError_t launch_grid_lds(const ForestDev& f, const GridParams& g, int32_t tb, size_t lds, hipStream_t stream) {
+    const auto kern = forest_grid_lds_kernel<J>;
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    const int64_t blocks = grid_workgroups(g, J);
     if (!grid_fits(blocks)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kLdsThreads), lds, stream, rank_dev(f),
                        tree_blocks(f.n_trees, f.group_trees, tb), g);
     return hipGetLastError();
+}
+
+// Rows per wavefront: 8 or 16 where 32 would leave CUs without their two
+// workgroups.  Shorter chunks walk more first rows, whose share grows with the
+// depth: 8 while its workgroups x depth stay within 16 per CU, then 16.
+// Measured (us a step at 8 / 16 / 32 rows): 64 boards x 64 x 1024 with 500 trees
+// of depth 8 (512 workgroups at 8 rows) 573 / 779 / 1054, with 2000 of depth 10
+// 4133 / 3366 / 4563, 256 boards of the former 1999 / 1427 / 1265.
+// *ordered: 32 rows, and more workgroups than start at once: only then does a
+// work order pay.
+hipError_t grid_rows(const ForestDev& f, const GridParams& g, int* J, bool* ordered) {
+    int dev = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    auto fits = [&](int rows) { return grid_workgroups(g, rows) * std::max(f.depth, 1) <= 16 * (int64_t)cus; };
+    *J = fits(8) ? 8 : fits(16) ? 16 : kLdsJ;
+    *ordered = *J == kLdsJ && grid_workgroups(g, kLdsJ) > 2 * (int64_t)cus;
+    return hipSuccess;
 }
 
 template <int NF>
@@ -542,9 +523,48 @@ hipError_t launch_grid_global(const ForestDev& f, const GridParams& g, hipStream
 }  // namespace
 
 
+namespace {
+
+// Estimated cost of each pair of a work order, (scenario, J consecutive
+// iterations): by how many thresholds' ranks KV and batch move from one row
+// to the next in the first rank group (each threshold crossed changes a
+// decision of some tree, which may cost a walk).  One wavefront per pair, one
+// row a lane.  Writes cost[i] and the pair's code i = s * n_chunks + chunk.
+// (One thread per pair, searching quantiles of the thresholds for its rows in
+// turn, took 130 us however few the pairs.)
+constexpr int kCostWaves = 4;
+
+__global__ __launch_bounds__(kCostWaves* kWave) void pair_cost_kernel(RankDev D, const int32_t* __restrict__ kv,
+                                                                      const int32_t* __restrict__ batch, int64_t n,
+                                                                      int32_t H, int32_t J,
+                                                                      uint32_t* __restrict__ cost,
+                                                                      uint32_t* __restrict__ code) {
+    const int64_t pair = (int64_t)blockIdx.x * kCostWaves + threadIdx.x / kWave;
+    if (pair >= n) return;
+    const int32_t n_chunks = (H + J - 1) / J;
+    const int64_t s = pair / n_chunks;
+    const int32_t j0 = (int32_t)(pair % n_chunks) * J, j1 = min(j0 + J, H);
+    int32_t sum = 0, before = -1;   // the last rank pair of the step before
+    for (int32_t j = j0; j < j1; j += kWave) {
+        const int64_t i = s * H + min(j + lane_id(), j1 - 1);
+        const int32_t r = (int32_t)rank_row(D, 0, (float)kv[i], (float)batch[i]);
+        if (j == j0) before = __builtin_amdgcn_readfirstlane(r);
+        const int32_t p = wave_shift_up1(r, before);
+        sum += abs((r & 0xffff) - (p & 0xffff)) + abs((int32_t)((uint32_t)r >> 16) - (int32_t)((uint32_t)p >> 16));
+        before = __builtin_amdgcn_readlane(r, kWave - 1);
+    }
+    sum = wave_sum(sum);
+    if (lane_id() == 0) {
+        cost[pair] = (uint32_t)sum;
+        code[pair] = (uint32_t)pair;
+    }
+}
+
+}  // namespace
+
 hipError_t pair_order_plan(const ForestDev& f, int64_t n, int64_t min_pairs, PairOrderPlan* p) {
     *p = PairOrderPlan{0, 0, 0, 0};
-    if (!f.cuts_kv || !f.cuts_bs || n < min_pairs || n >= (int64_t)1 << 31) return hipSuccess;
+    if (!f.orderable || n < min_pairs || n >= (int64_t)1 << 31) return hipSuccess;
     size_t temp = 0;
     const hipError_t e = hipcub::DeviceRadixSort::SortPairsDescending(
         nullptr, temp, (const uint32_t*)nullptr, (uint32_t*)nullptr, (const uint32_t*)nullptr, (uint32_t*)nullptr,
@@ -557,14 +577,20 @@ hipError_t pair_order_plan(const ForestDev& f, int64_t n, int64_t min_pairs, Pai
     return hipSuccess;
 }
 
-hipError_t pair_order_sort(const PairOrderPlan& p, void* ws, const uint32_t** order, hipStream_t stream) {
+hipError_t pair_order(const ForestDev& f, const PairOrderPlan& p, const int32_t* kv, const int32_t* batch, int32_t H,
+                      int32_t J, void* ws, const uint32_t** order, hipStream_t stream) {
     unsigned char* base = (unsigned char*)ws;
+    uint32_t* cost = (uint32_t*)base;
+    uint32_t* code = (uint32_t*)(base + p.arr);
     uint32_t* cost_sorted = (uint32_t*)(base + 2 * p.arr);
     uint32_t* sorted = (uint32_t*)(base + 3 * p.arr);
+    hipLaunchKernelGGL(pair_cost_kernel, dim3((unsigned)((p.n + kCostWaves - 1) / kCostWaves)),
+                       dim3(kCostWaves * kWave), 0, stream, rank_dev(f), kv, batch, p.n, H, J, cost, code);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
     size_t temp = p.temp;
-    const hipError_t e = hipcub::DeviceRadixSort::SortPairsDescending(
-        base + 4 * p.arr, temp, pair_order_cost(p, ws), cost_sorted, pair_order_code(p, ws), sorted, (int)p.n, 0, 32,
-        stream);
+    e = hipcub::DeviceRadixSort::SortPairsDescending(base + 4 * p.arr, temp, cost, cost_sorted, code, sorted, (int)p.n,
+                                                     0, 32, stream);
     if (e != hipSuccess) return e;
     *order = sorted;
     return hipSuccess;
@@ -579,7 +605,11 @@ hipError_t plan_order(const ForestDev& f, const GridParams& g, PairOrderPlan* p)
     *p = PairOrderPlan{0, 0, 0, 0};
     size_t lds = 0;
     if (lds_trees_per_block(f, &lds) <= 0) return hipSuccess;   // the global kernel takes no order
-    return pair_order_plan(f, g.S * ((g.H + kOrderJ - 1) / kOrderJ), 2 * 16, p);
+    int J = 0;
+    bool ordered = false;
+    const hipError_t e = grid_rows(f, g, &J, &ordered);
+    if (e != hipSuccess || !ordered) return e;
+    return pair_order_plan(f, g.S * ((g.H + kOrderJ - 1) / kOrderJ), 1, p);
 }
 
 }  // namespace
@@ -604,14 +634,16 @@ hipError_t launch_forest_grid(const ForestDev& f, const GridParams& g_in, void* 
     // the order only speeds the kernel up: without room for it the items
     // keep their natural numbering
     if (p.n > 0 && ws && ws_bytes >= p.bytes) {
-        hipLaunchKernelGGL(grid_cost_kernel, dim3((unsigned)((p.n + kCostThreads - 1) / kCostThreads)),
-                           dim3(kCostThreads), 0, stream, f.cuts_kv, f.n_cuts_kv, f.cuts_bs, f.n_cuts_bs, g.kv,
-                           g.batch, g.S, g.H, kOrderJ, pair_order_cost(p, ws), pair_order_code(p, ws));
-        e = hipGetLastError();
-        if (e == hipSuccess) e = pair_order_sort(p, ws, &g.order, stream);
+        e = pair_order(f, p, g.kv, g.batch, g.H, kOrderJ, ws, &g.order, stream);
         if (e != hipSuccess) return e;
     }
-    return launch_grid_lds(f, g, tb, lds, stream);
+    int J = 0;
+    bool ordered = false;
+    e = grid_rows(f, g, &J, &ordered);
+    if (e != hipSuccess) return e;
+    return J == 32   ? launch_grid_lds<32>(f, g, tb, lds, stream)
+           : J == 16 ? launch_grid_lds<16>(f, g, tb, lds, stream)
+                     : launch_grid_lds<8>(f, g, tb, lds, stream);
 }
 
 // Workspace of the grid kernel's work order for callers that cannot

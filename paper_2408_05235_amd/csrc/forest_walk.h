@@ -138,19 +138,38 @@ __device__ __forceinline__ void stage_piece(const uint4* src, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(base), "v"(src) : "memory", "m0");
 }
 
-// Enqueues this wavefront's pieces of block b into the LDS buffer at byte
-// address dst.
-__device__ __forceinline__ void stage_block(const RankDev& D, const TreeBlocks& B, int32_t b, uint32_t dst, int wave,
+// Bytes of a staged tree: the whole record, or (HALF) its nodes and leaf
+// values only, for walks that never look at a box.
+template <bool HALF>
+__host__ __device__ inline uint32_t staged_bytes(int32_t depth) {
+    const uint32_t whole = rank_record_bytes(depth);
+    return HALF && depth > 0 ? whole / 2 : whole;
+}
+
+// Enqueues this wavefront's pieces of trees [first, first + cnt) into the LDS
+// buffer at byte address dst.
+template <bool HALF>
+__device__ __forceinline__ void stage_trees(const RankDev& D, int32_t first, int32_t cnt, uint32_t dst, int wave,
                                             int n_waves) {
     const uint32_t rec_words = rank_record_bytes(D.depth) / 16u;
-    const int32_t first = block_first(D, B, b);
-    const uint32_t words = (uint32_t)block_count(D, B, b, first) * rec_words;
+    const int32_t log_words = 31 - __builtin_clz(staged_bytes<HALF>(D.depth) / 16u);
+    const uint32_t words = (uint32_t)cnt << log_words;
     const uint4* src = D.records + (int64_t)first * rec_words;
     const uint32_t n_pieces = (words + kWave - 1) / kWave;
     for (uint32_t pc = (uint32_t)wave; pc < n_pieces; pc += (uint32_t)n_waves) {
         const uint32_t i = pc * kWave + lane_id();
-        stage_piece(src + (i < words ? i : 0u), dst + pc * kStagePiece);
+        const uint32_t w = i < words ? i : 0u;
+        const uint32_t at = HALF ? (w >> log_words) * rec_words + (w & ((1u << log_words) - 1u)) : w;
+        stage_piece(src + at, dst + pc * kStagePiece);
     }
+}
+
+// The same for block b.
+template <bool HALF = false>
+__device__ __forceinline__ void stage_block(const RankDev& D, const TreeBlocks& B, int32_t b, uint32_t dst, int wave,
+                                            int n_waves) {
+    const int32_t first = block_first(D, B, b);
+    stage_trees<HALF>(D, first, block_count(D, B, b, first), dst, wave, n_waves);
 }
 
 // Hand-over of NB LDS buffers of tree blocks between the wavefronts of a
@@ -197,7 +216,7 @@ __device__ __forceinline__ int32_t sync_load(const int32_t* p) {
 
 // Makes block b >= 1 available in its buffer at LDS byte address buf;
 // n_waves wavefronts share the buffers.
-template <int NB = 2>
+template <int NB = 2, bool HALF = false>
 __device__ __forceinline__ bool stage_acquire(StageSync* sync, int32_t b, int n_waves, const RankDev& D,
                                               const TreeBlocks& B, uint32_t buf) {
     const int cur = b % NB;
@@ -219,7 +238,7 @@ __device__ __forceinline__ bool stage_acquire(StageSync* sync, int32_t b, int n_
                 __builtin_amdgcn_s_sleep(1);
                 ++spins;
             }
-            stage_block(D, B, b, buf, 0, 1);
+            stage_block<HALF>(D, B, b, buf, 0, 1);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             if (lane_id() == 0) __hip_atomic_store(&sync->ready[cur], b, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
             break;

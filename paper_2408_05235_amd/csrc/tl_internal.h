@@ -149,14 +149,10 @@ struct ForestDev {
     const float* dict;
     const uint16_t* starts;
     int32_t group_trees, n_groups;
-    // Quantiles of the forest's KV (feature 1) and batch (feature 2)
-    // thresholds, ascending, at most kMaxCuts each (NULL / 0 when
-    // n_features < 3).  Between two rows, the number of cuts crossed by KV
-    // and batch estimates how many tree decisions change: the cost model
-    // for ordering the grid kernel's work.
-    const float* cuts_kv;
-    const float* cuts_bs;
-    int32_t n_cuts_kv, n_cuts_bs;
+    // Whether KV and batch both have a finite threshold: between two rows,
+    // the thresholds that KV and batch cross estimate how many tree decisions
+    // change, the cost model for ordering the grid and column kernels' work.
+    bool orderable;
 };
 
 struct GridParams {
@@ -194,6 +190,29 @@ struct GatherParams {
     const float* engine;            // [S] (4 features)
     float* out;                     // [S][F][H]
 };
+
+// A call with few rows (small.hip): the rows of the projection grid (grid),
+// of one frequency per scenario (as ColumnParams), or a caller's own (rows).
+struct SmallParams {
+    bool grid;
+    int64_t S;
+    int32_t F, H;
+    const float* freqs;             // grid, or with fidx
+    float freq;                     // neither
+    const int32_t* fidx;            // nullable; rows with an index < 0 are left alone
+    const int32_t* kv;
+    const int32_t* batch;
+    const float* engine;            // 4-feature forests, else NULL
+    const float* rows;              // nullable
+    int64_t n_rows;
+    int32_t nf;
+    float* out;                     // [rows]
+};
+inline int64_t small_rows(const SmallParams& p) { return p.rows ? p.n_rows : p.S * (p.grid ? p.F : 1) * p.H; }
+// Scratch bytes of launch_forest_small for this call; 0 when it does not
+// apply or the other kernels are faster.
+size_t small_bytes(const ForestDev& f, const SmallParams& p);
+hipError_t launch_forest_small(const ForestDev& f, const SmallParams& p, void* ws, hipStream_t stream);
 
 hipError_t launch_lattice_inputs(const LatticeDev& L, int64_t s0, int64_t count, int32_t* kv, int32_t* batch,
                                  float* engine, hipStream_t stream);
@@ -242,12 +261,12 @@ hipError_t order_forest_column(const ForestDev& f, ColumnParams& c, void* ws, hi
 // leaf-reuse kernel, fidx or ws, a plain launch_forest_column.
 hipError_t column_live_bytes(const ForestDev& f, const ColumnParams& c, size_t* bytes);
 hipError_t launch_forest_column_live(const ForestDev& f, const ColumnParams& c, void* ws, hipStream_t stream);
-// A work order: n pairs sorted by an estimated cost, most expensive first.
+// A work order: n pairs (scenario s, J consecutive iterations), code s *
+// ceil(H / J) + chunk, sorted by an estimated cost, most expensive first.
 // Its workspace holds four arrays of one 32-bit word per pair (cost, code,
-// and their sorted copies) and the sort's temporary storage.  The caller
-// fills pair_order_cost / pair_order_code (pair i's cost and its code),
-// then pair_order_sort points *order at the codes sorted by cost.
-// pair_order_plan gives n = 0 (no order) when the forest has no cuts to
+// and their sorted copies) and the sort's temporary storage.  pair_order
+// enqueues the estimate and the sort, and points *order at the sorted codes.
+// pair_order_plan gives n = 0 (no order) when the forest has no thresholds to
 // estimate costs with, or n < min_pairs.
 struct PairOrderPlan {
     int64_t n;          // pairs; 0 = no order
@@ -256,9 +275,8 @@ struct PairOrderPlan {
     size_t bytes;       // 4 * arr + temp
 };
 hipError_t pair_order_plan(const ForestDev& f, int64_t n, int64_t min_pairs, PairOrderPlan* p);
-inline uint32_t* pair_order_cost(const PairOrderPlan&, void* ws) { return (uint32_t*)ws; }
-inline uint32_t* pair_order_code(const PairOrderPlan& p, void* ws) { return (uint32_t*)((unsigned char*)ws + p.arr); }
-hipError_t pair_order_sort(const PairOrderPlan& p, void* ws, const uint32_t** order, hipStream_t stream);
+hipError_t pair_order(const ForestDev& f, const PairOrderPlan& p, const int32_t* kv, const int32_t* batch, int32_t H,
+                      int32_t J, void* ws, const uint32_t** order, hipStream_t stream);
 // The same kernel on arbitrary rows [n_rows][n_features] (3 or 4 features,
 // LDS records present); hipErrorNotSupported when the forest has no records.
 hipError_t launch_forest_rows_lds(const ForestDev& f, const float* rows, int64_t n_rows, float* out,

@@ -8,7 +8,10 @@ import subprocess
 
 import pytest
 
-from test_sanitizers import CSRC, HERE, SAN
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HERE = os.path.join(ROOT, "tests", "sanitize")
+CSRC = os.path.join(ROOT, "paper_2408_05235_amd", "csrc")
+SAN = ["-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all"]
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="no host compiler")
