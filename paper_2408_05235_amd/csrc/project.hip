@@ -26,10 +26,11 @@
 // Admissions only happen after the last iteration at which the in-flight
 // batch alone exceeds the capacity, which makes the lifetime check equal to
 // checking the whole projected vector from the current iteration on.
-// Without a batch cap, up to 64 requests are tried at once at their FIFO
-// targets with one check of their summed contribution; when that fails the
-// batch shrinks, and below 8 requests a growing number of them are admitted
-// one at a time before batching again.
+// Without a batch cap the whole queue is tried at its FIFO targets first,
+// with O(1) events per request and one check of the summed curve (boards whose
+// capacity never binds are done then), else the longest part of it that fits;
+// past that, where the capacity binds, the requests that the head's start has
+// room for are admitted together.
 #include "device_util.h"
 #include "tl_internal.h"
 
@@ -124,6 +125,100 @@ __device__ __forceinline__ void add_request(int32_t* KV, int32_t c, int32_t a, i
     }
 }
 
+// The stride-N prefix sums of X[0 .. H), in place: X[t] += X[t - N] (already
+// summed).  One wavefront.
+__device__ __forceinline__ void strided_scan(int32_t* X, int32_t H, int32_t N) {
+    const int lane = lane_id();
+    const int32_t lane_mod = lane % N;
+    for (int32_t t0 = 0; t0 < H; t0 += kWave) {
+        const int32_t t = t0 + lane;
+        const bool in = t < H;
+        int32_t c = in ? X[t] : 0;
+        for (int32_t d = N; d < kWave; d <<= 1) {
+            const int32_t u = __shfl_up(c, d);
+            if (lane >= d) c += u;
+        }
+        const int32_t prev = t0 + lane_mod - N;
+        if (prev >= 0 && in) c += X[prev];
+        if (in) X[t] = c;
+    }
+}
+
+// The prefix sums of X[0 .. H), in place; the last iteration whose sum
+// exceeds cap (-1: none), and the first such one from `from` on (H: none).
+__device__ __forceinline__ int32_t prefix_scan(int32_t* X, int32_t H, int32_t cap, int32_t from, int32_t* first_over) {
+    int32_t carry = 0, last_over = -1, first = H;
+    for (int32_t t0 = 0; t0 < H; t0 += kWave) {
+        const int32_t t = t0 + lane_id();
+        const bool in = t < H;
+        const int32_t y = wave_incl_scan(in ? X[t] : 0) + carry;
+        carry = __builtin_amdgcn_readlane(y, kWave - 1);
+        if (in) {
+            X[t] = y;
+            if (y > cap) {
+                last_over = t;
+                if (t >= from) first = min(first, t);
+            }
+        }
+    }
+    *first_over = H - wave_max(H - first);
+    return wave_max(last_over);
+}
+
+// Undoes prefix_scan and strided_scan, in place: X[t] -= X[t - 1], then
+// X[t] -= X[t - N] of those differences.  From the last iteration down, so
+// that every read comes before the write of what it reads.
+__device__ __forceinline__ void unscan(int32_t* X, int32_t H, int32_t N) {
+    constexpr int kU = 4;
+    for (int32_t t1 = (H + kU * kWave - 1) / (kU * kWave) * (kU * kWave); t1 > 0; t1 -= kU * kWave) {
+        int32_t v[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int32_t t = t1 - (u + 1) * kWave + lane_id();
+            v[u] = 0;
+            if (t < H) {
+                v[u] = X[t];
+                if (t >= 1) v[u] -= X[t - 1];
+                if (t >= N) v[u] -= X[t - N];
+                if (t > N) v[u] += X[t - N - 1];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int32_t t = t1 - (u + 1) * kWave + lane_id();
+            if (t < H) X[t] = v[u];
+        }
+    }
+}
+
+// Events of a request with c cached tokens in the batch on [a, e), a < H, in
+// an array whose stride-N prefix sums' prefix sums are the KV curve (what
+// unscan leaves): sign times its KV blocks ceil((c + t - a) / N).  A jump of v
+// at p is +v at p and -v at p + N; the comb of its new blocks starts at its
+// first new-block iteration and stops at the first comb point past its end.
+__device__ __forceinline__ void add_events(int32_t* X, int32_t c, int32_t a, int64_t e, int32_t H, int32_t N,
+                                           const DivU32& divN, int32_t sign) {
+    const int32_t v = (int32_t)ceil_div_u32((uint32_t)c, divN);
+    if (v) {
+        atomicAdd(&X[a], sign * v);
+        if (N < H - a) atomicAdd(&X[a + N], -sign * v);
+    }
+    const int32_t rc = (int32_t)((uint32_t)c - div_u32((uint32_t)c, divN) * (uint32_t)N);
+    const int64_t j0 = (int64_t)a + (rc == 0 ? 1 : N + 1 - rc);
+    if (j0 < min(e, (int64_t)H)) {
+        atomicAdd(&X[j0], sign);
+        if (e < H) {
+            const int64_t jend = j0 + (int64_t)N * (int32_t)ceil_div_u32((uint32_t)(e - j0), divN);
+            if (jend < H) atomicAdd(&X[jend], -sign);
+        }
+    }
+    if (e < H) {
+        const int32_t w = (int32_t)ceil_div_u32((uint32_t)(c + (int32_t)(e - a) - 1), divN);
+        atomicAdd(&X[e], -sign * w);
+        if (e + N < H) atomicAdd(&X[e + N], sign * w);
+    }
+}
+
 // Scenario order for long FIFO loops: one wavefront per scenario, whose time
 // grows with its number of requests; launched heaviest first, the last
 // wavefronts of the grid are short ones instead of whichever came last.  A
@@ -165,10 +260,6 @@ __global__ __launch_bounds__(256) void order_place_kernel(const int64_t* off, in
     const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (s < S) order[atomicAdd(&counts[order_bucket(off, s)], 1u)] = (int32_t)s;
 }
-
-// Smallest batch of queued requests tried at once (no batch cap): below it the
-// admission loop takes requests one at a time.
-constexpr int32_t kMinBatch = 8;
 
 // BD_LDS: the batch difference array lives in LDS beside the KV curve, as a
 // batch cap needs (the admission loop reads its running sums).  Without a
@@ -261,21 +352,7 @@ __global__ __launch_bounds__(64) void project_kernel(ProjectParams P) {
     }
     if (cand && lane == 0) inflight_comb(cand_p, cand_l, H, N, divN, KV);
     __syncthreads();
-    {
-        const int32_t lane_mod = lane % N;
-        for (int32_t t0 = 0; t0 < H; t0 += kWave) {
-            const int32_t t = t0 + lane;
-            const bool in = t < H;
-            int32_t c = in ? KV[t] : 0;
-            for (int32_t d = N; d < kWave; d <<= 1) {
-                const int32_t u = __shfl_up(c, d);
-                if (lane >= d) c += u;
-            }
-            const int32_t prev = t0 + lane_mod - N;
-            if (prev >= 0 && in) c += KV[prev];
-            if (in) KV[t] = c;
-        }
-    }
+    strided_scan(KV, H, N);
     __syncthreads();
 
     // pass B2: jumps, batch events, deadline checkpoints
@@ -309,21 +386,8 @@ __global__ __launch_bounds__(64) void project_kernel(ProjectParams P) {
     // bound (pass A) is at least the KV of every iteration: when it fits the
     // capacity, no admission check can fail and the checks are skipped
     const bool kv_fits = cap >= 0 && bound <= (uint64_t)cap;
-    int32_t last_over = -1;
-    {
-        int32_t carry_kv = 0;
-        for (int32_t t0 = 0; t0 < H; t0 += kWave) {
-            const int32_t t = t0 + lane;
-            const bool in = t < H;
-            const int32_t y = wave_incl_scan(in ? KV[t] : 0) + carry_kv;
-            carry_kv = __builtin_amdgcn_readlane(y, kWave - 1);
-            if (in) {
-                KV[t] = y;
-                if (y > cap) last_over = t;
-            }
-        }
-    }
-    last_over = wave_max(last_over);
+    int32_t first_over = H;   // (of the whole queue's sum, below)
+    const int32_t last_over = prefix_scan(KV, H, cap, 0, &first_over);
     const bool has_bcap = BD_LDS && P.batch_cap != nullptr;   // (the host takes BD_LDS with a cap)
     const int32_t bcap = has_bcap ? P.batch_cap[s] : 0;
     if (last_over >= 0 || (has_bcap && n_in > bcap)) fl |= TL_FLAG_OVERCOMMIT;
@@ -339,14 +403,127 @@ __global__ __launch_bounds__(64) void project_kernel(ProjectParams P) {
         int32_t j = 0;
         int32_t run = 0;    // batch size at j (prefix of BD; kept only under a batch cap)
         if (has_bcap) run = __builtin_amdgcn_readfirstlane(BD[0]);
-        int32_t bsz = kWave;   // requests tried as one batch (no batch cap)
-        int32_t seq_left = 0;  // one-at-a-time admissions before the next batch try
-        int32_t backoff = 1;   // ... after the next run of failed batches
+        // (no batch cap) how the next requests are tried, see below
+        bool at_targets = true;
+        bool alone = false;
+        int32_t fmax = kWave;          // requests tried at one start at most
+        int32_t calm = 0, calm_need = 4;
+        int32_t streak = 0, streak_need = 0;
         int64_t cb = lo - kWave;
         int32_t q_arr = 0, q_c = 0, q_len = 0, q_lost = 0;
+        // (no batch cap) running maximum of the chunk's arrivals, the blocks
+        // a request starts with, and their running sum
+        int32_t q_max = -1, q_c0 = 0, q_sum = 0;
         uint64_t q_dl = kNoDeadline;
         uint64_t mask = 0;
         for (;;) {
+            if (!has_bcap && mask == 0 && streak >= streak_need && hi - (cb + kWave) >= 2 * kWave) {
+                // All remaining requests at once, each at its FIFO target (the
+                // running maximum of the arrivals, from max(j, last_over +
+                // 1)): O(1) events a request, one scan, one check.  When the
+                // sum fits everywhere, so does every request's own check at
+                // its target (each sees the KV of the requests before it, which
+                // is no more than the sum): these are the admissions that the
+                // one-at-a-time loop makes.  Otherwise the most leading chunks
+                // of 64 requests that fit together are found by bisection.
+                const int64_t first = cb + kWave;
+                const int32_t n_ch = (int32_t)((hi - first + kWave - 1) / kWave);
+                const int32_t lo_j = max(j, last_over + 1);
+                // chunks k0 .. to - 1, `run` being the running maximum of the
+                // targets before chunk k0; those from `from` on add their
+                // events times sign, or commit their batch events, deadlines
+                // and n_end.  Returns the running maximum before chunk `at`.
+                auto chunks = [&](int32_t k0, int32_t run, int32_t from, int32_t to, int32_t at, int32_t sign,
+                                  bool commit) {
+                    int32_t before = run;
+                    // the next chunk's fields are fetched while one is worked on
+                    int32_t na = -1, np = 0, ng = 0, nr = 0;
+                    auto fetch = [&](int32_t k) {
+                        const int64_t i = first + (int64_t)k * kWave + lane;
+                        na = -1;
+                        if (k < to && i < hi) {
+                            na = P.arr[i];
+                            np = P.prompt[i];
+                            ng = P.gen[i];
+                            nr = P.rem[i];
+                        }
+                    };
+                    fetch(k0);
+                    for (int32_t k = k0; k < to; ++k) {
+                        const int64_t i = first + (int64_t)k * kWave + lane;
+                        int32_t a = na;
+                        const int32_t c = np + ng, len = nr;
+                        const bool q = a >= 0 && entry_ok(np, ng, nr, a);
+                        fetch(k + 1);
+                        a = max(wave_incl_max(q ? a : -1), run);
+                        run = __builtin_amdgcn_readlane(a, kWave - 1);
+                        if (k + 1 == at) before = run;
+                        if (k < from) continue;
+                        if (q && a < H) {
+                            const int64_t e = (int64_t)a + len;
+                            if (!commit) {
+                                add_events(KV, c, a, e, H, N, divN, sign);
+                            } else {
+                                atomicAdd(&BD[a], 1);
+                                if (e < H) atomicAdd(&BD[e], -1);
+                                const uint64_t dl = P.deadline ? P.deadline[i] : kNoDeadline;
+                                if (e <= H && dl != kNoDeadline && !(P.lost && P.lost[i]))
+                                    atomicMin((unsigned long long*)&outDL[e - 1], (unsigned long long)dl);
+                                n_end = max(n_end, (int32_t)min(e, (int64_t)H));
+                            }
+                        }
+                    }
+                    return before;
+                };
+                int32_t ok = 0, ok_run = lo_j, bad = n_ch + 1, cur = 0, want = n_ch, guess = 0;
+                for (;;) {
+                    unscan(KV, H, N);
+                    const int32_t run = want > cur ? chunks(ok, ok_run, cur, want, want, 1, false)
+                                                   : chunks(ok, ok_run, want, cur, want, -1, false);
+                    strided_scan(KV, H, N);
+                    const bool fits = prefix_scan(KV, H, cap, last_over + 1, &first_over) <= last_over || kv_fits;
+                    cur = want;
+                    if (want == ok) break;   // what did not fit is taken out again
+                    if (fits) {
+                        ok = want;
+                        ok_run = run;
+                        if (bad - ok <= 1) break;
+                    } else {
+                        bad = want;
+                    }
+                    want = (ok + bad) / 2;   // == ok when bad == ok + 1
+                    if (bad == n_ch) {
+                        // First guess: the chunks that have arrived when the
+                        // whole sum first exceeds the capacity; without later
+                        // arrivals it falls from there.  Second: one more.
+                        if (ok == 0) {
+                            int32_t k_over = 0;
+                            for (int32_t k0 = 0; k0 < n_ch; k0 += kWave) {
+                                const int32_t k = k0 + lane;
+                                const int32_t a = k < n_ch ? P.arr[first + (int64_t)k * kWave] : INT32_MAX;
+                                k_over += (int32_t)__builtin_popcountll(__ballot(a <= first_over));
+                            }
+                            guess = k_over - 1;
+                        } else {
+                            guess = ok + 1;
+                        }
+                        if (guess > ok && guess < bad) want = guess;
+                    }
+                }
+                if (ok > 0) {
+                    chunks(0, lo_j, 0, ok, ok, 1, true);
+                    n_end = wave_max(n_end);
+                    if (ok_run >= H) break;   // the head cannot start within the horizon
+                    j = ok_run;
+                }
+                cb += (int64_t)ok * kWave;
+                streak = 0;
+                if (ok < n_ch) {
+                    streak_need = min(64, max(4, 2 * streak_need));
+                    at_targets = false;
+                    calm = 0;
+                }
+            }
             while (mask == 0) {
                 cb += kWave;
                 if (cb >= hi) break;
@@ -362,23 +539,21 @@ __global__ __launch_bounds__(64) void project_kernel(ProjectParams P) {
                     q_dl = P.deadline ? P.deadline[i] : kNoDeadline;
                 }
                 mask = __ballot(q);
+                if (!has_bcap && mask) {
+                    q_max = wave_incl_max(q ? q_arr : -1);
+                    q_c0 = q ? (int32_t)ceil_div_u32((uint32_t)q_c, divN) : 0;
+                    q_sum = wave_incl_scan(q_c0);
+                }
             }
             if (mask == 0) break;
 
-            if (!has_bcap && bsz > 1 && seq_left == 0) {
-                // Batched admission of the next bsz queued requests, each at
-                // its FIFO target: the running maximum of the arrivals, from
-                // max(j, last_over + 1).  Their summed contribution is added
-                // to the KV curve and checked once.  If the sum fits
-                // everywhere, so does every request's own check at its target
-                // (each sees the KV of the requests before it, which is no
-                // more than the sum): these are exactly the admissions the
-                // one-at-a-time loop makes.  Otherwise the contributions are
-                // taken out again and fewer are tried.
+            if (!has_bcap && at_targets) {
+                // The rest of this chunk of the queue, each at its FIFO
+                // target, as above; their contributions are added to the KV
+                // curve iteration by iteration and taken out again when they
+                // do not fit.
                 const int32_t lo_j = max(j, last_over + 1);
-                const uint32_t below = __builtin_amdgcn_mbcnt_hi(
-                    (uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-                const bool mem = ((mask >> lane) & 1) && (int32_t)below < bsz;
+                const bool mem = (mask >> lane) & 1;
                 const int32_t a = wave_incl_max(mem ? max(q_arr, lo_j) : -1);
                 const uint64_t memm = __ballot(mem);
                 const uint64_t over = __ballot(mem && a >= H);
@@ -413,15 +588,10 @@ __global__ __launch_bounds__(64) void project_kernel(ProjectParams P) {
                         const int32_t lim = __builtin_amdgcn_readlane(lim_l, m);
                         add_request<true, POW2, 1>(KV, cm, am, lim, divN);
                     }
-                    // shrink the batch; once down to single requests, admit
-                    // a growing number of them one at a time before batching
-                    // again (the capacity binds)
-                    bsz >>= 2;
-                    if (bsz < kMinBatch) {
-                        bsz = kMinBatch;
-                        seq_left = backoff;
-                        backoff = min(2 * backoff, 256);
-                    }
+                    at_targets = false;
+                    streak = 0;
+                    calm = 0;
+                    calm_need = min(256, 2 * calm_need);
                     continue;
                 }
                 if ((take >> lane) & 1) {
@@ -434,14 +604,96 @@ __global__ __launch_bounds__(64) void project_kernel(ProjectParams P) {
                 n_end = max(n_end, r_end);
                 j = __builtin_amdgcn_readlane(a, 63 - __clzll((long long)take));
                 mask &= ~take;
-                bsz = min(kWave, 2 * bsz);
-                backoff = 1;
+                ++streak;
+                if (streak >= 4) calm_need = 4;
                 if (over) break;
                 continue;
             }
 
-            // One request at a time (under a batch cap, or after batches
-            // failed).  The head of the queue: uniform lane, lane reads.
+            if (!has_bcap && !alone) {
+                // The capacity binds: the head and the requests behind it that
+                // have arrived by its start j, as many as the KV of iteration
+                // j itself leaves room for.  When their sum fits everywhere,
+                // they are the one-at-a-time loop's admissions at j, and the
+                // next of them does not fit at j.  A head without room at j
+                // starts no earlier than the next iteration that has it.
+                const bool queued = (mask >> lane) & 1;
+                const int hl = __ffsll((unsigned long long)mask) - 1;
+                const int32_t start = max(max(j, last_over + 1), __builtin_amdgcn_readlane(q_max, hl));
+                const int32_t c_h = __builtin_amdgcn_readlane(q_c0, hl);
+                int32_t room = -1, found = -1;
+                for (int32_t t0 = start; t0 < H; t0 += kWave) {
+                    const int32_t t = t0 + lane;
+                    const int32_t left = cap - KV[min(t, H - 1)];
+                    const uint64_t m = __ballot(t < H && left >= c_h);
+                    if (m) {
+                        const int l = __ffsll((unsigned long long)m) - 1;
+                        found = t0 + l;
+                        room = __builtin_amdgcn_readlane(left, l);
+                        break;
+                    }
+                }
+                if (found < 0) break;   // the head cannot start within the horizon
+                if (found > start) calm = 0;
+                j = found;
+                // the requests behind it that have arrived (those before it in
+                // the chunk, admitted by now, arrived no later than j)
+                const bool mem = queued && q_max <= j;
+                const int32_t sum = q_sum - (__builtin_amdgcn_readlane(q_sum, hl) - c_h);
+                const uint32_t below = __builtin_amdgcn_mbcnt_hi(
+                    (uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                const uint64_t take = __ballot(mem && sum <= room && (int32_t)below < fmax);
+                const uint64_t blocked = __ballot(mem && sum > room);
+                if ((take & (take - 1)) == 0) {
+                    alone = true;   // one request: checked below before it is added
+                    continue;
+                }
+                const int32_t lim_l = q_len >= H - j ? H : j + q_len;
+                int32_t r_end = 0;
+                for (uint64_t mm = take; mm; mm &= mm - 1) {
+                    const int m = __ffsll((unsigned long long)mm) - 1;
+                    const int32_t lim = __builtin_amdgcn_readlane(lim_l, m);
+                    r_end = max(r_end, lim);
+                    add_request<false, POW2, 1>(KV, __builtin_amdgcn_readlane(q_c, m), j, lim, divN);
+                }
+                bool over = false;
+                for (int32_t t0 = j; t0 < r_end; t0 += 8 * kWave) {
+                    int32_t v[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) v[u] = KV[min(t0 + u * kWave + lane, r_end - 1)];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) over |= v[u] > cap;
+                }
+                if (__ballot(over) != 0) {
+                    for (uint64_t mm = take; mm; mm &= mm - 1) {
+                        const int m = __ffsll((unsigned long long)mm) - 1;
+                        add_request<true, POW2, 1>(KV, __builtin_amdgcn_readlane(q_c, m), j,
+                                                   __builtin_amdgcn_readlane(lim_l, m), divN);
+                    }
+                    fmax = max(1, (int32_t)__builtin_popcountll(take) >> 2);
+                    calm = 0;
+                    continue;
+                }
+                if ((take >> lane) & 1) {
+                    const int64_t e = (int64_t)j + q_len;
+                    if (e < H) atomicAdd(&BD[e], -1);
+                    if (e <= H && !q_lost && q_dl != kNoDeadline)
+                        atomicMin((unsigned long long*)&outDL[e - 1], (unsigned long long)q_dl);
+                }
+                if (lane == 0) atomicAdd(&BD[j], (int32_t)__builtin_popcountll(take));
+                n_end = max(n_end, r_end);
+                mask &= ~take;
+                fmax = min(kWave, 2 * fmax);
+                calm = blocked ? 0 : calm + 1;
+                if (calm >= calm_need) {
+                    at_targets = true;
+                    streak = 0;
+                }
+                continue;
+            }
+
+            // One request at a time (under a batch cap, or one without
+            // company).  The head of the queue: uniform lane, lane reads.
             const int hl = __ffsll((unsigned long long)mask) - 1;
             const int32_t h_arr = __builtin_amdgcn_readlane(q_arr, hl);
             const int32_t h_c = __builtin_amdgcn_readlane(q_c, hl);
@@ -539,7 +791,8 @@ __global__ __launch_bounds__(64) void project_kernel(ProjectParams P) {
             run += 1;
             n_end = max(n_end, lim);
             mask &= mask - 1;
-            if (seq_left > 0) --seq_left;
+            alone = false;
+            fmax = min(kWave, 2 * fmax);
         }
     }
     __syncthreads();
