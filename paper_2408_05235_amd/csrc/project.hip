@@ -1,26 +1,24 @@
 // Stage 1: KV usage and batch-size projection (Sec. 4.2, Eq. 1-2) with FIFO
 // admission of queued requests under the KV check of Sec. 4.3.2.
 //
-// One 64-lane wavefront per scenario; the per-iteration curves live in LDS.
+// One workgroup of four wavefronts per scenario; the per-iteration curves live
+// in LDS.
 //
 // In-flight requests are turned into O(1) events each instead of O(r) curve
 // updates.  For a request with c cached tokens active on [0, e):
 //   KV_i[j] = ceil((c + j) / N)   (Eq. 1 with j - s_i = g_i + j)
 // starts at ceil(c / N), grows by one block at every j >= 1 with
-// c + j == 1 (mod N) -- a comb of period N beginning at j0 -- and drops to 0
-// at e.  So KV = prefix-sum over j of
-//   (jumps at 0 and e)  +  C[j],  C[j] = C[j - N] + comb_diff[j],
-// where comb_diff gets +1 at j0 and -1 at the first comb point >= e.  The
-// batch curve is the prefix sum of +1 at 0 / -1 at e.  One LDS array holds
-// the comb differences, then (scanned in place) C, then C plus the jumps,
-// then KV: two H-long int32 arrays per scenario in all, so more scenarios'
-// wavefronts share a compute unit.
+// c + j == 1 (mod N) -- a comb of period N -- and drops to 0 at e.  An array
+// X whose stride-N prefix sums are the curve's differences takes +1 / -1 at the
+// comb's ends and, for a jump of v at p, +v at p and -v at p + N; a stride-N
+// and a plain prefix sum, in place, give KV.  The batch curve is the prefix sum
+// of +1 at 0 / -1 at e.  Every request is read once.
 //
 // For admission control a new query can be appended to every scenario as a
 // request that starts now (Sec. 4.3.2, the "virtual" scoreboard); it adds
 // in-flight events like the others.
 //
-// Queued requests are admitted in FIFO order by the same wave, each at the
+// Queued requests are admitted in FIFO order by the same workgroup, each at the
 // first iteration from its arrival (and from the previous admission) where
 // its KV contribution over its in-horizon lifetime fits under the capacity.
 // Admissions only happen after the last iteration at which the in-flight
@@ -54,103 +52,152 @@ __device__ __forceinline__ int32_t sum_range(const int32_t* DA, int32_t j, int32
     return wave_sum(acc);
 }
 
-// Events of one request that holds c cached tokens now and stays in the batch
-// on [0, e), in two parts.  The block comb: +1 at its first new-block
-// iteration j0 and -1 at the first comb point at or past e (a stride-N prefix
-// scan turns these into the per-iteration increments).  The jumps: batch +1
-// at 0 / -1 at e, KV +ceil(c/N) at 0 (counted in kv0) and -KV_i[e-1] at e;
-// the request is counted in n_in and n_end.
-__device__ __forceinline__ void inflight_comb(int32_t c, int32_t e, int32_t H, int32_t N, const DivU32& divN,
-                                              int32_t* X) {
-    const int32_t lim = min(e, H);
-    const int32_t rc = (int32_t)((uint32_t)c - div_u32((uint32_t)c, divN) * (uint32_t)N);
-    const int32_t j0 = (rc == 0) ? 1 : (N + 1 - rc);
-    if (j0 < lim) {
-        atomicAdd(&X[j0], 1);
-        if (e < H) {
-            const int32_t jend = j0 + N * (int32_t)ceil_div_u32((uint32_t)(e - j0), divN);
-            if (jend < H) atomicAdd(&X[jend], -1);
-        }
-    }
+// One workgroup of W (1 or kProjWaves) wavefronts projects a scenario; what
+// its wavefronts tell each other.
+constexpr int kProjWaves = 4;
+
+struct ProjShared {
+    uint64_t u64[kProjWaves];
+    int32_t i32[4][kProjWaves];
+    uint32_t flag[2];
+};
+
+// Waits until this wavefront's global stores and atomics have reached the L2
+// cache, where all of its workgroup's are ordered; a barrier after it makes
+// them precede the other wavefronts' later ones.  (A device-scope fence also
+// writes the whole L2 back: 1024 boards took 190 us with two of them.)
+__device__ __forceinline__ void global_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// A barrier between accesses to the curves in LDS; one wavefront's are
+// processed in order and need none.
+template <int W>
+__device__ __forceinline__ void curves_sync() {
+    if (W > 1) __syncthreads();
+    else asm volatile("" ::: "memory");
 }
 
-__device__ __forceinline__ void inflight_jumps(int32_t c, int32_t e, int32_t H, const DivU32& divN, int32_t* BI,
-                                               int32_t* X, int32_t& n_in, int32_t& kv0, int32_t& n_end) {
-    ++n_in;
-    kv0 += (int32_t)ceil_div_u32((uint32_t)c, divN);
-    n_end = max(n_end, min(e, H));
-    if (e < H) {
-        atomicAdd(&BI[e], -1);
-        atomicAdd(&X[e], -(int32_t)ceil_div_u32((uint32_t)(c + e - 1), divN));
-    }
+// Whether the condition holds on some thread of the workgroup.  `turn`
+// alternates between two flags: one is cleared while the other is in use, and
+// the caller has a barrier between a call and the next.
+template <int W>
+__device__ __forceinline__ bool any_thread(ProjShared& sh, int& turn, bool c) {
+    if (W == 1) return __ballot(c) != 0;
+    if (__ballot(c) != 0 && lane_id() == 0) sh.flag[turn] = 1;
+    __syncthreads();
+    const bool r = sh.flag[turn] != 0;
+    turn ^= 1;
+    if (threadIdx.x == 0) sh.flag[turn] = 0;
+    return r;
 }
 
 // Adds (or, NEG, takes away) the KV blocks ceil((c + t - a) / N) of a request
 // with c cached tokens that starts at iteration a (Eq. 1) to KV[t] for every
 // t in [a, lim), a <= lim <= H, 64 iterations per step, by LDS adds that
-// return nothing.  POW2: N is a power of two no larger than 64 (log2 N =
-// divN.l), so the division is a shift and the value grows by exactly 64 / N
-// from one step to the next; the whole steps go 2 * UNROLL per loop trip.
-// Otherwise every step divides, UNROLL steps per trip.
-template <bool NEG, bool POW2, int UNROLL>
-__device__ __forceinline__ void add_request(int32_t* KV, int32_t c, int32_t a, int32_t lim, const DivU32& divN) {
-    const int lane = lane_id();
+// return nothing; wavefront w of n takes steps w, w + n, ...
+// POW2: N is a power of two no larger than 64 (log2 N = divN.l), so the
+// division is a shift and the value grows by exactly 64 / N from one step to
+// the next.
+template <bool NEG, bool POW2>
+__device__ __forceinline__ void add_request(int32_t* KV, int32_t c, int32_t a, int32_t lim, const DivU32& divN,
+                                            int w, int n) {
+    const int32_t lane = lane_id();
     if (POW2) {
-        int32_t v = (int32_t)(((uint32_t)c + divN.d - 1u + (uint32_t)lane) >> divN.l);
+        const int32_t whole = (int32_t)((uint32_t)(lim - a) / kWave);
+        int32_t v = (int32_t)(((uint32_t)c + divN.d - 1u + (uint32_t)(w * kWave + lane)) >> divN.l);
         if (NEG) v = -v;
-        const int32_t step = NEG ? -(kWave >> divN.l) : (kWave >> divN.l);
-        int32_t* q = KV + a + lane;
-        int32_t n = (int32_t)((uint32_t)(lim - a) / kWave);   // whole steps
-        for (; n >= 2 * UNROLL; n -= 2 * UNROLL) {
+        const int32_t step = (NEG ? -n : n) * (kWave >> divN.l);
+        int32_t* q = KV + a + w * kWave + lane;
+        int32_t k = w;
+        for (; k + 7 * n < whole; k += 8 * n) {
 #pragma unroll
-            for (int u = 0; u < 2 * UNROLL; ++u) atomicAdd(q + u * kWave, v + u * step);
-            q += 2 * UNROLL * kWave;
-            v += 2 * UNROLL * step;
+            for (int u = 0; u < 8; ++u) atomicAdd(q + u * n * kWave, v + u * step);
+            q += 8 * n * kWave;
+            v += 8 * step;
         }
-        for (; n > 0; --n) {
+        for (; k < whole; k += n) {
             atomicAdd(q, v);
-            q += kWave;
+            q += n * kWave;
             v += step;
         }
-        if (lane < ((lim - a) & (kWave - 1))) atomicAdd(q, v);
+        if (k == whole && lane < ((lim - a) & (kWave - 1))) atomicAdd(q, v);
     } else {
-#pragma unroll UNROLL
-        for (int32_t t0 = a; t0 < lim; t0 += kWave) {
-            const int32_t t = t0 + lane;
-            if (t < lim) {
-                const int32_t v = (int32_t)ceil_div_u32((uint32_t)(c + t - a), divN);
-                atomicAdd(&KV[t], NEG ? -v : v);
-            }
+        for (int32_t t = a + w * kWave + lane; t < lim; t += n * kWave) {
+            const int32_t v = (int32_t)ceil_div_u32((uint32_t)(c + t - a), divN);
+            atomicAdd(&KV[t], NEG ? -v : v);
         }
     }
 }
 
+// The scans below are a workgroup's: its wavefronts take consecutive runs of
+// whole 64-iteration steps.  They begin and end with a barrier.
+struct ScanRun {
+    int32_t from, to;
+};
+template <int W>
+__device__ __forceinline__ ScanRun scan_run(int32_t H, int w) {
+    const int32_t per = (H + W * kWave - 1) / (W * kWave) * kWave;
+    return ScanRun{min(w * per, H), min((w + 1) * per, H)};
+}
+
 // The stride-N prefix sums of X[0 .. H), in place: X[t] += X[t - N] (already
-// summed).  One wavefront.
+// summed).
+template <int W, bool POW2>
 __device__ __forceinline__ void strided_scan(int32_t* X, int32_t H, int32_t N) {
     const int lane = lane_id();
+    const int w = threadIdx.x / kWave;
+    curves_sync<W>();
+    // POW2: N divides 64, so a lane keeps its residue; each wavefront sums its
+    // own run, then adds the last sums of the runs before it.  Otherwise one
+    // wavefront does it all.
+    const ScanRun r = POW2 ? scan_run<W>(H, w) : ScanRun{0, w == 0 ? H : 0};
     const int32_t lane_mod = lane % N;
-    for (int32_t t0 = 0; t0 < H; t0 += kWave) {
+    for (int32_t t0 = r.from; t0 < r.to; t0 += kWave) {
         const int32_t t = t0 + lane;
-        const bool in = t < H;
+        const bool in = t < r.to;
         int32_t c = in ? X[t] : 0;
         for (int32_t d = N; d < kWave; d <<= 1) {
             const int32_t u = __shfl_up(c, d);
             if (lane >= d) c += u;
         }
         const int32_t prev = t0 + lane_mod - N;
-        if (prev >= 0 && in) c += X[prev];
+        if (prev >= r.from && in) c += X[prev];
         if (in) X[t] = c;
+    }
+    curves_sync<W>();
+    if (POW2 && W > 1) {
+        int32_t carry = 0;
+        for (int v = 0; v < w; ++v) {
+            const ScanRun q = scan_run<W>(H, v);
+            // (runs before one that is not empty are whole)
+            if (r.from < r.to) carry += X[q.to - N + lane_mod];
+        }
+        curves_sync<W>();
+        for (int32_t t = r.from + lane; t < r.to; t += kWave) X[t] += carry;
+        curves_sync<W>();
     }
 }
 
 // The prefix sums of X[0 .. H), in place; the last iteration whose sum
 // exceeds cap (-1: none), and the first such one from `from` on (H: none).
-__device__ __forceinline__ int32_t prefix_scan(int32_t* X, int32_t H, int32_t cap, int32_t from, int32_t* first_over) {
+template <int W>
+__device__ __forceinline__ int32_t prefix_scan(ProjShared& sh, int32_t* X, int32_t H, int32_t cap, int32_t from,
+                                               int32_t* first_over) {
+    const int lane = lane_id();
+    const int w = threadIdx.x / kWave;
+    const ScanRun r = scan_run<W>(H, w);
+    curves_sync<W>();
+    if (W > 1) {
+        int32_t sum = 0;
+        for (int32_t t = r.from + lane; t < r.to; t += kWave) sum += X[t];
+        sum = wave_sum(sum);
+        if (lane == 0) sh.i32[0][w] = sum;
+        curves_sync<W>();
+    }
     int32_t carry = 0, last_over = -1, first = H;
-    for (int32_t t0 = 0; t0 < H; t0 += kWave) {
-        const int32_t t = t0 + lane_id();
-        const bool in = t < H;
+    for (int v = 0; v < w; ++v) carry += sh.i32[0][v];
+    for (int32_t t0 = r.from; t0 < r.to; t0 += kWave) {
+        const int32_t t = t0 + lane;
+        const bool in = t < r.to;
         const int32_t y = wave_incl_scan(in ? X[t] : 0) + carry;
         carry = __builtin_amdgcn_readlane(y, kWave - 1);
         if (in) {
@@ -161,20 +208,41 @@ __device__ __forceinline__ int32_t prefix_scan(int32_t* X, int32_t H, int32_t ca
             }
         }
     }
-    *first_over = H - wave_max(H - first);
-    return wave_max(last_over);
+    last_over = wave_max(last_over);
+    first = H - wave_max(H - first);
+    if (W == 1) {
+        curves_sync<W>();
+        *first_over = first;
+        return last_over;
+    }
+    if (lane == 0) {
+        sh.i32[1][w] = last_over;
+        sh.i32[2][w] = first;
+    }
+    curves_sync<W>();
+    last_over = -1;
+    first = H;
+    for (int v = 0; v < W; ++v) {
+        last_over = max(last_over, sh.i32[1][v]);
+        first = min(first, sh.i32[2][v]);
+    }
+    *first_over = first;
+    return last_over;
 }
 
 // Undoes prefix_scan and strided_scan, in place: X[t] -= X[t - 1], then
 // X[t] -= X[t - N] of those differences.  From the last iteration down, so
 // that every read comes before the write of what it reads.
+template <int W>
 __device__ __forceinline__ void unscan(int32_t* X, int32_t H, int32_t N) {
-    constexpr int kU = 4;
-    for (int32_t t1 = (H + kU * kWave - 1) / (kU * kWave) * (kU * kWave); t1 > 0; t1 -= kU * kWave) {
+    constexpr int kU = 4, kThreads = W * kWave;
+    for (int32_t t1 = (H + kU * kThreads - 1) / (kU * kThreads) * (kU * kThreads); t1 > 0;
+         t1 -= kU * kThreads) {
+        curves_sync<W>();
         int32_t v[kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            const int32_t t = t1 - (u + 1) * kWave + lane_id();
+            const int32_t t = t1 - (u + 1) * kThreads + (int32_t)threadIdx.x;
             v[u] = 0;
             if (t < H) {
                 v[u] = X[t];
@@ -183,23 +251,26 @@ __device__ __forceinline__ void unscan(int32_t* X, int32_t H, int32_t N) {
                 if (t > N) v[u] += X[t - N - 1];
             }
         }
+        curves_sync<W>();
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            const int32_t t = t1 - (u + 1) * kWave + lane_id();
+            const int32_t t = t1 - (u + 1) * kThreads + (int32_t)threadIdx.x;
             if (t < H) X[t] = v[u];
         }
     }
+    curves_sync<W>();
 }
 
 // Events of a request with c cached tokens in the batch on [a, e), a < H, in
-// an array whose stride-N prefix sums' prefix sums are the KV curve (what
-// unscan leaves): sign times its KV blocks ceil((c + t - a) / N).  A jump of v
-// at p is +v at p and -v at p + N; the comb of its new blocks starts at its
-// first new-block iteration and stops at the first comb point past its end.
+// an array whose stride-N prefix sums' prefix sums are the KV curve: sign times
+// its KV blocks ceil((c + t - a) / N).  A jump of v at p is +v at p and -v at
+// p + N; the comb of its new blocks starts at its first new-block iteration and
+// stops at the first comb point past its end.  START: with the jump at a.
+template <bool START>
 __device__ __forceinline__ void add_events(int32_t* X, int32_t c, int32_t a, int64_t e, int32_t H, int32_t N,
                                            const DivU32& divN, int32_t sign) {
-    const int32_t v = (int32_t)ceil_div_u32((uint32_t)c, divN);
-    if (v) {
+    if (START) {
+        const int32_t v = (int32_t)ceil_div_u32((uint32_t)c, divN);
         atomicAdd(&X[a], sign * v);
         if (N < H - a) atomicAdd(&X[a + N], -sign * v);
     }
@@ -217,6 +288,42 @@ __device__ __forceinline__ void add_events(int32_t* X, int32_t c, int32_t a, int
         atomicAdd(&X[e], -sign * w);
         if (e + N < H) atomicAdd(&X[e + N], sign * w);
     }
+}
+
+// Adds (or takes away) the contributions of the chunk's requests in `take`,
+// request m starting at a (its own lane's) and ending, in the horizon, at
+// lim: whole requests to the wavefronts in turn.  *r_end: the last end.
+template <int W, bool NEG, bool POW2>
+__device__ __forceinline__ void add_members(int32_t* KV, uint64_t take, int32_t c, int32_t a, int32_t lim,
+                                            const DivU32& divN, int wave, int32_t* r_end) {
+    int32_t end = 0;
+    int i = 0;
+    for (uint64_t mm = take; mm; mm &= mm - 1, ++i) {
+        const int m = __ffsll((unsigned long long)mm) - 1;
+        const int32_t l = __builtin_amdgcn_readlane(lim, m);
+        end = max(end, l);
+        if (i % W == wave)
+            add_request<NEG, POW2>(KV, __builtin_amdgcn_readlane(c, m), __builtin_amdgcn_readlane(a, m), l, divN, 0, 1);
+    }
+    *r_end = end;
+}
+
+// After such additions: whether KV stays within cap on [from, to).  Every
+// wavefront checks a part; a barrier before and one after.
+template <int W>
+__device__ __forceinline__ bool members_fit(ProjShared& sh, int& turn, const int32_t* KV, int32_t from, int32_t to,
+                                            int32_t cap) {
+    curves_sync<W>();
+    bool over = false;
+    if (cap != INT32_MAX)
+        for (int32_t t0 = from; t0 < to; t0 += 4 * W * kWave) {
+            int32_t v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = KV[min(t0 + u * W * kWave + (int32_t)threadIdx.x, to - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) over |= v[u] > cap;
+        }
+    return !any_thread<W>(sh, turn, over);
 }
 
 // Scenario order for long FIFO loops: one wavefront per scenario, whose time
@@ -266,140 +373,179 @@ __global__ __launch_bounds__(256) void order_place_kernel(const int64_t* off, in
 // cap it is only added to and finally prefix-summed, so it accumulates with
 // atomics in the scenario's own batch output row instead: half the LDS, twice
 // the scenario wavefronts per CU.
-template <bool BD_LDS, bool POW2>
-__global__ __launch_bounds__(64) void project_kernel(ProjectParams P) {
+template <bool BD_LDS, bool POW2, int W>
+__global__ __launch_bounds__(W* kWave) void project_kernel(ProjectParams P) {
     extern __shared__ int32_t lds[];
+    __shared__ ProjShared sh;
     const int32_t H = P.H;
     const int32_t N = P.N;
     const DivU32 divN{(uint32_t)N, P.div_m, P.div_l};
     const int lane = lane_id();
+    const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int64_t s = P.order_ws ? (int64_t)((const int32_t*)P.order_ws + kOrderBuckets)[blockIdx.x] : blockIdx.x;
     int32_t* outB = P.batch + s * H;
-    int32_t* KV = lds;                      // comb diff, comb prefix, + jumps, then KV values
+    int32_t* KV = lds;                      // events, then KV values
     int32_t* BI = BD_LDS ? lds + H : outB;  // batch difference array
     int32_t* outKV = P.kv + s * H;
     uint64_t* outDL = P.deadline_at + s * H;
 
-    for (int32_t t = lane; t < H; t += kWave) {
+    for (int32_t t = threadIdx.x; t < H; t += W * kWave) {
         KV[t] = 0;
         BI[t] = 0;
         outDL[t] = kNoDeadline;
     }
-    __threadfence();
+    if (threadIdx.x < 2) sh.flag[threadIdx.x] = 0;
+    int turn = 0;
+    global_done();
     __syncthreads();
 
     const int64_t lo = P.off[s];
     const int64_t hi = P.off[s + 1];
     const bool bad_range = lo < 0 || hi < lo || hi > P.n_requests || hi - lo > 0x7fffffffll;
 
-    // pass A: validity, size guard, lost / queue information
+    // Every request once, each wavefront a run of them: validity, size guard,
+    // lost / queue information; the in-flight ones' KV events (the jumps at
+    // iteration 0 summed in registers), batch events and deadlines.
     uint64_t bound = 0;
     uint32_t fl = 0;
-    int32_t has_queue = 0;
+    int32_t has_queue = 0, n_end = 0, n_in = 0, kv0 = 0;
+    int32_t arr_max = -1, arr_min = INT32_MAX;   // of the run's queued arrivals
     if (!bad_range) {
-        int32_t arr_carry = -1;
-        for (int64_t base = lo; base < hi; base += kWave) {
+        const int64_t per = (hi - lo + W * kWave - 1) / (W * kWave) * kWave;
+        const int64_t r0 = lo + wave * per, r1 = min(r0 + per, hi);
+        for (int64_t base = r0; base < r1; base += kWave) {
             const int64_t i = base + lane;
-            const bool in = i < hi;
+            const bool in = i < r1;
             int32_t p = 0, g = 0, r = 0, a = -1;
-            if (in) { p = P.prompt[i]; g = P.gen[i]; r = P.rem[i]; a = P.arr[i]; }
+            uint64_t d = kNoDeadline;
+            bool is_lost = false;
+            if (in) {
+                p = P.prompt[i];
+                g = P.gen[i];
+                r = P.rem[i];
+                a = P.arr[i];
+                if (P.lost) is_lost = P.lost[i] != 0;
+                if (P.deadline) d = P.deadline[i];
+            }
             const bool ok = in && entry_ok(p, g, r, a);
             if (in && !ok) fl |= TL_FLAG_BAD_REQUEST;
             if (ok) bound += ceil_div_u32((uint32_t)(p + g + H), divN);
-            if (ok && a == -1 && P.lost && P.lost[i]) fl |= TL_FLAG_LOST;
+            if (ok && a == -1) {
+                if (is_lost) fl |= TL_FLAG_LOST;
+                ++n_in;
+                kv0 += (int32_t)ceil_div_u32((uint32_t)(p + g), divN);
+                n_end = max(n_end, min(r, H));
+                add_events<false>(KV, p + g, 0, r, H, N, divN, 1);
+                if (r < H) atomicAdd(&BI[r], -1);
+                if (r <= H && !is_lost && d != kNoDeadline)
+                    atomicMin((unsigned long long*)&outDL[r - 1], (unsigned long long)d);
+            }
             const bool queued = ok && a >= 0;
-            if (queued && a < H) has_queue = 1;
-            // queue order: each queued arrival must be >= every earlier one
-            const int32_t v = queued ? a : -1;
-            const int32_t incl = wave_incl_max(v);
-            const int32_t excl = max(wave_shift_up1(incl, -1), arr_carry);
-            if (queued && a < excl) fl |= TL_FLAG_UNSORTED;
-            arr_carry = max(arr_carry, lane63(incl));
+            if (__ballot(queued)) {
+                if (queued && a < H) has_queue = 1;
+                // queue order: each queued arrival must be >= every earlier one
+                const int32_t incl = wave_incl_max(queued ? a : -1);
+                const int32_t excl = max(wave_shift_up1(incl, -1), arr_max);
+                if (queued && a < excl) fl |= TL_FLAG_UNSORTED;
+                arr_max = max(arr_max, lane63(incl));
+                if (queued) arr_min = min(arr_min, a);
+            }
         }
     }
     // the appended query (admission control): one more request that starts
     // now; a malformed one is left out and flagged
-    int32_t cand_p = 0, cand_l = 0;
-    bool cand = false;
     if (P.cand_len && !bad_range) {
-        cand_p = P.cand_prompt[s];
-        cand_l = P.cand_len[s];
-        cand = entry_ok(cand_p, 0, cand_l, -1);
-        if (!cand) fl |= TL_FLAG_BAD_CANDIDATE;
-        else if (lane == 0) bound += ceil_div_u32((uint32_t)(cand_p + H), divN);
+        const int32_t cand_p = P.cand_prompt[s];
+        const int32_t cand_l = P.cand_len[s];
+        if (!entry_ok(cand_p, 0, cand_l, -1)) {
+            fl |= TL_FLAG_BAD_CANDIDATE;
+        } else if (threadIdx.x == 0) {
+            bound += ceil_div_u32((uint32_t)(cand_p + H), divN);
+            ++n_in;
+            kv0 += (int32_t)ceil_div_u32((uint32_t)cand_p, divN);
+            n_end = max(n_end, min(cand_l, H));
+            add_events<false>(KV, cand_p, 0, cand_l, H, N, divN, 1);
+            if (cand_l < H) atomicAdd(&BI[cand_l], -1);
+        }
     }
+    // over the wavefronts; a run's arrivals below an earlier run's largest
+    // are out of order too
     bound = wave_sum_u64(bound);
-    fl = wave_or(fl);
-    has_queue = wave_max(has_queue);
+    fl = wave_or(fl) | (wave_max(has_queue) ? 1u << 31 : 0u);
+    arr_min = INT32_MAX - wave_max(INT32_MAX - arr_min);
+    n_end = wave_max(n_end);
+    n_in = wave_sum(n_in);
+    kv0 = wave_sum(kv0);
+    // (every atomic on the outputs is done before another wavefront goes on)
+    global_done();
+    if (lane == 0) {
+        sh.u64[wave] = bound;
+        sh.i32[0][wave] = (int32_t)fl;
+        sh.i32[1][wave] = n_end;
+        sh.i32[2][wave] = arr_min;
+        sh.i32[3][wave] = arr_max;
+        if (n_in) atomicAdd(&BI[0], n_in);
+        if (kv0) {
+            atomicAdd(&KV[0], kv0);
+            if (N < H) atomicAdd(&KV[N], -kv0);
+        }
+    }
+    __syncthreads();
+    bound = 0;
+    fl = 0;
+    n_end = 0;
+    arr_max = -1;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        bound += sh.u64[w];
+        fl |= (uint32_t)sh.i32[0][w];
+        n_end = max(n_end, sh.i32[1][w]);
+        if (sh.i32[2][w] < arr_max) fl |= TL_FLAG_UNSORTED;
+        arr_max = max(arr_max, sh.i32[3][w]);
+    }
+    // (wavefront-uniform, like everything the admission loop decides on)
+    fl = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)fl);
+    n_end = __builtin_amdgcn_readfirstlane(n_end);
+    bound = lane63_u64(bound);
+    const bool has_queue_any = (fl >> 31) != 0;
+    fl &= ~(1u << 31);
 
     if (bad_range || bound > 0x7fffffffull) {
-        for (int32_t t = lane; t < H; t += kWave) { outB[t] = 0; outKV[t] = 0; }
-        if (lane == 0) {
+        for (int32_t t = threadIdx.x; t < H; t += W * kWave) {
+            outB[t] = 0;
+            outKV[t] = 0;
+            outDL[t] = kNoDeadline;
+        }
+        if (threadIdx.x == 0) {
             P.n_iters[s] = 0;
             P.flags[s] = bad_range ? TL_FLAG_OVERFLOW : ((fl & TL_FLAG_BAD_REQUEST) | TL_FLAG_OVERFLOW);
         }
         return;
     }
 
-    // pass B1: the in-flight requests' block combs, then their stride-N
-    // prefix in place (every later write adds to it)
-    for (int64_t base = lo; base < hi; base += kWave) {
-        const int64_t i = base + lane;
-        if (i >= hi) continue;
-        const int32_t p = P.prompt[i], g = P.gen[i], r = P.rem[i], a = P.arr[i];
-        if (!entry_ok(p, g, r, a) || a != -1) continue;
-        inflight_comb(p + g, r, H, N, divN, KV);
-    }
-    if (cand && lane == 0) inflight_comb(cand_p, cand_l, H, N, divN, KV);
-    __syncthreads();
-    strided_scan(KV, H, N);
-    __syncthreads();
-
-    // pass B2: jumps, batch events, deadline checkpoints
-    int32_t n_end = 0, n_in = 0, kv0 = 0;
-    for (int64_t base = lo; base < hi; base += kWave) {
-        const int64_t i = base + lane;
-        if (i >= hi) continue;
-        const int32_t p = P.prompt[i], g = P.gen[i], r = P.rem[i], a = P.arr[i];
-        if (!entry_ok(p, g, r, a) || a != -1) continue;
-        const int32_t e = r;
-        inflight_jumps(p + g, e, H, divN, BI, KV, n_in, kv0, n_end);
-        const bool is_lost = P.lost && P.lost[i];
-        const uint64_t d = P.deadline ? P.deadline[i] : kNoDeadline;
-        if (e <= H && !is_lost && d != kNoDeadline) atomicMin((unsigned long long*)&outDL[e - 1], (unsigned long long)d);
-    }
-    if (cand && lane == 0) inflight_jumps(cand_p, cand_l, H, divN, BI, KV, n_in, kv0, n_end);
-    n_in = wave_sum(n_in);
-    kv0 = wave_sum(kv0);
-    n_end = wave_max(n_end);
-    if (lane == 0) {
-        if (BD_LDS) BI[0] += n_in;
-        else atomicAdd(&BI[0], n_in);
-        KV[0] += kv0;
-    }
-    __syncthreads();
-
-    // the KV prefix sum; last over-capacity iteration.  The batch curve stays
+    // the KV curve; last over-capacity iteration.  The batch curve stays
     // a difference array: admissions add their +1 / -1 to it and the output
     // takes its prefix sum.
     const int32_t cap = P.kv_cap[s];
-    // bound (pass A) is at least the KV of every iteration: when it fits the
+    // bound is at least the KV of every iteration: when it fits the
     // capacity, no admission check can fail and the checks are skipped
     const bool kv_fits = cap >= 0 && bound <= (uint64_t)cap;
     int32_t first_over = H;   // (of the whole queue's sum, below)
-    const int32_t last_over = prefix_scan(KV, H, cap, 0, &first_over);
+    strided_scan<W, POW2>(KV, H, N);
+    const int32_t last_over = __builtin_amdgcn_readfirstlane(prefix_scan<W>(sh, KV, H, cap, 0, &first_over));
     const bool has_bcap = BD_LDS && P.batch_cap != nullptr;   // (the host takes BD_LDS with a cap)
     const int32_t bcap = has_bcap ? P.batch_cap[s] : 0;
-    if (last_over >= 0 || (has_bcap && n_in > bcap)) fl |= TL_FLAG_OVERCOMMIT;
+    if (last_over >= 0 || (has_bcap && __builtin_amdgcn_readfirstlane(BI[0]) > bcap)) fl |= TL_FLAG_OVERCOMMIT;
 
-    // FIFO admission of queued requests.  One wave does it; every value the
-    // loop carries (iteration j, batch size, the head's fields, check
-    // outcomes) is wave-uniform and kept in scalar registers.  LDS accesses
-    // of one wave are processed in order, so one lane's updates are seen by
-    // the later reads of every lane.
+    // FIFO admission of queued requests.  Every wavefront runs the loop: the
+    // values it carries (iteration j, batch size, the head's fields, check
+    // outcomes) are the same in all of them, wavefront-uniform and kept in
+    // scalar registers.  They come from reads of the curves between barriers;
+    // the additions to the curves and the checks over many iterations are
+    // shared out, and wavefront 0 alone writes the batch events and deadlines.
     int32_t* BD = BI;   // batch differences: in-flight requests, then admitted ones
-    if (has_queue) {
-        __syncthreads();
+    if (has_queue_any) {
+        curves_sync<W>();
         int32_t j = 0;
         int32_t run = 0;    // batch size at j (prefix of BD; kept only under a batch cap)
         if (has_bcap) run = __builtin_amdgcn_readfirstlane(BD[0]);
@@ -429,19 +575,39 @@ __global__ __launch_bounds__(64) void project_kernel(ProjectParams P) {
                 const int64_t first = cb + kWave;
                 const int32_t n_ch = (int32_t)((hi - first + kWave - 1) / kWave);
                 const int32_t lo_j = max(j, last_over + 1);
-                // chunks k0 .. to - 1, `run` being the running maximum of the
-                // targets before chunk k0; those from `from` on add their
-                // events times sign, or commit their batch events, deadlines
-                // and n_end.  Returns the running maximum before chunk `at`.
-                auto chunks = [&](int32_t k0, int32_t run, int32_t from, int32_t to, int32_t at, int32_t sign,
-                                  bool commit) {
-                    int32_t before = run;
+                // Chunks from .. to - 1, a run of them per wavefront: their
+                // events times sign, or (commit) their batch events, deadlines
+                // and n_end.
+                auto run_before = [&](int32_t k) {   // running maximum of the targets before chunk k
+                    int32_t m = lo_j;
+                    if (fl & TL_FLAG_UNSORTED) {
+                        for (int64_t i = first + lane; i < min(first + (int64_t)k * kWave, hi); i += kWave) {
+                            const int32_t a = P.arr[i];
+                            if (a > m && entry_ok(P.prompt[i], P.gen[i], P.rem[i], a)) m = a;
+                        }
+                        return wave_max(m);
+                    }
+                    // sorted: the last valid queued entry before the chunk
+                    for (int64_t i1 = first + (int64_t)k * kWave; i1 > first; i1 -= kWave) {
+                        const int64_t i = i1 - kWave + lane;
+                        const int32_t a = i < hi ? P.arr[i] : -1;
+                        const bool q = a >= 0 && entry_ok(P.prompt[i], P.gen[i], P.rem[i], a);
+                        if (__ballot(q)) return max(m, wave_max(q ? a : -1));
+                    }
+                    return m;
+                };
+                auto chunks = [&](int32_t from, int32_t to, int32_t sign, bool commit) {
+                    // each wavefront a run of chunks
+                    const int32_t per = (to - from + W - 1) / W;
+                    const int32_t k0 = min(from + wave * per, to), k1 = min(k0 + per, to);
+                    if (k0 >= k1) return;
+                    int32_t run = run_before(k0);
                     // the next chunk's fields are fetched while one is worked on
                     int32_t na = -1, np = 0, ng = 0, nr = 0;
                     auto fetch = [&](int32_t k) {
                         const int64_t i = first + (int64_t)k * kWave + lane;
                         na = -1;
-                        if (k < to && i < hi) {
+                        if (k < k1 && i < hi) {
                             na = P.arr[i];
                             np = P.prompt[i];
                             ng = P.gen[i];
@@ -449,7 +615,7 @@ __global__ __launch_bounds__(64) void project_kernel(ProjectParams P) {
                         }
                     };
                     fetch(k0);
-                    for (int32_t k = k0; k < to; ++k) {
+                    for (int32_t k = k0; k < k1; ++k) {
                         const int64_t i = first + (int64_t)k * kWave + lane;
                         int32_t a = na;
                         const int32_t c = np + ng, len = nr;
@@ -457,12 +623,10 @@ __global__ __launch_bounds__(64) void project_kernel(ProjectParams P) {
                         fetch(k + 1);
                         a = max(wave_incl_max(q ? a : -1), run);
                         run = __builtin_amdgcn_readlane(a, kWave - 1);
-                        if (k + 1 == at) before = run;
-                        if (k < from) continue;
                         if (q && a < H) {
                             const int64_t e = (int64_t)a + len;
                             if (!commit) {
-                                add_events(KV, c, a, e, H, N, divN, sign);
+                                add_events<true>(KV, c, a, e, H, N, divN, sign);
                             } else {
                                 atomicAdd(&BD[a], 1);
                                 if (e < H) atomicAdd(&BD[e], -1);
@@ -473,20 +637,18 @@ __global__ __launch_bounds__(64) void project_kernel(ProjectParams P) {
                             }
                         }
                     }
-                    return before;
                 };
-                int32_t ok = 0, ok_run = lo_j, bad = n_ch + 1, cur = 0, want = n_ch, guess = 0;
+                int32_t ok = 0, bad = n_ch + 1, cur = 0, want = n_ch, guess = 0;
                 for (;;) {
-                    unscan(KV, H, N);
-                    const int32_t run = want > cur ? chunks(ok, ok_run, cur, want, want, 1, false)
-                                                   : chunks(ok, ok_run, want, cur, want, -1, false);
-                    strided_scan(KV, H, N);
-                    const bool fits = prefix_scan(KV, H, cap, last_over + 1, &first_over) <= last_over || kv_fits;
+                    unscan<W>(KV, H, N);
+                    if (want > cur) chunks(cur, want, 1, false);
+                    else chunks(want, cur, -1, false);
+                    strided_scan<W, POW2>(KV, H, N);
+                    const bool fits = prefix_scan<W>(sh, KV, H, cap, last_over + 1, &first_over) <= last_over || kv_fits;
                     cur = want;
                     if (want == ok) break;   // what did not fit is taken out again
                     if (fits) {
                         ok = want;
-                        ok_run = run;
                         if (bad - ok <= 1) break;
                     } else {
                         bad = want;
@@ -511,10 +673,16 @@ __global__ __launch_bounds__(64) void project_kernel(ProjectParams P) {
                     }
                 }
                 if (ok > 0) {
-                    chunks(0, lo_j, 0, ok, ok, 1, true);
+                    chunks(0, ok, 1, true);
                     n_end = wave_max(n_end);
-                    if (ok_run >= H) break;   // the head cannot start within the horizon
-                    j = ok_run;
+                    curves_sync<W>();
+                    if (lane == 0) sh.i32[0][wave] = n_end;
+                    curves_sync<W>();
+                    for (int w = 0; w < W; ++w) n_end = max(n_end, sh.i32[0][w]);
+                    n_end = __builtin_amdgcn_readfirstlane(n_end);
+                    const int32_t run = run_before(ok);
+                    if (run >= H) break;   // the head cannot start within the horizon
+                    j = run;
                 }
                 cb += (int64_t)ok * kWave;
                 streak = 0;
@@ -561,40 +729,20 @@ __global__ __launch_bounds__(64) void project_kernel(ProjectParams P) {
                 if (take == 0) break;   // the head cannot start within the horizon
                 // each member's in-horizon end, on its own lane
                 const int32_t lim_l = q_len >= H - a ? H : a + q_len;
-                const int32_t r_end = wave_max(((take >> lane) & 1) ? lim_l : 0);
-                for (uint64_t mm = take; mm; mm &= mm - 1) {
-                    const int m = __ffsll((unsigned long long)mm) - 1;
-                    const int32_t am = __builtin_amdgcn_readlane(a, m);
-                    const int32_t cm = __builtin_amdgcn_readlane(q_c, m);
-                    const int32_t lim = __builtin_amdgcn_readlane(lim_l, m);
-                    // LDS adds without a returned value: no wait per chunk
-                    add_request<false, POW2, 1>(KV, cm, am, lim, divN);
-                }
                 const int32_t a_first = __builtin_amdgcn_readlane(a, __ffsll((unsigned long long)take) - 1);
-                bool bad = false;
-                if (!kv_fits) {
-                    int32_t t0 = a_first;
-#pragma unroll 4
-                    for (; t0 + kWave <= r_end; t0 += kWave) bad |= KV[t0 + lane] > cap;
-                    if (t0 + lane < r_end) bad |= KV[t0 + lane] > cap;
-                }
-                const bool fits = __ballot(bad) == 0;
-                if (!fits) {
+                int32_t r_end = 0;
+                add_members<W, false, POW2>(KV, take, q_c, a, lim_l, divN, wave, &r_end);
+                if (!members_fit<W>(sh, turn, KV, a_first, r_end, kv_fits ? INT32_MAX : cap)) {
                     // take the batch's contributions out again
-                    for (uint64_t mm = take; mm; mm &= mm - 1) {
-                        const int m = __ffsll((unsigned long long)mm) - 1;
-                        const int32_t am = __builtin_amdgcn_readlane(a, m);
-                        const int32_t cm = __builtin_amdgcn_readlane(q_c, m);
-                        const int32_t lim = __builtin_amdgcn_readlane(lim_l, m);
-                        add_request<true, POW2, 1>(KV, cm, am, lim, divN);
-                    }
+                    add_members<W, true, POW2>(KV, take, q_c, a, lim_l, divN, wave, &r_end);
+                    curves_sync<W>();
                     at_targets = false;
                     streak = 0;
                     calm = 0;
                     calm_need = min(256, 2 * calm_need);
                     continue;
                 }
-                if ((take >> lane) & 1) {
+                if (wave == 0 && ((take >> lane) & 1)) {
                     const int64_t e = (int64_t)a + q_len;
                     atomicAdd(&BD[a], 1);
                     if (e < H) atomicAdd(&BD[e], -1);
@@ -650,37 +798,23 @@ __global__ __launch_bounds__(64) void project_kernel(ProjectParams P) {
                 }
                 const int32_t lim_l = q_len >= H - j ? H : j + q_len;
                 int32_t r_end = 0;
-                for (uint64_t mm = take; mm; mm &= mm - 1) {
-                    const int m = __ffsll((unsigned long long)mm) - 1;
-                    const int32_t lim = __builtin_amdgcn_readlane(lim_l, m);
-                    r_end = max(r_end, lim);
-                    add_request<false, POW2, 1>(KV, __builtin_amdgcn_readlane(q_c, m), j, lim, divN);
-                }
-                bool over = false;
-                for (int32_t t0 = j; t0 < r_end; t0 += 8 * kWave) {
-                    int32_t v[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) v[u] = KV[min(t0 + u * kWave + lane, r_end - 1)];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) over |= v[u] > cap;
-                }
-                if (__ballot(over) != 0) {
-                    for (uint64_t mm = take; mm; mm &= mm - 1) {
-                        const int m = __ffsll((unsigned long long)mm) - 1;
-                        add_request<true, POW2, 1>(KV, __builtin_amdgcn_readlane(q_c, m), j,
-                                                   __builtin_amdgcn_readlane(lim_l, m), divN);
-                    }
+                // (everyone has read the curve above before it changes)
+                curves_sync<W>();
+                add_members<W, false, POW2>(KV, take, q_c, j, lim_l, divN, wave, &r_end);
+                if (!members_fit<W>(sh, turn, KV, j, r_end, cap)) {
+                    add_members<W, true, POW2>(KV, take, q_c, j, lim_l, divN, wave, &r_end);
+                    curves_sync<W>();
                     fmax = max(1, (int32_t)__builtin_popcountll(take) >> 2);
                     calm = 0;
                     continue;
                 }
-                if ((take >> lane) & 1) {
+                if (wave == 0 && ((take >> lane) & 1)) {
                     const int64_t e = (int64_t)j + q_len;
                     if (e < H) atomicAdd(&BD[e], -1);
                     if (e <= H && !q_lost && q_dl != kNoDeadline)
                         atomicMin((unsigned long long*)&outDL[e - 1], (unsigned long long)q_dl);
                 }
-                if (lane == 0) atomicAdd(&BD[j], (int32_t)__builtin_popcountll(take));
+                if (threadIdx.x == 0) atomicAdd(&BD[j], (int32_t)__builtin_popcountll(take));
                 n_end = max(n_end, r_end);
                 mask &= ~take;
                 fmax = min(kWave, 2 * fmax);
@@ -776,8 +910,9 @@ __global__ __launch_bounds__(64) void project_kernel(ProjectParams P) {
             if (!admitted) break;
             const int64_t e = (int64_t)j + h_len;
             const int32_t lim = (int32_t)min(e, (int64_t)H);
-            add_request<false, POW2, 4>(KV, h_c, j, lim, divN);
-            if (lane == 0) {
+            curves_sync<W>();   // everyone has read the curves
+            add_request<false, POW2>(KV, h_c, j, lim, divN, wave, W);
+            if (threadIdx.x == 0) {
                 if (BD_LDS) {
                     BD[j] += 1;
                     if (e < H) BD[e] -= 1;
@@ -791,50 +926,58 @@ __global__ __launch_bounds__(64) void project_kernel(ProjectParams P) {
             run += 1;
             n_end = max(n_end, lim);
             mask &= mask - 1;
+            curves_sync<W>();
             alone = false;
             fmax = min(kWave, 2 * fmax);
         }
     }
+    global_done();
     __syncthreads();
 
-    // outputs: curves (batch = prefix sum of BD), scalars
-    if (BD_LDS) {
-        int32_t carry_b = 0;
-        for (int32_t t0 = 0; t0 < H; t0 += kWave) {
-            const int32_t t = t0 + lane;
-            const bool in = t < H;
-            const int32_t b = wave_incl_scan(in ? BD[t] : 0) + carry_b;
-            carry_b = __builtin_amdgcn_readlane(b, kWave - 1);
-            if (!in) continue;
-            const int32_t k = KV[t];
-            outB[t] = b;
-            outKV[t] = k;
+    // outputs: curves (batch = prefix sum of BD), scalars.  Each wavefront a
+    // run of iterations: its total, then its sums.  (Differences kept in the
+    // output row were added at L2 by atomics: they are read there, eight
+    // 64-iteration chunks in flight at a time.)
+    const ScanRun run = scan_run<W>(H, wave);
+    constexpr int kChunks = 8;
+    auto load = [&](int32_t t) {
+        return BD_LDS ? BD[t] : __hip_atomic_load(&BD[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    int32_t total = 0;
+    for (int32_t g0 = run.from; g0 < run.to; g0 += kChunks * kWave) {
+        int32_t d[kChunks];
+#pragma unroll
+        for (int c = 0; c < kChunks; ++c) {
+            const int32_t t = g0 + c * kWave + lane;
+            d[c] = t < run.to ? load(t) : 0;
         }
-    } else {
-        // the differences were added at L2 by atomics: read them there,
-        // eight 64-iteration chunks in flight at a time, then scan
-        constexpr int kChunks = 8;
-        int32_t carry_b = 0;
-        for (int32_t g0 = 0; g0 < H; g0 += kChunks * kWave) {
-            int32_t d[kChunks];
 #pragma unroll
-            for (int c = 0; c < kChunks; ++c) {
-                const int32_t t = g0 + c * kWave + lane;
-                d[c] = t < H ? __hip_atomic_load(&BD[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
-            }
+        for (int c = 0; c < kChunks; ++c) total += d[c];
+    }
+    total = wave_sum(total);
+    if (lane == 0) sh.i32[3][wave] = total;
+    __syncthreads();
+    int32_t carry_b = 0;
+    for (int w = 0; w < wave; ++w) carry_b += sh.i32[3][w];
+    for (int32_t g0 = run.from; g0 < run.to; g0 += kChunks * kWave) {
+        int32_t d[kChunks];
 #pragma unroll
-            for (int c = 0; c < kChunks; ++c) {
-                const int32_t t = g0 + c * kWave + lane;
-                const int32_t b = wave_incl_scan(d[c]) + carry_b;
-                carry_b = __builtin_amdgcn_readlane(b, kWave - 1);
-                if (t < H) {
-                    outB[t] = b;
-                    outKV[t] = KV[t];
-                }
+        for (int c = 0; c < kChunks; ++c) {
+            const int32_t t = g0 + c * kWave + lane;
+            d[c] = t < run.to ? load(t) : 0;
+        }
+#pragma unroll
+        for (int c = 0; c < kChunks; ++c) {
+            const int32_t t = g0 + c * kWave + lane;
+            const int32_t b = wave_incl_scan(d[c]) + carry_b;
+            carry_b = __builtin_amdgcn_readlane(b, kWave - 1);
+            if (t < run.to) {
+                outB[t] = b;
+                outKV[t] = KV[t];
             }
         }
     }
-    if (lane == 0) {
+    if (threadIdx.x == 0) {
         P.n_iters[s] = n_end;
         P.flags[s] = fl;
     }
@@ -926,9 +1069,21 @@ hipError_t launch_project(const ProjectParams& p, hipStream_t stream) {
     // block sizes that are powers of two up to 64 take shifts instead of
     // divisions in the admission loops
     const bool pow2 = p.N <= kWave && (p.N & (p.N - 1)) == 0;
-    void (*const kern)(ProjectParams) = bd_lds ? (pow2 ? project_kernel<true, true> : project_kernel<true, false>)
-                                               : (pow2 ? project_kernel<false, true> : project_kernel<false, false>);
-    if (lds > 64 * 1024) {
+    // Four wavefronts a scenario share its scans, request passes and additions;
+    // with long loops on more scenarios than fill the device at four each, one
+    // does: every wavefront runs the loop.  Measured (us at 1 / 4): 1024 boards
+    // in flight 28 / 14, one board x 2048 23 / 10, boards under arrivals 64:
+    // 4387 / 3467, 2048: 5153 / 4225, 4096: 5316 / 6800; 256 boards behind a
+    // batch cap 357 / 322.
+    const bool one = !bd_lds && p.n_scenarios > 2048;
+    const int w = one ? 1 : kProjWaves;
+    void (*const kerns[2][2][2])(ProjectParams) = {
+        {{project_kernel<false, false, 1>, project_kernel<false, false, kProjWaves>},
+         {project_kernel<false, true, 1>, project_kernel<false, true, kProjWaves>}},
+        {{project_kernel<true, false, 1>, project_kernel<true, false, kProjWaves>},
+         {project_kernel<true, true, 1>, project_kernel<true, true, kProjWaves>}}};
+    void (*const kern)(ProjectParams) = kerns[bd_lds][pow2][!one];
+    if (lds + sizeof(ProjShared) > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
@@ -943,7 +1098,7 @@ hipError_t launch_project(const ProjectParams& p, hipStream_t stream) {
         const hipError_t e0 = hipGetLastError();
         if (e0 != hipSuccess) return e0;
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)p.n_scenarios), dim3(64), lds, stream, p);
+    hipLaunchKernelGGL(kern, dim3((unsigned)p.n_scenarios), dim3(w * kWave), lds, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !p.rows) return e;
     const int64_t blocks = p.n_scenarios * ((p.H + kRowsThreads - 1) / kRowsThreads);
