@@ -152,7 +152,7 @@ struct GridItem {
 template <int J, int PER>
 __device__ __forceinline__ GridItem grid_item(const GridParams& P, int64_t item) {
     const int32_t n_chunks = (P.H + J * PER - 1) / (J * PER);
-    const int32_t n_fg = (P.F + kWave - 1) / kWave;
+    const int32_t n_fg = (P.F + kWave - 1) / kWave;   // (1 where a wavefront takes two parts of a chunk)
     GridItem g;
     g.valid = item < P.S * n_fg * n_chunks * PER;
     const int64_t it = g.valid ? item / PER : 0;
@@ -203,9 +203,9 @@ constexpr int kRowGroup = 8;   // rows whose (KV, batch) hull is tested as one
 // other groups test row by row.  A lane whose row leaves the intersection
 // walks only the trees whose own box it left (both in one pass when the
 // wavefront needs both) and reads the new leaves' values and boxes.
-template <int J, int NT>
+template <int J, int NT, class Hulls>
 __device__ __forceinline__ void eval_trees(uint32_t tree, uint32_t rec_bytes, int32_t depth, const uint4* rows4,
-                                           const Box (&hull)[J / kRowGroup], uint32_t fe, float (&acc)[J]) {
+                                           Hulls&& hulls, uint32_t fe, const uint32_t (&first)[NT], float (&acc)[J]) {
     static_assert(J % kRowGroup == 0 && kRowGroup % 4 == 0, "whole row groups");
     static_assert(NT == 1 || NT == 2, "one tree or a pair");
     // the rows are re-read from LDS for each group that needs them rather
@@ -216,23 +216,18 @@ __device__ __forceinline__ void eval_trees(uint32_t tree, uint32_t rec_bytes, in
     // the walked tree's box is read again
     Box box, b0, b1 = empty_box();
     float v[NT];
-    {
-        // the chunk's first row walks every tree on every lane, outside the
-        // group loop so that the loop's walks carry no first-row case
-        uint32_t k[NT];
-        walk<NT>(tree, rec_bytes, depth, rows4[0].x, fe, k);
-        v[0] = leaf_value(k[0]);
-        b0 = leaf_box(k[0], tree);
-        box = b0;
-        if (NT == 2) {
-            v[NT - 1] = leaf_value(k[NT - 1]);
-            b1 = leaf_box(k[NT - 1], tree1);
-            box = box_meet(b0, b1);
-        }
+    v[0] = leaf_value(first[0]);
+    b0 = leaf_box(first[0], tree);
+    box = b0;
+    if (NT == 2) {
+        v[NT - 1] = leaf_value(first[NT - 1]);
+        b1 = leaf_box(first[NT - 1], tree1);
+        box = box_meet(b0, b1);
     }
 #pragma unroll
     for (int gi = 0; gi < J / kRowGroup; ++gi) {
-        const uint32_t outside = pair_above(hull[gi].lo, box.lo) | pair_above(box.hi, hull[gi].hi);
+        const Box hull = hulls(gi);
+        const uint32_t outside = pair_above(hull.lo, box.lo) | pair_above(box.hi, hull.hi);
         const bool test_rows = __builtin_amdgcn_ballot_w64(outside != 0) != 0;   // wavefront-uniform
         uint4 q = make_uint4(0, 0, 0, 0);
 #pragma unroll
@@ -293,10 +288,15 @@ __device__ __forceinline__ void eval_trees(uint32_t tree, uint32_t rec_bytes, in
     }
 }
 
-template <int J>
+// PARTS: a wavefront takes PARTS (1 or 2) consecutive parts of J rows of one
+// scenario, 64 / PARTS lanes each: with at most 32 frequencies two parts fill
+// its lanes.  A row, and a group's hull, then differ between the halves: the
+// hulls are read from LDS instead of held in scalar registers.
+template <int J, int PARTS>
 __global__ __launch_bounds__(kLdsThreads, kLdsWavesPerSimd) void forest_grid_lds_kernel(RankDev D, TreeBlocks B,
                                                                                              GridParams P) {
-    static_assert(J <= kWave, "one lane ranks each row");
+    constexpr int kRows = J * PARTS, kLanes = kWave / PARTS, kGroups = J / kRowGroup;
+    static_assert(kRows <= kWave, "one lane ranks each row");
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t rec_bytes = rank_record_bytes(D.depth);
     const uint32_t buf_bytes = stage_buffer_bytes(B.tb, rec_bytes);
@@ -304,13 +304,18 @@ __global__ __launch_bounds__(kLdsThreads, kLdsWavesPerSimd) void forest_grid_lds
     const int wave = threadIdx.x / kWave;
     const int lane = lane_id();
     const int64_t item = __builtin_amdgcn_readfirstlane((int64_t)blockIdx.x * kLdsWaves + wave);
-    const GridItem g = grid_item<J, kOrderJ / J>(P, item);
+    GridItem g = grid_item<kRows, kOrderJ / kRows>(P, item);
     const int32_t F = P.F, H = P.H;
-    const bool active = g.valid && g.f < F;
-    // the J rank pairs of this wavefront are the same for every lane; they
-    // sit in LDS after the tree buffers and are read as broadcasts
-    uint32_t* rows = (uint32_t*)(smem + kLdsBuffers * buf_bytes) + wave * J;
-    StageSync* sync = (StageSync*)(smem + kLdsBuffers * buf_bytes + (size_t)kLdsWaves * J * sizeof(uint32_t));
+    const int part = lane / kLanes;
+    if (PARTS > 1) g.f = lane % kLanes;
+    const int32_t j0 = g.j0 + part * J, nj = min(J, H - j0);   // the lane's rows (nj <= 0: none)
+    const bool active = g.valid && g.f < F && nj > 0;
+    // the rank pairs of this wavefront's rows are the same for every lane of a
+    // part; they sit in LDS after the tree buffers and are read as broadcasts,
+    // after them the groups' hulls (PARTS > 1)
+    constexpr int kWords = kRows + (PARTS > 1 ? 2 * kGroups * PARTS : 0);
+    uint32_t* rows = (uint32_t*)(smem + kLdsBuffers * buf_bytes) + wave * kWords;
+    StageSync* sync = (StageSync*)(smem + kLdsBuffers * buf_bytes + (size_t)kLdsWaves * kWords * sizeof(uint32_t));
     if (threadIdx.x == 0) stage_sync_init<kLdsBuffers>(sync);
 
     // staging: block 0 by every wavefront before the barrier, the others
@@ -325,17 +330,15 @@ __global__ __launch_bounds__(kLdsThreads, kLdsWavesPerSimd) void forest_grid_lds
     for (int32_t grp = 0; grp < D.n_groups; ++grp) {
         // this group's ranks of the lane's frequency and engine size (a NaN
         // ranks above every threshold: every right turn, as in a plain walk)
-        // and of row `lane` (rows past the chunk repeat its last)
-        const int32_t j = g.j0 + min(min(lane, J - 1), g.nj - 1);
+        // and of row `lane` (rows past the horizon repeat its last)
+        const int32_t j = min(g.j0 + min(lane, kRows - 1), H - 1);
         const uint32_t fe = rank_lane(D, grp, P.freqs[g.f < F ? g.f : F - 1], P.engine ? P.engine[g.s] : 0.0f);
         const uint32_t own = rank_row(D, grp, (float)P.kv[g.s * H + j], (float)P.batch[g.s * H + j]);
-        if (lane < J) rows[lane] = own;
+        if (lane < kRows) rows[lane] = own;
         asm volatile("" ::: "memory");
-        // per row group, the box of its rows (wavefront-uniform)
-        const uint4* rows4 = (const uint4*)rows;
-        Box hull[J / kRowGroup];
-#pragma unroll
-        for (int gi = 0; gi < J / kRowGroup; ++gi) {
+        // per row group, the box of its rows
+        const uint4* rows4 = (const uint4*)(rows + part * J);
+        auto group_hull = [&](int gi) {
             uint32_t lo = 0xffffffffu, hi = 0;
 #pragma unroll
             for (int i = 0; i < kRowGroup / 4; ++i) {
@@ -343,12 +346,29 @@ __global__ __launch_bounds__(kLdsThreads, kLdsWavesPerSimd) void forest_grid_lds
                 lo = pair_min(lo, pair_min(pair_min(q.x, q.y), pair_min(q.z, q.w)));
                 hi = pair_max(hi, pair_max(pair_max(q.x, q.y), pair_max(q.z, q.w)));
             }
-            hull[gi].lo = to_sgpr(lo);
-            hull[gi].hi = to_sgpr(hi);
+            return Box{lo, hi};
+        };
+        Box hull[kGroups];
+        const uint2* hull_at = (const uint2*)(rows + kRows) + part * kGroups;
+#pragma unroll
+        for (int gi = 0; gi < kGroups; ++gi) {
+            const Box h = group_hull(gi);
+            if (PARTS == 1) {   // wavefront-uniform
+                hull[gi].lo = to_sgpr(h.lo);
+                hull[gi].hi = to_sgpr(h.hi);
+            } else if (lane % kLanes == 0) {
+                ((uint2*)hull_at)[gi] = make_uint2(h.lo, h.hi);
+            }
         }
+        auto hulls = [&](int gi) {
+            if (PARTS == 1) return hull[gi];
+            asm volatile("" ::: "memory");   // read when needed, not held in registers
+            const uint2 h = hull_at[gi];
+            return Box{h.x, h.y};
+        };
         // the ranks are complete before this wavefront stages again: the
         // walks then never wait for a copy in flight
-        asm volatile("" ::"v"(fe));
+        asm volatile("" ::"v"(fe) : "memory");
         const int32_t b_end = min((grp + 1) * B.group_blocks, B.n_blocks);
         for (int32_t b = grp * B.group_blocks; b < b_end; ++b) {
             const uint32_t buf = lds_addr(smem) + (uint32_t)(b % kLdsBuffers) * buf_bytes;
@@ -361,18 +381,41 @@ __global__ __launch_bounds__(kLdsThreads, kLdsWavesPerSimd) void forest_grid_lds
                 // walked in one pass, so the two chains of dependent LDS
                 // reads overlap.
                 int32_t tt = 0;
-                for (; tt + 1 < cnt; tt += 2)
-                    eval_trees<J, 2>(buf + tt * rec_bytes, rec_bytes, D.depth, rows4, hull, fe, acc);
-                if (tt < cnt) eval_trees<J, 1>(buf + tt * rec_bytes, rec_bytes, D.depth, rows4, hull, fe, acc);
+                const uint32_t row0 = rows4[0].x;
+                auto pair = [&](uint32_t tree, const uint32_t(&first)[2]) {
+                    eval_trees<J, 2>(tree, rec_bytes, D.depth, rows4, hulls, fe, first, acc);
+                };
+                // the first row's walks four trees at once (37 boards x 23 x
+                // 777, 250 trees of depth 7: 218 -> 207 us a step; 256 x 32 x
+                // 4096, 300 of depth 8: 1528 -> 1497)
+                for (; tt + 3 < cnt; tt += 4) {
+                    const uint32_t tree = buf + tt * rec_bytes;
+                    uint32_t k[4];
+                    walk<4>(tree, rec_bytes, D.depth, row0, fe, k);
+                    pair(tree, {k[0], k[1]});
+                    pair(tree + 2 * rec_bytes, {k[2], k[3]});
+                }
+                for (; tt + 1 < cnt; tt += 2) {
+                    const uint32_t tree = buf + tt * rec_bytes;
+                    uint32_t k[2];
+                    walk<2>(tree, rec_bytes, D.depth, row0, fe, k);
+                    pair(tree, k);
+                }
+                if (tt < cnt) {
+                    const uint32_t tree = buf + tt * rec_bytes;
+                    uint32_t k[1];
+                    walk<1>(tree, rec_bytes, D.depth, row0, fe, k);
+                    eval_trees<J, 1>(tree, rec_bytes, D.depth, rows4, hulls, fe, k, acc);
+                }
             }
             stage_release<kLdsBuffers>(sync, b, kLdsWaves);
         }
     }
     if (active) {
-        float* o = P.out + ((int64_t)g.s * F + g.f) * H + g.j0;
+        float* o = P.out + ((int64_t)g.s * F + g.f) * H + j0;
 #pragma unroll
         for (int jj = 0; jj < J; ++jj)
-            if (jj < g.nj) o[jj] = sync_ok ? acc[jj] : __builtin_nanf("");
+            if (jj < nj) o[jj] = sync_ok ? acc[jj] : __builtin_nanf("");
     }
 }
 
@@ -457,11 +500,12 @@ hipError_t launch_nf(const ForestDev& f, const float* rows, int64_t n_rows, floa
 
 // Trees per staged block for the LDS kernel: the buffers and the wavefronts'
 // rows must fit the LDS budget.  0 = the LDS kernel cannot run.
-int32_t lds_trees_per_block(const ForestDev& f, size_t* lds_bytes) {
+int32_t lds_trees_per_block(const ForestDev& f, size_t budget, size_t* lds_bytes) {
     if (!f.records || f.depth > kMaxRecordDepth) return 0;
     const uint32_t rec_bytes = rank_record_bytes(f.depth);
-    const size_t head = (size_t)kLdsWaves * kLdsJ * sizeof(uint32_t) + sizeof(StageSync);
-    auto fits = [&](int32_t tb) { return kLdsBuffers * (size_t)stage_buffer_bytes(tb, rec_bytes) + head <= kLdsBudget; };
+    // (two parts: 64 rows and 8 hulls a wavefront)
+    const size_t head = (size_t)kLdsWaves * (kWave + 16) * sizeof(uint32_t) + sizeof(StageSync);
+    auto fits = [&](int32_t tb) { return kLdsBuffers * (size_t)stage_buffer_bytes(tb, rec_bytes) + head <= budget; };
     // whole pairs of trees where two fit
     int32_t tb = 64;
     while (tb > 1 && !fits(tb)) tb -= tb > 2 ? 2 : 1;
@@ -470,16 +514,19 @@ int32_t lds_trees_per_block(const ForestDev& f, size_t* lds_bytes) {
     return tb;
 }
 
+// Parts of a chunk a wavefront takes: two where their frequencies fit.
+int grid_parts(const GridParams& g) { return g.F <= kWave / 2 ? 2 : 1; }
+
 int64_t grid_workgroups(const GridParams& g, int J) {
     const int64_t n_chunks = (g.H + kOrderJ - 1) / kOrderJ;
     const int64_t n_fg = (g.F + kWave - 1) / kWave;
-    const int64_t items = g.S * n_fg * n_chunks * (kOrderJ / J);
+    const int64_t items = g.S * n_fg * n_chunks * (kOrderJ / (J * grid_parts(g)));
     return (items + kLdsWaves - 1) / kLdsWaves;
 }
 
-template <int J>
+template <int J, int PARTS>
 hipError_t launch_grid_lds(const ForestDev& f, const GridParams& g, int32_t tb, size_t lds, hipStream_t stream) {
-    const auto kern = forest_grid_lds_kernel<J>;
+    const auto kern = forest_grid_lds_kernel<J, PARTS>;
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     const int64_t blocks = grid_workgroups(g, J);
@@ -496,8 +543,8 @@ hipError_t launch_grid_lds(const ForestDev& f, const GridParams& g, int32_t tb, 
 // of depth 8 (512 workgroups at 8 rows) 573 / 779 / 1054, with 2000 of depth 10
 // 4133 / 3366 / 4563, 256 boards of the former 1999 / 1427 / 1265.
 // *ordered: 32 rows, and more workgroups than start at once: only then does a
-// work order pay.
-hipError_t grid_rows(const ForestDev& f, const GridParams& g, int* J, bool* ordered) {
+// work order pay.  *alone: at most one workgroup per CU.
+hipError_t grid_rows(const ForestDev& f, const GridParams& g, int* J, bool* ordered, bool* alone) {
     int dev = 0, cus = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
@@ -505,6 +552,7 @@ hipError_t grid_rows(const ForestDev& f, const GridParams& g, int* J, bool* orde
     auto fits = [&](int rows) { return grid_workgroups(g, rows) * std::max(f.depth, 1) <= 16 * (int64_t)cus; };
     *J = fits(8) ? 8 : fits(16) ? 16 : kLdsJ;
     *ordered = *J == kLdsJ && grid_workgroups(g, kLdsJ) > 2 * (int64_t)cus;
+    *alone = grid_workgroups(g, *J) <= cus;
     return hipSuccess;
 }
 
@@ -604,10 +652,11 @@ namespace {
 hipError_t plan_order(const ForestDev& f, const GridParams& g, PairOrderPlan* p) {
     *p = PairOrderPlan{0, 0, 0, 0};
     size_t lds = 0;
-    if (lds_trees_per_block(f, &lds) <= 0) return hipSuccess;   // the global kernel takes no order
+    if (lds_trees_per_block(f, kLdsBudget, &lds) <= 0) return hipSuccess;   // the global kernel takes no order
     int J = 0;
     bool ordered = false;
-    const hipError_t e = grid_rows(f, g, &J, &ordered);
+    bool alone = false;
+    const hipError_t e = grid_rows(f, g, &J, &ordered, &alone);
     if (e != hipSuccess || !ordered) return e;
     return pair_order_plan(f, g.S * ((g.H + kOrderJ - 1) / kOrderJ), 1, p);
 }
@@ -626,7 +675,7 @@ hipError_t launch_forest_grid(const ForestDev& f, const GridParams& g_in, void* 
     GridParams g = g_in;
     g.order = nullptr;
     size_t lds = 0;
-    const int32_t tb = lds_trees_per_block(f, &lds);
+    int32_t tb = lds_trees_per_block(f, kLdsBudget, &lds);
     if (tb <= 0) return f.n_features == 4 ? launch_grid_global<4>(f, g, stream) : launch_grid_global<3>(f, g, stream);
     PairOrderPlan p;
     hipError_t e = plan_order(f, g, &p);
@@ -639,11 +688,18 @@ hipError_t launch_forest_grid(const ForestDev& f, const GridParams& g_in, void* 
     }
     int J = 0;
     bool ordered = false;
-    e = grid_rows(f, g, &J, &ordered);
+    bool alone = false;
+    e = grid_rows(f, g, &J, &ordered, &alone);
     if (e != hipSuccess) return e;
-    return J == 32   ? launch_grid_lds<32>(f, g, tb, lds, stream)
-           : J == 16 ? launch_grid_lds<16>(f, g, tb, lds, stream)
-                     : launch_grid_lds<8>(f, g, tb, lds, stream);
+    // a workgroup with a CU to itself stages twice as many trees at a time
+    if (alone) tb = lds_trees_per_block(f, 2 * kLdsBudget, &lds);
+    if (grid_parts(g) == 2)
+        return J == 32   ? launch_grid_lds<32, 2>(f, g, tb, lds, stream)
+               : J == 16 ? launch_grid_lds<16, 2>(f, g, tb, lds, stream)
+                         : launch_grid_lds<8, 2>(f, g, tb, lds, stream);
+    return J == 32   ? launch_grid_lds<32, 1>(f, g, tb, lds, stream)
+           : J == 16 ? launch_grid_lds<16, 1>(f, g, tb, lds, stream)
+                     : launch_grid_lds<8, 1>(f, g, tb, lds, stream);
 }
 
 // Workspace of the grid kernel's work order for callers that cannot
