@@ -17,14 +17,18 @@ from ._lib import check, lib
 
 
 def _p(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the raw handle of torch.cuda.current_stream(), without a Stream object
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _need(t, dtype, name, shape=None):
+    if (t is not None and t.is_cuda and t.dtype == dtype and t.is_contiguous()
+            and (shape is None or t.shape == shape)):
+        return t
     if t is None:
         raise ValueError(f"{name} is required")
     if not t.is_cuda:

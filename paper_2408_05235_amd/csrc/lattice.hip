@@ -87,6 +87,25 @@ __device__ __forceinline__ float walk_global(const ForestDev& f, const float (&x
 
 constexpr int kGatherThreads = 256;
 
+// 4 N consecutive values of a lattice point to as many rows of the output.
+struct __attribute__((packed, aligned(4))) Float4At4 {
+    float x, y, z, w;
+};
+template <int N>
+__device__ __forceinline__ void put_values(const float* t, float* out, int32_t H) {
+    Float4At4 v[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = ((const Float4At4*)t)[k];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        float* o = out + (int64_t)(4 * k) * H;
+        __builtin_nontemporal_store(v[k].x, o);
+        __builtin_nontemporal_store(v[k].y, o + H);
+        __builtin_nontemporal_store(v[k].z, o + 2 * (int64_t)H);
+        __builtin_nontemporal_store(v[k].w, o + 3 * (int64_t)H);
+    }
+}
+
 // One thread per (scenario, iteration): it reads KV and batch once, then the
 // contiguous run of the lattice point's F values, and writes them to the F
 // outputs of the row (consecutive iterations of a workgroup write
@@ -110,31 +129,20 @@ __global__ __launch_bounds__(kGatherThreads) void lattice_gather_kernel(ForestDe
     if (e >= 0 && kv >= 0 && kv <= L.kv_max && b >= 0 && b <= L.batch_max) {
         const float* t = L.table + ((((int64_t)e * L.nB + b) * L.nC) * kLatticeChunk + kv) * F;
         int32_t fi = 0;
-        if ((F & 3) == 0) {
-            // runs of 4k floats start 16-byte aligned: 64 values at a time,
-            // all loads in flight before the (streaming) stores
-            for (; fi + 64 <= F; fi += 64) {
-                float4 v[16];
+        // 64 values at a time, then 16, then the rest: all of a step's loads
+        // in flight before its (streaming) stores.  A point's run starts at a
+        // multiple of 4 F bytes: the 16-byte loads need 4-byte alignment only.
+        // (One load, one store at a time where 4 did not divide F: 1024 boards
+        // x 17 frequencies x 512 iterations took 37 us.)
+        for (; fi + 64 <= F; fi += 64) put_values<16>(t + fi, out + (int64_t)fi * P.H, P.H);
+        for (; fi + 16 <= F; fi += 16) put_values<4>(t + fi, out + (int64_t)fi * P.H, P.H);
+        float v[15];
 #pragma unroll
-                for (int k = 0; k < 16; ++k) v[k] = *(const float4*)(t + fi + 4 * k);
+        for (int k = 0; k < 15; ++k)
+            if (fi + k < F) v[k] = t[fi + k];
 #pragma unroll
-                for (int k = 0; k < 16; ++k) {
-                    float* o = out + (int64_t)(fi + 4 * k) * P.H;
-                    __builtin_nontemporal_store(v[k].x, o);
-                    __builtin_nontemporal_store(v[k].y, o + P.H);
-                    __builtin_nontemporal_store(v[k].z, o + 2 * (int64_t)P.H);
-                    __builtin_nontemporal_store(v[k].w, o + 3 * (int64_t)P.H);
-                }
-            }
-            for (; fi < F; fi += 4) {
-                const float4 v = *(const float4*)(t + fi);
-                out[(int64_t)fi * P.H] = v.x;
-                out[(int64_t)(fi + 1) * P.H] = v.y;
-                out[(int64_t)(fi + 2) * P.H] = v.z;
-                out[(int64_t)(fi + 3) * P.H] = v.w;
-            }
-        }
-        for (; fi < F; ++fi) out[(int64_t)fi * P.H] = t[fi];
+        for (int k = 0; k < 15; ++k)
+            if (fi + k < F) __builtin_nontemporal_store(v[k], out + (int64_t)(fi + k) * P.H);
     } else {
         for (int32_t fi = 0; fi < F; ++fi) {
             const float x[4] = {L.freqs[fi], (float)kv, (float)b, xe};

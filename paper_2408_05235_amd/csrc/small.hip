@@ -168,6 +168,13 @@ __global__ __launch_bounds__(kSumWaves* kWave) void forest_sum_kernel(const floa
 constexpr size_t kSmallScratchBytes = (size_t)64 << 20;
 constexpr int64_t kSliceRows = 1024;               // a slice is whole tiles
 
+// More than 64 KiB of dynamic LDS has to be asked for (a call into the runtime
+// that these short calls otherwise save).
+hipError_t allow_lds(const void* kern, size_t lds) {
+    if (lds <= 64 * 1024) return hipSuccess;
+    return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+}
+
 int64_t slice_rows(int32_t n_trees, int64_t n_rows) {
     const int64_t most = (int64_t)(kSmallScratchBytes / sizeof(float)) / std::max(1, n_trees) / kSliceRows * kSliceRows;
     const int64_t all = (n_rows + kSliceRows - 1) / kSliceRows * kSliceRows;
@@ -190,7 +197,7 @@ hipError_t launch_leaves(const ForestDev& f, const SmallParams& p, int64_t first
     while (tb > 1 && 2 * (size_t)stage_buffer_bytes(tb, bytes) > budget) tb -= tb > 4 ? (tb + 3) % 4 + 1 : 1;
     const size_t lds = (C.tb > tb ? 2 : 1) * (size_t)stage_buffer_bytes(tb, bytes);
     const auto kern = forest_leaves_kernel<KIND, WAVES>;
-    const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const hipError_t e = allow_lds((const void*)kern, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)tiles, (unsigned)C.n_blocks), dim3(WAVES * kWave), lds, stream,
                        rank_dev(f), C, tb, p, first, n, values);
@@ -203,7 +210,7 @@ hipError_t launch_small(const ForestDev& f, const SmallParams& p, int64_t n_rows
     const int64_t step = slice_rows(f.n_trees, n_rows);
     const size_t lds = (f.n_trees > kSumSeg ? 2 : 1) * (size_t)std::min(f.n_trees, kSumSeg) * kWave * sizeof(float);
     const auto sum = forest_sum_kernel<KIND>;
-    hipError_t e = hipFuncSetAttribute((const void*)sum, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipError_t e = allow_lds((const void*)sum, lds);
     for (int64_t first = 0; first < n_rows && e == hipSuccess; first += step) {
         const int64_t n = std::min(step, n_rows - first);
         // a large tile shares a staged chunk among more rows; a small one
