@@ -224,6 +224,18 @@ bool capturing(hipStream_t st) {
     return cs != hipStreamCaptureStatusNone;
 }
 
+// While another thread captures a stream (in the default, global mode), the
+// calls that choose and grow a workspace -- event queries, allocations -- are
+// refused on every thread and end that capture.  They belong to no captured
+// stream: this thread's mode is relaxed around them.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    RelaxedCapture(const RelaxedCapture&) = delete;
+    RelaxedCapture& operator=(const RelaxedCapture&) = delete;
+};
+
 // Runs launch(ws, ws_bytes) with one of the forest's cached workspaces of at
 // least `need` bytes, all of its launches on st.  In the steady state
 // nothing is allocated; a larger need than any before replaces the
@@ -234,6 +246,7 @@ template <class Launch>
 hipError_t with_workspace(const tl_forest* f, size_t need, hipStream_t st, Launch&& launch) {
     if (need == 0 || capturing(st)) return launch(nullptr, (size_t)0);
     std::lock_guard<std::mutex> lock(f->ws_mutex);
+    const RelaxedCapture relaxed;
     hipError_t e;
     tl_forest::Workspace* w = nullptr;
     for (tl_forest::Workspace& c : f->ws)

@@ -155,3 +155,51 @@ def test_captured_binary_search_replays(gpu):
         for k in eager:
             assert np.array_equal(got[k], eager[k]), (k, "eager after replay", rep)
     forest.close()
+
+
+def test_call_on_another_thread_while_capturing(gpu):
+    """A call on another thread and stream while this thread captures: it asks
+    whether the forest's scratch is idle, which must neither fail nor end the
+    capture (in the default mode, which holds for every thread)."""
+    import threading
+    import torch
+    from paper_2408_05235_amd import api
+    rng = np.random.default_rng(47)
+    fd = random_forest(rng, 30, 8, 3)
+    kv, bs = random_curves(rng, 6, 300)
+    freqs = synth.frequency_grid(64)
+    exp = oracle.forest_predict(fd, oracle.rows(freqs, bs, kv, None, 3))
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    dkv, dbs, dfr = t(kv), t(bs), t(freqs)
+    outs = [torch.full((6, 64, 300), -1.0, dtype=torch.float32, device="cuda") for _ in range(2)]
+    forest = api.Forest.from_dict(fd)
+    forest.tl_forest_predict_grid(dfr, dkv, dbs, out=outs[0])   # its scratch belongs to this stream now
+    outs[0].fill_(-1.0)
+    other = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    errors = []
+
+    def work():
+        try:
+            with torch.cuda.stream(other):
+                forest.tl_forest_predict_grid(dfr, dkv, dbs, out=outs[1])
+        except Exception as e:   # raised again below, on the test's own thread
+            errors.append(e)
+
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        th = threading.Thread(target=work)
+        th.start()
+        th.join(60)
+        forest.tl_forest_predict_grid(dfr, dkv, dbs, out=outs[0])
+    assert not errors, errors
+    torch.cuda.synchronize()
+    assert np.array_equal(outs[1].cpu().numpy(), exp)
+    for rep in range(3):
+        outs[0].fill_(-1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(outs[0].cpu().numpy(), exp), f"replay {rep}"
+        assert np.array_equal(forest.tl_forest_predict_grid(dfr, dkv, dbs).cpu().numpy(), exp)
+        torch.cuda.synchronize()
+    forest.close()
