@@ -1,6 +1,5 @@
 // Host-side preparation of a tree ensemble for the kernels (plain C++, no
-// HIP): the KV / batch box of every leaf, the LDS tree records and the
-// threshold cuts of the work-order cost model.  Trees are complete, depth d,
+// HIP): the KV / batch box of every leaf and the LDS tree records.  Trees are complete, depth d,
 // heap order: internal node k tests x[feature] < threshold and continues at
 // 2k+1 if true, at 2k+2 otherwise (Sec. 4.3.1 model M).
 #pragma once
@@ -32,7 +31,8 @@ void leaf_boxes(int32_t n_trees, int32_t depth, const uint8_t* feature, const fl
 // x < ceil(hi); clamping can only shrink the box).
 uint32_t box_bound(float x, uint32_t maxv);
 
-// The records of all trees (record_layout(depth).bytes each, back to back,
+// Records with fp32 thresholds (no kernel reads them; the host check compares
+// their boxes with walks): all trees (record_layout(depth).bytes each, back to back,
 // plus 64 bytes of padding) from the node arrays [n_trees][2^depth - 1], the
 // leaves [n_trees][2^depth] and the leaf boxes.  depth <= kMaxRecordDepth.
 void build_records(int32_t n_trees, int32_t depth, const uint8_t* feature, const float* threshold, const float* leaf,
@@ -52,7 +52,7 @@ struct RankForest {
 void build_rank_records(int32_t n_trees, int32_t depth, const uint8_t* feature, const float* threshold,
                         const float* leaf, RankForest& out);
 
-// Up to kMaxCuts quantiles of the finite thresholds of feature fi over
+// (Also for the host check only.)  Up to kMaxCuts quantiles of the finite thresholds of feature fi over
 // n_nodes nodes, ascending.
 std::vector<float> threshold_cuts(int64_t n_nodes, const uint8_t* feature, const float* threshold, int fi);
 

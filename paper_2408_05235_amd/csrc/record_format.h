@@ -1,5 +1,5 @@
-// Formats of the forest data the host builds and the kernels read: the
-// LDS-staged tree records and the threshold cuts.  No HIP headers, so the
+// Formats of the forest data the host builds and the kernels read, the
+// LDS-staged tree records above all.  No HIP headers, so the
 // host-side builders (host_forest.cpp) also compile as plain C++.
 #pragma once
 
@@ -17,8 +17,9 @@ constexpr int32_t kMaxCuts = 4096;
 
 constexpr int kMaxRecordDepth = 11;
 
-// One tree as the LDS-staged kernels read it (byte ranges, each starting on
-// a 16-byte boundary):
+// One tree with fp32 thresholds and leaf boxes as integer bounds (byte ranges,
+// each starting on a 16-byte boundary).  The kernels read the rank records
+// below; this form is only built by the host check of the leaf boxes.
 //   [0, boxes)      2^d node slots of 16 bytes, slot k = (threshold,
 //                   sel_lo, sel_hi, value of leaf k).  The selectors are
 //                   byte-permute selectors that pick the tested feature c
@@ -37,7 +38,6 @@ constexpr int kMaxRecordDepth = 11;
 //                   a clamped box is a subset of the leaf's own, so a row
 //                   inside it still reaches the leaf, and a row outside it
 //                   only walks the tree again.
-// A block of consecutive trees is one contiguous byte range, staged as is.
 constexpr uint32_t kBoxKvMax = (1u << 20) - 1;
 constexpr uint32_t kBoxBatchMax = (1u << 12) - 1;
 
@@ -74,6 +74,7 @@ TL_HOST_DEVICE inline RecordLayout record_layout(int32_t depth) {
 //   [8 * 2^d, 16 * 2^d)   leaf boxes, 8 bytes per leaf: the lowest and the
 //                         highest (KV rank | batch rank << 16) that the leaf's
 //                         path allows (kEmptyBox for leaves no row reaches)
+// A block of consecutive trees is one contiguous byte range, staged as is.
 constexpr int32_t kMaxRank = 65534;
 constexpr uint32_t kEmptyBoxLo = 0xffffffffu, kEmptyBoxHi = 0u;
 
