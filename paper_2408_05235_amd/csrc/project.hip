@@ -1073,9 +1073,11 @@ hipError_t launch_project(const ProjectParams& p, hipStream_t stream) {
     // with long loops on more scenarios than fill the device at four each, one
     // does: every wavefront runs the loop.  Measured (us at 1 / 4): 1024 boards
     // in flight 28 / 14, one board x 2048 23 / 10, boards under arrivals 64:
-    // 4387 / 3467, 2048: 5153 / 4225, 4096: 5316 / 6800; 256 boards behind a
-    // batch cap 357 / 322.
-    const bool one = !bd_lds && p.n_scenarios > 2048;
+    // 4387 / 3467, 2048: 5153 / 4225, 4096: 5316 / 6800.
+    // Behind a batch cap one does too: its requests are admitted one at a time,
+    // a barrier each between four (us at 4, one-wavefront kernel before: 1487
+    // boards x 2212 758, 452; 2152 x 2867 1150, 822; 268 x 302 130, 91).
+    const bool one = p.batch_cap != nullptr || (!bd_lds && p.n_scenarios > 2048);
     const int w = one ? 1 : kProjWaves;
     void (*const kerns[2][2][2])(ProjectParams) = {
         {{project_kernel<false, false, 1>, project_kernel<false, false, kProjWaves>},
