@@ -13,6 +13,7 @@
 
 #include "device_util.h"
 #include "host_forest.h"
+#include "scratch.h"
 #include "tl.h"
 #include "tl_internal.h"
 
@@ -21,22 +22,8 @@ struct tl_forest {
     tl::ForestDev dev;
     void* mem;        // every array of `dev`
     // Scratch of the grid and column kernels' work orders and of calls with
-    // few rows, on the forest's device: kept from call to call, each array
-    // only replaced by a larger one when a larger call comes.  `done` is
-    // recorded on the stream of the last call that used it.  A call takes the
-    // array its stream used last, else an idle one, else it waits for another
-    // stream's; kWorkspaces streams can use the forest without waiting.
-    struct Workspace {
-        void* ptr = nullptr;
-        size_t bytes = 0;
-        hipEvent_t done = nullptr;
-        hipStream_t stream = nullptr;
-        bool used = false;
-    };
-    static constexpr int kWorkspaces = 4;
-    mutable std::mutex ws_mutex;
-    mutable Workspace ws[kWorkspaces];
-    mutable int ws_next = 0;
+    // few rows, on the forest's device.
+    mutable tl::ScratchPool<4> scratch;
 };
 
 struct tl_lattice {
@@ -199,10 +186,7 @@ void tl_forest_destroy(tl_forest* f) {
     (void)hipSetDevice(f->device);
     (void)hipDeviceSynchronize();
     (void)hipFree(f->mem);
-    for (tl_forest::Workspace& w : f->ws) {
-        if (w.ptr) (void)hipFree(w.ptr);
-        if (w.done) (void)hipEventDestroy(w.done);
-    }
+    f->scratch.release();
     (void)hipSetDevice(cur);
     delete f;
 }
@@ -224,88 +208,14 @@ bool capturing(hipStream_t st) {
     return cs != hipStreamCaptureStatusNone;
 }
 
-// While another thread captures a stream (in the default, global mode), the
-// calls that choose and grow a workspace -- event queries, allocations -- are
-// refused on every thread and end that capture.  They belong to no captured
-// stream: this thread's mode is relaxed around them.
-struct RelaxedCapture {
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-    RelaxedCapture(const RelaxedCapture&) = delete;
-    RelaxedCapture& operator=(const RelaxedCapture&) = delete;
-};
-
-// Runs launch(ws, ws_bytes) with one of the forest's cached workspaces of at
-// least `need` bytes, all of its launches on st.  In the steady state
-// nothing is allocated; a larger need than any before replaces the
-// workspace (after the last call that used it is done).  Without a
-// workspace (need 0, allocation failed, or the stream is being captured)
-// launch gets (nullptr, 0) and runs without, which changes only its speed.
+// Runs launch(ws, ws_bytes) with scratch of the forest's of at least `need`
+// bytes, all of its launches on st.  Without it (need 0, allocation failed, or
+// the stream is being captured) launch gets (nullptr, 0) and runs without,
+// which changes only its speed.
 template <class Launch>
 hipError_t with_workspace(const tl_forest* f, size_t need, hipStream_t st, Launch&& launch) {
-    if (need == 0 || capturing(st)) return launch(nullptr, (size_t)0);
-    std::lock_guard<std::mutex> lock(f->ws_mutex);
-    const RelaxedCapture relaxed;
-    hipError_t e;
-    tl_forest::Workspace* w = nullptr;
-    for (tl_forest::Workspace& c : f->ws)
-        if (c.used && c.stream == st) { w = &c; break; }
-    for (int i = 0; i < tl_forest::kWorkspaces && !w; ++i) {
-        tl_forest::Workspace& c = f->ws[i];
-        if (!c.used) {
-            w = &c;
-        } else {
-            e = hipEventQuery(c.done);
-            if (e == hipSuccess) w = &c;
-            else if (e != hipErrorNotReady) return e;
-            else (void)hipGetLastError();   // not ready: no error of the launches below
-        }
-    }
-    if (!w) {
-        w = &f->ws[f->ws_next];
-        f->ws_next = (f->ws_next + 1) % tl_forest::kWorkspaces;
-    }
-    if (!w->done) {
-        e = hipEventCreateWithFlags(&w->done, hipEventDisableTiming);
-        if (e != hipSuccess) {
-            w->done = nullptr;
-            (void)hipGetLastError();
-            return launch(nullptr, (size_t)0);
-        }
-    }
-    if (need > w->bytes) {
-        if (w->ptr) {
-            if (w->used) {
-                e = hipEventSynchronize(w->done);
-                if (e != hipSuccess) return e;
-            }
-            (void)hipFree(w->ptr);
-            w->ptr = nullptr;
-            w->bytes = 0;
-            w->used = false;
-        }
-        if (hipMalloc(&w->ptr, need) == hipSuccess) {
-            w->bytes = need;
-        } else {
-            w->ptr = nullptr;
-            (void)hipGetLastError();   // clear the allocation error before the launches check theirs
-        }
-    }
-    if (!w->ptr) return launch(nullptr, (size_t)0);
-    if (w->used && w->stream != st) {
-        e = hipStreamWaitEvent(st, w->done, 0);
-        if (e != hipSuccess) return e;
-    }
-    const hipError_t el = launch(w->ptr, w->bytes);
-    // recorded also after a failed launch, whose earlier kernels may have
-    // been enqueued on st and use the workspace
-    e = hipEventRecord(w->done, st);
-    if (e == hipSuccess) {
-        w->stream = st;
-        w->used = true;
-    }
-    return el != hipSuccess ? el : e;
+    if (need == 0 || capturing(st)) return launch((void*)nullptr, (size_t)0);
+    return f->scratch.with(need, st, launch);
 }
 
 tl::SmallParams small_params(const tl::GridParams& g) {
@@ -447,7 +357,6 @@ struct OrderWorkspace {
     void* ptr = nullptr;
     size_t bytes = 0;
     hipEvent_t done = nullptr;
-    hipStream_t stream = nullptr;
     bool used = false;
 };
 OrderWorkspace g_order_ws[kOrderDevices];
@@ -484,7 +393,8 @@ hipError_t project_launch(tl::ProjectParams p, hipStream_t st) {
         }
     }
     if (!w.ptr) return tl::launch_project(p, st);
-    if (w.used && w.stream != st) {
+    // (its own stream's too: a handle does not tell streams apart, see scratch.h)
+    if (w.used) {
         e = hipStreamWaitEvent(st, w.done, 0);
         if (e != hipSuccess) return e;
     }
@@ -493,10 +403,7 @@ hipError_t project_launch(tl::ProjectParams p, hipStream_t st) {
     // recorded also after a failed launch, whose order kernels may have been
     // enqueued on st and use the workspace
     e = hipEventRecord(w.done, st);
-    if (e == hipSuccess) {
-        w.stream = st;
-        w.used = true;
-    }
+    if (e == hipSuccess) w.used = true;
     return el != hipSuccess ? el : e;
 }
 

@@ -1,0 +1,132 @@
+// Device scratch of the library that is kept from call to call and shared by
+// the calls on several streams and threads.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <mutex>
+#include <thread>
+
+namespace tl {
+
+// While another thread captures a stream (in the default, global mode), the
+// calls that choose and grow a workspace -- event queries, allocations -- are
+// refused on every thread and end that capture.  They belong to no captured
+// stream: this thread's mode is relaxed around them.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    RelaxedCapture(const RelaxedCapture&) = delete;
+    RelaxedCapture& operator=(const RelaxedCapture&) = delete;
+};
+
+// Up to SLOTS arrays on one device, each only replaced by a larger one when a
+// larger call comes.  `done` is recorded on the stream of the last call that
+// used the array.  A call takes the array its stream used last, else an idle
+// one, else another stream's: SLOTS streams can use the pool without waiting
+// for each other.  Every call that takes a used array waits (on the device) for
+// its event, its own stream's as well: a stream's handle does not tell streams
+// apart (hipStreamPerThread is one handle for a stream in every thread, and a
+// new stream may get the handle of a destroyed one), and on the stream that
+// recorded the event the wait costs nothing.
+template <int SLOTS>
+class ScratchPool {
+public:
+    // Runs launch(ws, ws_bytes) with an array of at least `need` bytes, all of
+    // its launches on st (a stream that is not being captured).  In the steady
+    // state nothing is allocated; a larger need than any before replaces the
+    // array (after the last call that used it is done).  When the allocation
+    // fails launch gets (nullptr, 0).
+    template <class Launch>
+    hipError_t with(size_t need, hipStream_t st, Launch&& launch) {
+        std::lock_guard<std::mutex> lock(mutex_);
+        const RelaxedCapture relaxed;
+        const std::thread::id thread = st == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id();
+        hipError_t e;
+        Slot* w = nullptr;
+        for (Slot& c : slots_)
+            if (c.used && c.stream == st && c.thread == thread) { w = &c; break; }
+        for (int i = 0; i < SLOTS && !w; ++i) {
+            Slot& c = slots_[i];
+            if (!c.used) {
+                w = &c;
+            } else if (SLOTS > 1) {
+                e = hipEventQuery(c.done);
+                if (e == hipSuccess) w = &c;
+                else if (e != hipErrorNotReady) return e;
+                else (void)hipGetLastError();   // not ready: no error of the launches below
+            }
+        }
+        if (!w) {
+            w = &slots_[next_];
+            next_ = (next_ + 1) % SLOTS;
+        }
+        if (!w->done) {
+            e = hipEventCreateWithFlags(&w->done, hipEventDisableTiming);
+            if (e != hipSuccess) {
+                w->done = nullptr;
+                (void)hipGetLastError();
+                return launch((void*)nullptr, (size_t)0);
+            }
+        }
+        if (need > w->bytes) {
+            if (w->ptr) {
+                if (w->used) {
+                    e = hipEventSynchronize(w->done);
+                    if (e != hipSuccess) return e;
+                }
+                (void)hipFree(w->ptr);
+                w->ptr = nullptr;
+                w->bytes = 0;
+                w->used = false;
+            }
+            if (hipMalloc(&w->ptr, need) == hipSuccess) {
+                w->bytes = need;
+            } else {
+                w->ptr = nullptr;
+                (void)hipGetLastError();   // clear the allocation error before the launches check theirs
+            }
+        }
+        if (!w->ptr) return launch((void*)nullptr, (size_t)0);
+        if (w->used) {
+            e = hipStreamWaitEvent(st, w->done, 0);
+            if (e != hipSuccess) return e;
+        }
+        const hipError_t el = launch(w->ptr, w->bytes);
+        // recorded also after a failed launch, whose earlier kernels may have
+        // been enqueued on st and use the array
+        e = hipEventRecord(w->done, st);
+        if (e == hipSuccess) {
+            w->stream = st;
+            w->thread = thread;
+            w->used = true;
+        }
+        return el != hipSuccess ? el : e;
+    }
+
+    // Gives everything back; no call uses the pool any more and the device is
+    // idle.
+    void release() {
+        for (Slot& w : slots_) {
+            if (w.ptr) (void)hipFree(w.ptr);
+            if (w.done) (void)hipEventDestroy(w.done);
+            w = Slot();
+        }
+    }
+
+private:
+    struct Slot {
+        void* ptr = nullptr;
+        size_t bytes = 0;
+        hipEvent_t done = nullptr;
+        hipStream_t stream = nullptr;
+        std::thread::id thread;   // of hipStreamPerThread
+        bool used = false;
+    };
+    std::mutex mutex_;
+    Slot slots_[SLOTS];
+    int next_ = 0;
+};
+
+}  // namespace tl
