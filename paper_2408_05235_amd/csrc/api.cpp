@@ -7,7 +7,6 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
-#include <mutex>
 #include <new>
 #include <vector>
 
@@ -345,66 +344,21 @@ tl_status project_params(const tl_project_args* a, const char* who, bool with_ro
 }
 
 // The projection's scenario order (heaviest first, for long FIFO loops) needs
-// a workspace of one word per scenario: owned by the library, one per device,
-// allocated on first use and replaced only by a larger one.  A call on
-// another stream than the previous user first waits (on the device) for that
-// user's projection.  Without the workspace (allocation failure, device
-// number out of range, a stream being captured) the scenarios run in their
-// own order: same results.
+// a workspace of one word per scenario: owned by the library, one per device.
+// Without it (allocation failure, device number out of range, a stream being
+// captured) the scenarios run in their own order: same results.
 constexpr int kOrderDevices = 64;
-struct OrderWorkspace {
-    std::mutex m;
-    void* ptr = nullptr;
-    size_t bytes = 0;
-    hipEvent_t done = nullptr;
-    bool used = false;
-};
-OrderWorkspace g_order_ws[kOrderDevices];
+tl::ScratchPool<1> g_order_scratch[kOrderDevices];
 
 hipError_t project_launch(tl::ProjectParams p, hipStream_t st) {
     const size_t need = tl::project_order_bytes(p);
     int dev = -1;
     if (need == 0 || capturing(st) || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kOrderDevices)
         return tl::launch_project(p, st);
-    OrderWorkspace& w = g_order_ws[dev];
-    std::lock_guard<std::mutex> lock(w.m);
-    hipError_t e = hipSuccess;
-    if (!w.done && hipEventCreateWithFlags(&w.done, hipEventDisableTiming) != hipSuccess) {
-        w.done = nullptr;
-        (void)hipGetLastError();
+    return g_order_scratch[dev].with(need, st, [&](void* ws, size_t) {
+        p.order_ws = ws;
         return tl::launch_project(p, st);
-    }
-    if (need > w.bytes) {
-        if (w.ptr) {
-            if (w.used) {
-                e = hipEventSynchronize(w.done);
-                if (e != hipSuccess) return e;
-            }
-            (void)hipFree(w.ptr);
-            w.ptr = nullptr;
-            w.bytes = 0;
-            w.used = false;
-        }
-        if (hipMalloc(&w.ptr, need) == hipSuccess) {
-            w.bytes = need;
-        } else {
-            w.ptr = nullptr;
-            (void)hipGetLastError();   // clear the allocation error before the launches check theirs
-        }
-    }
-    if (!w.ptr) return tl::launch_project(p, st);
-    // (its own stream's too: a handle does not tell streams apart, see scratch.h)
-    if (w.used) {
-        e = hipStreamWaitEvent(st, w.done, 0);
-        if (e != hipSuccess) return e;
-    }
-    p.order_ws = w.ptr;
-    const hipError_t el = tl::launch_project(p, st);
-    // recorded also after a failed launch, whose order kernels may have been
-    // enqueued on st and use the workspace
-    e = hipEventRecord(w.done, st);
-    if (e == hipSuccess) w.used = true;
-    return el != hipSuccess ? el : e;
+    });
 }
 
 }  // namespace

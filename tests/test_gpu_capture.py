@@ -203,3 +203,78 @@ def test_call_on_another_thread_while_capturing(gpu):
         assert np.array_equal(forest.tl_forest_predict_grid(dfr, dkv, dbs).cpu().numpy(), exp)
         torch.cuda.synchronize()
     forest.close()
+
+
+def test_projection_on_another_thread_while_capturing(gpu):
+    """A projection with long queues, larger than any before, on another thread
+    while this one captures: it allocates the scenario order's scratch and
+    then a larger one, which must neither fail nor end the capture."""
+    import threading
+    import torch
+    from paper_2408_05235_amd import api
+    rng = np.random.default_rng(50)
+    freqs = synth.frequency_grid(64)
+    fd = random_forest(rng, 30, 8, 3)
+    kv, bs = random_curves(rng, 6, 300)
+    exp = oracle.forest_predict(fd, oracle.rows(freqs, bs, kv, None, 3))
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    dkv, dbs, dfr = t(kv), t(bs), t(freqs)
+    grid_out = torch.full((6, 64, 300), -1.0, dtype=torch.float32, device="cuda")
+    forest = api.Forest.from_dict(fd)
+    boards = []
+    for S in (400, 70000):
+        # one block of boards, repeated: 1024 requests each
+        inp = random_boards(rng, 8, 16, 16, rmax=0)
+        n = 1024 * 8
+        arr = np.full((8, 1024), -1, np.int32)
+        arr[:, 100:] = np.sort(rng.integers(0, 20, (8, 924)), axis=1)
+        inp.update(req_offset=np.arange(9, dtype=np.int64) * 1024, prompt=rng.integers(1, 90, n).astype(np.int32),
+                   generated=np.zeros(n, np.int32), remaining=rng.integers(1, 20, n).astype(np.int32),
+                   arrival=arr.reshape(-1), deadline_ns=rng.integers(1, 10 ** 9, n).astype(np.uint64),
+                   lost=np.zeros(n, np.uint8), kv_capacity=np.full(8, 2000, np.int32), batch_cap=None)
+        one = oracle.project(inp)
+        d = api.upload(dict(inp, tbt_slo_ns=np.zeros(8, np.uint64), freqs_mhz=np.zeros(1, np.float32),
+                            engine_size=None, n_features=3))
+        rep = S // 8
+        d["n_scenarios"] = S
+        d["req_offset"] = torch.arange(S + 1, device="cuda", dtype=torch.int64) * 1024
+        for k in ("prompt", "generated", "remaining", "arrival", "deadline_ns", "lost", "kv_capacity"):
+            d[k] = d[k].repeat(rep)
+        out = dict(batch=torch.empty((S, 16), dtype=torch.int32, device="cuda"),
+                   kv=torch.empty((S, 16), dtype=torch.int32, device="cuda"),
+                   deadline_at=torch.empty((S, 16), dtype=torch.int64, device="cuda"),
+                   n_iters=torch.empty(S, dtype=torch.int32, device="cuda"),
+                   flags=torch.empty(S, dtype=torch.int32, device="cuda"))
+        boards.append((S, d, out, one))
+    other = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    errors = []
+
+    def work():
+        try:
+            with torch.cuda.stream(other):
+                for _, d, out, _ in boards:
+                    api.tl_project(d["req_offset"], d["prompt"], d["generated"], d["remaining"], d["arrival"],
+                                   d["kv_capacity"], 16, 16, d["deadline_ns"], d["lost"], None, want_rows=False,
+                                   out=out)
+        except Exception as e:   # raised again below, on the test's own thread
+            errors.append(e)
+
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        th = threading.Thread(target=work)
+        th.start()
+        th.join(60)
+        forest.tl_forest_predict_grid(dfr, dkv, dbs, out=grid_out)
+    assert not errors, errors
+    torch.cuda.synchronize()
+    for S, _, out, one in boards:
+        for k in ("batch", "kv", "deadline_at", "n_iters", "flags"):
+            got = out[k].cpu().numpy().view(one[k].dtype)
+            assert np.array_equal(got, np.tile(one[k], (S // 8,) + (1,) * (one[k].ndim - 1))), (S, k)
+    for rep in range(3):
+        grid_out.fill_(-1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(grid_out.cpu().numpy(), exp), f"replay {rep}"
+    forest.close()
