@@ -189,7 +189,8 @@ tl_status tl_adjust_lengths(int64_t n_scenarios, int64_t n_requests, const int64
  * requests per scenario) are projected heaviest first (results do not depend
  * on the order).  The order takes 4 bytes per scenario of device scratch
  * that the library owns, one per device: allocated on the first such call,
- * kept, and replaced only when more scenarios come.  If that allocation
+ * kept, and replaced only when more scenarios come (as the forest's, see
+ * tl_forest_predict_grid; without ever waiting on the host).  If that allocation
  * fails the scenarios run in their own order (same results), as they do
  * while the stream is being captured into a graph.  Calls share it: a call
  * on another stream than the previous one first waits (on the device) for
@@ -253,7 +254,10 @@ tl_status tl_forest_predict(const tl_forest* forest, const float* rows, int64_t 
  * bytes per (scenario, 64-iteration chunk) plus a radix sort's temporary
  * storage of device scratch, which the forest handle owns: up to four arrays,
  * allocated when a call first needs one, kept, and replaced only when a larger
- * call comes, so repeated calls of one size allocate nothing.  If that
+ * call comes, so repeated calls of one size allocate nothing.  Arrays are
+ * powers of two in size, and a replaced one is freed with the handle, so
+ * that a larger call does not wait on the host either (only where no memory is
+ * left does it free the replaced arrays first, which waits).  If that
  * allocation fails, or the stream is being captured into a graph, the call
  * runs without the ordering (same results; tl_forest_predict_grid_noalloc
  * keeps it under capture).  A call takes the array its stream used last, or an

@@ -22,7 +22,10 @@ struct RelaxedCapture {
 };
 
 // Up to SLOTS arrays on one device, each only replaced by a larger one when a
-// larger call comes.  `done` is recorded on the stream of the last call that
+// larger call comes.  Sizes are powers of two, so calls that grow slowly seldom
+// allocate, and a replaced array is kept until the pool is given back: freeing
+// it would wait for the device, and together the replaced ones are smaller than
+// the one in use.  `done` is recorded on the stream of the last call that
 // used the array.  A call takes the array its stream used last, else an idle
 // one, else another stream's: SLOTS streams can use the pool without waiting
 // for each other.  Every call that takes a used array waits (on the device) for
@@ -35,9 +38,9 @@ class ScratchPool {
 public:
     // Runs launch(ws, ws_bytes) with an array of at least `need` bytes, all of
     // its launches on st (a stream that is not being captured).  In the steady
-    // state nothing is allocated; a larger need than any before replaces the
-    // array (after the last call that used it is done).  When the allocation
-    // fails launch gets (nullptr, 0).
+    // state nothing is allocated, and nothing waits on the host.  Where no
+    // memory is left the replaced arrays are freed and exactly `need` bytes
+    // asked for; when that fails too launch gets (nullptr, 0).
     template <class Launch>
     hipError_t with(size_t need, hipStream_t st, Launch&& launch) {
         std::lock_guard<std::mutex> lock(mutex_);
@@ -71,22 +74,8 @@ public:
             }
         }
         if (need > w->bytes) {
-            if (w->ptr) {
-                if (w->used) {
-                    e = hipEventSynchronize(w->done);
-                    if (e != hipSuccess) return e;
-                }
-                (void)hipFree(w->ptr);
-                w->ptr = nullptr;
-                w->bytes = 0;
-                w->used = false;
-            }
-            if (hipMalloc(&w->ptr, need) == hipSuccess) {
-                w->bytes = need;
-            } else {
-                w->ptr = nullptr;
-                (void)hipGetLastError();   // clear the allocation error before the launches check theirs
-            }
+            e = grow(*w, need);
+            if (e != hipSuccess) return e;
         }
         if (!w->ptr) return launch((void*)nullptr, (size_t)0);
         if (w->used) {
@@ -109,21 +98,62 @@ public:
     // idle.
     void release() {
         for (Slot& w : slots_) {
-            if (w.ptr) (void)hipFree(w.ptr);
+            free_arrays(w);
             if (w.done) (void)hipEventDestroy(w.done);
             w = Slot();
         }
     }
 
 private:
+    static constexpr int kMinLog = 16, kMaxReplaced = 48;   // (sizes 2^16, 2^17, ...)
     struct Slot {
         void* ptr = nullptr;
         size_t bytes = 0;
+        void* replaced[kMaxReplaced] = {};
+        int n_replaced = 0;
         hipEvent_t done = nullptr;
         hipStream_t stream = nullptr;
         std::thread::id thread;   // of hipStreamPerThread
         bool used = false;
     };
+
+    // A larger array for w.  The replaced one's users may still run: the new
+    // one's are ordered behind them (w.used stays), so that w.done is the last of
+    // them all.
+    hipError_t grow(Slot& w, size_t need) {
+        int log = kMinLog;
+        while (log < 62 && ((size_t)1 << log) < need) ++log;
+        void* p = nullptr;
+        if (w.n_replaced < kMaxReplaced && hipMalloc(&p, (size_t)1 << log) == hipSuccess) {
+            if (w.ptr) w.replaced[w.n_replaced++] = w.ptr;
+            w.bytes = (size_t)1 << log;
+        } else {
+            (void)hipGetLastError();   // clear the allocation error before the launches check theirs
+            if (w.used) {
+                const hipError_t e = hipEventSynchronize(w.done);
+                if (e != hipSuccess) return e;
+                w.used = false;
+            }
+            free_arrays(w);
+            if (hipMalloc(&p, need) == hipSuccess) {
+                w.bytes = need;
+            } else {
+                p = nullptr;
+                (void)hipGetLastError();
+            }
+        }
+        w.ptr = p;
+        return hipSuccess;
+    }
+
+    static void free_arrays(Slot& w) {
+        if (w.ptr) (void)hipFree(w.ptr);
+        for (int i = 0; i < w.n_replaced; ++i) (void)hipFree(w.replaced[i]);
+        w.ptr = nullptr;
+        w.bytes = 0;
+        w.n_replaced = 0;
+    }
+
     std::mutex mutex_;
     Slot slots_[SLOTS];
     int next_ = 0;

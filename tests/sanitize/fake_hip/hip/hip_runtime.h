@@ -26,6 +26,9 @@ struct State {
     std::map<Stream, Clocks> at;               // per stream: what its next operation comes after
     Clocks done;                               // what the host knows to be finished
     std::map<void*, std::size_t> live;         // allocations
+    std::map<void*, std::pair<Stream, int>> last_use;   // told by the test
+    bool idle = false;                         // nothing runs on the device
+    bool freed_in_use = false;
     std::size_t free_bytes = (std::size_t)-1;  // left on the device
     int syncs = 0, allocs = 0;
     bool capturing = false;                    // another thread captures in the global mode
@@ -111,13 +114,18 @@ hipError_t hipMalloc(T** p, std::size_t n) {
     s.live[(void*)*p] = n;
     return hipSuccess;
 }
-// freeing waits for the whole device
+// freeing waits for the whole device, which scratch.h does not count on
 inline hipError_t hipFree(void* p) {
     if (hipError_t r = fake::unsafe_call()) return r;
     fake::State& s = fake::state();
     ++s.syncs;
     if (s.free_bytes != (std::size_t)-1) s.free_bytes += s.live.at(p);
     s.live.erase(p);
+    const auto u = s.last_use.find(p);
+    if (u != s.last_use.end()) {
+        s.freed_in_use |= !s.idle && s.done[u->second.first] < u->second.second;
+        s.last_use.erase(u);
+    }
     delete[] (char*)p;
     return hipSuccess;
 }

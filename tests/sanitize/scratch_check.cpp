@@ -28,7 +28,11 @@ struct Pool {
     std::map<void*, Use> last;   // of each array
     bool got = false;
     bool ordered = true;
-    ~Pool() { pool.release(); }
+    ~Pool() {
+        check(!fake::state().freed_in_use, "nothing in use is freed");
+        fake::state().idle = true;
+        pool.release();
+    }
     hipError_t call(hipStream_t st, size_t need) {
         return pool.with(need, st, [&](void* p, size_t bytes) {
             got = p != nullptr;
@@ -41,6 +45,7 @@ struct Pool {
                 ordered &= seen != now.end() && seen->second >= it->second.at.at(it->second.stream);
             }
             last[p] = Use{fake::stream(st), now};
+            fake::state().last_use[p] = {fake::stream(st), now.at(fake::stream(st))};
             return hipSuccess;
         });
     }
@@ -84,21 +89,55 @@ void while_another_thread_captures() {
 
 void without_memory() {
     fake::state() = fake::State();
-    fake::state().free_bytes = 5000;
+    fake::state().free_bytes = 500000;
     Pool p;
-    check(p.call(handle(0), 3000) == hipSuccess && p.got, "fits");
-    check(p.call(handle(0), 4500) == hipSuccess && p.got, "fits in place of the smaller one");
-    check(p.call(handle(0), 6000) == hipSuccess && !p.got, "runs without");
-    check(p.call(handle(0), 2000) == hipSuccess && p.got, "and with it again");
+    check(p.call(handle(0), 300000) == hipSuccess && p.got, "fits, its power of two does not");
+    check(p.call(handle(0), 450000) == hipSuccess && p.got, "fits in place of the smaller one");
+    check(p.call(handle(0), 600000) == hipSuccess && !p.got, "runs without");
+    check(p.call(handle(0), 200000) == hipSuccess && p.got, "and with it again");
     check(p.ordered, "ordered");
+}
+
+void many_streams_and_little_memory() {
+    unsigned x = 1;
+    for (int rep = 0; rep < 200; ++rep) {
+        fake::state() = fake::State();
+        fake::state().free_bytes = 1200000;
+        Pool p;
+        for (int i = 1; i <= 40; ++i) {
+            x = x * 1664525u + 1013904223u;
+            check(p.call(handle(x >> 8 & 7), 1000 + (x >> 12) % (20000 * i)) == hipSuccess, "on many streams");
+        }
+        check(p.ordered, "ordered");
+    }
+}
+
+// Slowly growing needs: nothing waits for the device, few allocations, and no
+// more memory than four times the largest need.
+void growing() {
+    fake::state() = fake::State();
+    {
+        Pool p;
+        size_t need = 100000;
+        for (int i = 0; i < 500; ++i, need += need / 50) p.call(handle(0), need);
+        size_t held = 0;
+        for (const auto& a : fake::state().live) held += a.second;
+        check(p.ordered && p.got, "ordered");
+        check(fake::state().syncs == 0, "growing waits for nothing");
+        check(fake::state().allocs <= 16, "and seldom allocates");
+        check(held <= 4 * need, "and keeps little");
+    }
+    check(fake::state().live.empty(), "everything is given back");
 }
 
 }  // namespace
 
 int main() {
+    growing();
     streams_and_threads();
     while_another_thread_captures();
     without_memory();
+    many_streams_and_little_memory();
     std::printf("%d checks\n", checks);
     return 0;
 }

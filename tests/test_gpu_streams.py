@@ -101,3 +101,28 @@ def test_projections_on_per_thread_streams(gpu, monkeypatch):
                                          deadline_at=o["deadline_at"].cpu().numpy().view(np.uint64),
                                          n_iters=o["n_iters"].cpu().numpy(),
                                          flags=o["flags"].cpu().numpy().view(np.uint32)), exp)
+
+
+def test_growing_calls_on_several_streams(gpu):
+    """Row counts that grow from call to call, so that scratch is replaced while
+    calls on other streams still use it."""
+    import torch
+    from paper_2408_05235_amd import api
+    rng = np.random.default_rng(51)
+    fd = random_forest(rng, 150, 7, 3)
+    forest = api.Forest.from_dict(fd)
+    x = np.stack([rng.integers(1000, 2001, 20000), rng.integers(0, 500, 20000), rng.integers(0, 60, 20000)],
+                 1).astype(np.float32)
+    exp = oracle.forest_predict(fd, x)
+    dx = torch.from_numpy(x).cuda()
+    streams = [torch.cuda.Stream() for _ in range(6)]
+    outs = [torch.full((20000,), -1.0, device="cuda") for _ in range(60)]
+    torch.cuda.synchronize()
+    counts = [int(50 * 1.105 ** i) for i in range(60)]
+    for i, n in enumerate(counts):
+        with torch.cuda.stream(streams[i % 6]):
+            forest.tl_forest_predict(dx[:n], outs[i][:n])
+    torch.cuda.synchronize()
+    for n, o in zip(counts, outs):
+        assert np.array_equal(o[:n].cpu().numpy(), exp[:n]), n
+    forest.close()
