@@ -92,7 +92,7 @@ __global__ __launch_bounds__(kColThreads) void forest_column_lds_kernel(RankDev 
     const uint32_t rec_bytes = staged_bytes<true>(D.depth);
     const uint32_t buf_bytes = stage_buffer_bytes(B.tb, rec_bytes);
     const int wave = threadIdx.x / kWave;
-    const int64_t item = __builtin_amdgcn_readfirstlane((int64_t)blockIdx.x * kColWaves + wave);
+    const int64_t item = __builtin_amdgcn_readfirstlane((P.first_block + blockIdx.x) * kColWaves + wave);
     StageSync* sync = (StageSync*)(smem + 2 * buf_bytes);
     if (threadIdx.x == 0) stage_sync_init(sync);
     if (B.n_blocks > 0) stage_block<true>(D, B, 0, lds_addr(smem), wave, kColWaves);
@@ -249,12 +249,12 @@ __global__ __launch_bounds__(kColThreads) void forest_column_reuse_kernel(RankDe
     const uint32_t rec_bytes = rank_record_bytes(D.depth);
     const uint32_t buf_bytes = stage_buffer_bytes(B.tb, rec_bytes);
     const int wave = threadIdx.x / kWave;
-    const int64_t item = __builtin_amdgcn_readfirstlane((int64_t)blockIdx.x * kColWaves + wave);
+    const int64_t item = __builtin_amdgcn_readfirstlane((P.first_block + blockIdx.x) * kColWaves + wave);
     const int32_t span = kWave * RPL;
     const int32_t n_cols = (P.H + span - 1) / span;
     const int64_t n_items = LIVE ? (int64_t)*P.n_live : P.S * n_cols;
     // a workgroup wholly past the live items has nothing to stage for
-    if (LIVE && (int64_t)blockIdx.x * kColWaves >= n_items) return;
+    if (LIVE && (P.first_block + blockIdx.x) * kColWaves >= n_items) return;
     bool valid = item < n_items;
     // the (scenario, column) pair: item itself, or its entry of the work order
     const int64_t code = !valid ? 0 : P.order ? (int64_t)P.order[item] : item;
@@ -369,13 +369,15 @@ hipError_t launch_column_lds(const ForestDev& f, const ColumnParams& c, hipStrea
     size_t lds = 0;
     const int32_t tb =
         column_trees_per_block<true>(f, items > (int64_t)kColWaves * cus ? kColLdsHalf : kColLdsBudget, &lds);
-    if (!grid_fits((items + kColWaves - 1) / kColWaves)) return hipErrorInvalidConfiguration;
     const auto kern = forest_column_lds_kernel<NF, RPL, ROWS>;
     e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((items + kColWaves - 1) / kColWaves)), dim3(kColThreads), lds, stream,
-                       rank_dev(f), tree_blocks(f.n_trees, f.group_trees, tb), c);
-    return hipGetLastError();
+    return launch_parts((items + kColWaves - 1) / kColWaves, kColThreads, [&](dim3 grid, int64_t first) {
+        ColumnParams q = c;
+        q.first_block = first;
+        hipLaunchKernelGGL(kern, grid, dim3(kColThreads), lds, stream, rank_dev(f),
+                           tree_blocks(f.n_trees, f.group_trees, tb), q);
+    });
 }
 
 // Rows per lane of the leaf-reuse kernel for these rows: 16 (else 8) where
@@ -402,14 +404,16 @@ template <int RPL>
 hipError_t launch_column_reuse(const ForestDev& f, const ColumnParams& c, int32_t tb, size_t lds,
                                hipStream_t stream) {
     const int64_t items = c.S * ((c.H + kWave * RPL - 1) / (kWave * RPL));
-    if (!grid_fits((items + kColWaves - 1) / kColWaves)) return hipErrorInvalidConfiguration;
     const auto kern =
         c.n_live ? forest_column_reuse_kernel<RPL, true> : forest_column_reuse_kernel<RPL, false>;
     const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((items + kColWaves - 1) / kColWaves)), dim3(kColThreads), lds, stream,
-                       rank_dev(f), tree_blocks(f.n_trees, f.group_trees, tb), c);
-    return hipGetLastError();
+    return launch_parts((items + kColWaves - 1) / kColWaves, kColThreads, [&](dim3 grid, int64_t first) {
+        ColumnParams q = c;
+        q.first_block = first;
+        hipLaunchKernelGGL(kern, grid, dim3(kColThreads), lds, stream, rank_dev(f),
+                           tree_blocks(f.n_trees, f.group_trees, tb), q);
+    });
 }
 
 template <int NF>

@@ -303,7 +303,7 @@ __global__ __launch_bounds__(kLdsThreads, kLdsWavesPerSimd) void forest_grid_lds
 
     const int wave = threadIdx.x / kWave;
     const int lane = lane_id();
-    const int64_t item = __builtin_amdgcn_readfirstlane((int64_t)blockIdx.x * kLdsWaves + wave);
+    const int64_t item = __builtin_amdgcn_readfirstlane((P.first_block + blockIdx.x) * kLdsWaves + wave);
     GridItem g = grid_item<kRows, kOrderJ / kRows>(P, item);
     const int32_t F = P.F, H = P.H;
     const int part = lane / kLanes;
@@ -530,10 +530,12 @@ hipError_t launch_grid_lds(const ForestDev& f, const GridParams& g, int32_t tb, 
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     const int64_t blocks = grid_workgroups(g, J);
-    if (!grid_fits(blocks)) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kLdsThreads), lds, stream, rank_dev(f),
-                       tree_blocks(f.n_trees, f.group_trees, tb), g);
-    return hipGetLastError();
+    return launch_parts(blocks, kLdsThreads, [&](dim3 grid, int64_t first) {
+        GridParams q = g;
+        q.first_block = first;
+        hipLaunchKernelGGL(kern, grid, dim3(kLdsThreads), lds, stream, rank_dev(f),
+                           tree_blocks(f.n_trees, f.group_trees, tb), q);
+    });
 }
 
 // Rows per wavefront: 8 or 16 where 32 would leave CUs without their two
@@ -584,10 +586,10 @@ constexpr int kCostWaves = 4;
 
 __global__ __launch_bounds__(kCostWaves* kWave) void pair_cost_kernel(RankDev D, const int32_t* __restrict__ kv,
                                                                       const int32_t* __restrict__ batch, int64_t n,
-                                                                      int32_t H, int32_t J,
+                                                                      int32_t H, int32_t J, int64_t first_block,
                                                                       uint32_t* __restrict__ cost,
                                                                       uint32_t* __restrict__ code) {
-    const int64_t pair = (int64_t)blockIdx.x * kCostWaves + threadIdx.x / kWave;
+    const int64_t pair = (first_block + blockIdx.x) * kCostWaves + threadIdx.x / kWave;
     if (pair >= n) return;
     const int32_t n_chunks = (H + J - 1) / J;
     const int64_t s = pair / n_chunks;
@@ -632,9 +634,10 @@ hipError_t pair_order(const ForestDev& f, const PairOrderPlan& p, const int32_t*
     uint32_t* code = (uint32_t*)(base + p.arr);
     uint32_t* cost_sorted = (uint32_t*)(base + 2 * p.arr);
     uint32_t* sorted = (uint32_t*)(base + 3 * p.arr);
-    hipLaunchKernelGGL(pair_cost_kernel, dim3((unsigned)((p.n + kCostWaves - 1) / kCostWaves)),
-                       dim3(kCostWaves * kWave), 0, stream, rank_dev(f), kv, batch, p.n, H, J, cost, code);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_parts((p.n + kCostWaves - 1) / kCostWaves, kCostWaves * kWave, [&](dim3 grid, int64_t first) {
+        hipLaunchKernelGGL(pair_cost_kernel, grid, dim3(kCostWaves * kWave), 0, stream, rank_dev(f), kv, batch, p.n, H,
+                           J, first, cost, code);
+    });
     if (e != hipSuccess) return e;
     size_t temp = p.temp;
     e = hipcub::DeviceRadixSort::SortPairsDescending(base + 4 * p.arr, temp, cost, cost_sorted, code, sorted, (int)p.n,

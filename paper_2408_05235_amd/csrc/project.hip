@@ -382,7 +382,8 @@ __global__ __launch_bounds__(W* kWave) void project_kernel(ProjectParams P) {
     const DivU32 divN{(uint32_t)N, P.div_m, P.div_l};
     const int lane = lane_id();
     const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
-    const int64_t s = P.order_ws ? (int64_t)((const int32_t*)P.order_ws + kOrderBuckets)[blockIdx.x] : blockIdx.x;
+    const int64_t block = P.first_block + blockIdx.x;
+    const int64_t s = P.order_ws ? (int64_t)((const int32_t*)P.order_ws + kOrderBuckets)[block] : block;
     int32_t* outB = P.batch + s * H;
     int32_t* KV = lds;                      // events, then KV values
     int32_t* BI = BD_LDS ? lds + H : outB;  // batch difference array
@@ -1100,8 +1101,11 @@ hipError_t launch_project(const ProjectParams& p, hipStream_t stream) {
         const hipError_t e0 = hipGetLastError();
         if (e0 != hipSuccess) return e0;
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)p.n_scenarios), dim3(w * kWave), lds, stream, p);
-    hipError_t e = hipGetLastError();
+    const hipError_t e = launch_parts(p.n_scenarios, w * kWave, [&](dim3 grid, int64_t first) {
+        ProjectParams q = p;
+        q.first_block = first;
+        hipLaunchKernelGGL(kern, grid, dim3(w * kWave), lds, stream, q);
+    });
     if (e != hipSuccess || !p.rows) return e;
     const int64_t blocks = p.n_scenarios * ((p.H + kRowsThreads - 1) / kRowsThreads);
     if (!grid_fits(blocks)) return hipErrorInvalidConfiguration;

@@ -72,7 +72,7 @@ __device__ __forceinline__ bool feasible_wave(const float* ips, const uint64_t* 
 // be the minimum).
 __global__ __launch_bounds__(256) void select_kernel(SelectParams P) {
     __shared__ uint32_t round_ok;
-    const int64_t s = blockIdx.x;
+    const int64_t s = P.first_block + blockIdx.x;
     const int wave = threadIdx.x / kWave;
     const int lane = lane_id();
     const int32_t F = P.F, H = P.H;
@@ -191,7 +191,7 @@ __device__ __forceinline__ bool within_tbt(uint64_t t_r_n, uint64_t slo, int32_t
 // inside the horizon) is checked apart from the scheduled requests'
 // deadlines in deadline_at.
 __global__ __launch_bounds__(kTimeThreads) void admit_kernel(AdmitParams P) {
-    const int64_t s = blockIdx.x;
+    const int64_t s = P.first_block + blockIdx.x;
     const int32_t H = P.H;
     const uint32_t fl = P.proj_flags[s];
     uint32_t dec;
@@ -242,7 +242,7 @@ __global__ __launch_bounds__(kTimeThreads) void search_init_kernel(SearchParams 
 }
 
 __global__ __launch_bounds__(kTimeThreads) void search_kernel(SearchParams P, int mode) {
-    const int64_t s = blockIdx.x;
+    const int64_t s = P.first_block + blockIdx.x;
     int32_t* lo = P.work;
     int32_t* hi = P.work + P.S;
     int32_t* probe = P.work + 2 * P.S;
@@ -288,9 +288,11 @@ __global__ __launch_bounds__(256) void search_final_probe_kernel(SearchParams P)
 }  // namespace
 
 hipError_t launch_admit(const AdmitParams& p, hipStream_t stream) {
-    if (p.S == 0) return hipSuccess;
-    hipLaunchKernelGGL(admit_kernel, dim3((unsigned)p.S), dim3(kTimeThreads), 0, stream, p);
-    return hipGetLastError();
+    return launch_parts(p.S, kTimeThreads, [&](dim3 grid, int64_t first) {
+        AdmitParams q = p;
+        q.first_block = first;
+        hipLaunchKernelGGL(admit_kernel, grid, dim3(kTimeThreads), 0, stream, q);
+    });
 }
 
 hipError_t launch_search_step(const SearchParams& p, int mode, hipStream_t stream) {
@@ -301,14 +303,21 @@ hipError_t launch_search_step(const SearchParams& p, int mode, hipStream_t strea
         hipLaunchKernelGGL(search_init_kernel, dim3((unsigned)((p.S + kTimeThreads - 1) / kTimeThreads)),
                            dim3(kTimeThreads), 0, stream, p);
     } else {
-        hipLaunchKernelGGL(search_kernel, dim3((unsigned)p.S), dim3(kTimeThreads), 0, stream, p, mode);
+        return launch_parts(p.S, kTimeThreads, [&](dim3 grid, int64_t first) {
+            SearchParams q = p;
+            q.first_block = first;
+            hipLaunchKernelGGL(search_kernel, grid, dim3(kTimeThreads), 0, stream, q, mode);
+        });
     }
     return hipGetLastError();
 }
 
 hipError_t launch_select(const SelectParams& p, hipStream_t stream) {
-    hipLaunchKernelGGL(select_kernel, dim3((unsigned)p.S), dim3(256), 0, stream, p);
-    return hipGetLastError();
+    return launch_parts(p.S, kWavesPerBlock * kWave, [&](dim3 grid, int64_t first) {
+        SelectParams q = p;
+        q.first_block = first;
+        hipLaunchKernelGGL(select_kernel, grid, dim3(kWavesPerBlock * kWave), 0, stream, q);
+    });
 }
 
 }  // namespace tl

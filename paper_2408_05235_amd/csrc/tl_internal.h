@@ -41,6 +41,7 @@ struct ProjectParams {
     // nullable: workspace of project_order_bytes() bytes; with it the
     // scenarios are projected heaviest first (same results, shorter tail)
     void* order_ws;
+    int64_t first_block;            // of the launch (launch_parts), as below
 };
 
 // The model at one frequency per scenario on the projection grid:
@@ -68,6 +69,7 @@ struct ColumnParams {
     // i < n_rows; the fields above except `out` are not used
     const float* rows;
     int64_t n_rows;
+    int64_t first_block;
 };
 
 // Admission decision from the IPS at the maximum frequency.
@@ -82,6 +84,7 @@ struct AdmitParams {
     const int32_t* cand_len;
     const uint64_t* cand_deadline;  // nullable
     uint32_t* decision;
+    int64_t first_block;
 };
 
 // State and inputs of the binary search over frequencies: work holds lo[S],
@@ -99,6 +102,7 @@ struct SearchParams {
     int32_t* work;                  // [3][S]
     int32_t* freq_idx;
     uint32_t* status;
+    int64_t first_block;
 };
 
 // Scoreboard lengths from predicted lengths (Sec. 4.6).
@@ -125,6 +129,7 @@ struct SelectParams {
     const uint32_t* proj_flags;     // nullable
     int32_t* freq_idx;
     uint32_t* status;
+    int64_t first_block;
 };
 
 // Device copy of a tree ensemble.  Arrays are padded by at least 64 bytes.
@@ -167,6 +172,7 @@ struct GridParams {
     // optional work order: entry i is the (scenario, chunk) pair s * n_chunks
     // + chunk that the i-th item (of each frequency group) evaluates
     const uint32_t* order;
+    int64_t first_block;
 };
 
 // The model compiled to its input lattice (engine sizes x batch 0..batch_max
@@ -224,6 +230,23 @@ hipError_t launch_lattice_column(const ForestDev& f, const LatticeDev& L, const 
                                  const int32_t* fidx, int32_t f_all, hipStream_t stream);
 
 // A launch of `blocks` workgroups fits the grid (at most 2^31 - 1 in x).
+// A launch has fewer than 2^32 threads.  launch_parts calls launch(grid, first)
+// for up to four consecutive parts of `blocks` workgroups of `threads` threads
+// each; a kernel's workgroup number is blockIdx.x + first.  (Four: 2^26 - 4
+// scenarios of 256 threads each, as many as one wavefront each takes in one
+// launch; more are refused, as are counts that no memory could back.)
+constexpr int kMaxParts = 4;
+template <class Launch>
+hipError_t launch_parts(int64_t blocks, int threads, Launch&& launch) {
+    const int64_t most = 0xffffffffll / threads;
+    if (blocks > kMaxParts * most) return hipErrorInvalidConfiguration;
+    for (int64_t first = 0; first < blocks; first += most) {
+        launch(dim3((unsigned)(blocks - first < most ? blocks - first : most)), first);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 inline bool grid_fits(int64_t blocks) { return blocks >= 0 && blocks <= 0x7fffffffll; }
 
 hipError_t launch_project(const ProjectParams& p, hipStream_t stream);
