@@ -373,8 +373,13 @@ __global__ __launch_bounds__(256) void order_place_kernel(const int64_t* off, in
 // cap it is only added to and finally prefix-summed, so it accumulates with
 // atomics in the scenario's own batch output row instead: half the LDS, twice
 // the scenario wavefronts per CU.
-template <bool BD_LDS, bool POW2, int W>
+// CAP: with a batch cap.  A constant, so that neither kind of loop carries the
+// other's state (both in one kernel: 102 scalar registers spilled behind a cap,
+// each spill and reload an instruction in a chain bound by its latency; now
+// none).
+template <bool CAP, bool BD_LDS, bool POW2, int W>
 __global__ __launch_bounds__(W* kWave) void project_kernel(ProjectParams P) {
+    static_assert(BD_LDS || !CAP, "a batch cap reads running sums of the batch differences");
     extern __shared__ int32_t lds[];
     __shared__ ProjShared sh;
     const int32_t H = P.H;
@@ -534,9 +539,8 @@ __global__ __launch_bounds__(W* kWave) void project_kernel(ProjectParams P) {
     int32_t first_over = H;   // (of the whole queue's sum, below)
     strided_scan<W, POW2>(KV, H, N);
     const int32_t last_over = __builtin_amdgcn_readfirstlane(prefix_scan<W>(sh, KV, H, cap, 0, &first_over));
-    const bool has_bcap = BD_LDS && P.batch_cap != nullptr;   // (the host takes BD_LDS with a cap)
-    const int32_t bcap = has_bcap ? P.batch_cap[s] : 0;
-    if (last_over >= 0 || (has_bcap && __builtin_amdgcn_readfirstlane(BI[0]) > bcap)) fl |= TL_FLAG_OVERCOMMIT;
+    const int32_t bcap = CAP ? P.batch_cap[s] : 0;
+    if (last_over >= 0 || (CAP && __builtin_amdgcn_readfirstlane(BI[0]) > bcap)) fl |= TL_FLAG_OVERCOMMIT;
 
     // FIFO admission of queued requests.  Every wavefront runs the loop: the
     // values it carries (iteration j, batch size, the head's fields, check
@@ -549,7 +553,7 @@ __global__ __launch_bounds__(W* kWave) void project_kernel(ProjectParams P) {
         curves_sync<W>();
         int32_t j = 0;
         int32_t run = 0;    // batch size at j (prefix of BD; kept only under a batch cap)
-        if (has_bcap) run = __builtin_amdgcn_readfirstlane(BD[0]);
+        if (CAP) run = __builtin_amdgcn_readfirstlane(BD[0]);
         // (no batch cap) how the next requests are tried, see below
         bool at_targets = true;
         bool alone = false;
@@ -564,7 +568,7 @@ __global__ __launch_bounds__(W* kWave) void project_kernel(ProjectParams P) {
         uint64_t q_dl = kNoDeadline;
         uint64_t mask = 0;
         for (;;) {
-            if (!has_bcap && mask == 0 && streak >= streak_need && hi - (cb + kWave) >= 2 * kWave) {
+            if (!CAP && mask == 0 && streak >= streak_need && hi - (cb + kWave) >= 2 * kWave) {
                 // All remaining requests at once, each at its FIFO target (the
                 // running maximum of the arrivals, from max(j, last_over +
                 // 1)): O(1) events a request, one scan, one check.  When the
@@ -708,7 +712,7 @@ __global__ __launch_bounds__(W* kWave) void project_kernel(ProjectParams P) {
                     q_dl = P.deadline ? P.deadline[i] : kNoDeadline;
                 }
                 mask = __ballot(q);
-                if (!has_bcap && mask) {
+                if (!CAP && mask) {
                     q_max = wave_incl_max(q ? q_arr : -1);
                     q_c0 = q ? (int32_t)ceil_div_u32((uint32_t)q_c, divN) : 0;
                     q_sum = wave_incl_scan(q_c0);
@@ -716,7 +720,7 @@ __global__ __launch_bounds__(W* kWave) void project_kernel(ProjectParams P) {
             }
             if (mask == 0) break;
 
-            if (!has_bcap && at_targets) {
+            if (!CAP && at_targets) {
                 // The rest of this chunk of the queue, each at its FIFO
                 // target, as above; their contributions are added to the KV
                 // curve iteration by iteration and taken out again when they
@@ -759,7 +763,7 @@ __global__ __launch_bounds__(W* kWave) void project_kernel(ProjectParams P) {
                 continue;
             }
 
-            if (!has_bcap && !alone) {
+            if (!CAP && !alone) {
                 // The capacity binds: the head and the requests behind it that
                 // have arrived by its start j, as many as the KV of iteration
                 // j itself leaves room for.  When their sum fits everywhere,
@@ -839,11 +843,11 @@ __global__ __launch_bounds__(W* kWave) void project_kernel(ProjectParams P) {
                 (uint32_t)__builtin_amdgcn_readlane((int32_t)(uint32_t)q_dl, hl);
             const int32_t target = max(max(h_arr, j), last_over + 1);
             if (h_arr >= H || target >= H) break;
-            if (has_bcap && target > j) run += sum_range(BD, j, target);
+            if (CAP && target > j) run += sum_range(BD, j, target);
             j = target;
             bool admitted = false;
             for (;;) {
-                bool ok = !has_bcap || run < bcap;
+                bool ok = !CAP || run < bcap;
                 int32_t t_bad = -1;
                 if (ok) {
                     // 4 x 64 iterations per round (their LDS reads in flight
@@ -867,7 +871,7 @@ __global__ __launch_bounds__(W* kWave) void project_kernel(ProjectParams P) {
                     ok = t_bad < 0;
                 }
                 if (ok) { admitted = true; break; }
-                if (has_bcap && run >= bcap) {
+                if (CAP && run >= bcap) {
                     // The batch is full: the next start to try is the first
                     // later iteration with a free slot, found 64 iterations
                     // at a time from the batch differences (what stepping
@@ -905,7 +909,7 @@ __global__ __launch_bounds__(W* kWave) void project_kernel(ProjectParams P) {
                     nj = (int32_t)max((int64_t)nj, first);
                 }
                 if (nj >= H) break;
-                if (has_bcap) run += sum_range(BD, j, nj);
+                if (CAP) run += sum_range(BD, j, nj);
                 j = nj;
             }
             if (!admitted) break;
@@ -1075,17 +1079,24 @@ hipError_t launch_project(const ProjectParams& p, hipStream_t stream) {
     // does: every wavefront runs the loop.  Measured (us at 1 / 4): 1024 boards
     // in flight 28 / 14, one board x 2048 23 / 10, boards under arrivals 64:
     // 4387 / 3467, 2048: 5153 / 4225, 4096: 5316 / 6800.
-    // Behind a batch cap one does too: its requests are admitted one at a time,
-    // a barrier each between four (us at 4, one-wavefront kernel before: 1487
-    // boards x 2212 758, 452; 2152 x 2867 1150, 822; 268 x 302 130, 91).
-    const bool one = p.batch_cap != nullptr || (!bd_lds && p.n_scenarios > 2048);
+    // Behind a batch cap requests are admitted one at a time, a barrier each
+    // between four wavefronts: four only while every board has a CU to itself and
+    // its horizon is long enough for them to gain on the additions (us at 1 /
+    // 4, 256 boards x 4096 iterations 319 / 262, where the KV capacity binds 536 /
+    // 525; 2 x 666 96 / 89, 144 / 140; 1 x 512 61 / 59, 81 / 81; 268 x 302 92 /
+    // 97, 119 / 132; 1024 x 4096 337 / 348, 547 / 758; 4096 x 1024 220 / 571).
+    const bool cap = p.batch_cap != nullptr;
+    const bool one = cap ? p.n_scenarios > 256 || p.H < 512 : !bd_lds && p.n_scenarios > 2048;
     const int w = one ? 1 : kProjWaves;
-    void (*const kerns[2][2][2])(ProjectParams) = {
-        {{project_kernel<false, false, 1>, project_kernel<false, false, kProjWaves>},
-         {project_kernel<false, true, 1>, project_kernel<false, true, kProjWaves>}},
-        {{project_kernel<true, false, 1>, project_kernel<true, false, kProjWaves>},
-         {project_kernel<true, true, 1>, project_kernel<true, true, kProjWaves>}}};
-    void (*const kern)(ProjectParams) = kerns[bd_lds][pow2][!one];
+    void (*const capped[2][2])(ProjectParams) = {
+        {project_kernel<true, true, false, 1>, project_kernel<true, true, false, kProjWaves>},
+        {project_kernel<true, true, true, 1>, project_kernel<true, true, true, kProjWaves>}};
+    void (*const uncapped[2][2][2])(ProjectParams) = {
+        {{project_kernel<false, false, false, 1>, project_kernel<false, false, false, kProjWaves>},
+         {project_kernel<false, false, true, 1>, project_kernel<false, false, true, kProjWaves>}},
+        {{project_kernel<false, true, false, 1>, project_kernel<false, true, false, kProjWaves>},
+         {project_kernel<false, true, true, 1>, project_kernel<false, true, true, kProjWaves>}}};
+    void (*const kern)(ProjectParams) = cap ? capped[pow2][!one] : uncapped[bd_lds][pow2][!one];
     if (lds + sizeof(ProjShared) > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;

@@ -45,6 +45,17 @@ def test_queue_paths(S, H, N, R, Q, cap_kv, cap_batch, unsorted):
     assert_projection_equal(gpu_project(inp), oracle.project(inp))
 
 
+@pytest.mark.parametrize("S,H,N,R,Q,cap_kv,cap_batch", [
+    (2, 600, 16, 12, 300, 5000, 20), (256, 512, 16, 30, 90, 1400, 32), (257, 513, 64, 30, 90, 400, 32),
+    (3, 1100, 24, 40, 260, 1 << 20, 40), (2, 511, 100, 9, 130, 300, 9), (2, 800, 1, 16, 140, 12000, 24),
+])
+def test_batch_cap_paths(S, H, N, R, Q, cap_kv, cap_batch):
+    """Behind a batch cap, on each side of the rule for one or four wavefronts a
+    board, the batch full, the capacity binding, or both."""
+    inp = _boards(H + Q, S, H, N, R, Q, cap_kv, cap_batch, S % 2 == 1)
+    assert_projection_equal(gpu_project(inp), oracle.project(inp))
+
+
 def test_many_long_queues():
     inp = _boards(5, 2100, 90, 16, 4, 1030, 3000, None, False)
     assert_projection_equal(gpu_project(inp), oracle.project(inp))
