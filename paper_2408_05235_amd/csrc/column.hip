@@ -310,7 +310,7 @@ __global__ __launch_bounds__(256) void forest_column_global_kernel(const uint2* 
                                                                   const float* __restrict__ leaves,
                                                                   int32_t n_trees, int32_t depth, float base,
                                                                   ColumnParams P) {
-    const int64_t item = (int64_t)blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
+    const int64_t item = (P.first_block + blockIdx.x) * (256 / kWave) + threadIdx.x / kWave;
     const ColumnItem<1> c = column_item<1>(P, item);
     if (!c.row[0]) return;
     float x[4];
@@ -438,10 +438,12 @@ hipError_t launch_column(const ForestDev& f, const ColumnParams& c, hipStream_t 
         return launch_column_lds<NF, 1>(f, c, stream);
     }
     const int64_t items = c.S * ((c.H + kWave - 1) / kWave);
-    if (!grid_fits((items + 3) / 4)) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(forest_column_global_kernel<NF>, dim3((unsigned)((items + 3) / 4)), dim3(256), 0, stream,
-                       f.nodes, f.leaves, f.n_trees, f.depth, f.base_score, c);
-    return hipGetLastError();
+    return launch_parts((items + 3) / 4, 256, [&](dim3 grid, int64_t first) {
+        ColumnParams q = c;
+        q.first_block = first;
+        hipLaunchKernelGGL(forest_column_global_kernel<NF>, grid, dim3(256), 0, stream, f.nodes, f.leaves, f.n_trees,
+                           f.depth, f.base_score, q);
+    });
 }
 
 }  // namespace
@@ -539,7 +541,7 @@ hipError_t launch_forest_column_live(const ForestDev& f, const ColumnParams& c, 
     hipLaunchKernelGGL(column_live_clear_kernel, dim3(1), dim3(1), 0, stream, n_live);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (!grid_fits((items + 255) / 256)) return hipErrorInvalidConfiguration;
+    if (!grid_fits((items + 255) / 256, 256)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(column_live_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, stream, c.order,
                        c.fidx, items, n_cols, live, n_live);
     e = hipGetLastError();

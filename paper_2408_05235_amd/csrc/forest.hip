@@ -432,7 +432,7 @@ __global__ __launch_bounds__(256) void forest_grid_global_kernel(const uint2* __
     __shared__ float2 kvb[kGlobalWaves][J];
     const int wave = threadIdx.x / kWave;
     const int lane = lane_id();
-    const int64_t item = __builtin_amdgcn_readfirstlane((int64_t)blockIdx.x * kGlobalWaves + wave);
+    const int64_t item = __builtin_amdgcn_readfirstlane((P.first_block + blockIdx.x) * kGlobalWaves + wave);
     const GridItem g = grid_item<J, 1>(P, item);
     const int32_t F = P.F, H = P.H;
     const bool active = g.valid && g.f < F;
@@ -492,7 +492,7 @@ hipError_t launch_nf(const ForestDev& f, const float* rows, int64_t n_rows, floa
     constexpr int TPB = 256;
     const int64_t threads = (n_rows + RPT - 1) / RPT;
     const int64_t blocks = (threads + TPB - 1) / TPB;
-    if (!grid_fits(blocks)) return hipErrorInvalidConfiguration;
+    if (!grid_fits(blocks, TPB)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((forest_rows_kernel<NF, RPT>), dim3((unsigned)blocks), dim3(TPB), 0, stream,
                        f.nodes, f.leaves, f.n_trees, f.depth, f.base_score, rows, n_rows, out);
     return hipGetLastError();
@@ -564,10 +564,12 @@ hipError_t launch_grid_global(const ForestDev& f, const GridParams& g, hipStream
     const int64_t n_fg = (g.F + kWave - 1) / kWave;
     const int64_t items = g.S * n_fg * n_chunks;
     const int64_t blocks = (items + kGlobalWaves - 1) / kGlobalWaves;
-    if (!grid_fits(blocks)) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((forest_grid_global_kernel<NF, kGlobalJ>), dim3((unsigned)blocks), dim3(kGlobalWaves * kWave),
-                       0, stream, f.nodes, f.leaves, f.kvb_box, f.n_trees, f.depth, f.base_score, g);
-    return hipGetLastError();
+    return launch_parts(blocks, kGlobalWaves * kWave, [&](dim3 grid, int64_t first) {
+        GridParams q = g;
+        q.first_block = first;
+        hipLaunchKernelGGL((forest_grid_global_kernel<NF, kGlobalJ>), grid, dim3(kGlobalWaves * kWave), 0, stream,
+                           f.nodes, f.leaves, f.kvb_box, f.n_trees, f.depth, f.base_score, q);
+    });
 }
 
 }  // namespace

@@ -112,8 +112,9 @@ __device__ __forceinline__ void put_values(const float* t, float* out, int32_t H
 // consecutive addresses for each frequency).
 __global__ __launch_bounds__(kGatherThreads) void lattice_gather_kernel(ForestDev f, LatticeDev L, GatherParams P,
                                                                          int32_t n_jb) {
-    const int64_t s = blockIdx.x / (uint32_t)n_jb;
-    const int32_t j = (int32_t)(blockIdx.x % (uint32_t)n_jb) * kGatherThreads + threadIdx.x;
+    const uint32_t block = (uint32_t)P.first_block + blockIdx.x;   // (fewer than 2^26 of 256 threads)
+    const int64_t s = block / (uint32_t)n_jb;
+    const int32_t j = (int32_t)(block % (uint32_t)n_jb) * kGatherThreads + threadIdx.x;
     if (j >= P.H) return;
     const int32_t kv = P.kv[s * P.H + j];
     const int32_t b = P.batch[s * P.H + j];
@@ -157,8 +158,9 @@ __global__ __launch_bounds__(kGatherThreads) void lattice_gather_kernel(ForestDe
 __global__ __launch_bounds__(kGatherThreads) void lattice_column_kernel(ForestDev f, LatticeDev L, GatherParams P,
                                                                          const int32_t* fidx, int32_t f_all,
                                                                          int32_t n_jb) {
-    const int64_t s = blockIdx.x / (uint32_t)n_jb;
-    const int32_t j = (int32_t)(blockIdx.x % (uint32_t)n_jb) * kGatherThreads + threadIdx.x;
+    const uint32_t block = (uint32_t)P.first_block + blockIdx.x;   // (fewer than 2^26 of 256 threads)
+    const int64_t s = block / (uint32_t)n_jb;
+    const int32_t j = (int32_t)(block % (uint32_t)n_jb) * kGatherThreads + threadIdx.x;
     if (j >= P.H) return;
     const int32_t fi = fidx ? fidx[s] : f_all;
     if (fi < 0 || fi >= L.F) return;
@@ -188,16 +190,17 @@ hipError_t launch_lattice_column(const ForestDev& f, const LatticeDev& L, const 
     if (p.S == 0) return hipSuccess;
     const int32_t n_jb = (p.H + kGatherThreads - 1) / kGatherThreads;
     const int64_t blocks = p.S * n_jb;
-    if (!grid_fits(blocks)) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(lattice_column_kernel, dim3((unsigned)blocks), dim3(kGatherThreads), 0, stream, f, L, p, fidx,
-                       f_all, n_jb);
-    return hipGetLastError();
+    return launch_parts(blocks, kGatherThreads, [&](dim3 grid, int64_t first) {
+        GatherParams q = p;
+        q.first_block = first;
+        hipLaunchKernelGGL(lattice_column_kernel, grid, dim3(kGatherThreads), 0, stream, f, L, q, fidx, f_all, n_jb);
+    });
 }
 
 hipError_t launch_lattice_inputs(const LatticeDev& L, int64_t s0, int64_t count, int32_t* kv, int32_t* batch,
                                  float* engine, hipStream_t stream) {
     const int64_t n = count * kLatticeChunk;
-    if (!grid_fits((n + 255) / 256)) return hipErrorInvalidConfiguration;
+    if (!grid_fits((n + 255) / 256, 256)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(lattice_inputs_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, L, s0, count,
                        kv, batch, engine);
     return hipGetLastError();
@@ -206,7 +209,7 @@ hipError_t launch_lattice_inputs(const LatticeDev& L, int64_t s0, int64_t count,
 hipError_t launch_lattice_transpose(const float* src, float* table, int64_t s0, int64_t count, int32_t F,
                                     hipStream_t stream) {
     const int64_t blocks = count * ((F + kTile - 1) / kTile) * (kLatticeChunk / kTile);
-    if (!grid_fits(blocks)) return hipErrorInvalidConfiguration;
+    if (!grid_fits(blocks, 256)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(lattice_transpose_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, src, table, s0, F);
     return hipGetLastError();
 }
@@ -215,9 +218,11 @@ hipError_t launch_lattice_gather(const ForestDev& f, const LatticeDev& L, const 
     if (p.S == 0) return hipSuccess;
     const int32_t n_jb = (p.H + kGatherThreads - 1) / kGatherThreads;
     const int64_t blocks = p.S * n_jb;
-    if (!grid_fits(blocks)) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(lattice_gather_kernel, dim3((unsigned)blocks), dim3(kGatherThreads), 0, stream, f, L, p, n_jb);
-    return hipGetLastError();
+    return launch_parts(blocks, kGatherThreads, [&](dim3 grid, int64_t first) {
+        GatherParams q = p;
+        q.first_block = first;
+        hipLaunchKernelGGL(lattice_gather_kernel, grid, dim3(kGatherThreads), 0, stream, f, L, q, n_jb);
+    });
 }
 
 }  // namespace tl

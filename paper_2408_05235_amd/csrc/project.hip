@@ -998,8 +998,9 @@ template <int NF>
 __global__ __launch_bounds__(kRowsThreads) void expand_rows_kernel(ProjectParams P) {
     const int32_t H = P.H;
     const int32_t n_jb = (H + kRowsThreads - 1) / kRowsThreads;
-    const int64_t s = blockIdx.x / (uint32_t)n_jb;
-    const int32_t t = (int32_t)(blockIdx.x % (uint32_t)n_jb) * kRowsThreads + threadIdx.x;
+    const uint32_t block = (uint32_t)P.first_block + blockIdx.x;   // (fewer than 2^26 of 256 threads)
+    const int64_t s = block / (uint32_t)n_jb;
+    const int32_t t = (int32_t)(block % (uint32_t)n_jb) * kRowsThreads + threadIdx.x;
     if (t >= H) return;
     const float kf = (float)P.kv[s * H + t], bf = (float)P.batch[s * H + t];
     const float eng = NF == 4 ? P.engine[s] : 0.0f;
@@ -1021,7 +1022,7 @@ __global__ __launch_bounds__(kRowsThreads) void expand_rows_kernel(ProjectParams
 constexpr int kAdjustWaves = 4;
 
 __global__ __launch_bounds__(kAdjustWaves * kWave) void adjust_kernel(AdjustParams P) {
-    const int64_t s = (int64_t)blockIdx.x * kAdjustWaves + threadIdx.x / kWave;
+    const int64_t s = (P.first_block + blockIdx.x) * kAdjustWaves + threadIdx.x / kWave;
     if (s >= P.S) return;
     const int64_t lo = P.off[s], hi = P.off[s + 1];
     if (lo < 0 || hi < lo || hi > P.n_requests) return;
@@ -1049,10 +1050,11 @@ __global__ __launch_bounds__(kAdjustWaves * kWave) void adjust_kernel(AdjustPara
 }  // namespace
 
 hipError_t launch_adjust(const AdjustParams& p, hipStream_t stream) {
-    if (p.S == 0) return hipSuccess;
-    hipLaunchKernelGGL(adjust_kernel, dim3((unsigned)((p.S + kAdjustWaves - 1) / kAdjustWaves)),
-                       dim3(kAdjustWaves * kWave), 0, stream, p);
-    return hipGetLastError();
+    return launch_parts((p.S + kAdjustWaves - 1) / kAdjustWaves, kAdjustWaves * kWave, [&](dim3 grid, int64_t first) {
+        AdjustParams q = p;
+        q.first_block = first;
+        hipLaunchKernelGGL(adjust_kernel, grid, dim3(kAdjustWaves * kWave), 0, stream, q);
+    });
 }
 
 // Long FIFO loops: no batch cap and on average 1024 or more requests per
@@ -1119,12 +1121,12 @@ hipError_t launch_project(const ProjectParams& p, hipStream_t stream) {
     });
     if (e != hipSuccess || !p.rows) return e;
     const int64_t blocks = p.n_scenarios * ((p.H + kRowsThreads - 1) / kRowsThreads);
-    if (!grid_fits(blocks)) return hipErrorInvalidConfiguration;
-    if (p.nf == 4)
-        hipLaunchKernelGGL(expand_rows_kernel<4>, dim3((unsigned)blocks), dim3(kRowsThreads), 0, stream, p);
-    else
-        hipLaunchKernelGGL(expand_rows_kernel<3>, dim3((unsigned)blocks), dim3(kRowsThreads), 0, stream, p);
-    return hipGetLastError();
+    const auto rows = p.nf == 4 ? expand_rows_kernel<4> : expand_rows_kernel<3>;
+    return launch_parts(blocks, kRowsThreads, [&](dim3 grid, int64_t first) {
+        ProjectParams q = p;
+        q.first_block = first;
+        hipLaunchKernelGGL(rows, grid, dim3(kRowsThreads), 0, stream, q);
+    });
 }
 
 }  // namespace tl

@@ -116,6 +116,7 @@ struct AdjustParams {
     const uint32_t* den;
     const int32_t* max_tokens;
     int32_t* out;
+    int64_t first_block;
 };
 
 struct SelectParams {
@@ -195,6 +196,7 @@ struct GatherParams {
     const int32_t* batch;           // [S][H]
     const float* engine;            // [S] (4 features)
     float* out;                     // [S][F][H]
+    int64_t first_block;
 };
 
 // A call with few rows (small.hip): the rows of the projection grid (grid),
@@ -230,7 +232,8 @@ hipError_t launch_lattice_column(const ForestDev& f, const LatticeDev& L, const 
                                  const int32_t* fidx, int32_t f_all, hipStream_t stream);
 
 // A launch of `blocks` workgroups fits the grid (at most 2^31 - 1 in x).
-// A launch has fewer than 2^32 threads.  launch_parts calls launch(grid, first)
+// A launch has fewer than 2^32 threads (of more, the workgroups past them are
+// left out without an error).  launch_parts calls launch(grid, first)
 // for up to four consecutive parts of `blocks` workgroups of `threads` threads
 // each; a kernel's workgroup number is blockIdx.x + first.  (Four: 2^26 - 4
 // scenarios of 256 threads each, as many as one wavefront each takes in one
@@ -247,7 +250,7 @@ hipError_t launch_parts(int64_t blocks, int threads, Launch&& launch) {
     }
     return hipSuccess;
 }
-inline bool grid_fits(int64_t blocks) { return blocks >= 0 && blocks <= 0x7fffffffll; }
+inline bool grid_fits(int64_t blocks, int threads) { return blocks >= 0 && blocks <= 0xffffffffll / threads; }
 
 hipError_t launch_project(const ProjectParams& p, hipStream_t stream);
 // Workspace bytes for ordering the scenarios of a projection heaviest first;

@@ -69,6 +69,19 @@ def test_more_than_2_24_scenarios(gpu):
                                        p["flags"])
     _same(gi, bi, "binary freq_idx")
     _same(gs, bs, "binary status")
+    # the model as a table, and the lengths
+    lat = api.Lattice(forest, dfr, 60, 4)
+    _same(lat.tl_lattice_predict_grid(p["kv"], p["batch"]), ips, "lattice")
+    gi, _ = api.tl_select_freq_binary(forest, dfr, p["kv"], p["batch"], p["deadline_at"], p["n_iters"], dslo,
+                                      p["flags"], lattice=lat)
+    _same(gi, bi, "binary freq_idx with the lattice")
+    lat.close()
+    ones = np.full(BLOCK, 1, np.uint32)
+    exp_len = oracle.adjust_lengths(inp["req_offset"], inp["generated"], inp["remaining"] * 30, ones * 11, ones * 10,
+                                    np.full(BLOCK, 70, np.int32))
+    got_len = api.tl_adjust_lengths(off, d["generated"], d["remaining"] * 30, t(ones.view(np.int32) * 11),
+                                    t(ones.view(np.int32) * 10), t(np.full(BLOCK, 70, np.int32)))
+    _same(got_len, exp_len, "lengths")
     del got, p
     a = oracle.admit(dict(inp, tbt_slo_ns=slo), cand_p, cand_l, cand_d, float(freqs[-1]), fd)
     g = api.tl_admit(forest, float(freqs[-1]), dslo, t(cand_p), t(cand_l), *args, None, t(cand_d))
