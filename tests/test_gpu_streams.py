@@ -20,8 +20,12 @@ def _on_threads(n, work):
     errors = []
 
     def run(k):
+        import torch
         try:
             work(k)
+            # the stream ends with its thread and is not waited for by a
+            # synchronization of the device after that
+            torch.cuda.ExternalStream(PER_THREAD.value).synchronize()
         except Exception as e:       # raised again below, on the test's own thread
             errors.append(e)
 
