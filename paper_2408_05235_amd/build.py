@@ -16,7 +16,8 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB_DIR = os.path.join(PKG, "lib")
 LIB_PATH = os.path.join(LIB_DIR, "libtl.so")
 SOURCES = ["api.cpp", "host_forest.cpp", "project.hip", "forest.hip", "column.hip", "small.hip", "lattice.hip", "select.hip"]
-HEADERS = ["device_util.h", "tl_internal.h", "forest_walk.h", "record_format.h", "host_forest.h", "scratch.h"]
+HEADERS = ["device_util.h", "tl_internal.h", "forest_walk.h", "record_format.h", "host_forest.h", "queue_tries.h",
+           "scratch.h"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",

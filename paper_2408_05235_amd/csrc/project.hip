@@ -1,8 +1,8 @@
 // Stage 1: KV usage and batch-size projection (Sec. 4.2, Eq. 1-2) with FIFO
 // admission of queued requests under the KV check of Sec. 4.3.2.
 //
-// One workgroup of four wavefronts per scenario; the per-iteration curves live
-// in LDS.
+// One workgroup of one or four wavefronts per scenario (launch_project chooses);
+// the per-iteration curves live in LDS.
 //
 // In-flight requests are turned into O(1) events each instead of O(r) curve
 // updates.  For a request with c cached tokens active on [0, e):
@@ -26,10 +26,11 @@
 // checking the whole projected vector from the current iteration on.
 // Without a batch cap the whole queue is tried at its FIFO targets first,
 // with O(1) events per request and one check of the summed curve (boards whose
-// capacity never binds are done then), else the longest part of it that fits;
+// capacity never binds are done then), else a leading part of it that fits;
 // past that, where the capacity binds, the requests that the head's start has
 // room for are admitted together.
 #include "device_util.h"
+#include "queue_tries.h"
 #include "tl_internal.h"
 
 namespace tl {
@@ -326,9 +327,9 @@ __device__ __forceinline__ bool members_fit(ProjShared& sh, int& turn, const int
     return !any_thread<W>(sh, turn, over);
 }
 
-// Scenario order for long FIFO loops: one wavefront per scenario, whose time
-// grows with its number of requests; launched heaviest first, the last
-// wavefronts of the grid are short ones instead of whichever came last.  A
+// Scenario order for long FIFO loops: a scenario's time grows with its number
+// of requests; launched heaviest first, the last workgroups of the grid are
+// short ones instead of whichever came last.  A
 // counting sort over kOrderBuckets classes of the request count (six per
 // doubling), heaviest class first; the order inside a class is whatever the
 // atomics give (each scenario's results do not depend on it).  Workspace:
@@ -368,6 +369,8 @@ __global__ __launch_bounds__(256) void order_place_kernel(const int64_t* off, in
     if (s < S) order[atomicAdd(&counts[order_bucket(off, s)], 1u)] = (int32_t)s;
 }
 
+constexpr size_t kLdsPerCu = 160 * 1024;
+
 // BD_LDS: the batch difference array lives in LDS beside the KV curve, as a
 // batch cap needs (the admission loop reads its running sums).  Without a
 // cap it is only added to and finally prefix-summed, so it accumulates with
@@ -377,7 +380,8 @@ __global__ __launch_bounds__(256) void order_place_kernel(const int64_t* off, in
 // other's state (both in one kernel: 102 scalar registers spilled behind a cap,
 // each spill and reload an instruction in a chain bound by its latency; now
 // none).
-template <bool CAP, bool BD_LDS, bool POW2, int W>
+// W wavefronts a scenario, A (1 or W) of them in the admission loop.
+template <bool CAP, bool BD_LDS, bool POW2, int W, int A>
 __global__ __launch_bounds__(W* kWave) void project_kernel(ProjectParams P) {
     static_assert(BD_LDS || !CAP, "a batch cap reads running sums of the batch differences");
     extern __shared__ int32_t lds[];
@@ -542,9 +546,10 @@ __global__ __launch_bounds__(W* kWave) void project_kernel(ProjectParams P) {
     const int32_t bcap = CAP ? P.batch_cap[s] : 0;
     if (last_over >= 0 || (CAP && __builtin_amdgcn_readfirstlane(BI[0]) > bcap)) fl |= TL_FLAG_OVERCOMMIT;
 
-    // FIFO admission of queued requests.  Every wavefront runs the loop: the
-    // values it carries (iteration j, batch size, the head's fields, check
-    // outcomes) are the same in all of them, wavefront-uniform and kept in
+    // FIFO admission of queued requests.  Every wavefront takes part in the tries
+    // of the whole queue; the loop over the rest is run by A wavefronts, the
+    // others wait.  The values it carries (iteration j, batch size, the head's
+    // fields, check outcomes) are the same in all A, wavefront-uniform and kept in
     // scalar registers.  They come from reads of the curves between barriers;
     // the additions to the curves and the checks over many iterations are
     // shared out, and wavefront 0 alone writes the batch events and deadlines.
@@ -567,8 +572,9 @@ __global__ __launch_bounds__(W* kWave) void project_kernel(ProjectParams P) {
         int32_t q_max = -1, q_c0 = 0, q_sum = 0;
         uint64_t q_dl = kNoDeadline;
         uint64_t mask = 0;
+        bool whole = !CAP && hi - lo >= 2 * kWave;
         for (;;) {
-            if (!CAP && mask == 0 && streak >= streak_need && hi - (cb + kWave) >= 2 * kWave) {
+            if (whole) {
                 // All remaining requests at once, each at its FIFO target (the
                 // running maximum of the arrivals, from max(j, last_over +
                 // 1)): O(1) events a request, one scan, one check.  When the
@@ -643,40 +649,26 @@ __global__ __launch_bounds__(W* kWave) void project_kernel(ProjectParams P) {
                         }
                     }
                 };
-                int32_t ok = 0, bad = n_ch + 1, cur = 0, want = n_ch, guess = 0;
+                QueueTries t(n_ch);
+                int32_t cur = 0;
                 for (;;) {
                     unscan<W>(KV, H, N);
-                    if (want > cur) chunks(cur, want, 1, false);
-                    else chunks(want, cur, -1, false);
+                    if (t.want > cur) chunks(cur, t.want, 1, false);
+                    else chunks(t.want, cur, -1, false);
                     strided_scan<W, POW2>(KV, H, N);
                     const bool fits = prefix_scan<W>(sh, KV, H, cap, last_over + 1, &first_over) <= last_over || kv_fits;
-                    cur = want;
-                    if (want == ok) break;   // what did not fit is taken out again
-                    if (fits) {
-                        ok = want;
-                        if (bad - ok <= 1) break;
-                    } else {
-                        bad = want;
-                    }
-                    want = (ok + bad) / 2;   // == ok when bad == ok + 1
-                    if (bad == n_ch) {
-                        // First guess: the chunks that have arrived when the
-                        // whole sum first exceeds the capacity; without later
-                        // arrivals it falls from there.  Second: one more.
-                        if (ok == 0) {
-                            int32_t k_over = 0;
-                            for (int32_t k0 = 0; k0 < n_ch; k0 += kWave) {
-                                const int32_t k = k0 + lane;
-                                const int32_t a = k < n_ch ? P.arr[first + (int64_t)k * kWave] : INT32_MAX;
-                                k_over += (int32_t)__builtin_popcountll(__ballot(a <= first_over));
-                            }
-                            guess = k_over - 1;
-                        } else {
-                            guess = ok + 1;
+                    cur = t.want;
+                    int32_t guess = -1;
+                    if (!fits && cur == n_ch) {
+                        for (int32_t k0 = 0; k0 < n_ch; k0 += kWave) {
+                            const int32_t k = k0 + lane;
+                            const int32_t a = k < n_ch ? P.arr[first + (int64_t)k * kWave] : INT32_MAX;
+                            guess += (int32_t)__builtin_popcountll(__ballot(a <= first_over));
                         }
-                        if (guess > ok && guess < bad) want = guess;
                     }
+                    if (!t.after(fits, guess)) break;
                 }
+                const int32_t ok = t.ok;
                 if (ok > 0) {
                     chunks(0, ok, 1, true);
                     n_end = wave_max(n_end);
@@ -697,243 +689,268 @@ __global__ __launch_bounds__(W* kWave) void project_kernel(ProjectParams P) {
                     calm = 0;
                 }
             }
-            while (mask == 0) {
-                cb += kWave;
-                if (cb >= hi) break;
-                const int64_t i = cb + lane;
-                bool q = false;
-                if (i < hi) {
-                    q_arr = P.arr[i];
-                    const int32_t p = P.prompt[i], g = P.gen[i];
-                    q_len = P.rem[i];
-                    q = entry_ok(p, g, q_len, q_arr) && q_arr >= 0;
-                    q_c = p + g;
-                    q_lost = P.lost ? P.lost[i] : 0;
-                    q_dl = P.deadline ? P.deadline[i] : kNoDeadline;
-                }
-                mask = __ballot(q);
-                if (!CAP && mask) {
-                    q_max = wave_incl_max(q ? q_arr : -1);
-                    q_c0 = q ? (int32_t)ceil_div_u32((uint32_t)q_c, divN) : 0;
-                    q_sum = wave_incl_scan(q_c0);
-                }
-            }
-            if (mask == 0) break;
-
-            if (!CAP && at_targets) {
-                // The rest of this chunk of the queue, each at its FIFO
-                // target, as above; their contributions are added to the KV
-                // curve iteration by iteration and taken out again when they
-                // do not fit.
-                const int32_t lo_j = max(j, last_over + 1);
-                const bool mem = (mask >> lane) & 1;
-                const int32_t a = wave_incl_max(mem ? max(q_arr, lo_j) : -1);
-                const uint64_t memm = __ballot(mem);
-                const uint64_t over = __ballot(mem && a >= H);
-                const uint64_t take = over ? (memm & ((over & (~over + 1)) - 1)) : memm;
-                if (take == 0) break;   // the head cannot start within the horizon
-                // each member's in-horizon end, on its own lane
-                const int32_t lim_l = q_len >= H - a ? H : a + q_len;
-                const int32_t a_first = __builtin_amdgcn_readlane(a, __ffsll((unsigned long long)take) - 1);
-                int32_t r_end = 0;
-                add_members<W, false, POW2>(KV, take, q_c, a, lim_l, divN, wave, &r_end);
-                if (!members_fit<W>(sh, turn, KV, a_first, r_end, kv_fits ? INT32_MAX : cap)) {
-                    // take the batch's contributions out again
-                    add_members<W, true, POW2>(KV, take, q_c, a, lim_l, divN, wave, &r_end);
-                    curves_sync<W>();
-                    at_targets = false;
-                    streak = 0;
-                    calm = 0;
-                    calm_need = min(256, 2 * calm_need);
-                    continue;
-                }
-                if (wave == 0 && ((take >> lane) & 1)) {
-                    const int64_t e = (int64_t)a + q_len;
-                    atomicAdd(&BD[a], 1);
-                    if (e < H) atomicAdd(&BD[e], -1);
-                    if (e <= H && !q_lost && q_dl != kNoDeadline)
-                        atomicMin((unsigned long long*)&outDL[e - 1], (unsigned long long)q_dl);
-                }
-                n_end = max(n_end, r_end);
-                j = __builtin_amdgcn_readlane(a, 63 - __clzll((long long)take));
-                mask &= ~take;
-                ++streak;
-                if (streak >= 4) calm_need = 4;
-                if (over) break;
-                continue;
-            }
-
-            if (!CAP && !alone) {
-                // The capacity binds: the head and the requests behind it that
-                // have arrived by its start j, as many as the KV of iteration
-                // j itself leaves room for.  When their sum fits everywhere,
-                // they are the one-at-a-time loop's admissions at j, and the
-                // next of them does not fit at j.  A head without room at j
-                // starts no earlier than the next iteration that has it.
-                const bool queued = (mask >> lane) & 1;
-                const int hl = __ffsll((unsigned long long)mask) - 1;
-                const int32_t start = max(max(j, last_over + 1), __builtin_amdgcn_readlane(q_max, hl));
-                const int32_t c_h = __builtin_amdgcn_readlane(q_c0, hl);
-                int32_t room = -1, found = -1;
-                for (int32_t t0 = start; t0 < H; t0 += kWave) {
-                    const int32_t t = t0 + lane;
-                    const int32_t left = cap - KV[min(t, H - 1)];
-                    const uint64_t m = __ballot(t < H && left >= c_h);
-                    if (m) {
-                        const int l = __ffsll((unsigned long long)m) - 1;
-                        found = t0 + l;
-                        room = __builtin_amdgcn_readlane(left, l);
+            bool again = false;
+            if (A == W || wave == 0) {
+                for (;;) {
+                    if (!CAP && mask == 0 && streak >= streak_need && hi - (cb + kWave) >= 2 * kWave) {
+                        again = true;
                         break;
                     }
-                }
-                if (found < 0) break;   // the head cannot start within the horizon
-                if (found > start) calm = 0;
-                j = found;
-                // the requests behind it that have arrived (those before it in
-                // the chunk, admitted by now, arrived no later than j)
-                const bool mem = queued && q_max <= j;
-                const int32_t sum = q_sum - (__builtin_amdgcn_readlane(q_sum, hl) - c_h);
-                const uint32_t below = __builtin_amdgcn_mbcnt_hi(
-                    (uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-                const uint64_t take = __ballot(mem && sum <= room && (int32_t)below < fmax);
-                const uint64_t blocked = __ballot(mem && sum > room);
-                if ((take & (take - 1)) == 0) {
-                    alone = true;   // one request: checked below before it is added
-                    continue;
-                }
-                const int32_t lim_l = q_len >= H - j ? H : j + q_len;
-                int32_t r_end = 0;
-                // (everyone has read the curve above before it changes)
-                curves_sync<W>();
-                add_members<W, false, POW2>(KV, take, q_c, j, lim_l, divN, wave, &r_end);
-                if (!members_fit<W>(sh, turn, KV, j, r_end, cap)) {
-                    add_members<W, true, POW2>(KV, take, q_c, j, lim_l, divN, wave, &r_end);
-                    curves_sync<W>();
-                    fmax = max(1, (int32_t)__builtin_popcountll(take) >> 2);
-                    calm = 0;
-                    continue;
-                }
-                if (wave == 0 && ((take >> lane) & 1)) {
-                    const int64_t e = (int64_t)j + q_len;
-                    if (e < H) atomicAdd(&BD[e], -1);
-                    if (e <= H && !q_lost && q_dl != kNoDeadline)
-                        atomicMin((unsigned long long*)&outDL[e - 1], (unsigned long long)q_dl);
-                }
-                if (threadIdx.x == 0) atomicAdd(&BD[j], (int32_t)__builtin_popcountll(take));
-                n_end = max(n_end, r_end);
-                mask &= ~take;
-                fmax = min(kWave, 2 * fmax);
-                calm = blocked ? 0 : calm + 1;
-                if (calm >= calm_need) {
-                    at_targets = true;
-                    streak = 0;
-                }
-                continue;
-            }
-
-            // One request at a time (under a batch cap, or one without
-            // company).  The head of the queue: uniform lane, lane reads.
-            const int hl = __ffsll((unsigned long long)mask) - 1;
-            const int32_t h_arr = __builtin_amdgcn_readlane(q_arr, hl);
-            const int32_t h_c = __builtin_amdgcn_readlane(q_c, hl);
-            const int32_t h_len = __builtin_amdgcn_readlane(q_len, hl);
-            const int32_t h_lost = __builtin_amdgcn_readlane(q_lost, hl);
-            const uint64_t h_dl =
-                ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int32_t)(q_dl >> 32), hl) << 32) |
-                (uint32_t)__builtin_amdgcn_readlane((int32_t)(uint32_t)q_dl, hl);
-            const int32_t target = max(max(h_arr, j), last_over + 1);
-            if (h_arr >= H || target >= H) break;
-            if (CAP && target > j) run += sum_range(BD, j, target);
-            j = target;
-            bool admitted = false;
-            for (;;) {
-                bool ok = !CAP || run < bcap;
-                int32_t t_bad = -1;
-                if (ok) {
-                    // 4 x 64 iterations per round (their LDS reads in flight
-                    // together); the earliest overflowing iteration wins
-                    const int32_t lim = kv_fits ? j : (int32_t)min((int64_t)j + h_len, (int64_t)H);
-                    for (int32_t t0 = j; t0 < lim && t_bad < 0; t0 += 4 * kWave) {
-                        uint64_t m[4];
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            const int32_t t = t0 + k * kWave + lane;
-                            bool badt = false;
-                            if (t < lim)
-                                badt = KV[t] + (int32_t)(POW2 ? ((uint32_t)(h_c + t - j) + divN.d - 1u) >> divN.l
-                                                              : ceil_div_u32((uint32_t)(h_c + t - j), divN)) > cap;
-                            m[k] = __ballot(badt);
-                        }
-#pragma unroll
-                        for (int k = 3; k >= 0; --k)
-                            if (m[k]) t_bad = t0 + k * kWave + __ffsll((unsigned long long)m[k]) - 1;
+                while (mask == 0) {
+                    cb += kWave;
+                    if (cb >= hi) break;
+                    const int64_t i = cb + lane;
+                    bool q = false;
+                    if (i < hi) {
+                        q_arr = P.arr[i];
+                        const int32_t p = P.prompt[i], g = P.gen[i];
+                        q_len = P.rem[i];
+                        q = entry_ok(p, g, q_len, q_arr) && q_arr >= 0;
+                        q_c = p + g;
+                        q_lost = P.lost ? P.lost[i] : 0;
+                        q_dl = P.deadline ? P.deadline[i] : kNoDeadline;
                     }
-                    ok = t_bad < 0;
+                    mask = __ballot(q);
+                    if (!CAP && mask) {
+                        q_max = wave_incl_max(q ? q_arr : -1);
+                        q_c0 = q ? (int32_t)ceil_div_u32((uint32_t)q_c, divN) : 0;
+                        q_sum = wave_incl_scan(q_c0);
+                    }
                 }
-                if (ok) { admitted = true; break; }
-                if (CAP && run >= bcap) {
-                    // The batch is full: the next start to try is the first
-                    // later iteration with a free slot, found 64 iterations
-                    // at a time from the batch differences (what stepping
-                    // one iteration at a time reaches).
-                    int32_t base = j, r = run, found = -1;
-                    while (base + 1 < H) {
-                        const int32_t t = base + 1 + lane;
-                        const int32_t pre = wave_incl_scan(t < H ? BD[t] : 0) + r;   // batch size at t
-                        const uint64_t m = __ballot(t < H && pre < bcap);
+                if (mask == 0) break;
+
+                if (!CAP && at_targets) {
+                    // The rest of this chunk of the queue, each at its FIFO
+                    // target, as above; their contributions are added to the KV
+                    // curve iteration by iteration and taken out again when they
+                    // do not fit.
+                    const int32_t lo_j = max(j, last_over + 1);
+                    const bool mem = (mask >> lane) & 1;
+                    const int32_t a = wave_incl_max(mem ? max(q_arr, lo_j) : -1);
+                    const uint64_t memm = __ballot(mem);
+                    const uint64_t over = __ballot(mem && a >= H);
+                    const uint64_t take = over ? (memm & ((over & (~over + 1)) - 1)) : memm;
+                    if (take == 0) break;   // the head cannot start within the horizon
+                    // each member's in-horizon end, on its own lane
+                    const int32_t lim_l = q_len >= H - a ? H : a + q_len;
+                    const int32_t a_first = __builtin_amdgcn_readlane(a, __ffsll((unsigned long long)take) - 1);
+                    int32_t r_end = 0;
+                    add_members<A, false, POW2>(KV, take, q_c, a, lim_l, divN, wave, &r_end);
+                    if (!members_fit<A>(sh, turn, KV, a_first, r_end, kv_fits ? INT32_MAX : cap)) {
+                        // take the batch's contributions out again
+                        add_members<A, true, POW2>(KV, take, q_c, a, lim_l, divN, wave, &r_end);
+                        curves_sync<A>();
+                        at_targets = false;
+                        streak = 0;
+                        calm = 0;
+                        calm_need = min(256, 2 * calm_need);
+                        continue;
+                    }
+                    if (wave == 0 && ((take >> lane) & 1)) {
+                        const int64_t e = (int64_t)a + q_len;
+                        atomicAdd(&BD[a], 1);
+                        if (e < H) atomicAdd(&BD[e], -1);
+                        if (e <= H && !q_lost && q_dl != kNoDeadline)
+                            atomicMin((unsigned long long*)&outDL[e - 1], (unsigned long long)q_dl);
+                    }
+                    n_end = max(n_end, r_end);
+                    j = __builtin_amdgcn_readlane(a, 63 - __clzll((long long)take));
+                    mask &= ~take;
+                    ++streak;
+                    if (streak >= 4) calm_need = 4;
+                    if (over) break;
+                    continue;
+                }
+
+                if (!CAP && !alone) {
+                    // The capacity binds: the head and the requests behind it that
+                    // have arrived by its start j, as many as the KV of iteration
+                    // j itself leaves room for.  When their sum fits everywhere,
+                    // they are the one-at-a-time loop's admissions at j, and the
+                    // next of them does not fit at j.  A head without room at j
+                    // starts no earlier than the next iteration that has it.
+                    const bool queued = (mask >> lane) & 1;
+                    const int hl = __ffsll((unsigned long long)mask) - 1;
+                    const int32_t start = max(max(j, last_over + 1), __builtin_amdgcn_readlane(q_max, hl));
+                    const int32_t c_h = __builtin_amdgcn_readlane(q_c0, hl);
+                    int32_t room = -1, found = -1;
+                    for (int32_t t0 = start; t0 < H; t0 += kWave) {
+                        const int32_t t = t0 + lane;
+                        const int32_t left = cap - KV[min(t, H - 1)];
+                        const uint64_t m = __ballot(t < H && left >= c_h);
                         if (m) {
                             const int l = __ffsll((unsigned long long)m) - 1;
-                            found = base + 1 + l;
-                            r = __builtin_amdgcn_readlane(pre, l);
+                            found = t0 + l;
+                            room = __builtin_amdgcn_readlane(left, l);
                             break;
                         }
-                        r = __builtin_amdgcn_readlane(pre, kWave - 1);
-                        base += kWave;
                     }
-                    if (found < 0) break;
-                    run = r;
+                    if (found < 0) break;   // the head cannot start within the horizon
+                    if (found > start) calm = 0;
                     j = found;
+                    // the requests behind it that have arrived (those before it in
+                    // the chunk, admitted by now, arrived no later than j)
+                    const bool mem = queued && q_max <= j;
+                    const int32_t sum = q_sum - (__builtin_amdgcn_readlane(q_sum, hl) - c_h);
+                    const uint32_t below = __builtin_amdgcn_mbcnt_hi(
+                        (uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                    const uint64_t take = __ballot(mem && sum <= room && (int32_t)below < fmax);
+                    const uint64_t blocked = __ballot(mem && sum > room);
+                    if ((take & (take - 1)) == 0) {
+                        alone = true;   // one request: checked below before it is added
+                        continue;
+                    }
+                    const int32_t lim_l = q_len >= H - j ? H : j + q_len;
+                    int32_t r_end = 0;
+                    // (everyone has read the curve above before it changes)
+                    curves_sync<A>();
+                    add_members<A, false, POW2>(KV, take, q_c, j, lim_l, divN, wave, &r_end);
+                    if (!members_fit<A>(sh, turn, KV, j, r_end, cap)) {
+                        add_members<A, true, POW2>(KV, take, q_c, j, lim_l, divN, wave, &r_end);
+                        curves_sync<A>();
+                        fmax = max(1, (int32_t)__builtin_popcountll(take) >> 2);
+                        calm = 0;
+                        continue;
+                    }
+                    if (wave == 0 && ((take >> lane) & 1)) {
+                        const int64_t e = (int64_t)j + q_len;
+                        if (e < H) atomicAdd(&BD[e], -1);
+                        if (e <= H && !q_lost && q_dl != kNoDeadline)
+                            atomicMin((unsigned long long*)&outDL[e - 1], (unsigned long long)q_dl);
+                    }
+                    if (threadIdx.x == 0) atomicAdd(&BD[j], (int32_t)__builtin_popcountll(take));
+                    n_end = max(n_end, r_end);
+                    mask &= ~take;
+                    fmax = min(kWave, 2 * fmax);
+                    calm = blocked ? 0 : calm + 1;
+                    if (calm >= calm_need) {
+                        at_targets = true;
+                        streak = 0;
+                    }
                     continue;
                 }
-                // Next start to try.  If iteration t_bad overflowed, every
-                // start j2 in (j, t_bad] whose own contribution there,
-                // ceil((c + t_bad - j2) / N), exceeds room = cap - KV[t_bad]
-                // fails the same way: j2 < c + t_bad - N * room (all of
-                // them when room < 0).  Skipping those gives the same
-                // admission iteration.
-                int32_t nj = j + 1;
-                if (t_bad >= 0) {
-                    const int32_t room = cap - __builtin_amdgcn_readfirstlane(KV[t_bad]);
-                    int64_t first = (int64_t)t_bad + 1;
-                    if (room >= 0) first = min(first, (int64_t)h_c + t_bad - (int64_t)N * room);
-                    nj = (int32_t)max((int64_t)nj, first);
+
+                // One request at a time (under a batch cap, or one without
+                // company).  The head of the queue: uniform lane, lane reads.
+                const int hl = __ffsll((unsigned long long)mask) - 1;
+                const int32_t h_arr = __builtin_amdgcn_readlane(q_arr, hl);
+                const int32_t h_c = __builtin_amdgcn_readlane(q_c, hl);
+                const int32_t h_len = __builtin_amdgcn_readlane(q_len, hl);
+                const int32_t h_lost = __builtin_amdgcn_readlane(q_lost, hl);
+                const uint64_t h_dl =
+                    ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int32_t)(q_dl >> 32), hl) << 32) |
+                    (uint32_t)__builtin_amdgcn_readlane((int32_t)(uint32_t)q_dl, hl);
+                const int32_t target = max(max(h_arr, j), last_over + 1);
+                if (h_arr >= H || target >= H) break;
+                if (CAP && target > j) run += sum_range(BD, j, target);
+                j = target;
+                bool admitted = false;
+                for (;;) {
+                    bool ok = !CAP || run < bcap;
+                    int32_t t_bad = -1;
+                    if (ok) {
+                        // 4 x 64 iterations per round (their LDS reads in flight
+                        // together); the earliest overflowing iteration wins
+                        const int32_t lim = kv_fits ? j : (int32_t)min((int64_t)j + h_len, (int64_t)H);
+                        for (int32_t t0 = j; t0 < lim && t_bad < 0; t0 += 4 * kWave) {
+                            uint64_t m[4];
+    #pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                const int32_t t = t0 + k * kWave + lane;
+                                bool badt = false;
+                                if (t < lim)
+                                    badt = KV[t] + (int32_t)(POW2 ? ((uint32_t)(h_c + t - j) + divN.d - 1u) >> divN.l
+                                                                  : ceil_div_u32((uint32_t)(h_c + t - j), divN)) > cap;
+                                m[k] = __ballot(badt);
+                            }
+    #pragma unroll
+                            for (int k = 3; k >= 0; --k)
+                                if (m[k]) t_bad = t0 + k * kWave + __ffsll((unsigned long long)m[k]) - 1;
+                        }
+                        ok = t_bad < 0;
+                    }
+                    if (ok) { admitted = true; break; }
+                    if (CAP && run >= bcap) {
+                        // The batch is full: the next start to try is the first
+                        // later iteration with a free slot, found 64 iterations
+                        // at a time from the batch differences (what stepping
+                        // one iteration at a time reaches).
+                        int32_t base = j, r = run, found = -1;
+                        while (base + 1 < H) {
+                            const int32_t t = base + 1 + lane;
+                            const int32_t pre = wave_incl_scan(t < H ? BD[t] : 0) + r;   // batch size at t
+                            const uint64_t m = __ballot(t < H && pre < bcap);
+                            if (m) {
+                                const int l = __ffsll((unsigned long long)m) - 1;
+                                found = base + 1 + l;
+                                r = __builtin_amdgcn_readlane(pre, l);
+                                break;
+                            }
+                            r = __builtin_amdgcn_readlane(pre, kWave - 1);
+                            base += kWave;
+                        }
+                        if (found < 0) break;
+                        run = r;
+                        j = found;
+                        continue;
+                    }
+                    // Next start to try.  If iteration t_bad overflowed, every
+                    // start j2 in (j, t_bad] whose own contribution there,
+                    // ceil((c + t_bad - j2) / N), exceeds room = cap - KV[t_bad]
+                    // fails the same way: j2 < c + t_bad - N * room (all of
+                    // them when room < 0).  Skipping those gives the same
+                    // admission iteration.
+                    int32_t nj = j + 1;
+                    if (t_bad >= 0) {
+                        const int32_t room = cap - __builtin_amdgcn_readfirstlane(KV[t_bad]);
+                        int64_t first = (int64_t)t_bad + 1;
+                        if (room >= 0) first = min(first, (int64_t)h_c + t_bad - (int64_t)N * room);
+                        nj = (int32_t)max((int64_t)nj, first);
+                    }
+                    if (nj >= H) break;
+                    if (CAP) run += sum_range(BD, j, nj);
+                    j = nj;
                 }
-                if (nj >= H) break;
-                if (CAP) run += sum_range(BD, j, nj);
-                j = nj;
-            }
-            if (!admitted) break;
-            const int64_t e = (int64_t)j + h_len;
-            const int32_t lim = (int32_t)min(e, (int64_t)H);
-            curves_sync<W>();   // everyone has read the curves
-            add_request<false, POW2>(KV, h_c, j, lim, divN, wave, W);
-            if (threadIdx.x == 0) {
-                if (BD_LDS) {
-                    BD[j] += 1;
-                    if (e < H) BD[e] -= 1;
-                } else {
-                    atomicAdd(&BD[j], 1);
-                    if (e < H) atomicAdd(&BD[e], -1);
+                if (!admitted) break;
+                const int64_t e = (int64_t)j + h_len;
+                const int32_t lim = (int32_t)min(e, (int64_t)H);
+                curves_sync<A>();   // everyone has read the curves
+                add_request<false, POW2>(KV, h_c, j, lim, divN, wave, A);
+                if (threadIdx.x == 0) {
+                    if (BD_LDS) {
+                        BD[j] += 1;
+                        if (e < H) BD[e] -= 1;
+                    } else {
+                        atomicAdd(&BD[j], 1);
+                        if (e < H) atomicAdd(&BD[e], -1);
+                    }
+                    if (e <= H && !h_lost && h_dl != kNoDeadline)
+                        atomicMin((unsigned long long*)&outDL[e - 1], (unsigned long long)h_dl);
                 }
-                if (e <= H && !h_lost && h_dl != kNoDeadline)
-                    atomicMin((unsigned long long*)&outDL[e - 1], (unsigned long long)h_dl);
+                run += 1;
+                n_end = max(n_end, lim);
+                mask &= mask - 1;
+                curves_sync<A>();
+                alone = false;
+                fmax = min(kWave, 2 * fmax);
+                }
             }
-            run += 1;
-            n_end = max(n_end, lim);
-            mask &= mask - 1;
-            curves_sync<W>();
-            alone = false;
-            fmax = min(kWave, 2 * fmax);
+            if (A < W) {   // where the loop has come to
+                curves_sync<W>();
+                if (threadIdx.x == 0) {
+                    sh.u64[0] = (uint64_t)cb;
+                    sh.i32[0][0] = again;
+                    sh.i32[1][0] = j;
+                    sh.i32[2][0] = n_end;
+                }
+                curves_sync<W>();
+                cb = (int64_t)lane63_u64(sh.u64[0]);
+                again = __builtin_amdgcn_readfirstlane(sh.i32[0][0]) != 0;
+                j = __builtin_amdgcn_readfirstlane(sh.i32[1][0]);
+                n_end = __builtin_amdgcn_readfirstlane(sh.i32[2][0]);
+            }
+            if (!again) break;
+            whole = true;
         }
     }
     global_done();
@@ -1076,11 +1093,21 @@ hipError_t launch_project(const ProjectParams& p, hipStream_t stream) {
     // block sizes that are powers of two up to 64 take shifts instead of
     // divisions in the admission loops
     const bool pow2 = p.N <= kWave && (p.N & (p.N - 1)) == 0;
-    // Four wavefronts a scenario share its scans, request passes and additions;
-    // with long loops on more scenarios than fill the device at four each, one
-    // does: every wavefront runs the loop.  Measured (us at 1 / 4): 1024 boards
-    // in flight 28 / 14, one board x 2048 23 / 10, boards under arrivals 64:
-    // 4387 / 3467, 2048: 5153 / 4225, 4096: 5316 / 6800.
+    // Wavefronts a scenario.  Without a batch cap four share its request pass,
+    // scans and tries of the whole queue (us at one / four: 1024 boards in flight
+    // 28 / 14, one board x 2048 iterations 23 / 10, 1024 x 1024 with 800 queued and
+    // capacity to spare 62 / 38) where the device holds all boards at four each
+    // (five a CU with the registers they take), or where the LDS of a board
+    // leaves a CU few of them anyway.  Beyond, one: boards whose capacity binds
+    // spend their time in the loop, where four bring little and take the place of
+    // other boards (2048 x 1024 with 200 queued 482 / 760, 4096 under arrivals
+    // 4060 / 8172; 4096 x 3072 with 300 queued 2485 / 2624, with capacity to
+    // spare 269 / 156).
+    // Of four, one runs the loop and the others wait: with a barrier per
+    // admission 1024 x 1024 with 200 queued took 550 us instead of 409, with 1500
+    // on 2048 iterations 1116 instead of 880.  All four run it (they share the
+    // additions) while every board has a CU to itself (64 x 4096 with 400 queued
+    // one 641, four 608; 64 under arrivals 3439 / 3215).
     // Behind a batch cap requests are admitted one at a time, a barrier each
     // between four wavefronts: four only while every board has a CU to itself and
     // its horizon is long enough for them to gain on the additions (us at 1 /
@@ -1088,17 +1115,25 @@ hipError_t launch_project(const ProjectParams& p, hipStream_t stream) {
     // 525; 2 x 666 96 / 89, 144 / 140; 1 x 512 61 / 59, 81 / 81; 268 x 302 92 /
     // 97, 119 / 132; 1024 x 4096 337 / 348, 547 / 758; 4096 x 1024 220 / 571).
     const bool cap = p.batch_cap != nullptr;
-    const bool one = cap ? p.n_scenarios > 256 || p.H < 512 : !bd_lds && p.n_scenarios > 2048;
-    const int w = one ? 1 : kProjWaves;
+    constexpr int64_t kCus = 256;
+    const bool four = cap ? p.n_scenarios <= kCus && p.H >= 512
+                          : p.n_scenarios <= 5 * kCus || lds > kLdsPerCu / 7;
+    const int w = four ? kProjWaves : 1;
+    const bool all = p.n_scenarios <= kCus;
+    constexpr int W = kProjWaves;
     void (*const capped[2][2])(ProjectParams) = {
-        {project_kernel<true, true, false, 1>, project_kernel<true, true, false, kProjWaves>},
-        {project_kernel<true, true, true, 1>, project_kernel<true, true, true, kProjWaves>}};
-    void (*const uncapped[2][2][2])(ProjectParams) = {
-        {{project_kernel<false, false, false, 1>, project_kernel<false, false, false, kProjWaves>},
-         {project_kernel<false, false, true, 1>, project_kernel<false, false, true, kProjWaves>}},
-        {{project_kernel<false, true, false, 1>, project_kernel<false, true, false, kProjWaves>},
-         {project_kernel<false, true, true, 1>, project_kernel<false, true, true, kProjWaves>}}};
-    void (*const kern)(ProjectParams) = cap ? capped[pow2][!one] : uncapped[bd_lds][pow2][!one];
+        {project_kernel<true, true, false, 1, 1>, project_kernel<true, true, false, W, W>},
+        {project_kernel<true, true, true, 1, 1>, project_kernel<true, true, true, W, W>}};
+    void (*const uncapped[2][2][3])(ProjectParams) = {
+        {{project_kernel<false, false, false, 1, 1>, project_kernel<false, false, false, W, 1>,
+          project_kernel<false, false, false, W, W>},
+         {project_kernel<false, false, true, 1, 1>, project_kernel<false, false, true, W, 1>,
+          project_kernel<false, false, true, W, W>}},
+        {{project_kernel<false, true, false, 1, 1>, project_kernel<false, true, false, W, 1>,
+          project_kernel<false, true, false, W, W>},
+         {project_kernel<false, true, true, 1, 1>, project_kernel<false, true, true, W, 1>,
+          project_kernel<false, true, true, W, W>}}};
+    void (*const kern)(ProjectParams) = cap ? capped[pow2][four] : uncapped[bd_lds][pow2][four ? 1 + all : 0];
     if (lds + sizeof(ProjShared) > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;

@@ -56,6 +56,56 @@ def test_batch_cap_paths(S, H, N, R, Q, cap_kv, cap_batch):
     assert_projection_equal(gpu_project(inp), oracle.project(inp))
 
 
-def test_many_long_queues():
-    inp = _boards(5, 2100, 90, 16, 4, 1030, 3000, None, False)
+@pytest.mark.parametrize("S,H,N,R,Q,cap_kv", [
+    (257, 400, 16, 6, 700, 900), (1280, 130, 24, 4, 260, 300), (1281, 130, 16, 4, 260, 300), (300, 2950, 16, 30, 130, 500),
+    (1290, 2950, 8, 3, 190, 500), (5, 640, 16, 10, 2600, 700), (258, 70, 16, 2, 1100, 500), (1281, 64, 16, 0, 200, 0),
+])
+def test_loop_wavefronts(S, H, N, R, Q, cap_kv):
+    """On each side of the rules for one or four wavefronts a board and in the
+    admission loop; malformed entries, late arrivals among them, at the heads of
+    the queue's chunks of 64."""
+    inp = _boards(H + Q, S, H, N, R, Q, cap_kv, None, S % 2 == 0)
+    heads = np.arange(0, S * (R + Q), 64)
+    inp["prompt"][heads] = -5
+    inp["arrival"][heads[heads % (R + Q) >= R]] = H - 1
     assert_projection_equal(gpu_project(inp), oracle.project(inp))
+
+
+@pytest.mark.parametrize("unsorted", [False, True])
+@pytest.mark.parametrize("N,H,cap_kv", [(16, 90, 3000), (16, 300, 700), (24, 90, 1 << 20), (24, 270, 900), (100, 257, 400)])
+def test_many_long_queues(N, H, cap_kv, unsorted):
+    """More boards than the device holds at four wavefronts each, 1024 or more
+    requests on each: one wavefront a board, projected heaviest first."""
+    inp = _boards(N + H, 1300, H, N, 4, 1030, cap_kv, None, unsorted)
+    assert_projection_equal(gpu_project(inp), oracle.project(inp))
+
+
+def test_many_long_queues_with_a_new_query():
+    """The same with a new query each (tl_admit): decisions against the oracle
+    on some of the boards, projections on all."""
+    import torch
+    from paper_2408_05235_amd import api
+    from test_gpu_parity import random_forest
+    rng = np.random.default_rng(7)
+    S, H, N = 1300, 90, 16
+    inp = _boards(8, S, H, N, 4, 1030, 2000, None, False)
+    fd = random_forest(rng, 20, 5, 3, kvmax=3000, bmax=200)
+    cp, cl = rng.integers(1, 400, S).astype(np.int32), rng.integers(1, 120, S).astype(np.int32)
+    cd = rng.integers(1, 1 << 33, S).astype(np.uint64)
+    slo = rng.integers(10, 60, S).astype(np.uint64) * 10 ** 6
+    t = lambda a: torch.from_numpy(a.view(np.int64) if a.dtype == np.uint64 else a).cuda()
+    forest = api.Forest.from_dict(fd)
+    g = api.tl_admit(forest, 1800.0, t(slo), t(cp), t(cl), t(inp["req_offset"]), t(inp["prompt"]), t(inp["generated"]),
+                     t(inp["remaining"]), t(inp["arrival"]), t(inp["kv_capacity"]), H, N, t(inp["deadline_ns"]),
+                     t(inp["lost"]), None, None, t(cd))
+    dec = g["decision"].cpu().numpy().view(np.uint32)
+    for s in [0, 1, 2, 3, S // 2, S - 2, S - 1]:
+        lo, hi = int(inp["req_offset"][s]), int(inp["req_offset"][s + 1])
+        one = dict(inp, n_scenarios=1, req_offset=np.array([0, hi - lo], np.int64), kv_capacity=inp["kv_capacity"][s:s + 1],
+                   tbt_slo_ns=slo[s:s + 1], n_features=3,
+                   **{k: inp[k][lo:hi] for k in ("prompt", "generated", "remaining", "arrival", "deadline_ns", "lost")})
+        o = oracle.admit(one, cp[s:s + 1], cl[s:s + 1], cd[s:s + 1], 1800.0, fd)
+        assert dec[s] == o["decision"][0], s
+        for k in ("batch", "kv", "deadline_at", "n_iters", "flags"):
+            assert np.array_equal(g[k][s].cpu().numpy().view(o[k].dtype), o[k][0]), (s, k)
+    forest.close()

@@ -33,11 +33,11 @@ def _resources(tmp_path, name):
                     reason="no hipcc")
 def test_projection_behind_a_batch_cap_keeps_its_registers(tmp_path):
     kernels = _resources(tmp_path, "project.hip")
-    # project_kernel<CAP, BD_LDS, POW2, W>
+    # project_kernel<CAP, BD_LDS, POW2, W, A>
     found = {m.groups(): r for k, r in kernels.items()
-             for m in [re.search(r"project_kernelILb([01])ELb([01])ELb([01])ELi(\d)E", k)] if m}
-    assert len(found) == 12
-    for (cap, _, _, waves), r in found.items():
+             for m in [re.search(r"project_kernelILb([01])ELb([01])ELb([01])ELi(\d)ELi(\d)E", k)] if m}
+    assert len(found) == 16
+    for (cap, _, _, waves, _), r in found.items():
         assert r["ScratchSize"] == 0 and r["VGPRs Spill"] == 0
         if cap == "1":
             assert r["SGPRs Spill"] <= (0 if waves == "1" else 8), r
