@@ -117,21 +117,59 @@ __global__ __launch_bounds__(256) void select_kernel(SelectParams P) {
     }
 }
 
-// Eq. 3-4 at one frequency for one scenario, by a workgroup of kTimeWaves
-// wavefronts: with per-iteration times of `ips` over the n projected
-// iterations, returns T_R[n] and whether some deadline of `dl` (T_R[j+1] <
-// dl[j]) is missed; *miss_own tells whether T_R[own_at + 1] < d_own fails
-// (own_at < 0: none).  Each wavefront takes a run of consecutive iterations,
-// four a lane and 256 at a time: its run's total first, then, from the totals
-// of the wavefronts before it, the times of its iterations.  Every thread
-// returns the same values; all of them call it.  (One wavefront stepping
-// through the iterations 64 at a time was a chain of loads and scans: 13 us for
-// 2048 iterations, however few the scenarios.)
+// Eq. 3 at one frequency over iterations [r0, r1) of one scenario, by one
+// wavefront, PER consecutive iterations a lane: with T_R[r0] = carry, whether some
+// deadline of `dl` (T_R[j+1] < dl[j]) is missed on a lane (*miss), and whether
+// T_R[own_at + 1] < d_own fails (*miss_own).  Returns T_R[r1].
+template <int PER>
+__device__ __forceinline__ uint64_t run_times(const float* ips, const uint64_t* dl, int32_t r0, int32_t r1,
+                                              uint64_t carry, int32_t own_at, uint64_t d_own, bool* miss,
+                                              bool* miss_own) {
+    for (int32_t j0 = r0; j0 < r1; j0 += kWave * PER) {
+        const int32_t jb = j0 + PER * lane_id();
+        uint64_t t[PER], step = 0;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            step += jb + k < r1 ? latency_ns(ips[jb + k]) : 0ull;
+            t[k] = step;
+        }
+        const uint64_t before = wave_incl_scan_u64(step) - step + carry;   // T_R[jb]
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            if (jb + k < r1) {
+                const uint64_t d = dl[jb + k];
+                *miss |= d != kNoDeadline && !(before + t[k] < d);
+                *miss_own |= jb + k == own_at && !(before + t[k] < d_own);
+            }
+        carry = lane63_u64(before + step);
+    }
+    return carry;
+}
+
+// Eq. 3-4 at one frequency for one scenario, by W wavefronts: with
+// per-iteration times of `ips` over the n projected iterations, returns T_R[n]
+// and whether some deadline of `dl` is missed; *miss_own tells whether
+// T_R[own_at + 1] < d_own fails (own_at < 0: none).  Every thread returns the
+// same values; all of them call it.
+// W = 4, a workgroup: each wavefront takes a run of consecutive iterations, its
+// run's total first, then, from the totals of the wavefronts before it, the times
+// of its iterations.  (One wavefront stepping through the iterations 64 at a time
+// was a chain of loads and scans: 13 us for 2048 iterations, however few the
+// scenarios.)  W = 1: one wavefront on its own, four scenarios a workgroup.
 constexpr int kTimeWaves = 4;
 constexpr int kTimeThreads = kTimeWaves * kWave;
 
-__device__ __forceinline__ uint64_t block_times(const float* ips, const uint64_t* dl, int32_t n, int32_t own_at,
-                                                uint64_t d_own, bool* miss, bool* miss_own) {
+template <int W>
+__device__ __forceinline__ uint64_t scenario_times(const float* ips, const uint64_t* dl, int32_t n, int32_t own_at,
+                                                   uint64_t d_own, bool* miss, bool* miss_own) {
+    bool m = false, mo = false;
+    if (W == 1) {
+        const uint64_t all = n <= kWave ? run_times<1>(ips, dl, 0, n, 0, own_at, d_own, &m, &mo)
+                                        : run_times<kPerLane>(ips, dl, 0, n, 0, own_at, d_own, &m, &mo);
+        *miss = __ballot(m) != 0;
+        *miss_own = __ballot(mo) != 0;
+        return all;
+    }
     __shared__ uint64_t totals[kTimeWaves];
     __shared__ uint32_t missed[2];
     const int wave = threadIdx.x / kWave;
@@ -153,25 +191,7 @@ __device__ __forceinline__ uint64_t block_times(const float* ips, const uint64_t
         if (w < wave) carry += totals[w];
         all += totals[w];
     }
-    bool m = false, mo = false;
-    for (int32_t j0 = r0; j0 < r1; j0 += kStep) {
-        const int32_t jb = j0 + kPerLane * lane_id();
-        uint64_t t[kPerLane], step = 0;
-#pragma unroll
-        for (int k = 0; k < kPerLane; ++k) {
-            step += jb + k < r1 ? latency_ns(ips[jb + k]) : 0ull;
-            t[k] = step;
-        }
-        const uint64_t before = wave_incl_scan_u64(step) - step + carry;   // T_R[jb]
-#pragma unroll
-        for (int k = 0; k < kPerLane; ++k)
-            if (jb + k < r1) {
-                const uint64_t d = dl[jb + k];
-                m |= d != kNoDeadline && !(before + t[k] < d);
-                mo |= jb + k == own_at && !(before + t[k] < d_own);
-            }
-        carry = lane63_u64(before + step);
-    }
+    run_times<kPerLane>(ips, dl, r0, r1, carry, own_at, d_own, &m, &mo);
     if (m) missed[0] = 1;
     if (mo) missed[1] = 1;
     __syncthreads();
@@ -180,6 +200,25 @@ __device__ __forceinline__ uint64_t block_times(const float* ips, const uint64_t
     return all;
 }
 
+// The scenario of this workgroup (W = 4) or wavefront (W = 1).
+template <int W>
+__device__ __forceinline__ int64_t time_scenario(int64_t first_block) {
+    const int64_t block = first_block + blockIdx.x;
+    return W == 1 ? block * kTimeWaves + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)) : block;
+}
+template <int W>
+__device__ __forceinline__ int time_thread() {
+    return W == 1 ? lane_id() : (int)threadIdx.x;
+}
+
+// Wavefronts per scenario of the checks at one frequency: four where they
+// shorten a chain of steps and the device has room for them.  Measured (us, a
+// search over 17 frequencies by table, five checks; one / four wavefronts):
+// 2048 scenarios x 256 iterations 42 / 46, x 1024 94 / 91, x 2048 156 / 145;
+// 4096 x 64 41 / 63, x 1024 134 / 149, x 4096 517 / 555; 65536 x 16 226 / 721; 64
+// x 256 41 / 41, x 4096 117 / 65.
+int time_waves(int64_t S, int32_t H) { return S > 2048 || H <= kStep ? 1 : kTimeWaves; }
+
 __device__ __forceinline__ bool within_tbt(uint64_t t_r_n, uint64_t slo, int32_t n) {
     const uint64_t budget = n == 0 ? ~0ull : (slo > ~0ull / (uint64_t)n) ? ~0ull : slo * (uint64_t)n;
     return t_r_n <= budget;
@@ -187,11 +226,13 @@ __device__ __forceinline__ bool within_tbt(uint64_t t_r_n, uint64_t slo, int32_t
 
 // Admission decision (Sec. 4.3.2 checks 1-3) of one new query per scenario
 // from the projection with it and M at the maximum frequency: one workgroup
-// per scenario; the deadline of the query itself (ending at cand_len, when
+// or wavefront per scenario; the deadline of the query itself (ending at cand_len, when
 // inside the horizon) is checked apart from the scheduled requests'
 // deadlines in deadline_at.
+template <int W>
 __global__ __launch_bounds__(kTimeThreads) void admit_kernel(AdmitParams P) {
-    const int64_t s = P.first_block + blockIdx.x;
+    const int64_t s = time_scenario<W>(P.first_block);
+    if (s >= P.S) return;
     const int32_t H = P.H;
     const uint32_t fl = P.proj_flags[s];
     uint32_t dec;
@@ -209,13 +250,14 @@ __global__ __launch_bounds__(kTimeThreads) void admit_kernel(AdmitParams P) {
         const uint64_t d_own = P.cand_deadline ? P.cand_deadline[s] : kNoDeadline;
         const int32_t own_at = (d_own != kNoDeadline && L <= H) ? L - 1 : -1;   // T_R[L] = T_R[own_at + 1]
         bool miss, miss_own;
-        const uint64_t t_r = block_times(P.ips + s * H, P.deadline_at + s * H, n, own_at, d_own, &miss, &miss_own);
+        const uint64_t t_r =
+            scenario_times<W>(P.ips + s * H, P.deadline_at + s * H, n, own_at, d_own, &miss, &miss_own);
         if (!within_tbt(t_r, P.tbt_slo_ns[s], n)) dec = TL_ADMIT_QUEUE_TBT;
         else if (miss) dec = TL_ADMIT_QUEUE_E2E;
         else if (miss_own) dec = TL_ADMIT_LOST;
         else dec = TL_ADMIT_OK;
     }
-    if (threadIdx.x == 0) P.decision[s] = dec;
+    if (time_thread<W>() == 0) P.decision[s] = dec;
 }
 
 // Binary search over the candidate frequencies (Sec. 4.5), one step per
@@ -225,7 +267,8 @@ __global__ __launch_bounds__(kTimeThreads) void admit_kernel(AdmitParams P) {
 // next probe is the midpoint while lo < hi.  The last step (final = true)
 // checks lo itself and writes the result.  Scenarios flagged overflow / lost
 // are settled by the first step (mode init) without probes.
-// One workgroup per scenario; the init, without times to add up, one thread.
+// One workgroup or wavefront per scenario; the init, without times to add up,
+// one thread.
 __global__ __launch_bounds__(kTimeThreads) void search_init_kernel(SearchParams P) {
     const int64_t s = (int64_t)blockIdx.x * kTimeThreads + threadIdx.x;
     if (s >= P.S) return;
@@ -241,8 +284,10 @@ __global__ __launch_bounds__(kTimeThreads) void search_init_kernel(SearchParams 
     }
 }
 
+template <int W>
 __global__ __launch_bounds__(kTimeThreads) void search_kernel(SearchParams P, int mode) {
-    const int64_t s = P.first_block + blockIdx.x;
+    const int64_t s = time_scenario<W>(P.first_block);
+    if (s >= P.S) return;
     int32_t* lo = P.work;
     int32_t* hi = P.work + P.S;
     int32_t* probe = P.work + 2 * P.S;
@@ -251,9 +296,10 @@ __global__ __launch_bounds__(kTimeThreads) void search_kernel(SearchParams P, in
     if (p < 0) return;
     const int32_t n = min(max(P.n_iters[s], 0), H);
     bool miss, miss_own;
-    const uint64_t t_r = block_times(P.ips + s * H, P.deadline_at + s * H, n, -1, kNoDeadline, &miss, &miss_own);
+    const uint64_t t_r =
+        scenario_times<W>(P.ips + s * H, P.deadline_at + s * H, n, -1, kNoDeadline, &miss, &miss_own);
     const bool ok = !miss && within_tbt(t_r, P.tbt_slo_ns[s], n);
-    if (threadIdx.x != 0) return;
+    if (time_thread<W>() != 0) return;
     if (mode == 2) {   // final check of lo
         P.freq_idx[s] = ok ? p : F - 1;
         P.status[s] = ok ? TL_STATUS_OK : TL_STATUS_INFEASIBLE;
@@ -288,10 +334,12 @@ __global__ __launch_bounds__(256) void search_final_probe_kernel(SearchParams P)
 }  // namespace
 
 hipError_t launch_admit(const AdmitParams& p, hipStream_t stream) {
-    return launch_parts(p.S, kTimeThreads, [&](dim3 grid, int64_t first) {
+    const bool one = time_waves(p.S, p.H) == 1;
+    const auto kern = one ? admit_kernel<1> : admit_kernel<kTimeWaves>;
+    return launch_parts(one ? (p.S + kTimeWaves - 1) / kTimeWaves : p.S, kTimeThreads, [&](dim3 grid, int64_t first) {
         AdmitParams q = p;
         q.first_block = first;
-        hipLaunchKernelGGL(admit_kernel, grid, dim3(kTimeThreads), 0, stream, q);
+        hipLaunchKernelGGL(kern, grid, dim3(kTimeThreads), 0, stream, q);
     });
 }
 
@@ -303,10 +351,13 @@ hipError_t launch_search_step(const SearchParams& p, int mode, hipStream_t strea
         hipLaunchKernelGGL(search_init_kernel, dim3((unsigned)((p.S + kTimeThreads - 1) / kTimeThreads)),
                            dim3(kTimeThreads), 0, stream, p);
     } else {
-        return launch_parts(p.S, kTimeThreads, [&](dim3 grid, int64_t first) {
+        const bool one = time_waves(p.S, p.H) == 1;
+        const auto kern = one ? search_kernel<1> : search_kernel<kTimeWaves>;
+        const int64_t blocks = one ? (p.S + kTimeWaves - 1) / kTimeWaves : p.S;
+        return launch_parts(blocks, kTimeThreads, [&](dim3 grid, int64_t first) {
             SearchParams q = p;
             q.first_block = first;
-            hipLaunchKernelGGL(search_kernel, grid, dim3(kTimeThreads), 0, stream, q, mode);
+            hipLaunchKernelGGL(kern, grid, dim3(kTimeThreads), 0, stream, q, mode);
         });
     }
     return hipGetLastError();

@@ -133,6 +133,24 @@ def test_binary_search_random(gpu, S, F, H, T, d, nf, mono, seed):
     assert len(set(st.tolist())) >= 2
 
 
+@pytest.mark.parametrize("S,F,H", [(2048, 5, 257), (2049, 5, 257), (2051, 3, 64), (2050, 3, 65), (7, 9, 256),
+                                   (7, 9, 257), (3, 4, 1025), (2049, 2, 513)])
+def test_checks_by_a_wavefront_or_a_workgroup(gpu, S, F, H):
+    """On each side of the rule for one or four wavefronts per scenario in the
+    checks, and of their steps of 64 and 256 iterations."""
+    rng = np.random.default_rng(S + H)
+    fd = random_forest(rng, 4, 4, 3, kvmax=3000, bmax=200)
+    fd["base_score"] = np.float32(45.0)
+    kv, bs = random_curves(rng, S, H, kvmax=3000, bmax=200)
+    freqs = synth.frequency_grid(F)
+    dl, n, tbt, flags = random_checks(rng, S, H, kv)
+    idx, st, work = gpu_binary(fd, freqs, kv, bs, dl, n, tbt, flags, None, want_ips=True)
+    ips = oracle.forest_predict(fd, oracle.rows(freqs, bs, kv, None, 3))
+    oi, os_ = oracle.select_binary(ips, dl, n, tbt, flags)
+    assert np.array_equal(idx, oi) and np.array_equal(st, os_)
+    assert_last_probe_ips(work, ips, last_probes(ips, dl, n, tbt, flags))
+
+
 @pytest.mark.parametrize("S,H", [(4096, 512), (2048, 1000), (4096, 1100), (8192, 1024)])
 def test_binary_search_at_reuse_sizes(gpu, S, H):
     """Grids large enough for the column kernel with leaf reuse along each
