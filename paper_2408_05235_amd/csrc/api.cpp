@@ -125,7 +125,9 @@ tl_status forest_create(int32_t n_trees, int32_t depth, int32_t n_features, floa
 
     tl_forest* f = new (std::nothrow) tl_forest();
     if (!f) return fail(TL_ENOMEM, "tl_forest_create: host allocation failed");
+    int cus = 0;
     hipError_t e = hipGetDevice(&f->device);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, f->device);
     if (e != hipSuccess) { delete f; return from_hip(e, "tl_forest_create: hipGetDevice"); }
     e = hipMalloc(&f->mem, image.size());
     if (e != hipSuccess) {
@@ -140,6 +142,7 @@ tl_status forest_create(int32_t n_trees, int32_t depth, int32_t n_features, floa
     }
     const unsigned char* const mem = (const unsigned char*)f->mem;
     auto array = [&](int q) { return part_bytes[q] > 0 ? mem + at[q] : nullptr; };
+    f->dev.cus = cus;
     f->dev.n_trees = n_trees;
     f->dev.depth = depth;
     f->dev.n_features = n_features;

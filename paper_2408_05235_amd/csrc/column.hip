@@ -334,12 +334,6 @@ __global__ __launch_bounds__(256) void forest_column_global_kernel(const uint2* 
     P.out[c.s * P.H + c.j[0]] = acc;
 }
 
-hipError_t device_cus(int* cus) {
-    int dev = 0;
-    const hipError_t e = hipGetDevice(&dev);
-    return e != hipSuccess ? e : hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev);
-}
-
 // Trees per staged block: double buffers within the LDS budget.  HALF: of
 // trees without their boxes.
 template <bool HALF>
@@ -360,17 +354,14 @@ template <int NF, int RPL, bool ROWS = false>
 hipError_t launch_column_lds(const ForestDev& f, const ColumnParams& c, hipStream_t stream) {
     const int64_t span = kWave * RPL;
     const int64_t items = ROWS ? (c.n_rows + span - 1) / span : c.S * ((c.H + span - 1) / span);
-    int cus = 0;
-    hipError_t e = device_cus(&cus);
-    if (e != hipSuccess) return e;
     // Half a CU's LDS where there are workgroups for both halves, all of it
     // where there are not: fewer, larger copies (500 trees of depth 8: 200 000
     // rows 182 us with all of it, 197 with half; a million 577 and 544).
     size_t lds = 0;
     const int32_t tb =
-        column_trees_per_block<true>(f, items > (int64_t)kColWaves * cus ? kColLdsHalf : kColLdsBudget, &lds);
+        column_trees_per_block<true>(f, items > (int64_t)kColWaves * f.cus ? kColLdsHalf : kColLdsBudget, &lds);
     const auto kern = forest_column_lds_kernel<NF, RPL, ROWS>;
-    e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     return launch_parts((items + kColWaves - 1) / kColWaves, kColThreads, [&](dim3 grid, int64_t first) {
         ColumnParams q = c;
@@ -382,22 +373,15 @@ hipError_t launch_column_lds(const ForestDev& f, const ColumnParams& c, hipStrea
 
 // Rows per lane of the leaf-reuse kernel for these rows: 16 (else 8) where
 // the horizon fills a wavefront's 64 x RPL rows and the grid still gives
-// every CU a workgroup; 0 when the kernel does not apply.  *cus: the
-// device's CUs.
-hipError_t reuse_rows_per_lane(const ForestDev& f, const ColumnParams& c, int* rpl, int* cus) {
-    *rpl = 0;
+// every CU a workgroup; 0 when the kernel does not apply.
+int reuse_rows_per_lane(const ForestDev& f, const ColumnParams& c) {
     size_t lds = 0;
-    if (c.rows || column_trees_per_block<false>(f, kColLdsBudget, &lds) <= 0) return hipSuccess;
-    const hipError_t e = device_cus(cus);
-    if (e != hipSuccess) return e;
+    if (c.rows || column_trees_per_block<false>(f, kColLdsBudget, &lds) <= 0) return 0;
     for (int r : {16, 8}) {
         const int64_t items = c.S * ((c.H + kWave * r - 1) / (kWave * r));
-        if (c.H >= kWave * r && items >= (int64_t)kColWaves * *cus) {
-            *rpl = r;
-            break;
-        }
+        if (c.H >= kWave * r && items >= (int64_t)kColWaves * f.cus) return r;
     }
-    return hipSuccess;
+    return 0;
 }
 
 template <int RPL>
@@ -421,19 +405,14 @@ hipError_t launch_column(const ForestDev& f, const ColumnParams& c, hipStream_t 
     size_t lds = 0;
     const int32_t tb = column_trees_per_block<false>(f, kColLdsBudget, &lds);
     if (tb > 0) {
-        int rpl = 0, cus = 0;
-        const hipError_t e = reuse_rows_per_lane(f, c, &rpl, &cus);
-        if (e != hipSuccess) return e;
+        const int rpl = reuse_rows_per_lane(f, c);
         if (rpl == 16) return launch_column_reuse<16>(f, c, tb, lds, stream);
         if (rpl == 8) return launch_column_reuse<8>(f, c, tb, lds, stream);
     }
     if (tb > 0) {
-        int cus = 0;
-        const hipError_t e = device_cus(&cus);
-        if (e != hipSuccess) return e;
         // rows per lane: 2, with twice the chains to overlap, where that
         // leaves every CU a workgroup and no idle stripes on short horizons
-        if (c.H > kWave && c.S * ((c.H + kWave * 2 - 1) / (kWave * 2)) >= (int64_t)kColWaves * cus)
+        if (c.H > kWave && c.S * ((c.H + kWave * 2 - 1) / (kWave * 2)) >= (int64_t)kColWaves * f.cus)
             return launch_column_lds<NF, 2>(f, c, stream);
         return launch_column_lds<NF, 1>(f, c, stream);
     }
@@ -486,12 +465,11 @@ __global__ __launch_bounds__(256) void column_live_kernel(const uint32_t* __rest
 hipError_t plan_column_order(const ForestDev& f, const ColumnParams& c, int* rpl, PairOrderPlan* p) {
     *p = PairOrderPlan{0, 0, 0, 0};
     if (c.S == 0) return hipSuccess;
-    int cus = 0;
-    const hipError_t e = reuse_rows_per_lane(f, c, rpl, &cus);
-    if (e != hipSuccess || *rpl == 0) return e;
+    *rpl = reuse_rows_per_lane(f, c);
+    if (*rpl == 0) return hipSuccess;
     const int64_t span = kWave * *rpl;
     const int64_t items = c.S * ((c.H + span - 1) / span);
-    return pair_order_plan(f, items, 2 * (int64_t)kColWaves * cus, p);
+    return pair_order_plan(f, items, 2 * (int64_t)kColWaves * f.cus, p);
 }
 
 }  // namespace
@@ -514,24 +492,20 @@ hipError_t order_forest_column(const ForestDev& f, ColumnParams& c, void* ws, hi
 
 hipError_t column_live_bytes(const ForestDev& f, const ColumnParams& c, size_t* bytes) {
     *bytes = 0;
-    int rpl = 0, cus = 0;
     if (c.S == 0 || !c.fidx) return hipSuccess;
-    const hipError_t e = reuse_rows_per_lane(f, c, &rpl, &cus);
-    if (e != hipSuccess || rpl == 0) return e;
+    const int rpl = reuse_rows_per_lane(f, c);
+    if (rpl == 0) return hipSuccess;
     const int64_t span = kWave * rpl;
     const int64_t items = c.S * ((c.H + span - 1) / span);
     // as for the work order: with one workgroup per CU the launch lasts as
     // long as its slowest workgroup, compacted or not
-    if (items < 2 * (int64_t)kColWaves * cus) return hipSuccess;
+    if (items < 2 * (int64_t)kColWaves * f.cus) return hipSuccess;
     *bytes = (((size_t)items * sizeof(uint32_t) + 255) & ~(size_t)255) + 256;
     return hipSuccess;
 }
 
 hipError_t launch_forest_column_live(const ForestDev& f, const ColumnParams& c, void* ws, hipStream_t stream) {
-    int rpl = 0, cus = 0;
-    hipError_t e = hipSuccess;
-    if (ws && c.fidx && c.S > 0) e = reuse_rows_per_lane(f, c, &rpl, &cus);
-    if (e != hipSuccess) return e;
+    const int rpl = ws && c.fidx && c.S > 0 ? reuse_rows_per_lane(f, c) : 0;
     if (rpl == 0) return launch_forest_column(f, c, stream);
     const int32_t span = kWave * rpl;
     const int32_t n_cols = (c.H + span - 1) / span;
@@ -539,7 +513,7 @@ hipError_t launch_forest_column_live(const ForestDev& f, const ColumnParams& c, 
     uint32_t* live = (uint32_t*)ws;
     int32_t* n_live = (int32_t*)((unsigned char*)ws + (((size_t)items * sizeof(uint32_t) + 255) & ~(size_t)255));
     hipLaunchKernelGGL(column_live_clear_kernel, dim3(1), dim3(1), 0, stream, n_live);
-    e = hipGetLastError();
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (!grid_fits((items + 255) / 256, 256)) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(column_live_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, stream, c.order,
@@ -562,14 +536,11 @@ hipError_t launch_forest_rows_lds(const ForestDev& f, const float* rows, int64_t
     c.rows = rows;
     c.n_rows = n_rows;
     c.out = out;
-    int cus = 0;
-    const hipError_t e = device_cus(&cus);
-    if (e != hipSuccess) return e;
     const bool four = f.n_features == 4;
     // two rows a lane where that leaves every CU a workgroup (four, at half
     // the wavefronts a CU: 500 trees of depth 8 on 3 M rows 1559 against 1443 us,
     // 2000 of depth 10 on 1.5 M 6037 against 4793)
-    if (n_rows >= (int64_t)2 * kColThreads * cus)
+    if (n_rows >= (int64_t)2 * kColThreads * f.cus)
         return four ? launch_column_lds<4, 2, true>(f, c, stream) : launch_column_lds<3, 2, true>(f, c, stream);
     return four ? launch_column_lds<4, 1, true>(f, c, stream) : launch_column_lds<3, 1, true>(f, c, stream);
 }

@@ -546,16 +546,12 @@ hipError_t launch_grid_lds(const ForestDev& f, const GridParams& g, int32_t tb, 
 // 4133 / 3366 / 4563, 256 boards of the former 1999 / 1427 / 1265.
 // *ordered: 32 rows, and more workgroups than start at once: only then does a
 // work order pay.  *alone: at most one workgroup per CU.
-hipError_t grid_rows(const ForestDev& f, const GridParams& g, int* J, bool* ordered, bool* alone) {
-    int dev = 0, cus = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-    auto fits = [&](int rows) { return grid_workgroups(g, rows) * std::max(f.depth, 1) <= 16 * (int64_t)cus; };
+void grid_rows(const ForestDev& f, const GridParams& g, int* J, bool* ordered, bool* alone) {
+    const int64_t cus = f.cus;
+    auto fits = [&](int rows) { return grid_workgroups(g, rows) * std::max(f.depth, 1) <= 16 * cus; };
     *J = fits(8) ? 8 : fits(16) ? 16 : kLdsJ;
-    *ordered = *J == kLdsJ && grid_workgroups(g, kLdsJ) > 2 * (int64_t)cus;
+    *ordered = *J == kLdsJ && grid_workgroups(g, kLdsJ) > 2 * cus;
     *alone = grid_workgroups(g, *J) <= cus;
-    return hipSuccess;
 }
 
 template <int NF>
@@ -661,8 +657,8 @@ hipError_t plan_order(const ForestDev& f, const GridParams& g, PairOrderPlan* p)
     int J = 0;
     bool ordered = false;
     bool alone = false;
-    const hipError_t e = grid_rows(f, g, &J, &ordered, &alone);
-    if (e != hipSuccess || !ordered) return e;
+    grid_rows(f, g, &J, &ordered, &alone);
+    if (!ordered) return hipSuccess;
     return pair_order_plan(f, g.S * ((g.H + kOrderJ - 1) / kOrderJ), 1, p);
 }
 
@@ -694,8 +690,7 @@ hipError_t launch_forest_grid(const ForestDev& f, const GridParams& g_in, void* 
     int J = 0;
     bool ordered = false;
     bool alone = false;
-    e = grid_rows(f, g, &J, &ordered, &alone);
-    if (e != hipSuccess) return e;
+    grid_rows(f, g, &J, &ordered, &alone);
     // a workgroup with a CU to itself stages twice as many trees at a time
     if (alone) tb = lds_trees_per_block(f, 2 * kLdsBudget, &lds);
     if (grid_parts(g) == 2)

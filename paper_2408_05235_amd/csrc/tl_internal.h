@@ -137,6 +137,7 @@ struct SelectParams {
 struct ForestDev {
     int32_t n_trees, depth, n_features;
     float base_score;
+    int32_t cus;            // of its device
     const uint2* nodes;     // [T][2^d]: .x = threshold bits, .y = feature (entry 2^d - 1 unused)
     const float* leaves;    // [T][2^d]
     // Per leaf, the KV (feature 1) and batch (feature 2) constraints of its

@@ -157,15 +157,17 @@ def test_captured_binary_search_replays(gpu):
     forest.close()
 
 
-def test_call_on_another_thread_while_capturing(gpu):
+@pytest.mark.parametrize("T", [30, 200])
+def test_call_on_another_thread_while_capturing(gpu, T):
     """A call on another thread and stream while this thread captures: it asks
     whether the forest's scratch is idle, which must neither fail nor end the
-    capture (in the default mode, which holds for every thread)."""
+    capture (in the default mode, which holds for every thread).  200 trees: a
+    call with few rows, which takes scratch; 30: one that takes none."""
     import threading
     import torch
     from paper_2408_05235_amd import api
     rng = np.random.default_rng(47)
-    fd = random_forest(rng, 30, 8, 3)
+    fd = random_forest(rng, T, 8, 3)
     kv, bs = random_curves(rng, 6, 300)
     freqs = synth.frequency_grid(64)
     exp = oracle.forest_predict(fd, oracle.rows(freqs, bs, kv, None, 3))

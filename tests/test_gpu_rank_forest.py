@@ -80,9 +80,8 @@ def test_several_rank_groups_along_the_horizon(H, S):
     assert np.array_equal(got[pick], exp)
 
 
-# trees of depth 11: calls of up to 330 000 grid rows (165 000 of the others)
-# run as ones with few rows; then 8, 16 or 32 grid rows a wavefront (the last
-# also with a work order), and one or two column rows a lane
+# too few trees to run as a call with few rows: 8, 16 or 32 grid rows a
+# wavefront (the last also with a work order), and one or two column rows a lane
 @pytest.mark.parametrize("S,F,H", [(5, 70, 190), (40, 70, 190), (250, 9, 190), (500, 5, 190), (1500, 3, 190)])
 def test_grid_kernel_choice(S, F, H):
     rng = np.random.default_rng(S)
@@ -151,3 +150,39 @@ def test_few_rows_many_trees(T):
     S, F, H = (6, 20, 75) if T > 1000 else (2, 9, 77)
     kv, bs = random_curves(rng, S, H, kvmax=3000, bmax=200)
     _grid(fd, synth.frequency_grid(F), kv, bs, None)
+
+
+@pytest.mark.parametrize("S,F,H,T,d,nf", [
+    (1, 17, 16, 23, 4, 3), (1, 17, 16, 24, 4, 3), (5, 70, 190, 16, 11, 4), (5, 70, 190, 17, 11, 4), (1, 1, 1, 134, 1, 3),
+    (2, 30, 500, 300, 1, 4), (2, 31, 500, 300, 1, 4),
+])
+def test_few_rows_choice(S, F, H, T, d, nf):
+    """Calls on each side of the rule by rows and levels that gives calls with
+    few rows two launches (the grid's rows as a caller's own as well)."""
+    rng = np.random.default_rng(S * F + T)
+    fd = random_forest(rng, T, d, nf, kvmax=3000, bmax=200)
+    kv, bs = random_curves(rng, S, H, kvmax=3000, bmax=200)
+    _grid(fd, synth.frequency_grid(F), kv, bs, rng.choice([1.0, 2.0, 4.0, 8.0], S).astype(np.float32) if nf == 4 else None)
+
+
+@pytest.mark.parametrize("S,H,T", [(3, 65, 18), (3, 65, 19), (700, 190, 60), (1000, 190, 60), (1100, 1, 40)])
+def test_few_column_rows_choice(S, H, T):
+    """The same for one candidate frequency per scenario, some flagged lost."""
+    import torch
+    from paper_2408_05235_amd import api
+    rng = np.random.default_rng(S)
+    fd = random_forest(rng, T, 11, 3, kvmax=3000, bmax=200)
+    kv, bs = random_curves(rng, S, H, kvmax=3000, bmax=200)
+    lost = rng.random(S) < 0.2
+    f = api.Forest.from_dict(fd)
+    out = dict(ips_work=torch.full((S, H), -1.0, device="cuda"))
+    full = lambda v, dt: torch.full((S,), v, dtype=dt, device="cuda")
+    freqs = np.array([1400.0], np.float32)
+    api.tl_select_freq_binary(f, _dev(freqs, np.float32), _dev(kv, np.int32), _dev(bs, np.int32),
+                              torch.full((S, H), -1, dtype=torch.int64, device="cuda"), full(H, torch.int32),
+                              full(30_000_000, torch.int64), _dev(lost * 2, np.int32), None, out)
+    got = out["ips_work"].cpu().numpy()
+    f.close()
+    exp = oracle.forest_predict(fd, oracle.rows(freqs, bs, kv, None, 3)).reshape(S, H)
+    exp[lost] = -1.0
+    assert np.array_equal(got, exp)
