@@ -20,9 +20,16 @@ def _p(t):
     return None if t is None else t.data_ptr()
 
 
+# The raw handle of torch.cuda.current_stream() without a Stream object, by
+# functions that torch keeps for its own use: None where it has them no more.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
-    # the raw handle of torch.cuda.current_stream(), without a Stream object
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None or _raw_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_raw_device())
 
 
 def _need(t, dtype, name, shape=None):
