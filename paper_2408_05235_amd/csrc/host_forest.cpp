@@ -42,45 +42,6 @@ void leaf_boxes(int32_t n_trees, int32_t depth, const uint8_t* feature, const fl
     }
 }
 
-uint32_t box_bound(float x, uint32_t maxv) {
-    const double c = std::ceil((double)x);
-    if (!(c > 0.0)) return 0;
-    if (c >= (double)maxv) return maxv;
-    return (uint32_t)c;
-}
-
-void build_records(int32_t n_trees, int32_t depth, const uint8_t* feature, const float* threshold, const float* leaf,
-                   const std::vector<Box>& boxes, std::vector<unsigned char>& out) {
-    // node slots (threshold, sel_lo, sel_hi, leaf value; sel_lo picks
-    // frequency / KV and batch / engine size by bit 0 of the feature, sel_hi
-    // between the two by bit 1), then the leaf boxes as packed integer bounds
-    constexpr uint32_t kLow = 0x03020100u, kHigh = 0x07060504u;
-    const int64_t n_int = (1ll << depth) - 1;
-    const int64_t n_leaf = 1ll << depth;
-    const RecordLayout R = record_layout(depth);
-    out.assign((size_t)n_trees * R.bytes + 64, 0);
-    for (int64_t t = 0; t < n_trees; ++t) {
-        unsigned char* rec = out.data() + (size_t)t * R.bytes;
-        uint32_t slot[4];
-        for (int64_t k = 0; k < n_leaf; ++k) {
-            slot[0] = slot[1] = slot[2] = 0;
-            if (k < n_int) {
-                const int64_t i = t * n_int + k;
-                const int fi = feature[i];
-                std::memcpy(&slot[0], &threshold[i], 4);
-                slot[1] = (fi & 1) ? kHigh : kLow;
-                slot[2] = (fi & 2) ? kHigh : kLow;
-            }
-            std::memcpy(&slot[3], &leaf[t * n_leaf + k], 4);
-            std::memcpy(rec + 16 * k, slot, 16);
-            const Box& b = boxes[(size_t)(t * n_leaf + k)];
-            const uint32_t w[2] = {box_bound(b.kv_lo, kBoxKvMax) | box_bound(b.batch_lo, kBoxBatchMax) << 20,
-                                   box_bound(b.kv_hi, kBoxKvMax) | box_bound(b.batch_hi, kBoxBatchMax) << 20};
-            std::memcpy(rec + R.boxes + 8 * k, w, 8);
-        }
-    }
-}
-
 namespace {
 
 // the order of non-NaN floats as the order of their 32-bit keys
@@ -218,17 +179,6 @@ void build_rank_records(int32_t n_trees, int32_t depth, const uint8_t* feature, 
             }
         }
     }
-}
-
-std::vector<float> threshold_cuts(int64_t n_nodes, const uint8_t* feature, const float* threshold, int fi) {
-    std::vector<float> t;
-    for (int64_t i = 0; i < n_nodes; ++i)
-        if (feature[i] == fi && std::isfinite(threshold[i])) t.push_back(threshold[i]);
-    std::sort(t.begin(), t.end());
-    if ((int64_t)t.size() <= kMaxCuts) return t;
-    std::vector<float> c(kMaxCuts);
-    for (int64_t i = 0; i < kMaxCuts; ++i) c[(size_t)i] = t[(size_t)(i * (int64_t)t.size() / kMaxCuts)];
-    return c;
 }
 
 }  // namespace host

@@ -1,6 +1,6 @@
 // Host-side preparation of a tree ensemble for the kernels (plain C++, no
-// HIP): the KV / batch box of every leaf and the LDS tree records.  Trees are complete, depth d,
-// heap order: internal node k tests x[feature] < threshold and continues at
+// HIP): the KV / batch box of every leaf for trees too deep to stage, the rank
+// records of the others.  Trees are complete, depth d, heap order: internal node k tests x[feature] < threshold and continues at
 // 2k+1 if true, at 2k+2 otherwise (Sec. 4.3.1 model M).
 #pragma once
 
@@ -26,18 +26,6 @@ struct Box {
 void leaf_boxes(int32_t n_trees, int32_t depth, const uint8_t* feature, const float* threshold,
                 std::vector<Box>& out);
 
-// One bound of a leaf box as stored in the records: ceil(x) clamped to
-// [0, maxv] (for integer inputs, x >= lo iff x >= ceil(lo) and x < hi iff
-// x < ceil(hi); clamping can only shrink the box).
-uint32_t box_bound(float x, uint32_t maxv);
-
-// Records with fp32 thresholds (no kernel reads them; the host check compares
-// their boxes with walks): all trees (record_layout(depth).bytes each, back to back,
-// plus 64 bytes of padding) from the node arrays [n_trees][2^depth - 1], the
-// leaves [n_trees][2^depth] and the leaf boxes.  depth <= kMaxRecordDepth.
-void build_records(int32_t n_trees, int32_t depth, const uint8_t* feature, const float* threshold, const float* leaf,
-                   const std::vector<Box>& boxes, std::vector<unsigned char>& out);
-
 // The rank records of all trees (rank_record_bytes(depth) each, back to back,
 // plus 64 bytes of padding), and the groups, dictionaries and bucket tables
 // that rank rows for them (record_format.h).  depth <= kMaxRecordDepth,
@@ -51,10 +39,6 @@ struct RankForest {
 };
 void build_rank_records(int32_t n_trees, int32_t depth, const uint8_t* feature, const float* threshold,
                         const float* leaf, RankForest& out);
-
-// (Also for the host check only.)  Up to kMaxCuts quantiles of the finite thresholds of feature fi over
-// n_nodes nodes, ascending.
-std::vector<float> threshold_cuts(int64_t n_nodes, const uint8_t* feature, const float* threshold, int fi);
 
 }  // namespace host
 }  // namespace tl

@@ -13,45 +13,7 @@
 
 namespace tl {
 
-constexpr int32_t kMaxCuts = 4096;
-
 constexpr int kMaxRecordDepth = 11;
-
-// One tree with fp32 thresholds and leaf boxes as integer bounds (byte ranges,
-// each starting on a 16-byte boundary).  The kernels read the rank records
-// below; this form is only built by the host check of the leaf boxes.
-//   [0, boxes)      2^d node slots of 16 bytes, slot k = (threshold,
-//                   sel_lo, sel_hi, value of leaf k).  The selectors are
-//                   byte-permute selectors that pick the tested feature c
-//                   out of (frequency, KV, batch, engine size): sel_lo picks
-//                   between frequency and KV and, with the same selector,
-//                   between batch and engine size (bit 0 of c), sel_hi
-//                   between the two picks (bit 1 of c).  A row goes to 2k+1
-//                   iff x_c < threshold.  Slot 2^d - 1 holds no node, only
-//                   the last leaf's value.
-//   [boxes, bytes)  leaf boxes, 8 bytes per leaf: the leaf's KV / batch box
-//                   (kvb_box) as integer bounds, word 0 = kv_lo | batch_lo
-//                   << 20, word 1 = kv_hi | batch_hi << 20, meaning kv_lo <=
-//                   KV < kv_hi and batch_lo <= batch < batch_hi for integer
-//                   KV and batch.  The bounds are rounded up to integers and
-//                   clamped to [0, 2^20 - 1] (KV) and [0, 2^12 - 1] (batch);
-//                   a clamped box is a subset of the leaf's own, so a row
-//                   inside it still reaches the leaf, and a row outside it
-//                   only walks the tree again.
-constexpr uint32_t kBoxKvMax = (1u << 20) - 1;
-constexpr uint32_t kBoxBatchMax = (1u << 12) - 1;
-
-struct RecordLayout {
-    uint32_t boxes, bytes;
-};
-
-TL_HOST_DEVICE inline RecordLayout record_layout(int32_t depth) {
-    const uint32_t n_leaf = 1u << depth;
-    RecordLayout r;
-    r.boxes = 16u * n_leaf;
-    r.bytes = r.boxes + ((8u * n_leaf + 15u) & ~15u);
-    return r;
-}
 
 // The tree records that the kernels stage into LDS hold ranks instead of
 // thresholds.  Trees are cut into groups of group_trees consecutive trees;

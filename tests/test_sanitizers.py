@@ -3,7 +3,7 @@
 The C oracle (every entry point, on edge cases: empty and malformed
 scoreboards, queues under caps, the size guard, special IPS values, depth 0
 to 12 forests with NaN / inf thresholds) and the library's host-side forest
-preparation (leaf boxes, tree records, cuts; checked against plain tree walks
+preparation (leaf boxes; checked against plain tree walks
 on odd depths and NaN / inf thresholds) are built with gcc / g++ and
 -fsanitize=address,undefined; a sanitizer report or a failed check fails the
 test, and the checksum of everything computed must equal that of a plain -O2
