@@ -134,15 +134,20 @@ __global__ __launch_bounds__(kGatherThreads) void lattice_gather_kernel(ForestDe
         // in flight before its (streaming) stores.  A point's run starts at a
         // multiple of 4 F bytes: the 16-byte loads need 4-byte alignment only.
         // (One load, one store at a time where 4 did not divide F: 1024 boards
-        // x 17 frequencies x 512 iterations took 37 us.)
+        // x 17 frequencies x 512 iterations took 37 us.  Single values for all
+        // of the rest: 4096 boards x 4 x 1024 60 us, by 16 bytes 33.)
         for (; fi + 64 <= F; fi += 64) put_values<16>(t + fi, out + (int64_t)fi * P.H, P.H);
         for (; fi + 16 <= F; fi += 16) put_values<4>(t + fi, out + (int64_t)fi * P.H, P.H);
-        float v[15];
+        if (F - fi >= 12) put_values<3>(t + fi, out + (int64_t)fi * P.H, P.H);
+        else if (F - fi >= 8) put_values<2>(t + fi, out + (int64_t)fi * P.H, P.H);
+        else if (F - fi >= 4) put_values<1>(t + fi, out + (int64_t)fi * P.H, P.H);
+        fi += (F - fi) & ~3;
+        float v[3];
 #pragma unroll
-        for (int k = 0; k < 15; ++k)
+        for (int k = 0; k < 3; ++k)
             if (fi + k < F) v[k] = t[fi + k];
 #pragma unroll
-        for (int k = 0; k < 15; ++k)
+        for (int k = 0; k < 3; ++k)
             if (fi + k < F) __builtin_nontemporal_store(v[k], out + (int64_t)(fi + k) * P.H);
     } else {
         for (int32_t fi = 0; fi < F; ++fi) {

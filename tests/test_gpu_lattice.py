@@ -47,6 +47,23 @@ def test_lattice_random(gpu, F, T, d, nf, kv_max, b_max, seed):
     lat.close()
 
 
+@pytest.mark.parametrize("F", [2, 3, 4, 6, 8, 11, 12, 15, 16, 19, 24, 31, 47, 63, 64, 65, 79, 95])
+def test_lattice_every_remainder(gpu, F):
+    """Frequency counts around the lookup's groups of 64, 16, 12, 8, 4 and
+    single values, on and off the lattice."""
+    from paper_2408_05235_amd import api
+    rng = np.random.default_rng(1200 + F)
+    fd = random_forest(rng, 6, 4, 3, kvmax=120, bmax=9)
+    kv, bs = random_curves(rng, 3, 290, kvmax=110, bmax=9)
+    freqs = synth.frequency_grid(F)
+    f = api.Forest.from_dict(fd)
+    lat = api.Lattice(f, _t(freqs), 100, 8)
+    got = lat.tl_lattice_predict_grid(_t(kv), _t(bs)).cpu().numpy()
+    assert np.array_equal(got, oracle.forest_predict(fd, oracle.rows(freqs, bs, kv, None, 3)))
+    lat.close()
+    f.close()
+
+
 def test_lattice_scaled_c3(gpu):
     """c3's forest (300 of its trees) over the lattice the workload spans,
     in the controller: the same IPS and selection as the grid kernel."""
