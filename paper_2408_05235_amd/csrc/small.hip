@@ -239,15 +239,20 @@ size_t small_bytes(const ForestDev& f, const SmallParams& p) {
     // rows 178 against 203 us, 300 000 rows 483 against 403; the grid of 4 boards
     // x 64 x 1024 436 against 421, 16 boards 1559 against 546.)
     if (n > (p.grid ? 30000 : 15000) * (int64_t)f.depth) return 0;
-    // ... and from this many levels on (two more a tree; twice as many from
+    // ... and from this many levels on (three more a tree; twice as many from
     // depth 10, where a buffer holds few trees): the second launch takes about
     // 5 us, which few trees' walks are over in.  (us, two launches / one: the
     // grid of one board x 17 x 512 with 20 trees of depth 4 11 / 11, 40 11 / 17, 8
     // boards with 20 of 8 18 / 16, 40 24 / 27; 1024 rows with 20 of 8 12 / 11, 40 12 /
     // 19; a search on one board x 16 with 30 of 8 70 / 59, 40 69 / 73; on 8 x 512
     // with 20 of 8 78 / 75, 30 87 / 100, 10 of 10 90 / 80, 15 92 / 96.)
-    const int64_t levels = (int64_t)f.n_trees * (f.depth < 10 ? f.depth + 2 : 2 * f.depth);
-    if (levels <= (p.grid ? 140 + n / 300 : n < 1024 ? 400 : 230 + n / 300)) return 0;
+    const int64_t levels = (int64_t)f.n_trees * (f.depth < 10 ? f.depth + 3 : 2 * f.depth);
+    // (No more than that on larger calls, where the grid kernel's time depends on
+    // how KV and batch move: 60 trees of depth 5, one board x 64 x 2048 with
+    // KV drawn anew at every iteration 34 / 133.)
+    const int64_t most = p.grid ? std::min<int64_t>(150 + n / 300, 270)
+                       : n < 1024 ? 400 : std::min<int64_t>(250 + n / 300, 350);
+    if (levels <= most) return 0;
     return (size_t)slice_rows(f.n_trees, n) * f.n_trees * sizeof(float);
 }
 

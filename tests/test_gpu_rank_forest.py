@@ -153,7 +153,7 @@ def test_few_rows_many_trees(T):
 
 
 @pytest.mark.parametrize("S,F,H,T,d,nf", [
-    (1, 17, 16, 23, 4, 3), (1, 17, 16, 24, 4, 3), (5, 70, 190, 16, 11, 4), (5, 70, 190, 17, 11, 4), (1, 1, 1, 134, 1, 3),
+    (1, 17, 16, 21, 4, 3), (1, 17, 16, 22, 4, 3), (5, 70, 190, 12, 11, 4), (5, 70, 190, 13, 11, 4), (1, 1, 1, 101, 1, 3),
     (2, 30, 500, 300, 1, 4), (2, 31, 500, 300, 1, 4),
 ])
 def test_few_rows_choice(S, F, H, T, d, nf):
