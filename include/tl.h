@@ -232,10 +232,10 @@ tl_status tl_project(const tl_project_args* args, void* stream);
  * Stage 2 -- the model M on arbitrary feature rows (Sec. 4.3.1).
  * rows [n_rows][n_features of the forest] fp32 row-major; out [n_rows] fp32.
  * Calls with few rows (here, on the grid and at one frequency per scenario)
- * are cut along the trees as well and take up to 64 MiB of the forest
- * handle's device scratch (tl_forest_predict_grid says how it is kept);
- * without it, or under stream capture, they give the same results in more
- * time.
+ * of forests with many trees are cut along the trees as well and take up to 64
+ * MiB of the forest handle's device scratch (tl_forest_predict_grid says how it
+ * is kept); without it, or under stream capture, they give the same results in
+ * more time.
  * ---------------------------------------------------------------------- */
 tl_status tl_forest_predict(const tl_forest* forest, const float* rows, int64_t n_rows,
                             float* out, void* stream);
@@ -264,7 +264,8 @@ tl_status tl_forest_predict(const tl_forest* forest, const float* rows, int64_t 
  * runs without the ordering (same results; tl_forest_predict_grid_noalloc
  * keeps it under capture).  A call takes the array its stream used last, or an
  * idle one; when four other streams' calls still use all of them it first
- * waits (on the device) for the previous call's work.  The forest's device
+ * waits (on the device) for the previous call's work.  (On hipStreamPerThread
+ * every thread has a stream of its own.)  The forest's device
  * must be the current device.
  * ---------------------------------------------------------------------- */
 tl_status tl_forest_predict_grid(const tl_forest* forest, int64_t n_scenarios, int32_t n_freqs,
@@ -369,7 +370,9 @@ tl_status tl_select_freq(const float* ips, int64_t n_scenarios, int32_t n_freqs,
  * Scratch: 20 bytes per wavefront plus a radix sort's temporary storage, in
  * the forest's device scratch, as for tl_forest_predict_grid (the larger of
  * the two needs is kept; neither ordering nor compaction under stream
- * capture or without the scratch).  Nothing else is allocated.
+ * capture or without the scratch).  With few rows (S x H) and many trees the
+ * model's evaluations take up to 64 MiB of it instead (tl_forest_predict).
+ * Nothing else is allocated.
  * lattice (nullable): a table of the same forest and frequency count
  * (tl_lattice_create; TL_EINVAL otherwise); M at the probes is then read
  * from it, at the lattice's own frequencies (the same values when it was
@@ -410,7 +413,8 @@ tl_status tl_select_freq_binary(const tl_forest* forest, int64_t n_scenarios, in
  * of scenarios flagged TL_FLAG_OVERFLOW hold M on the zero curves).  All
  * arrays are device arrays of the caller; the only scratch is the
  * projection's scenario order, as for tl_project, and the model kernel's
- * work order, as for tl_select_freq_binary.
+ * work order or, with few rows, its leaf values, as for
+ * tl_select_freq_binary.
  * Errors as for tl_project, plus a NULL forest, ips, decision, tbt_slo_ns,
  * cand_prompt or cand_len, or a forest without 3 or 4 features: TL_EINVAL.
  * ---------------------------------------------------------------------- */

@@ -17,8 +17,8 @@
 // fp32 add per tree; a walk happens on roughly one row in twenty.
 //
 //   forest_grid_lds_kernel     (depth <= 11) A 1024-thread workgroup (16
-//       wavefronts, 16 x 64 x 64 rows) walks the ensemble in blocks of trees
-//       staged in LDS buffers.  A tree is one rank record (nodes, leaf values,
+//       wavefronts of 32, 16 or 8 iterations x 64 frequencies, see grid_rows)
+//       walks the ensemble in blocks of trees staged in LDS buffers.  A tree is one rank record (nodes, leaf values,
 //       leaf boxes; record_format.h), so a block is one contiguous copy, made
 //       straight from global memory into LDS and handed from wavefront to
 //       wavefront without block barriers (stage_acquire / stage_release).

@@ -9,8 +9,8 @@
 //   forest_leaves_kernel   a workgroup takes a tile of rows (one row a lane)
 //       and a chunk of trees staged into LDS, and writes the value of the
 //       leaf that each row reaches in each tree to a scratch array
-//       [64 rows][tree][row of the 64].  Four trees are walked at once (four chains of dependent
-//       LDS reads in flight a lane).
+//       [64 rows][tree][row of the 64].  Four trees are walked at once (four
+//       chains of dependent LDS reads in flight a lane).
 //   forest_sum_kernel      adds each row's values in tree order: eight
 //       wavefronts fetch the values of 64 rows, 32 trees a wavefront in
 //       flight, through LDS, and one of them adds.
