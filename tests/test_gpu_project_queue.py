@@ -58,7 +58,8 @@ def test_batch_cap_paths(S, H, N, R, Q, cap_kv, cap_batch):
 
 @pytest.mark.parametrize("S,H,N,R,Q,cap_kv", [
     (257, 400, 16, 6, 700, 900), (1280, 130, 24, 4, 260, 300), (1281, 130, 16, 4, 260, 300), (300, 2950, 16, 30, 130, 500),
-    (1290, 2950, 8, 3, 190, 500), (5, 640, 16, 10, 2600, 700), (258, 70, 16, 2, 1100, 500), (1281, 64, 16, 0, 200, 0),
+    (1290, 2950, 8, 3, 190, 500), (5, 640, 16, 10, 2600, 700), (258, 70, 16, 2, 1100, 500), (270, 70, 24, 2, 1100, 400),
+    (1281, 64, 16, 0, 200, 0),
 ])
 def test_loop_wavefronts(S, H, N, R, Q, cap_kv):
     """On each side of the rules for one or four wavefronts a board and in the
