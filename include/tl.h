@@ -33,7 +33,8 @@
  *   - Data-dependent anomalies never fail a call: they are reported per
  *     scenario through TL_FLAG_* bits and TL_STATUS_* values.
  *   - Results are deterministic: bit-identical across runs and launches.
- *   - A call takes up to 2^26 - 4 scenarios (memory permitting); launches of
+ *   - A call takes up to 2^26 - 4 scenarios (memory permitting; feature rows
+ *     written out and table lookups: scenarios x 256 iterations); launches of
  *     more fail with TL_EDEVICE.
  */
 #ifndef TL_H

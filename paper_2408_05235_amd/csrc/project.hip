@@ -581,8 +581,10 @@ __global__ __launch_bounds__(W* kWave) void project_kernel(ProjectParams P) {
                 // sum fits everywhere, so does every request's own check at
                 // its target (each sees the KV of the requests before it, which
                 // is no more than the sum): these are the admissions that the
-                // one-at-a-time loop makes.  Otherwise the most leading chunks
-                // of 64 requests that fit together are found by bisection.
+                // one-at-a-time loop makes.  Otherwise some leading chunks of 64
+                // requests that fit together: the chunks that have arrived when
+                // the whole sum first exceeds the capacity (without later
+                // arrivals it falls from there), and the like (QueueTries).
                 const int64_t first = cb + kWave;
                 const int32_t n_ch = (int32_t)((hi - first + kWave - 1) / kWave);
                 const int32_t lo_j = max(j, last_over + 1);
@@ -696,243 +698,243 @@ __global__ __launch_bounds__(W* kWave) void project_kernel(ProjectParams P) {
                         again = true;
                         break;
                     }
-                while (mask == 0) {
-                    cb += kWave;
-                    if (cb >= hi) break;
-                    const int64_t i = cb + lane;
-                    bool q = false;
-                    if (i < hi) {
-                        q_arr = P.arr[i];
-                        const int32_t p = P.prompt[i], g = P.gen[i];
-                        q_len = P.rem[i];
-                        q = entry_ok(p, g, q_len, q_arr) && q_arr >= 0;
-                        q_c = p + g;
-                        q_lost = P.lost ? P.lost[i] : 0;
-                        q_dl = P.deadline ? P.deadline[i] : kNoDeadline;
-                    }
-                    mask = __ballot(q);
-                    if (!CAP && mask) {
-                        q_max = wave_incl_max(q ? q_arr : -1);
-                        q_c0 = q ? (int32_t)ceil_div_u32((uint32_t)q_c, divN) : 0;
-                        q_sum = wave_incl_scan(q_c0);
-                    }
-                }
-                if (mask == 0) break;
-
-                if (!CAP && at_targets) {
-                    // The rest of this chunk of the queue, each at its FIFO
-                    // target, as above; their contributions are added to the KV
-                    // curve iteration by iteration and taken out again when they
-                    // do not fit.
-                    const int32_t lo_j = max(j, last_over + 1);
-                    const bool mem = (mask >> lane) & 1;
-                    const int32_t a = wave_incl_max(mem ? max(q_arr, lo_j) : -1);
-                    const uint64_t memm = __ballot(mem);
-                    const uint64_t over = __ballot(mem && a >= H);
-                    const uint64_t take = over ? (memm & ((over & (~over + 1)) - 1)) : memm;
-                    if (take == 0) break;   // the head cannot start within the horizon
-                    // each member's in-horizon end, on its own lane
-                    const int32_t lim_l = q_len >= H - a ? H : a + q_len;
-                    const int32_t a_first = __builtin_amdgcn_readlane(a, __ffsll((unsigned long long)take) - 1);
-                    int32_t r_end = 0;
-                    add_members<A, false, POW2>(KV, take, q_c, a, lim_l, divN, wave, &r_end);
-                    if (!members_fit<A>(sh, turn, KV, a_first, r_end, kv_fits ? INT32_MAX : cap)) {
-                        // take the batch's contributions out again
-                        add_members<A, true, POW2>(KV, take, q_c, a, lim_l, divN, wave, &r_end);
-                        curves_sync<A>();
-                        at_targets = false;
-                        streak = 0;
-                        calm = 0;
-                        calm_need = min(256, 2 * calm_need);
-                        continue;
-                    }
-                    if (wave == 0 && ((take >> lane) & 1)) {
-                        const int64_t e = (int64_t)a + q_len;
-                        atomicAdd(&BD[a], 1);
-                        if (e < H) atomicAdd(&BD[e], -1);
-                        if (e <= H && !q_lost && q_dl != kNoDeadline)
-                            atomicMin((unsigned long long*)&outDL[e - 1], (unsigned long long)q_dl);
-                    }
-                    n_end = max(n_end, r_end);
-                    j = __builtin_amdgcn_readlane(a, 63 - __clzll((long long)take));
-                    mask &= ~take;
-                    ++streak;
-                    if (streak >= 4) calm_need = 4;
-                    if (over) break;
-                    continue;
-                }
-
-                if (!CAP && !alone) {
-                    // The capacity binds: the head and the requests behind it that
-                    // have arrived by its start j, as many as the KV of iteration
-                    // j itself leaves room for.  When their sum fits everywhere,
-                    // they are the one-at-a-time loop's admissions at j, and the
-                    // next of them does not fit at j.  A head without room at j
-                    // starts no earlier than the next iteration that has it.
-                    const bool queued = (mask >> lane) & 1;
-                    const int hl = __ffsll((unsigned long long)mask) - 1;
-                    const int32_t start = max(max(j, last_over + 1), __builtin_amdgcn_readlane(q_max, hl));
-                    const int32_t c_h = __builtin_amdgcn_readlane(q_c0, hl);
-                    int32_t room = -1, found = -1;
-                    for (int32_t t0 = start; t0 < H; t0 += kWave) {
-                        const int32_t t = t0 + lane;
-                        const int32_t left = cap - KV[min(t, H - 1)];
-                        const uint64_t m = __ballot(t < H && left >= c_h);
-                        if (m) {
-                            const int l = __ffsll((unsigned long long)m) - 1;
-                            found = t0 + l;
-                            room = __builtin_amdgcn_readlane(left, l);
-                            break;
+                    while (mask == 0) {
+                        cb += kWave;
+                        if (cb >= hi) break;
+                        const int64_t i = cb + lane;
+                        bool q = false;
+                        if (i < hi) {
+                            q_arr = P.arr[i];
+                            const int32_t p = P.prompt[i], g = P.gen[i];
+                            q_len = P.rem[i];
+                            q = entry_ok(p, g, q_len, q_arr) && q_arr >= 0;
+                            q_c = p + g;
+                            q_lost = P.lost ? P.lost[i] : 0;
+                            q_dl = P.deadline ? P.deadline[i] : kNoDeadline;
+                        }
+                        mask = __ballot(q);
+                        if (!CAP && mask) {
+                            q_max = wave_incl_max(q ? q_arr : -1);
+                            q_c0 = q ? (int32_t)ceil_div_u32((uint32_t)q_c, divN) : 0;
+                            q_sum = wave_incl_scan(q_c0);
                         }
                     }
-                    if (found < 0) break;   // the head cannot start within the horizon
-                    if (found > start) calm = 0;
-                    j = found;
-                    // the requests behind it that have arrived (those before it in
-                    // the chunk, admitted by now, arrived no later than j)
-                    const bool mem = queued && q_max <= j;
-                    const int32_t sum = q_sum - (__builtin_amdgcn_readlane(q_sum, hl) - c_h);
-                    const uint32_t below = __builtin_amdgcn_mbcnt_hi(
-                        (uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-                    const uint64_t take = __ballot(mem && sum <= room && (int32_t)below < fmax);
-                    const uint64_t blocked = __ballot(mem && sum > room);
-                    if ((take & (take - 1)) == 0) {
-                        alone = true;   // one request: checked below before it is added
-                        continue;
-                    }
-                    const int32_t lim_l = q_len >= H - j ? H : j + q_len;
-                    int32_t r_end = 0;
-                    // (everyone has read the curve above before it changes)
-                    curves_sync<A>();
-                    add_members<A, false, POW2>(KV, take, q_c, j, lim_l, divN, wave, &r_end);
-                    if (!members_fit<A>(sh, turn, KV, j, r_end, cap)) {
-                        add_members<A, true, POW2>(KV, take, q_c, j, lim_l, divN, wave, &r_end);
-                        curves_sync<A>();
-                        fmax = max(1, (int32_t)__builtin_popcountll(take) >> 2);
-                        calm = 0;
-                        continue;
-                    }
-                    if (wave == 0 && ((take >> lane) & 1)) {
-                        const int64_t e = (int64_t)j + q_len;
-                        if (e < H) atomicAdd(&BD[e], -1);
-                        if (e <= H && !q_lost && q_dl != kNoDeadline)
-                            atomicMin((unsigned long long*)&outDL[e - 1], (unsigned long long)q_dl);
-                    }
-                    if (threadIdx.x == 0) atomicAdd(&BD[j], (int32_t)__builtin_popcountll(take));
-                    n_end = max(n_end, r_end);
-                    mask &= ~take;
-                    fmax = min(kWave, 2 * fmax);
-                    calm = blocked ? 0 : calm + 1;
-                    if (calm >= calm_need) {
-                        at_targets = true;
-                        streak = 0;
-                    }
-                    continue;
-                }
+                    if (mask == 0) break;
 
-                // One request at a time (under a batch cap, or one without
-                // company).  The head of the queue: uniform lane, lane reads.
-                const int hl = __ffsll((unsigned long long)mask) - 1;
-                const int32_t h_arr = __builtin_amdgcn_readlane(q_arr, hl);
-                const int32_t h_c = __builtin_amdgcn_readlane(q_c, hl);
-                const int32_t h_len = __builtin_amdgcn_readlane(q_len, hl);
-                const int32_t h_lost = __builtin_amdgcn_readlane(q_lost, hl);
-                const uint64_t h_dl =
-                    ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int32_t)(q_dl >> 32), hl) << 32) |
-                    (uint32_t)__builtin_amdgcn_readlane((int32_t)(uint32_t)q_dl, hl);
-                const int32_t target = max(max(h_arr, j), last_over + 1);
-                if (h_arr >= H || target >= H) break;
-                if (CAP && target > j) run += sum_range(BD, j, target);
-                j = target;
-                bool admitted = false;
-                for (;;) {
-                    bool ok = !CAP || run < bcap;
-                    int32_t t_bad = -1;
-                    if (ok) {
-                        // 4 x 64 iterations per round (their LDS reads in flight
-                        // together); the earliest overflowing iteration wins
-                        const int32_t lim = kv_fits ? j : (int32_t)min((int64_t)j + h_len, (int64_t)H);
-                        for (int32_t t0 = j; t0 < lim && t_bad < 0; t0 += 4 * kWave) {
-                            uint64_t m[4];
-    #pragma unroll
-                            for (int k = 0; k < 4; ++k) {
-                                const int32_t t = t0 + k * kWave + lane;
-                                bool badt = false;
-                                if (t < lim)
-                                    badt = KV[t] + (int32_t)(POW2 ? ((uint32_t)(h_c + t - j) + divN.d - 1u) >> divN.l
-                                                                  : ceil_div_u32((uint32_t)(h_c + t - j), divN)) > cap;
-                                m[k] = __ballot(badt);
-                            }
-    #pragma unroll
-                            for (int k = 3; k >= 0; --k)
-                                if (m[k]) t_bad = t0 + k * kWave + __ffsll((unsigned long long)m[k]) - 1;
+                    if (!CAP && at_targets) {
+                        // The rest of this chunk of the queue, each at its FIFO
+                        // target, as above; their contributions are added to the KV
+                        // curve iteration by iteration and taken out again when they
+                        // do not fit.
+                        const int32_t lo_j = max(j, last_over + 1);
+                        const bool mem = (mask >> lane) & 1;
+                        const int32_t a = wave_incl_max(mem ? max(q_arr, lo_j) : -1);
+                        const uint64_t memm = __ballot(mem);
+                        const uint64_t over = __ballot(mem && a >= H);
+                        const uint64_t take = over ? (memm & ((over & (~over + 1)) - 1)) : memm;
+                        if (take == 0) break;   // the head cannot start within the horizon
+                        // each member's in-horizon end, on its own lane
+                        const int32_t lim_l = q_len >= H - a ? H : a + q_len;
+                        const int32_t a_first = __builtin_amdgcn_readlane(a, __ffsll((unsigned long long)take) - 1);
+                        int32_t r_end = 0;
+                        add_members<A, false, POW2>(KV, take, q_c, a, lim_l, divN, wave, &r_end);
+                        if (!members_fit<A>(sh, turn, KV, a_first, r_end, kv_fits ? INT32_MAX : cap)) {
+                            // take the batch's contributions out again
+                            add_members<A, true, POW2>(KV, take, q_c, a, lim_l, divN, wave, &r_end);
+                            curves_sync<A>();
+                            at_targets = false;
+                            streak = 0;
+                            calm = 0;
+                            calm_need = min(256, 2 * calm_need);
+                            continue;
                         }
-                        ok = t_bad < 0;
+                        if (wave == 0 && ((take >> lane) & 1)) {
+                            const int64_t e = (int64_t)a + q_len;
+                            atomicAdd(&BD[a], 1);
+                            if (e < H) atomicAdd(&BD[e], -1);
+                            if (e <= H && !q_lost && q_dl != kNoDeadline)
+                                atomicMin((unsigned long long*)&outDL[e - 1], (unsigned long long)q_dl);
+                        }
+                        n_end = max(n_end, r_end);
+                        j = __builtin_amdgcn_readlane(a, 63 - __clzll((long long)take));
+                        mask &= ~take;
+                        ++streak;
+                        if (streak >= 4) calm_need = 4;
+                        if (over) break;
+                        continue;
                     }
-                    if (ok) { admitted = true; break; }
-                    if (CAP && run >= bcap) {
-                        // The batch is full: the next start to try is the first
-                        // later iteration with a free slot, found 64 iterations
-                        // at a time from the batch differences (what stepping
-                        // one iteration at a time reaches).
-                        int32_t base = j, r = run, found = -1;
-                        while (base + 1 < H) {
-                            const int32_t t = base + 1 + lane;
-                            const int32_t pre = wave_incl_scan(t < H ? BD[t] : 0) + r;   // batch size at t
-                            const uint64_t m = __ballot(t < H && pre < bcap);
+
+                    if (!CAP && !alone) {
+                        // The capacity binds: the head and the requests behind it that
+                        // have arrived by its start j, as many as the KV of iteration
+                        // j itself leaves room for.  When their sum fits everywhere,
+                        // they are the one-at-a-time loop's admissions at j, and the
+                        // next of them does not fit at j.  A head without room at j
+                        // starts no earlier than the next iteration that has it.
+                        const bool queued = (mask >> lane) & 1;
+                        const int hl = __ffsll((unsigned long long)mask) - 1;
+                        const int32_t start = max(max(j, last_over + 1), __builtin_amdgcn_readlane(q_max, hl));
+                        const int32_t c_h = __builtin_amdgcn_readlane(q_c0, hl);
+                        int32_t room = -1, found = -1;
+                        for (int32_t t0 = start; t0 < H; t0 += kWave) {
+                            const int32_t t = t0 + lane;
+                            const int32_t left = cap - KV[min(t, H - 1)];
+                            const uint64_t m = __ballot(t < H && left >= c_h);
                             if (m) {
                                 const int l = __ffsll((unsigned long long)m) - 1;
-                                found = base + 1 + l;
-                                r = __builtin_amdgcn_readlane(pre, l);
+                                found = t0 + l;
+                                room = __builtin_amdgcn_readlane(left, l);
                                 break;
                             }
-                            r = __builtin_amdgcn_readlane(pre, kWave - 1);
-                            base += kWave;
                         }
-                        if (found < 0) break;
-                        run = r;
+                        if (found < 0) break;   // the head cannot start within the horizon
+                        if (found > start) calm = 0;
                         j = found;
+                        // the requests behind it that have arrived (those before it in
+                        // the chunk, admitted by now, arrived no later than j)
+                        const bool mem = queued && q_max <= j;
+                        const int32_t sum = q_sum - (__builtin_amdgcn_readlane(q_sum, hl) - c_h);
+                        const uint32_t below = __builtin_amdgcn_mbcnt_hi(
+                            (uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                        const uint64_t take = __ballot(mem && sum <= room && (int32_t)below < fmax);
+                        const uint64_t blocked = __ballot(mem && sum > room);
+                        if ((take & (take - 1)) == 0) {
+                            alone = true;   // one request: checked below before it is added
+                            continue;
+                        }
+                        const int32_t lim_l = q_len >= H - j ? H : j + q_len;
+                        int32_t r_end = 0;
+                        // (everyone has read the curve above before it changes)
+                        curves_sync<A>();
+                        add_members<A, false, POW2>(KV, take, q_c, j, lim_l, divN, wave, &r_end);
+                        if (!members_fit<A>(sh, turn, KV, j, r_end, cap)) {
+                            add_members<A, true, POW2>(KV, take, q_c, j, lim_l, divN, wave, &r_end);
+                            curves_sync<A>();
+                            fmax = max(1, (int32_t)__builtin_popcountll(take) >> 2);
+                            calm = 0;
+                            continue;
+                        }
+                        if (wave == 0 && ((take >> lane) & 1)) {
+                            const int64_t e = (int64_t)j + q_len;
+                            if (e < H) atomicAdd(&BD[e], -1);
+                            if (e <= H && !q_lost && q_dl != kNoDeadline)
+                                atomicMin((unsigned long long*)&outDL[e - 1], (unsigned long long)q_dl);
+                        }
+                        if (threadIdx.x == 0) atomicAdd(&BD[j], (int32_t)__builtin_popcountll(take));
+                        n_end = max(n_end, r_end);
+                        mask &= ~take;
+                        fmax = min(kWave, 2 * fmax);
+                        calm = blocked ? 0 : calm + 1;
+                        if (calm >= calm_need) {
+                            at_targets = true;
+                            streak = 0;
+                        }
                         continue;
                     }
-                    // Next start to try.  If iteration t_bad overflowed, every
-                    // start j2 in (j, t_bad] whose own contribution there,
-                    // ceil((c + t_bad - j2) / N), exceeds room = cap - KV[t_bad]
-                    // fails the same way: j2 < c + t_bad - N * room (all of
-                    // them when room < 0).  Skipping those gives the same
-                    // admission iteration.
-                    int32_t nj = j + 1;
-                    if (t_bad >= 0) {
-                        const int32_t room = cap - __builtin_amdgcn_readfirstlane(KV[t_bad]);
-                        int64_t first = (int64_t)t_bad + 1;
-                        if (room >= 0) first = min(first, (int64_t)h_c + t_bad - (int64_t)N * room);
-                        nj = (int32_t)max((int64_t)nj, first);
+
+                    // One request at a time (under a batch cap, or one without
+                    // company).  The head of the queue: uniform lane, lane reads.
+                    const int hl = __ffsll((unsigned long long)mask) - 1;
+                    const int32_t h_arr = __builtin_amdgcn_readlane(q_arr, hl);
+                    const int32_t h_c = __builtin_amdgcn_readlane(q_c, hl);
+                    const int32_t h_len = __builtin_amdgcn_readlane(q_len, hl);
+                    const int32_t h_lost = __builtin_amdgcn_readlane(q_lost, hl);
+                    const uint64_t h_dl =
+                        ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int32_t)(q_dl >> 32), hl) << 32) |
+                        (uint32_t)__builtin_amdgcn_readlane((int32_t)(uint32_t)q_dl, hl);
+                    const int32_t target = max(max(h_arr, j), last_over + 1);
+                    if (h_arr >= H || target >= H) break;
+                    if (CAP && target > j) run += sum_range(BD, j, target);
+                    j = target;
+                    bool admitted = false;
+                    for (;;) {
+                        bool ok = !CAP || run < bcap;
+                        int32_t t_bad = -1;
+                        if (ok) {
+                            // 4 x 64 iterations per round (their LDS reads in flight
+                            // together); the earliest overflowing iteration wins
+                            const int32_t lim = kv_fits ? j : (int32_t)min((int64_t)j + h_len, (int64_t)H);
+                            for (int32_t t0 = j; t0 < lim && t_bad < 0; t0 += 4 * kWave) {
+                                uint64_t m[4];
+        #pragma unroll
+                                for (int k = 0; k < 4; ++k) {
+                                    const int32_t t = t0 + k * kWave + lane;
+                                    bool badt = false;
+                                    if (t < lim)
+                                        badt = KV[t] + (int32_t)(POW2 ? ((uint32_t)(h_c + t - j) + divN.d - 1u) >> divN.l
+                                                                      : ceil_div_u32((uint32_t)(h_c + t - j), divN)) > cap;
+                                    m[k] = __ballot(badt);
+                                }
+        #pragma unroll
+                                for (int k = 3; k >= 0; --k)
+                                    if (m[k]) t_bad = t0 + k * kWave + __ffsll((unsigned long long)m[k]) - 1;
+                            }
+                            ok = t_bad < 0;
+                        }
+                        if (ok) { admitted = true; break; }
+                        if (CAP && run >= bcap) {
+                            // The batch is full: the next start to try is the first
+                            // later iteration with a free slot, found 64 iterations
+                            // at a time from the batch differences (what stepping
+                            // one iteration at a time reaches).
+                            int32_t base = j, r = run, found = -1;
+                            while (base + 1 < H) {
+                                const int32_t t = base + 1 + lane;
+                                const int32_t pre = wave_incl_scan(t < H ? BD[t] : 0) + r;   // batch size at t
+                                const uint64_t m = __ballot(t < H && pre < bcap);
+                                if (m) {
+                                    const int l = __ffsll((unsigned long long)m) - 1;
+                                    found = base + 1 + l;
+                                    r = __builtin_amdgcn_readlane(pre, l);
+                                    break;
+                                }
+                                r = __builtin_amdgcn_readlane(pre, kWave - 1);
+                                base += kWave;
+                            }
+                            if (found < 0) break;
+                            run = r;
+                            j = found;
+                            continue;
+                        }
+                        // Next start to try.  If iteration t_bad overflowed, every
+                        // start j2 in (j, t_bad] whose own contribution there,
+                        // ceil((c + t_bad - j2) / N), exceeds room = cap - KV[t_bad]
+                        // fails the same way: j2 < c + t_bad - N * room (all of
+                        // them when room < 0).  Skipping those gives the same
+                        // admission iteration.
+                        int32_t nj = j + 1;
+                        if (t_bad >= 0) {
+                            const int32_t room = cap - __builtin_amdgcn_readfirstlane(KV[t_bad]);
+                            int64_t first = (int64_t)t_bad + 1;
+                            if (room >= 0) first = min(first, (int64_t)h_c + t_bad - (int64_t)N * room);
+                            nj = (int32_t)max((int64_t)nj, first);
+                        }
+                        if (nj >= H) break;
+                        if (CAP) run += sum_range(BD, j, nj);
+                        j = nj;
                     }
-                    if (nj >= H) break;
-                    if (CAP) run += sum_range(BD, j, nj);
-                    j = nj;
-                }
-                if (!admitted) break;
-                const int64_t e = (int64_t)j + h_len;
-                const int32_t lim = (int32_t)min(e, (int64_t)H);
-                curves_sync<A>();   // everyone has read the curves
-                add_request<false, POW2>(KV, h_c, j, lim, divN, wave, A);
-                if (threadIdx.x == 0) {
-                    if (BD_LDS) {
-                        BD[j] += 1;
-                        if (e < H) BD[e] -= 1;
-                    } else {
-                        atomicAdd(&BD[j], 1);
-                        if (e < H) atomicAdd(&BD[e], -1);
+                    if (!admitted) break;
+                    const int64_t e = (int64_t)j + h_len;
+                    const int32_t lim = (int32_t)min(e, (int64_t)H);
+                    curves_sync<A>();   // everyone has read the curves
+                    add_request<false, POW2>(KV, h_c, j, lim, divN, wave, A);
+                    if (threadIdx.x == 0) {
+                        if (BD_LDS) {
+                            BD[j] += 1;
+                            if (e < H) BD[e] -= 1;
+                        } else {
+                            atomicAdd(&BD[j], 1);
+                            if (e < H) atomicAdd(&BD[e], -1);
+                        }
+                        if (e <= H && !h_lost && h_dl != kNoDeadline)
+                            atomicMin((unsigned long long*)&outDL[e - 1], (unsigned long long)h_dl);
                     }
-                    if (e <= H && !h_lost && h_dl != kNoDeadline)
-                        atomicMin((unsigned long long*)&outDL[e - 1], (unsigned long long)h_dl);
-                }
-                run += 1;
-                n_end = max(n_end, lim);
-                mask &= mask - 1;
-                curves_sync<A>();
-                alone = false;
-                fmax = min(kWave, 2 * fmax);
+                    run += 1;
+                    n_end = max(n_end, lim);
+                    mask &= mask - 1;
+                    curves_sync<A>();
+                    alone = false;
+                    fmax = min(kWave, 2 * fmax);
                 }
             }
             if (A < W) {   // where the loop has come to
