@@ -44,38 +44,21 @@ public:
     template <class Launch>
     hipError_t with(size_t need, hipStream_t st, Launch&& launch) {
         std::lock_guard<std::mutex> lock(mutex_);
-        const RelaxedCapture relaxed;
         const std::thread::id thread = st == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id();
         hipError_t e;
         Slot* w = nullptr;
         for (Slot& c : slots_)
             if (c.used && c.stream == st && c.thread == thread) { w = &c; break; }
-        for (int i = 0; i < SLOTS && !w; ++i) {
-            Slot& c = slots_[i];
-            if (!c.used) {
-                w = &c;
-            } else if (SLOTS > 1) {
-                e = hipEventQuery(c.done);
-                if (e == hipSuccess) w = &c;
-                else if (e != hipErrorNotReady) return e;
-                else (void)hipGetLastError();   // not ready: no error of the launches below
+        if (!w || need > w->bytes) {
+            const RelaxedCapture relaxed;
+            if (!w) {
+                e = choose(&w);
+                if (e != hipSuccess) return e;
             }
-        }
-        if (!w) {
-            w = &slots_[next_];
-            next_ = (next_ + 1) % SLOTS;
-        }
-        if (!w->done) {
-            e = hipEventCreateWithFlags(&w->done, hipEventDisableTiming);
-            if (e != hipSuccess) {
-                w->done = nullptr;
-                (void)hipGetLastError();
-                return launch((void*)nullptr, (size_t)0);
+            if (w->done && need > w->bytes) {
+                e = grow(*w, need);
+                if (e != hipSuccess) return e;
             }
-        }
-        if (need > w->bytes) {
-            e = grow(*w, need);
-            if (e != hipSuccess) return e;
         }
         if (!w->ptr) return launch((void*)nullptr, (size_t)0);
         if (w->used) {
@@ -116,6 +99,33 @@ private:
         std::thread::id thread;   // of hipStreamPerThread
         bool used = false;
     };
+
+    // An idle array's slot, else the next in turn, with an event unless none
+    // can be had (its array is empty then).
+    hipError_t choose(Slot** out) {
+        Slot* w = nullptr;
+        for (int i = 0; i < SLOTS && !w; ++i) {
+            Slot& c = slots_[i];
+            if (!c.used) {
+                w = &c;
+            } else if (SLOTS > 1) {
+                const hipError_t e = hipEventQuery(c.done);
+                if (e == hipSuccess) w = &c;
+                else if (e != hipErrorNotReady) return e;
+                else (void)hipGetLastError();   // not ready: no error of the launches below
+            }
+        }
+        if (!w) {
+            w = &slots_[next_];
+            next_ = (next_ + 1) % SLOTS;
+        }
+        if (!w->done && hipEventCreateWithFlags(&w->done, hipEventDisableTiming) != hipSuccess) {
+            w->done = nullptr;
+            (void)hipGetLastError();
+        }
+        *out = w;
+        return hipSuccess;
+    }
 
     // A larger array for w.  The replaced one's users may still run: the new
     // one's are ordered behind them (w.used stays), so that w.done is the last of

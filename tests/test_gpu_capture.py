@@ -184,7 +184,8 @@ def test_call_on_another_thread_while_capturing(gpu, T):
     def work():
         try:
             with torch.cuda.stream(other):
-                forest.tl_forest_predict_grid(dfr, dkv, dbs, out=outs[1])
+                for _ in range(3):   # (from the second on with scratch of its own)
+                    forest.tl_forest_predict_grid(dfr, dkv, dbs, out=outs[1])
         except Exception as e:   # raised again below, on the test's own thread
             errors.append(e)
 
