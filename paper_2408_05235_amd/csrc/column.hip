@@ -92,7 +92,7 @@ __global__ __launch_bounds__(kColThreads) void forest_column_lds_kernel(RankDev 
     const uint32_t rec_bytes = staged_bytes<true>(D.depth);
     const uint32_t buf_bytes = stage_buffer_bytes(B.tb, rec_bytes);
     const int wave = threadIdx.x / kWave;
-    const int64_t item = __builtin_amdgcn_readfirstlane((P.first_block + blockIdx.x) * kColWaves + wave);
+    const int64_t item = __builtin_amdgcn_readfirstlane((int64_t)blockIdx.x * kColWaves + wave);
     StageSync* sync = (StageSync*)(smem + 2 * buf_bytes);
     if (threadIdx.x == 0) stage_sync_init(sync);
     if (B.n_blocks > 0) stage_block<true>(D, B, 0, lds_addr(smem), wave, kColWaves);
@@ -249,12 +249,12 @@ __global__ __launch_bounds__(kColThreads) void forest_column_reuse_kernel(RankDe
     const uint32_t rec_bytes = rank_record_bytes(D.depth);
     const uint32_t buf_bytes = stage_buffer_bytes(B.tb, rec_bytes);
     const int wave = threadIdx.x / kWave;
-    const int64_t item = __builtin_amdgcn_readfirstlane((P.first_block + blockIdx.x) * kColWaves + wave);
+    const int64_t item = __builtin_amdgcn_readfirstlane((int64_t)blockIdx.x * kColWaves + wave);
     const int32_t span = kWave * RPL;
     const int32_t n_cols = (P.H + span - 1) / span;
     const int64_t n_items = LIVE ? (int64_t)*P.n_live : P.S * n_cols;
     // a workgroup wholly past the live items has nothing to stage for
-    if (LIVE && (P.first_block + blockIdx.x) * kColWaves >= n_items) return;
+    if (LIVE && (int64_t)blockIdx.x * kColWaves >= n_items) return;
     bool valid = item < n_items;
     // the (scenario, column) pair: item itself, or its entry of the work order
     const int64_t code = !valid ? 0 : P.order ? (int64_t)P.order[item] : item;
@@ -310,7 +310,7 @@ __global__ __launch_bounds__(256) void forest_column_global_kernel(const uint2* 
                                                                   const float* __restrict__ leaves,
                                                                   int32_t n_trees, int32_t depth, float base,
                                                                   ColumnParams P) {
-    const int64_t item = (P.first_block + blockIdx.x) * (256 / kWave) + threadIdx.x / kWave;
+    const int64_t item = (int64_t)blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
     const ColumnItem<1> c = column_item<1>(P, item);
     if (!c.row[0]) return;
     float x[4];
@@ -363,12 +363,11 @@ hipError_t launch_column_lds(const ForestDev& f, const ColumnParams& c, hipStrea
     const auto kern = forest_column_lds_kernel<NF, RPL, ROWS>;
     const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    return launch_parts((items + kColWaves - 1) / kColWaves, kColThreads, [&](dim3 grid, int64_t first) {
-        ColumnParams q = c;
-        q.first_block = first;
-        hipLaunchKernelGGL(kern, grid, dim3(kColThreads), lds, stream, rank_dev(f),
-                           tree_blocks(f.n_trees, f.group_trees, tb), q);
-    });
+    const int64_t blocks = (items + kColWaves - 1) / kColWaves;
+    if (!grid_fits(blocks, kColThreads)) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kColThreads), lds, stream, rank_dev(f),
+                       tree_blocks(f.n_trees, f.group_trees, tb), c);
+    return hipGetLastError();
 }
 
 // Rows per lane of the leaf-reuse kernel for these rows: 16 (else 8) where
@@ -392,12 +391,11 @@ hipError_t launch_column_reuse(const ForestDev& f, const ColumnParams& c, int32_
         c.n_live ? forest_column_reuse_kernel<RPL, true> : forest_column_reuse_kernel<RPL, false>;
     const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    return launch_parts((items + kColWaves - 1) / kColWaves, kColThreads, [&](dim3 grid, int64_t first) {
-        ColumnParams q = c;
-        q.first_block = first;
-        hipLaunchKernelGGL(kern, grid, dim3(kColThreads), lds, stream, rank_dev(f),
-                           tree_blocks(f.n_trees, f.group_trees, tb), q);
-    });
+    const int64_t blocks = (items + kColWaves - 1) / kColWaves;
+    if (!grid_fits(blocks, kColThreads)) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kColThreads), lds, stream, rank_dev(f),
+                       tree_blocks(f.n_trees, f.group_trees, tb), c);
+    return hipGetLastError();
 }
 
 template <int NF>
@@ -417,18 +415,33 @@ hipError_t launch_column(const ForestDev& f, const ColumnParams& c, hipStream_t 
         return launch_column_lds<NF, 1>(f, c, stream);
     }
     const int64_t items = c.S * ((c.H + kWave - 1) / kWave);
-    return launch_parts((items + 3) / 4, 256, [&](dim3 grid, int64_t first) {
-        ColumnParams q = c;
-        q.first_block = first;
-        hipLaunchKernelGGL(forest_column_global_kernel<NF>, grid, dim3(256), 0, stream, f.nodes, f.leaves, f.n_trees,
-                           f.depth, f.base_score, q);
-    });
+    if (!grid_fits((items + 3) / 4, 256)) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(forest_column_global_kernel<NF>, dim3((unsigned)((items + 3) / 4)), dim3(256), 0, stream,
+                       f.nodes, f.leaves, f.n_trees, f.depth, f.base_score, c);
+    return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_forest_column(const ForestDev& f, const ColumnParams& c, hipStream_t stream) {
     if (c.S == 0) return hipSuccess;
+    // More wavefronts of one row a lane than one launch takes: parts of whole
+    // scenarios, in their own order.
+    const int64_t most = std::max<int64_t>(1, (kMaxLaunchWaves - kColWaves) / ((c.H + kWave - 1) / kWave));
+    if (c.S > kMaxParts * most) return hipErrorInvalidConfiguration;
+    for (int64_t s0 = 0; s0 < c.S && c.S > most; s0 += most) {
+        ColumnParams p = c;
+        p.S = std::min(most, c.S - s0);
+        p.kv += s0 * c.H;
+        p.batch += s0 * c.H;
+        if (p.fidx) p.fidx += s0;
+        if (p.engine) p.engine += s0;
+        p.out += s0 * c.H;
+        p.order = nullptr;
+        p.n_live = nullptr;
+        const hipError_t e = launch_forest_column(f, p, stream);
+        if (e != hipSuccess || s0 + most >= c.S) return e;
+    }
     return f.n_features == 4 ? launch_column<4>(f, c, stream) : launch_column<3>(f, c, stream);
 }
 
@@ -532,6 +545,14 @@ hipError_t launch_forest_rows_lds(const ForestDev& f, const float* rows, int64_t
     const int32_t tb = (f.n_features == 3 || f.n_features == 4) ? column_trees_per_block<false>(f, kColLdsBudget, &lds) : 0;
     if (tb <= 0) return hipErrorNotSupported;
     if (n_rows == 0) return hipSuccess;
+    // Parts of as many rows as one launch takes at one a lane.
+    const int64_t most = (kMaxLaunchWaves - kColWaves) * kWave;
+    if (n_rows > kMaxParts * most) return hipErrorInvalidConfiguration;
+    for (int64_t r0 = 0; n_rows > most && r0 < n_rows; r0 += most) {
+        const hipError_t e =
+            launch_forest_rows_lds(f, rows + r0 * f.n_features, std::min(most, n_rows - r0), out + r0, stream);
+        if (e != hipSuccess || r0 + most >= n_rows) return e;
+    }
     ColumnParams c{};
     c.rows = rows;
     c.n_rows = n_rows;

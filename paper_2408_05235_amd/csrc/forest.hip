@@ -303,7 +303,7 @@ __global__ __launch_bounds__(kLdsThreads, kLdsWavesPerSimd) void forest_grid_lds
 
     const int wave = threadIdx.x / kWave;
     const int lane = lane_id();
-    const int64_t item = __builtin_amdgcn_readfirstlane((P.first_block + blockIdx.x) * kLdsWaves + wave);
+    const int64_t item = __builtin_amdgcn_readfirstlane((int64_t)blockIdx.x * kLdsWaves + wave);
     GridItem g = grid_item<kRows, kOrderJ / kRows>(P, item);
     const int32_t F = P.F, H = P.H;
     const int part = lane / kLanes;
@@ -432,7 +432,7 @@ __global__ __launch_bounds__(256) void forest_grid_global_kernel(const uint2* __
     __shared__ float2 kvb[kGlobalWaves][J];
     const int wave = threadIdx.x / kWave;
     const int lane = lane_id();
-    const int64_t item = __builtin_amdgcn_readfirstlane((P.first_block + blockIdx.x) * kGlobalWaves + wave);
+    const int64_t item = __builtin_amdgcn_readfirstlane((int64_t)blockIdx.x * kGlobalWaves + wave);
     const GridItem g = grid_item<J, 1>(P, item);
     const int32_t F = P.F, H = P.H;
     const bool active = g.valid && g.f < F;
@@ -530,12 +530,10 @@ hipError_t launch_grid_lds(const ForestDev& f, const GridParams& g, int32_t tb, 
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     const int64_t blocks = grid_workgroups(g, J);
-    return launch_parts(blocks, kLdsThreads, [&](dim3 grid, int64_t first) {
-        GridParams q = g;
-        q.first_block = first;
-        hipLaunchKernelGGL(kern, grid, dim3(kLdsThreads), lds, stream, rank_dev(f),
-                           tree_blocks(f.n_trees, f.group_trees, tb), q);
-    });
+    if (!grid_fits(blocks, kLdsThreads)) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kLdsThreads), lds, stream, rank_dev(f),
+                       tree_blocks(f.n_trees, f.group_trees, tb), g);
+    return hipGetLastError();
 }
 
 // Rows per wavefront: 8 or 16 where 32 would leave CUs without their two
@@ -560,12 +558,10 @@ hipError_t launch_grid_global(const ForestDev& f, const GridParams& g, hipStream
     const int64_t n_fg = (g.F + kWave - 1) / kWave;
     const int64_t items = g.S * n_fg * n_chunks;
     const int64_t blocks = (items + kGlobalWaves - 1) / kGlobalWaves;
-    return launch_parts(blocks, kGlobalWaves * kWave, [&](dim3 grid, int64_t first) {
-        GridParams q = g;
-        q.first_block = first;
-        hipLaunchKernelGGL((forest_grid_global_kernel<NF, kGlobalJ>), grid, dim3(kGlobalWaves * kWave), 0, stream,
-                           f.nodes, f.leaves, f.kvb_box, f.n_trees, f.depth, f.base_score, q);
-    });
+    if (!grid_fits(blocks, kGlobalWaves * kWave)) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((forest_grid_global_kernel<NF, kGlobalJ>), dim3((unsigned)blocks), dim3(kGlobalWaves * kWave),
+                       0, stream, f.nodes, f.leaves, f.kvb_box, f.n_trees, f.depth, f.base_score, g);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -584,10 +580,10 @@ constexpr int kCostWaves = 4;
 
 __global__ __launch_bounds__(kCostWaves* kWave) void pair_cost_kernel(RankDev D, const int32_t* __restrict__ kv,
                                                                       const int32_t* __restrict__ batch, int64_t n,
-                                                                      int32_t H, int32_t J, int64_t first_block,
+                                                                      int32_t H, int32_t J,
                                                                       uint32_t* __restrict__ cost,
                                                                       uint32_t* __restrict__ code) {
-    const int64_t pair = (first_block + blockIdx.x) * kCostWaves + threadIdx.x / kWave;
+    const int64_t pair = (int64_t)blockIdx.x * kCostWaves + threadIdx.x / kWave;
     if (pair >= n) return;
     const int32_t n_chunks = (H + J - 1) / J;
     const int64_t s = pair / n_chunks;
@@ -612,7 +608,8 @@ __global__ __launch_bounds__(kCostWaves* kWave) void pair_cost_kernel(RankDev D,
 
 hipError_t pair_order_plan(const ForestDev& f, int64_t n, int64_t min_pairs, PairOrderPlan* p) {
     *p = PairOrderPlan{0, 0, 0, 0};
-    if (!f.orderable || n < min_pairs || n >= (int64_t)1 << 31) return hipSuccess;
+    if (!f.orderable || n < min_pairs || !grid_fits((n + kCostWaves - 1) / kCostWaves, kCostWaves * kWave))
+        return hipSuccess;
     size_t temp = 0;
     const hipError_t e = hipcub::DeviceRadixSort::SortPairsDescending(
         nullptr, temp, (const uint32_t*)nullptr, (uint32_t*)nullptr, (const uint32_t*)nullptr, (uint32_t*)nullptr,
@@ -632,10 +629,9 @@ hipError_t pair_order(const ForestDev& f, const PairOrderPlan& p, const int32_t*
     uint32_t* code = (uint32_t*)(base + p.arr);
     uint32_t* cost_sorted = (uint32_t*)(base + 2 * p.arr);
     uint32_t* sorted = (uint32_t*)(base + 3 * p.arr);
-    hipError_t e = launch_parts((p.n + kCostWaves - 1) / kCostWaves, kCostWaves * kWave, [&](dim3 grid, int64_t first) {
-        hipLaunchKernelGGL(pair_cost_kernel, grid, dim3(kCostWaves * kWave), 0, stream, rank_dev(f), kv, batch, p.n, H,
-                           J, first, cost, code);
-    });
+    hipLaunchKernelGGL(pair_cost_kernel, dim3((unsigned)((p.n + kCostWaves - 1) / kCostWaves)),
+                       dim3(kCostWaves * kWave), 0, stream, rank_dev(f), kv, batch, p.n, H, J, cost, code);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     size_t temp = p.temp;
     e = hipcub::DeviceRadixSort::SortPairsDescending(base + 4 * p.arr, temp, cost, cost_sorted, code, sorted, (int)p.n,
@@ -675,6 +671,25 @@ hipError_t launch_forest_grid(const ForestDev& f, const GridParams& g_in, void* 
                               hipStream_t stream) {
     GridParams g = g_in;
     g.order = nullptr;
+    // Grids of more wavefronts than one launch takes go in parts of whole
+    // scenarios, each a grid of its own.  (By a workgroup offset in the kernel's
+    // parameters every grid paid for it: 256 boards x 32 x 4096 1115 -> 1136 us.)
+    const int64_t waves = (g.F + kWave - 1) / kWave * (((int64_t)g.H + kOrderJ - 1) / kOrderJ) * (kOrderJ / kLdsJ);
+    const int64_t most = std::max<int64_t>(1, (kMaxLaunchWaves - kLdsWaves) / waves);
+    if (g.S > kMaxParts * most) return hipErrorInvalidConfiguration;
+    if (g.S > most) {
+        for (int64_t s0 = 0; s0 < g_in.S; s0 += most) {
+            g = g_in;
+            g.S = std::min(most, g_in.S - s0);
+            g.kv += s0 * g.H;
+            g.batch += s0 * g.H;
+            if (g.engine) g.engine += s0;
+            g.out += s0 * g.F * g.H;
+            const hipError_t e = launch_forest_grid(f, g, ws, ws_bytes, stream);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     size_t lds = 0;
     int32_t tb = lds_trees_per_block(f, kLdsBudget, &lds);
     if (tb <= 0) return f.n_features == 4 ? launch_grid_global<4>(f, g, stream) : launch_grid_global<3>(f, g, stream);

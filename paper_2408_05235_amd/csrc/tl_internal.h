@@ -69,7 +69,6 @@ struct ColumnParams {
     // i < n_rows; the fields above except `out` are not used
     const float* rows;
     int64_t n_rows;
-    int64_t first_block;
 };
 
 // Admission decision from the IPS at the maximum frequency.
@@ -174,7 +173,6 @@ struct GridParams {
     // optional work order: entry i is the (scenario, chunk) pair s * n_chunks
     // + chunk that the i-th item (of each frequency group) evaluates
     const uint32_t* order;
-    int64_t first_block;
 };
 
 // The model compiled to its input lattice (engine sizes x batch 0..batch_max
@@ -234,12 +232,15 @@ hipError_t launch_lattice_column(const ForestDev& f, const LatticeDev& L, const 
 
 // A launch of `blocks` workgroups fits the grid (at most 2^31 - 1 in x).
 // A launch has fewer than 2^32 threads (of more, the workgroups past them are
-// left out without an error).  launch_parts calls launch(grid, first)
-// for up to four consecutive parts of `blocks` workgroups of `threads` threads
-// each; a kernel's workgroup number is blockIdx.x + first.  (Four: 2^26 - 4
+// left out without an error).  The model's kernels go in parts of whole scenarios
+// or rows, the others by launch_parts, which calls launch(grid, first)
+// for up to kMaxParts consecutive parts of `blocks` workgroups of `threads` threads
+// each; a kernel's workgroup number is blockIdx.x + first.  (2^26 - 4
 // scenarios of 256 threads each, as many as one wavefront each takes in one
 // launch; more are refused, as are counts that no memory could back.)
 constexpr int kMaxParts = 4;
+// Wavefronts of a launch.
+constexpr int64_t kMaxLaunchWaves = 0xffffffffll / 64;
 template <class Launch>
 hipError_t launch_parts(int64_t blocks, int threads, Launch&& launch) {
     const int64_t most = 0xffffffffll / threads;
